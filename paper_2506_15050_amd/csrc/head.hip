@@ -3,7 +3,7 @@
 // (the quantity inside the ratio of Eq. (ppoloss)); logits never reach memory.
 //
 // bf16 path (matrix cores).  The logits of a 256-token x 256-vocabulary tile
-// are accumulated with v_mfma_f32_16x16x32_bf16 (or 32x32x16, see head_tile.h).
+// are accumulated with v_mfma_f32_16x16x32_bf16 (head_tile.h).
 // The MFMA "row" operand is the W tile and the "column" operand the gathered
 // hidden rows, so the accumulators a lane holds for one block all belong to ONE
 // token (column lane % 16) and to different vocabulary entries: the running
@@ -111,10 +111,10 @@ struct LaneSoftmax {
         }
     }
 
-    // acc holds logits: lane owns column lane%32 of block tb; entry e of block vb
-    // is vocabulary id v_wave + vb*32 + (e/4)*8 + (lane/32)*4 + e%4.  Clears acc.
-    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, int64_t, int64_t,
-                                         int vt, int wv, int, int lane) {
+    // acc holds logits: lane owns column lane % 16 of block tb; entry e of block vb
+    // is vocabulary id v_wave + row_in_wave(vb, e, lane / 16).  Clears acc.
+    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task&,
+                                         int64_t, int64_t, int vt, int wv, int, int lane) {
         constexpr int kVB = C::kVB, kTB = C::kTB, kE = C::kAccElems;
         const int grp = lane / C::kMI, V = p.V;
         const int v_wave = vt * C::kTileV + wv * C::kWaveV;
@@ -187,8 +187,8 @@ struct LaneSoftmax {
     // Merge the lane groups (same token, different vocabulary rows), then
     // the kWavesV waves that share a token, and write the split's triple.
     // s_merge: LDS scratch [kWavesV][3][kTileT] floats, idle at this point.
-    __device__ __forceinline__ void finish(const HeadParams& p, float* s_merge, int64_t tok0, int64_t m_eff,
-                                                int sp, int wv, int wt, int lane, int tid) {
+    __device__ __forceinline__ void finish(const HeadParams& p, float* s_merge, const Task& task, int64_t tok0,
+                                           int64_t m_eff, int wv, int wt, int lane, int tid) {
         constexpr int kTileT = C::kTileT;
 #pragma unroll
         for (int off = C::kMI; off < 64; off <<= 1) {            // butterfly over the 64 / kMI lane groups
@@ -223,22 +223,57 @@ struct LaneSoftmax {
                 gs += s_merge[(q * 3 + 1) * kTileT + col] * __builtin_amdgcn_exp2f(s_merge[(q * 3 + 0) * kTileT + col] - gm);
                 gt += s_merge[(q * 3 + 2) * kTileT + col];
             }
-            float* out = p.part + (int64_t)sp * p.M + t;
+            const Grid& g = task.rest ? p.rest : p.first;
+            const int64_t tokens = (int64_t)g.rows * kTileT, plane = tokens * g.cols;
+            float* out = (task.rest ? p.part_rest : p.part_first) + task.col * tokens + (t - (int64_t)g.row0 * kTileT);
             out[0] = gm;
-            out[(int64_t)p.splits * p.M] = gs;
-            out[2 * (int64_t)p.splits * p.M] = gt;
+            out[plane] = gs;
+            out[2 * plane] = gt;
         }
     }
 };
 
-__global__ __launch_bounds__(256) void head_combine_kernel(
-    const float* __restrict__ part, int splits, int64_t M, const int64_t* __restrict__ m_actual,
+// Merge the columns' triples into logp and lse: 32 tokens per workgroup, 8 threads per token, each taking every
+// eighth column (coalesced over the tokens), merged through LDS.  (One thread per token walking up to 64 columns
+// twice took 20 us whatever the batch: a chain of dependent loads.)
+struct Partials {
+    const float *first, *rest;
+    int64_t first_tokens;              // tokens of the first grid; the others belong to the rest
+    int64_t first_stride, rest_stride; // tokens between two columns
+    int first_cols, rest_cols;
+};
+constexpr int kMergeTokens = 32, kMergeLanes = 8;
+__global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel(
+    Partials q, int64_t M, const int64_t* __restrict__ m_actual,
     const int32_t* __restrict__ sel_rows, const int32_t* __restrict__ sel_targets, int64_t n_rows,
     int V, const int32_t* __restrict__ out_index, float* __restrict__ logp,
     float* __restrict__ lse, int32_t* status) {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float s_part[3][kMergeLanes][kMergeTokens];
+    const int tok = threadIdx.x % kMergeTokens, sub = threadIdx.x / kMergeTokens;
+    const int64_t m = (int64_t)blockIdx.x * kMergeTokens + tok;
     const int64_t m_eff = m_actual ? min(M, *m_actual) : M;
-    if (m >= m_eff) return;
+    float mx = kNegBig, sum = 0.f, tz = 0.f;
+    if (m < m_eff) {
+        const bool rest = m >= q.first_tokens;
+        const float* part = rest ? q.rest + (m - q.first_tokens) : q.first + m;
+        const int64_t stride = rest ? q.rest_stride : q.first_stride;
+        const int cols = rest ? q.rest_cols : q.first_cols;
+        const int64_t plane = stride * cols;
+#pragma unroll 4
+        for (int c = sub; c < cols; c += kMergeLanes) {
+            const float* at = part + c * stride;
+            const float om = at[0], os = at[plane], ot = at[2 * plane];
+            const float nm = fmaxf(mx, om);
+            sum = sum * exp2f(mx - nm) + os * exp2f(om - nm);
+            mx = nm;
+            tz += ot;
+        }
+    }
+    s_part[0][sub][tok] = mx;
+    s_part[1][sub][tok] = sum;
+    s_part[2][sub][tok] = tz;
+    __syncthreads();
+    if (sub != 0 || m >= m_eff) return;
     const int64_t o = out_index ? (int64_t)out_index[m] : m;
     const int64_t row = sel_rows[m];
     const int tgt = sel_targets[m];
@@ -249,50 +284,23 @@ __global__ __launch_bounds__(256) void head_combine_kernel(
         if (lse) lse[o] = __builtin_nanf("");
         return;
     }
-    const int64_t plane = (int64_t)splits * M;
     float gm = kNegBig;
-    for (int s = 0; s < splits; ++s) gm = fmaxf(gm, part[(int64_t)s * M + m]);
+#pragma unroll
+    for (int s = 0; s < kMergeLanes; ++s) gm = fmaxf(gm, s_part[0][s][tok]);
     float gs = 0.f, gt = 0.f;
-    for (int s = 0; s < splits; ++s) {
-        gs += part[plane + (int64_t)s * M + m] * exp2f(part[(int64_t)s * M + m] - gm);
-        gt += part[2 * plane + (int64_t)s * M + m];
+#pragma unroll
+    for (int s = 0; s < kMergeLanes; ++s) {
+        gs += s_part[1][s][tok] * exp2f(s_part[0][s][tok] - gm);
+        gt += s_part[2][s][tok];
     }
     const float l = (gm + log2f(gs)) * kLn2;
     logp[o] = gt - l;
     if (lse) lse[o] = l;
 }
 
-// Kernel variants (0 is what the library runs; a tuning build can select another through TPPO_HEAD_VARIANT).
-using Cfg0 = HeadCfg<256, 256, 2, 4, 64, 2, 1, 32, 16, 8>;   // v_mfma_f32_16x16x32_bf16, one W block per MFMA step
-using Cfg1 = HeadCfg<256, 256, 2, 4, 64, 2, 1, 16, 32>;      // v_mfma_f32_32x32x16_bf16
-using Cfg2 = HeadCfg<256, 256, 2, 4, 64, 2, 1, 0, 32>;       // the same, transfers issued back to back
-#ifdef TPPO_TUNING
-// Two workgroups of 4 wavefronts per CU, 256 x 128 tiles, half-size stages: the two drift apart, so one's
-// log-softmax fold and stage hand-overs fall into the other's MFMAs.  Measured: correct, and a third slower
-// than variant 0 on every shape (0.34 / 0.38 / 0.38 of peak against 0.43 / 0.53 / 0.54 at H = 1024 / 3584 /
-// 5120): half cache lines per transfer and 1.5x the L2 -> LDS bytes per flop cost more than the overlap gains.
-using Cfg3 = HeadCfg<256, 128, 2, 2, 32, 2, 2, 24, 16, 8>;
-#endif
-
-template <class C>
-constexpr HeadVariant make_variant() {
-    return {head_mfma_kernel<C, LaneSoftmax>, C::kTileV, C::kTileT, C::kThreads, C::kLdsBytes, C::kWgsPerCu};
-}
-#ifdef TPPO_TUNING
-static const HeadVariant kVariants[] = {make_variant<Cfg0>(), make_variant<Cfg1>(), make_variant<Cfg2>(), make_variant<Cfg3>()};
-#else
-static const HeadVariant kVariants[] = {make_variant<Cfg0>()};
-#endif
-[[maybe_unused]] [[maybe_unused]] constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-
-static const HeadVariant& pick_variant() {
-    int id = 0;
-#ifdef TPPO_TUNING
-    if (const char* e = getenv("TPPO_HEAD_VARIANT")) id = atoi(e);       // tuning builds only
-    if (id < 0 || id >= kNumVariants) id = 0;
-#endif
-    return kVariants[id];
-}
+// Most partial triples a sweep of M tokens can write (plan_sweep: up to 4 columns in the whole rounds, kRestTasks
+// tiles in the rest): grows with M, so a workspace sized for the largest batch serves every smaller one.
+static int64_t most_triples(int64_t M) { return 4 * ((M + kTile - 1) / kTile * kTile) + kRestTasks * kTile; }
 
 static bool mfma_eligible(const void* hidden, int64_t H, int64_t ld_h, const void* w, int64_t ld_w,
                           tppo_dtype dt) {
@@ -307,12 +315,7 @@ extern "C" size_t tppo_token_logprobs_workspace_bytes(int64_t M, int64_t H, int6
     using namespace tppo;
     (void)H;
     if (M <= 0 || V <= 0 || dt != TPPO_BF16) return 256;
-    size_t need = 0;
-    for (const HeadVariant& hv : kVariants) {
-        const size_t n = (size_t)3 * (size_t)choose_splits(hv, M, V) * (size_t)M * sizeof(float);
-        need = n > need ? n : need;
-    }
-    return round_up(need, 256) + arrivals_bytes(M);
+    return round_up((size_t)3 * (size_t)most_triples(M) * sizeof(float), 256) + arrivals_bytes(M);
 }
 
 extern "C" int tppo_token_logprobs(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden,
@@ -356,15 +359,19 @@ extern "C" int tppo_token_logprobs(const void* hidden, int64_t n_rows, int64_t H
     p.sel_rows = sel_rows;
     p.sel_targets = sel_targets;
     p.m_actual = m_actual;
-    p.part = static_cast<float*>(workspace);
     p.n_rows = n_rows; p.ld_h = ld_hidden; p.ld_w = ld_w;
     p.H = (int)H;
-    const HeadVariant& hv = pick_variant();
-    plan_sweep(p, hv, M, V, static_cast<char*>(workspace) + workspace_bytes_needed - arrivals_bytes(M));
-    if (launch_sweep(hv, p, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
-    hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, p.part,
-                       p.splits, M, m_actual, sel_rows, sel_targets, n_rows, (int)V, out_index, logp,
-                       lse, status);
+    plan_sweep(p, M, V);
+    const int64_t first_tokens = (int64_t)p.first.rows * kTile, rest_tokens = (int64_t)p.rest.rows * kTile;
+    p.part_first = static_cast<float*>(workspace);
+    p.part_rest = p.part_first + 3 * first_tokens * p.first.cols;
+    const size_t room = arrivals_bytes(M);
+    if (launch_sweep<LaneSoftmax>(p, static_cast<char*>(workspace) + workspace_bytes_needed - room, room, s) != TPPO_OK)
+        return TPPO_ERR_LAUNCH;
+    const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
+    hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),
+                       dim3(kMergeTokens * kMergeLanes), 0, s, q, M, m_actual, sel_rows, sel_targets, n_rows, (int)V,
+                       out_index, logp, lse, status);
     return launch_result();
 }
 

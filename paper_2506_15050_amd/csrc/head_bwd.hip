@@ -44,8 +44,8 @@ struct DzEpilogue {
         }
     }
 
-    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, int64_t tok0,
-                                         int64_t m_eff, int vt, int wv, int wt, int lane) {
+    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task&,
+                                         int64_t tok0, int64_t m_eff, int vt, int wv, int wt, int lane) {
         const int v_lane = vt * C::kTileV + wv * C::kWaveV + (lane / C::kMI) * 4;
         uint16_t* out = static_cast<uint16_t*>(p.out);
 #pragma unroll
@@ -54,16 +54,14 @@ struct DzEpilogue {
             if (t < m_eff) {
                 uint16_t* row = out + t * p.ld_out;
 #pragma unroll
-                for (int vb = 0; vb < C::kVB; ++vb)
-#pragma unroll
-                    for (int q = 0; q < C::kQuads; ++q) {
-                        const int v0 = v_lane + vb * C::kMI + q * (4 * C::kGroups);
+                for (int vb = 0; vb < C::kVB; ++vb) {
+                        const int v0 = v_lane + vb * C::kMI;
                         if (v0 < p.out_cols) {
                             uint32_t h[4];
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
                                 const int v = v0 + j;
-                                const float pz = __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][q * 4 + j], kLog2e, -lse2[tb]));
+                                const float pz = __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][j], kLog2e, -lse2[tb]));
                                 float dz = (v == tgt[tb] ? g[tb] : 0.f) - g[tb] * pz;
                                 dz = v < p.V ? dz : 0.f;                     // padding columns of the last tile
                                 h[j] = bf16_rne_bits(dz);
@@ -84,34 +82,36 @@ struct DzEpilogue {
                 for (int e = 0; e < C::kAccElems; ++e) acc[vb][tb][e] = 0.f;
     }
 
-    __device__ __forceinline__ void finish(const HeadParams&, float*, int64_t, int64_t, int, int, int, int, int) {}
+    __device__ __forceinline__ void finish(const HeadParams&, float*, const Task&, int64_t, int64_t, int, int, int, int) {}
 };
 
 // Epilogue 2: plain store of the fp32 tile, out[t, v] (+)= acc -- the sweep as an
-// "NT" product out[T, V] = tokens[T, K] . w_role[V, K]^T.
+// "NT" product out[T, V] = tokens[T, K] . w_role[V, K]^T.  A tile that holds one chunk of the contraction goes
+// whole into its place among the partial tiles.
 template <class C>
 struct StoreEpilogue {
     __device__ __forceinline__ void init(const HeadParams&, int64_t, int64_t, int, int) {}
 
-    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, int64_t tok0,
-                                         int64_t m_eff, int vt, int wv, int wt, int lane) {
-        const int v_lane = vt * C::kTileV + wv * C::kWaveV + (lane / C::kMI) * 4;
-        float* out = static_cast<float*>(p.out);
+    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task& task,
+                                         int64_t tok0, int64_t m_eff, int vt, int wv, int wt, int lane) {
+        const bool partial = task.rest && p.k_chunks > 1;
+        const int v_lane = (partial ? 0 : vt * C::kTileV) + wv * C::kWaveV + (lane / C::kMI) * 4;
+        float* out = partial ? p.part_rest + (int64_t)task.part * (C::kTileV * C::kTileT) - tok0 * C::kTileV
+                             : static_cast<float*>(p.out);
+        const int64_t ld_out = partial ? C::kTileV : p.ld_out, out_cols = partial ? C::kTileV : p.out_cols;
+        const bool accumulate = p.accumulate && !partial;
 #pragma unroll
         for (int tb = 0; tb < C::kTB; ++tb) {
             const int64_t t = tok0 + wt * C::kWaveT + tb * C::kMI + (lane % C::kMI);
             if (t < m_eff) {
-                float* row = out + t * p.ld_out;
+                float* row = out + t * ld_out;
 #pragma unroll
-                for (int vb = 0; vb < C::kVB; ++vb)
-#pragma unroll
-                    for (int q = 0; q < C::kQuads; ++q) {
-                        const int v0 = v_lane + vb * C::kMI + q * (4 * C::kGroups);
-                        if (v0 < p.out_cols) {
-                            float4 val = make_float4(acc[vb][tb][q * 4], acc[vb][tb][q * 4 + 1],
-                                                     acc[vb][tb][q * 4 + 2], acc[vb][tb][q * 4 + 3]);
+                for (int vb = 0; vb < C::kVB; ++vb) {
+                        const int v0 = v_lane + vb * C::kMI;
+                        if (v0 < out_cols) {
+                            float4 val = make_float4(acc[vb][tb][0], acc[vb][tb][1], acc[vb][tb][2], acc[vb][tb][3]);
                             float4* dst = reinterpret_cast<float4*>(row + v0);
-                            if (p.accumulate) {
+                            if (accumulate) {
                                 const float4 old = *dst;
                                 val.x += old.x; val.y += old.y; val.z += old.z; val.w += old.w;
                             }
@@ -128,8 +128,35 @@ struct StoreEpilogue {
                 for (int e = 0; e < C::kAccElems; ++e) acc[vb][tb][e] = 0.f;
     }
 
-    __device__ __forceinline__ void finish(const HeadParams&, float*, int64_t, int64_t, int, int, int, int, int) {}
+    __device__ __forceinline__ void finish(const HeadParams&, float*, const Task&, int64_t, int64_t, int, int, int, int) {}
 };
+
+// The output tiles whose contraction was cut: out (+)= the sum of their partial tiles, in chunk order.  One
+// workgroup per 16 rows of a tile, a float4 per thread and row.
+constexpr int kSumRows = 16;
+__global__ __launch_bounds__(256) void sum_chunks_kernel(HeadParams p) {
+    const int id = blockIdx.x / (kTile / kSumRows), r0 = blockIdx.x % (kTile / kSumRows) * kSumRows;
+    const Task task = task_at(p, p.first_tasks + id, 1);
+    const int64_t t0 = (int64_t)task.row * kTile + r0;
+    const int v = (threadIdx.x & 63) * 4, i = threadIdx.x >> 6;
+    const int64_t v0 = (int64_t)task.col * kTile + v;
+    if (v0 >= p.out_cols) return;
+    for (int r = i; r < kSumRows && t0 + r < p.M; r += 4) {
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float* at = p.part_rest + (int64_t)id * (kTile * kTile) + (r0 + r) * kTile + v;
+#pragma unroll 4
+        for (int c = 0; c < p.k_chunks; ++c) {
+            const float4 x = *reinterpret_cast<const float4*>(at + (int64_t)c * p.rest_tasks * (kTile * kTile));
+            sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
+        }
+        float4* dst = reinterpret_cast<float4*>(static_cast<float*>(p.out) + (t0 + r) * p.ld_out + v0);
+        if (p.accumulate) {
+            const float4 old = *dst;
+            sum.x += old.x; sum.y += old.y; sum.z += old.z; sum.w += old.w;
+        }
+        *dst = sum;
+    }
+}
 
 // dst[c, r] = src[index ? index[r] : r, c] for r < rows (0 for rows <= r < the
 // next multiple of 64), c < cols; 2-byte elements, 64 x 64 tiles through LDS,
@@ -181,15 +208,15 @@ static int launch_transpose(const uint16_t* src, int64_t rows, int64_t cols, int
     return launch_result();
 }
 
-using BwdCfg = HeadCfg<256, 256, 2, 4, 64, 2, 1, 32, 16, 8>;
-static const HeadVariant kDzVariant = {head_mfma_kernel<BwdCfg, DzEpilogue>, BwdCfg::kTileV, BwdCfg::kTileT,
-                                       BwdCfg::kThreads, BwdCfg::kLdsBytes, BwdCfg::kWgsPerCu};
-// The products' tiles are deep (K = the vocabulary, or a chunk of tokens) and their splits need no merge, so a
-// unit costs next to nothing besides its tiles: the schedule may cut the W-role rows into as many splits as
-// there are tiles, which rounds the work to whole tiles per workgroup instead of to five at a time.  Units in
-// row-major order, so that the XCDs share the long token-role rows (the operand that does not fit a cache).
-static const HeadVariant kGemmVariant = {head_mfma_kernel<BwdCfg, StoreEpilogue>, BwdCfg::kTileV, BwdCfg::kTileT,
-                                         BwdCfg::kThreads, BwdCfg::kLdsBytes, BwdCfg::kWgsPerCu, 0.02, 0};
+// out[M, N] (+)= tokens[M, K] . w_role[N, K]^T; `part` is scratch for the tiles whose contraction is cut
+static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, void* arrivals,
+                          size_t arrivals_room, hipStream_t s) {
+    plan_product(p, M, N, p.H / HeadCfg::kBK, part, part_bytes);
+    if (launch_sweep<StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+    if (p.k_chunks == 1) return TPPO_OK;
+    hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
+    return launch_result();
+}
 
 constexpr int64_t kBwdChunkDefault = 98304, kBwdChunkMax = 98304;
 
@@ -252,6 +279,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
     uint16_t* dzt = reinterpret_cast<uint16_t*>(ws + L.off_dzt);
     uint16_t* hidt = reinterpret_cast<uint16_t*>(ws + L.off_hidt);
     void* arrivals = ws + L.off_arrivals;
+    const size_t room = L.total - L.off_arrivals, dz_bytes = (size_t)chunk * L.v_pad * 2;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t* hid = static_cast<const uint16_t*>(hidden);
     const uint16_t* w = static_cast<const uint16_t*>(w_head);
@@ -272,16 +300,16 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         p.aux1 = in_index ? grad_logp : grad_logp + m0;
         p.aux_index = in_index ? in_index + m0 : nullptr;
         p.out = dz; p.ld_out = L.v_pad; p.out_cols = L.v_pad;
-        plan_sweep(p, kDzVariant, mc, V, arrivals);
-        if (launch_sweep(kDzVariant, p, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+        plan_sweep(p, mc, V);
+        if (launch_sweep<DzEpilogue>(p, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: rows of W^T; K = v_pad)
         if (grad_hidden) {
             HeadParams q = {};
             q.hidden = dz; q.n_rows = mc; q.ld_h = L.v_pad;
             q.w = wt; q.ld_w = L.v_pad; q.H = (int)L.v_pad;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
-            plan_sweep(q, kGemmVariant, mc, H, arrivals, "TPPO_GH_SPLITS", "TPPO_GH_ORDER");
-            if (launch_sweep(kGemmVariant, q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            // (dZ^T is not made yet: its place holds the partial tiles)
+            if (launch_product(q, mc, H, dzt, dz_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
         // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: rows of dZ^T; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
@@ -293,8 +321,8 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.w = hidt; q.ld_w = m_pad; q.H = (int)m_pad;
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
-            plan_sweep(q, kGemmVariant, V, H, arrivals, "TPPO_GW_SPLITS", "TPPO_GW_ORDER");
-            if (launch_sweep(kGemmVariant, q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            // (dZ is not needed any more: its place holds the partial tiles)
+            if (launch_product(q, V, H, dz, dz_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;
