@@ -25,9 +25,9 @@
  *     environment variable is read.
  *   - The matrix-core kernels of tppo_token_logprobs* are scheduled for the
  *     whole MI355X (256 compute units in 8 XCDs).  On a device that reports
- *     another number of compute units (a partition of the chip) the bf16 path
- *     returns TPPO_ERR_LAUNCH instead of running with its workgroups taking
- *     turns.
+ *     another number of compute units (a partition of the chip) bf16 calls with
+ *     H % 64 == 0 and aligned rows return TPPO_ERR_LAUNCH instead of running
+ *     with their workgroups taking turns; all others use the generic kernel.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All work is enqueued asynchronously on it; no call synchronises with the
  *     host, which is why scalar results are written to device memory.
@@ -162,11 +162,15 @@ int tppo_plan_build(const int32_t* resp_off, const int32_t* keep_len, const int3
  *
  * in : hidden  [n_rows, H] row-major with leading dimension ld_hidden (elements);
  *      w_head  [V, H] row-major (torch Linear.weight layout), leading dim ld_w;
- *      both of type `dt` (TPPO_BF16: bf16 inputs, fp32 accumulation on the
- *      matrix cores when H % 64 == 0 and both leading dimensions are multiples
- *      of 8 and the base pointers 16-byte aligned, otherwise a slower generic
- *      kernel; TPPO_F32: fp32 FMA kernel; the generic and the fp32 kernel keep
- *      one hidden row in LDS and take H <= 16320, beyond that TPPO_ERR_SIZE);
+ *      both of type `dt`.  Both types run on the matrix cores and accumulate in
+ *      fp32 (exact products of bf16, fp32 products of fp32).  Rows that do not
+ *      start and end at multiples of 16 bytes are copied into the workspace
+ *      first; where it has no room for that (the size function below cannot
+ *      see base pointers and leading dimensions) or an fp32 call has no
+ *      workspace, a generic kernel is used, a hundred times slower.
+ *      fp32, and bf16 with H % 64 != 0, leading dimensions not multiples of 8
+ *      or base pointers not 16-byte aligned: H <= 16320, beyond that
+ *      TPPO_ERR_SIZE;
  *      sel_rows[M], sel_targets[M] int32;
  *      m_actual: optional device int64 (e.g. counts+0 of tppo_select): only the
  *      first min(M, *m_actual) tokens are computed, so M can be a host-side

@@ -23,8 +23,11 @@
 namespace tppo {
 
 // ------------------------------------------------------------------ generic
-// One workgroup per kept token, one wavefront per vocabulary row at a time.
-// fp32 FMA; serves TPPO_F32 and bf16 shapes the MFMA path does not take.
+// One workgroup per kept token, one wavefront per vocabulary row at a time,
+// fp32 FMA: every token reads all of W, so it runs at a hundredth of the matrix
+// cores' rate.  Serves what the tiled kernel's 16-byte transfers cannot address:
+// base pointers or leading dimensions that are not multiples of 16 bytes where
+// the workspace has no room for aligned copies, and fp32 calls without a workspace.
 constexpr int kGenThreads = 256;
 constexpr int kGenMaxH = 16320;               // the hidden row (fp32) and 48 bytes of partial results share 64 KiB of LDS
 
@@ -302,10 +305,112 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
 // tiles in the rest): grows with M, so a workspace sized for the largest batch serves every smaller one.
 static int64_t most_triples(int64_t M) { return 4 * ((M + kTile - 1) / kTile * kTile) + kRestTasks * kTile; }
 
-static bool mfma_eligible(const void* hidden, int64_t H, int64_t ld_h, const void* w, int64_t ld_w,
-                          tppo_dtype dt) {
-    return dt == TPPO_BF16 && H >= 64 && H % 64 == 0 && ld_h % 8 == 0 && ld_w % 8 == 0 &&
-           is_aligned(hidden, 16) && is_aligned(w, 16);
+// Rows the tiled kernel cannot address (a row's start or length is no multiple of 16 bytes) are first copied, zero
+// padded, to rows of whole chunks: dst[i] = src[index ? index[i] : i], 16 bytes per lane.  One read and one write
+// of W and of the kept rows, against M reads of W by the generic kernel.
+constexpr int kPackThreads = 256;
+template <typename T>
+__global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const T* __restrict__ src, int64_t n_src, int H,
+                                                                 int64_t ld, const int32_t* __restrict__ index,
+                                                                 int64_t rows, const int64_t* __restrict__ m_actual,
+                                                                 T* __restrict__ dst, int chunks) {
+    constexpr int kPer = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(kPer), aligned(sizeof(T))));
+    const int64_t n = (m_actual ? min(rows, *m_actual) : rows) * chunks, step = (int64_t)gridDim.x * kPackThreads;
+    for (int64_t i = (int64_t)blockIdx.x * kPackThreads + threadIdx.x; i < n; i += step) {
+        const int64_t r = i / chunks;
+        const int k = (int)(i - r * chunks) * kPer;
+        const int64_t from = index ? min(max((int64_t)index[r], (int64_t)0), n_src - 1) : r;
+        const T* at = src + from * ld + k;
+        vec x;
+        if (k + kPer <= H) {
+            x = *reinterpret_cast<const vec*>(at);
+        } else {
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) x[e] = k + e < H ? at[e] : (T)0;
+        }
+        *reinterpret_cast<vec*>(dst + r * (int64_t)chunks * kPer + k) = x;
+    }
+}
+
+static size_t tiled_workspace(int64_t M) {
+    return arrivals_bytes(M) + round_up((size_t)3 * (size_t)most_triples(M) * sizeof(float), 256);
+}
+
+static bool rows_addressable(const void* p, int64_t ld, int64_t H, size_t esz) {
+    return is_aligned(p, 16) && (size_t)ld * esz % 16 == 0 && (size_t)H * esz % 16 == 0;
+}
+
+// aligned copies of W and of the kept rows, where the hidden size alone says they will be needed
+static size_t packed_row_bytes(int64_t H, size_t esz) { return round_up((size_t)H * esz, 16); }
+static size_t packed_bytes(int64_t M, int64_t H, int64_t V, size_t esz) {
+    return round_up((size_t)(V + M) * packed_row_bytes(H, esz), 256);
+}
+
+template <typename T>
+static int head_generic(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden, const void* w, int64_t V,
+                        int64_t ld_w, const int32_t* sel_rows, const int32_t* sel_targets, int64_t M,
+                        const int64_t* m_actual, const int32_t* out_index, float* logp, float* lse, int32_t* status,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(head_generic_kernel<T>, dim3((unsigned)M), dim3(kGenThreads), (size_t)H * sizeof(float), s,
+                       static_cast<const T*>(hidden), n_rows, (int)H, ld_hidden, static_cast<const T*>(w), (int)V, ld_w,
+                       sel_rows, sel_targets, M, m_actual, out_index, logp, lse, status);
+    return launch_result();
+}
+
+template <typename T>
+static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_index, float* logp, float* lse,
+                      int64_t n_rows, const int32_t* sel_rows, void* workspace, int32_t* status, hipStream_t s) {
+    typedef HeadCfg<T, false> Whole;
+    typedef HeadCfg<T, true> Ragged;
+    p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
+    plan_sweep(p, M, V);
+    const int64_t first_tokens = (int64_t)p.first.rows * kTile, rest_tokens = (int64_t)p.rest.rows * kTile;
+    const size_t room = arrivals_bytes(M);
+    char* ws = static_cast<char*>(workspace);
+    p.part_first = reinterpret_cast<float*>(ws + room);
+    p.part_rest = p.part_first + 3 * first_tokens * p.first.cols;
+    const int rc = p.H % Whole::kBK == 0 ? launch_sweep<Whole, LaneSoftmax>(p, ws, room, s)
+                                         : launch_sweep<Ragged, LaneSoftmax>(p, ws, room, s);
+    if (rc != TPPO_OK) return rc;
+    const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
+    hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),
+                       dim3(kMergeTokens * kMergeLanes), 0, s, q, M, p.m_actual, sel_rows, p.sel_targets, n_rows, (int)V,
+                       out_index, logp, lse, status);
+    return launch_result();
+}
+
+// Aligned copies first where the rows need them, then the tiled kernel.
+template <typename T>
+static int head_call(HeadParams& p, int64_t M, int64_t V, const int32_t* out_index, float* logp, float* lse,
+                     void* workspace, size_t tiled_bytes, bool pack_h, bool pack_w, int32_t* status, hipStream_t s) {
+    const int64_t n_rows = p.n_rows;
+    const int32_t* sel_rows = p.sel_rows;
+    const int chunks = (int)(packed_row_bytes(p.H, sizeof(T)) / 16), per_row = chunks * (16 / (int)sizeof(T));
+    T* copy = reinterpret_cast<T*>(static_cast<char*>(workspace) + tiled_bytes);
+    auto groups = [&](int64_t rows) {
+        const int64_t g = (rows * chunks + kPackThreads - 1) / kPackThreads;
+        return dim3((unsigned)(g < 16384 ? g : 16384));
+    };
+    if (pack_w) {
+        hipLaunchKernelGGL(pack_rows_kernel<T>, groups(V), dim3(kPackThreads), 0, s, static_cast<const T*>(p.w), V, p.H,
+                           p.ld_w, (const int32_t*)nullptr, V, (const int64_t*)nullptr, copy, chunks);
+        if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
+        p.w = copy;
+        p.ld_w = per_row;
+        copy += V * per_row;
+    }
+    if (pack_h) {
+        hipLaunchKernelGGL(pack_rows_kernel<T>, groups(M), dim3(kPackThreads), 0, s, static_cast<const T*>(p.hidden),
+                           p.n_rows, p.H, p.ld_h, p.sel_rows, M, p.m_actual, copy, chunks);
+        if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
+        p.hidden = copy;
+        p.ld_h = per_row;
+        p.n_rows = M;
+        p.sel_rows = nullptr;
+    }
+    if (pack_w || pack_h) p.H = per_row;                            // (zeros: they change no logit)
+    return head_tiled<T>(p, M, V, out_index, logp, lse, n_rows, sel_rows, workspace, status, s);
 }
 
 }  // namespace tppo
@@ -313,9 +418,9 @@ static bool mfma_eligible(const void* hidden, int64_t H, int64_t ld_h, const voi
 extern "C" size_t tppo_token_logprobs_workspace_bytes(int64_t M, int64_t H, int64_t V,
                                                       tppo_dtype dt) {
     using namespace tppo;
-    (void)H;
-    if (M <= 0 || V <= 0 || dt != TPPO_BF16) return 256;
-    return round_up((size_t)3 * (size_t)most_triples(M) * sizeof(float), 256) + arrivals_bytes(M);
+    if (M <= 0 || V <= 0 || H <= 0 || (dt != TPPO_BF16 && dt != TPPO_F32)) return 256;
+    const size_t esz = dt == TPPO_BF16 ? 2 : 4;
+    return tiled_workspace(M) + ((size_t)H * esz % 16 != 0 ? packed_bytes(M, H, V, esz) : 0);
 }
 
 extern "C" int tppo_token_logprobs(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden,
@@ -334,45 +439,37 @@ extern "C" int tppo_token_logprobs(const void* hidden, int64_t n_rows, int64_t H
     if (!hidden || !w_head || !sel_rows || !sel_targets || !logp) return TPPO_ERR_NULL;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (!mfma_eligible(hidden, H, ld_hidden, w_head, ld_w, dt)) {
-        if (H > kGenMaxH) return TPPO_ERR_SIZE;
-        const size_t lds = (size_t)H * sizeof(float);
-        if (dt == TPPO_F32)
-            hipLaunchKernelGGL(head_generic_kernel<float>, dim3((unsigned)M), dim3(kGenThreads), lds, s,
-                               static_cast<const float*>(hidden), n_rows, (int)H, ld_hidden,
-                               static_cast<const float*>(w_head), (int)V, ld_w, sel_rows, sel_targets, M,
-                               m_actual, out_index, logp, lse, status);
-        else
-            hipLaunchKernelGGL(head_generic_kernel<uint16_t>, dim3((unsigned)M), dim3(kGenThreads), lds, s,
-                               static_cast<const uint16_t*>(hidden), n_rows, (int)H, ld_hidden,
-                               static_cast<const uint16_t*>(w_head), (int)V, ld_w, sel_rows,
-                               sel_targets, M, m_actual, out_index, logp, lse, status);
-        return launch_result();
+    const size_t esz = dt == TPPO_BF16 ? 2 : 4;
+    const bool bf16 = dt == TPPO_BF16, have_ws = workspace && is_aligned(workspace, 256);
+    // Copies are needed of an operand whose rows are not addressable -- and of both when H itself is ragged, since
+    // the sweep runs over the padded H then.
+    const bool ragged = (size_t)H * esz % 16 != 0;
+    const bool pack_h = ragged || !rows_addressable(hidden, ld_hidden, H, esz);
+    const bool pack_w = ragged || !rows_addressable(w_head, ld_w, H, esz);
+    const size_t tiled = tiled_workspace(M), copies = packed_bytes(pack_h ? M : 0, H, pack_w ? V : 0, esz);
+    // bf16 rows of whole stages at aligned addresses: such a call needs its workspace and the whole chip; any
+    // other one has the generic kernel to fall back on, and its limit on H
+    const bool matrix_only = bf16 && !pack_h && !pack_w && H % 64 == 0;
+    if (!matrix_only && H > kGenMaxH) return TPPO_ERR_SIZE;
+    bool fits = have_ws && workspace_bytes >= tiled + ((pack_h || pack_w) ? copies : 0);
+    if (matrix_only && !fits) return TPPO_ERR_WORKSPACE;
+    if (!matrix_only) fits = fits && device_compute_units() == kSweepGroups;
+    if (!fits) {
+        return bf16 ? head_generic<uint16_t>(hidden, n_rows, H, ld_hidden, w_head, V, ld_w, sel_rows, sel_targets, M,
+                                             m_actual, out_index, logp, lse, status, s)
+                    : head_generic<float>(hidden, n_rows, H, ld_hidden, w_head, V, ld_w, sel_rows, sel_targets, M,
+                                          m_actual, out_index, logp, lse, status, s);
     }
-
-    const size_t workspace_bytes_needed = tppo_token_logprobs_workspace_bytes(M, H, V, dt);
-    if (!workspace || !is_aligned(workspace, 256) || workspace_bytes < workspace_bytes_needed)
-        return TPPO_ERR_WORKSPACE;
     HeadParams p = {};
-    p.hidden = static_cast<const uint16_t*>(hidden);
-    p.w = static_cast<const uint16_t*>(w_head);
+    p.hidden = hidden;
+    p.w = w_head;
     p.sel_rows = sel_rows;
     p.sel_targets = sel_targets;
     p.m_actual = m_actual;
     p.n_rows = n_rows; p.ld_h = ld_hidden; p.ld_w = ld_w;
     p.H = (int)H;
-    plan_sweep(p, M, V);
-    const int64_t first_tokens = (int64_t)p.first.rows * kTile, rest_tokens = (int64_t)p.rest.rows * kTile;
-    p.part_first = static_cast<float*>(workspace);
-    p.part_rest = p.part_first + 3 * first_tokens * p.first.cols;
-    const size_t room = arrivals_bytes(M);
-    if (launch_sweep<LaneSoftmax>(p, static_cast<char*>(workspace) + workspace_bytes_needed - room, room, s) != TPPO_OK)
-        return TPPO_ERR_LAUNCH;
-    const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
-    hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),
-                       dim3(kMergeTokens * kMergeLanes), 0, s, q, M, m_actual, sel_rows, sel_targets, n_rows, (int)V,
-                       out_index, logp, lse, status);
-    return launch_result();
+    return bf16 ? head_call<uint16_t>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, status, s)
+                : head_call<float>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, status, s);
 }
 
 extern "C" int tppo_version(void) { return TPPO_VERSION; }

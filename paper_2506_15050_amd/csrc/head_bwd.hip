@@ -208,11 +208,14 @@ static int launch_transpose(const uint16_t* src, int64_t rows, int64_t cols, int
     return launch_result();
 }
 
+using BwdCfg = HeadCfg<uint16_t, false>;
+
 // out[M, N] (+)= tokens[M, K] . w_role[N, K]^T; `part` is scratch for the tiles whose contraction is cut
 static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, void* arrivals,
                           size_t arrivals_room, hipStream_t s) {
-    plan_product(p, M, N, p.H / HeadCfg::kBK, part, part_bytes);
-    if (launch_sweep<StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+    p.k_tiles = p.H / BwdCfg::kBK;
+    plan_product(p, M, N, part, part_bytes);
+    if (launch_sweep<BwdCfg, StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
     hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
     return launch_result();
@@ -293,7 +296,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         // 1. dZ[mc, v_pad] (bf16): logits recomputed, softmax derivative applied
         HeadParams p = {};
         p.hidden = hid; p.n_rows = n_rows; p.ld_h = ld_hidden;
-        p.w = w; p.ld_w = ld_w; p.H = (int)H;
+        p.w = w; p.ld_w = ld_w; p.H = (int)H; p.k_tiles = (int)(H / BwdCfg::kBK);
         p.sel_rows = sel_rows + m0;
         p.sel_targets = sel_targets + m0;
         p.aux0 = in_index ? lse : lse + m0;
@@ -301,7 +304,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         p.aux_index = in_index ? in_index + m0 : nullptr;
         p.out = dz; p.ld_out = L.v_pad; p.out_cols = L.v_pad;
         plan_sweep(p, mc, V);
-        if (launch_sweep<DzEpilogue>(p, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+        if (launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: rows of W^T; K = v_pad)
         if (grad_hidden) {
             HeadParams q = {};

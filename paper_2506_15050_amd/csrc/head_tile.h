@@ -5,12 +5,14 @@
 // and a plain tile store (which makes the same sweep an "NT" GEMM).
 #pragma once
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 
 namespace tppo {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int kMaxSplits = 256;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -24,13 +26,14 @@ struct Grid {
 };
 
 struct HeadParams {
-    const uint16_t* hidden;
-    const uint16_t* w;
+    const void* hidden;
+    const void* w;
     const int32_t* sel_rows;
     const int32_t* sel_targets;
     const int64_t* m_actual;
     int64_t n_rows, ld_h, ld_w, M;
     int H, V, row_tiles, vocab_tiles;
+    int k_tiles;                       // K stages: H / kBK, rounded up
     // schedule
     Grid first, rest;                  // tasks 0 .. first_tasks - 1 come from `first`, the others from `rest`
     int first_tasks, rest_base, rest_tasks, k_chunks;
@@ -58,31 +61,44 @@ struct HeadParams {
 // of 16 consecutive rows, and the swizzle spreads them over all 16 slots of
 // the 256-byte bank window (measured: SQ_LDS_BANK_CONFLICT = 0).
 //
-// The MFMA is v_mfma_f32_16x16x32_bf16: same flops per cycle and same LDS bytes per flop as 32x32x16, but at the
+// The element type T is bf16 (uint16_t) or float; a stage's row is 128 bytes either way, and so are all transfers
+// and fragments.  fp32 runs four v_mfma_f32_16x16x4_f32 on a pair of 16-byte fragments: MFMA j takes element j of
+// every lane's chunk, i.e. k = j, 4 + j, 8 + j, 12 + j of the 16 -- the same set on both sides, in another order.
+// Its matrix rate is a sixteenth of bf16's, so nothing else matters there (measured: 2064 tokens, H = 1024,
+// V = 32000: 1.2 ms, 110 TFLOP/s of the 154 a large fp32 product reaches here; one token per workgroup with
+// plain multiply-adds took 77-80 ms).
+//
+// For bf16 the MFMA is v_mfma_f32_16x16x32_bf16: same flops per cycle and same LDS bytes per flop as 32x32x16, but at the
 // chip's power limit it sustains more (MFMA loop on LDS-fed fragments: 1.65 vs 1.55 PFLOP/s; on register-resident
 // ones 2.10 vs 1.83).  Lane l of a wave holds, for a 16 x 16 block, column l % 16 (a token) and rows
 // (l/16)*4 + e, e < 4 (vocabulary entries), and reads its operand fragments as 16 bytes: row l % 16, K chunk
 // l / 16 of the MFMA's K range.
+// RAGGED: H is not a multiple of a stage, and the chunks of the last one that lie beyond it are fetched as zeros (a
+// variant of its own: the selects cost registers that the plain one does not have to spare).
+template <typename T, bool RAGGED>
 struct HeadCfg {
+    static constexpr bool kRagged = RAGGED;
+    static constexpr int kEsz = sizeof(T), kPerChunk = 16 / kEsz;         // elements of a 16-byte chunk
+    typedef typename std::conditional<kEsz == 2, bf16x8, f32x4>::type Frag;
     static constexpr int kMI = 16, kGroups = 64 / kMI, kAccElems = 4;
     typedef float Acc __attribute__((__vector_size__(kAccElems * sizeof(float))));
-    static constexpr int kTileV = 256, kTileT = 256, kWavesV = 2, kWavesT = 4, kBK = 64, kStages = 2;
+    static constexpr int kTileV = 256, kTileT = 256, kWavesV = 2, kWavesT = 4, kBK = 128 / kEsz, kStages = 2;
     // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
     // a full memory queue
     static constexpr int kSpread = 32;
     static constexpr int kWaves = kWavesV * kWavesT, kThreads = kWaves * 64;
     static constexpr int kWaveV = kTileV / kWavesV, kWaveT = kTileT / kWavesT;    // wave tile
     static constexpr int kVB = kWaveV / kMI, kTB = kWaveT / kMI;                  // 16 x 16 blocks per wave
-    // an MFMA step: one W block over 32 K, against all token blocks
+    // an MFMA step: one W block over four chunks of K, against all token blocks
     static constexpr int kMfmaPerStep = kTB;
-    static constexpr int kRowBytes = kBK * 2, kChunks = kBK / 8;
+    static constexpr int kRowBytes = kBK * kEsz, kChunks = kRowBytes / 16;
     static constexpr int kRows = kTileV + kTileT;
     static constexpr int kStageBytes = kRows * kRowBytes;
     static constexpr int kLdsBytes = kStages * kStageBytes;
     static constexpr int kRowsPerDma = 1024 / kRowBytes;                  // one wave-wide 16 B/lane transfer
     static constexpr int kDmaPerStage = kRows / kRowsPerDma;
     static constexpr int kDmaPerWave = kDmaPerStage / kWaves;
-    static constexpr int kKSteps = (kBK / 32) * kVB;
+    static constexpr int kKSteps = (kChunks / 4) * kVB;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");
     static_assert(kKSteps % 2 == 0, "fragment double buffering assumes an even number of K steps");
@@ -179,10 +195,13 @@ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int all_k_ti
 //   init(p, tok0, m_eff, wt, lane)                          once per task,
 //   fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane)       after each finished tile of 256 W rows; clears acc,
 //   finish(p, lds_scratch, task, tok0, m_eff, wv, wt, lane, tid)  after the task's tiles (workgroup-wide).
+// what the chunks beyond a ragged H hold, in both operands
+static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
+
 template <class C, template <class> class Epi>
 __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(HeadParams p) {
     constexpr int kTileV = C::kTileV, kTileT = C::kTileT, kWaveV = C::kWaveV, kWaveT = C::kWaveT;
-    constexpr int kVB = C::kVB, kTB = C::kTB, kBK = C::kBK;
+    constexpr int kVB = C::kVB, kTB = C::kTB;
     constexpr int kDmaPerWave = C::kDmaPerWave, kKSteps = C::kKSteps;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -198,7 +217,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(H
     const int round = t / kSweepGroups;
     if (round > 0 && p.arrivals)                            // the first round starts aligned
         align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
-    const Task task = task_at(p, t, p.H / kBK);
+    const Task task = task_at(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
     if (tok0 >= m_eff) continue;                            // uniform over the workgroup
     const int vt_begin = task.vt_begin, vt_end = task.vt_end, k_tiles = task.k_tiles;
@@ -207,32 +226,38 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(H
     // ---- loader role: transfers wave*kDmaPerWave + q, each kRowsPerDma staged rows
     const int ld_row0 = wave * kDmaPerWave * C::kRowsPerDma + lane / C::kChunks;   // + q * kRowsPerDma
     const int ld_slot = lane % C::kChunks;
-    const uint16_t* src[kDmaPerWave];
-    const int k_first = task.k_begin * kBK;
+    const char* src[kDmaPerWave];
+    const int k_first = task.k_begin * C::kRowBytes, k_bytes = p.H * C::kEsz;
+    const int64_t ld_w = p.ld_w * C::kEsz, ld_h = p.ld_h * C::kEsz;
     int issue_vt = vt_begin, issue_kt = 0, issue_stage = 0, issue_kpos = k_first;
     auto point_at_tile = [&](int vt, bool w_only) {
 #pragma unroll
         for (int q = 0; q < kDmaPerWave; ++q) {
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
-            const int chunk = (ld_slot ^ C::swz(r)) * 8;
+            const int chunk = (ld_slot ^ C::swz(r)) * 16;
             if (r < kTileV) {
                 const int64_t v = min((int64_t)vt * kTileV + r, (int64_t)p.V - 1);
-                src[q] = p.w + v * p.ld_w + chunk;
+                src[q] = static_cast<const char*>(p.w) + v * ld_w + chunk;
             } else if (!w_only) {
                 const int64_t t = min(tok0 + (r - kTileV), m_eff - 1);
                 int64_t row = p.sel_rows ? (int64_t)p.sel_rows[t] : t;      // no list: rows in order
                 row = min(max(row, (int64_t)0), p.n_rows - 1);
-                src[q] = p.hidden + row * p.ld_h + chunk;
+                src[q] = static_cast<const char*>(p.hidden) + row * ld_h + chunk;
             }
         }
     };
     point_at_tile(vt_begin, false);
     auto issue_one = [&](int q) {
         const unsigned dst = lds_base + issue_stage * C::kStageBytes + wave * kDmaPerWave * 1024;
-        dma_16b_per_lane(src[q] + issue_kpos, dst + q * 1024);
+        const char* from = src[q] + issue_kpos;
+        if (C::kRagged && issue_kpos + C::kRowBytes > k_bytes) {    // (uniform) the last stage
+            const int chunk = (ld_slot ^ C::swz(ld_row0 + q * C::kRowsPerDma)) * 16;
+            if (issue_kpos + chunk >= k_bytes) from = reinterpret_cast<const char*>(&kZeroChunk);
+        }
+        dma_16b_per_lane(from, dst + q * 1024);
     };
     auto issue_advance = [&]() {        // next (vocabulary tile, k tile) in sweep order
-        issue_kpos += kBK;
+        issue_kpos += C::kRowBytes;
         issue_stage ^= 1;
         if (++issue_kt == k_tiles) {
             issue_kt = 0;
@@ -252,20 +277,20 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(H
 #pragma unroll
             for (int e = 0; e < C::kAccElems; ++e) acc[vb][tb][e] = 0.f;
 
-    // Fragments of MFMA step `step` of a stage (kKSteps steps per stage), double buffered: step = (K step of 32) *
+    // Fragments of MFMA step `step` of a stage (kKSteps steps per stage), double buffered: step = (four chunks of K) *
     // kVB + W block; the W block's fragment, K chunks 4 * (step / kVB) + group, and with a K step's first block
     // the token fragments of that K step.
-    bf16x8 fa[2], fb[2][kTB];
+    typename C::Frag fa[2], fb[2][kTB];
     auto load_frags = [&](int stage, int step) {
         const unsigned char* st = smem + stage * C::kStageBytes;
         const unsigned char* a_base = st + (wv * kWaveV) * C::kRowBytes;
         const unsigned char* b_base = st + (kTileV + wt * kWaveT) * C::kRowBytes;
         const int k32 = step / kVB, vb = step % kVB, c = k32 * 4 + frag_grp;
-        fa[step & 1] = *reinterpret_cast<const bf16x8*>(a_base + C::chunk_off(vb * 16 + frag_row, c));
+        fa[step & 1] = *reinterpret_cast<const typename C::Frag*>(a_base + C::chunk_off(vb * 16 + frag_row, c));
         if (vb == 0) {
 #pragma unroll
             for (int tb = 0; tb < kTB; ++tb)
-                fb[k32][tb] = *reinterpret_cast<const bf16x8*>(b_base + C::chunk_off(tb * 16 + frag_row, c));
+                fb[k32][tb] = *reinterpret_cast<const typename C::Frag*>(b_base + C::chunk_off(tb * 16 + frag_row, c));
         }
     };
     // An MFMA step with this wave's transfers of the stage being refilled issued between the MFMAs (`on` is
@@ -277,7 +302,13 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(H
         if (part < kSpreadSteps) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
-            acc[vb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[step & 1], fb[k32][tb], acc[vb][tb], 0, 0, 0);
+            if constexpr (C::kEsz == 2) {
+                acc[vb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[step & 1], fb[k32][tb], acc[vb][tb], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[vb][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[step & 1][j], fb[k32][tb][j], acc[vb][tb], 0, 0, 0);
+            }
             if (part < kSpreadSteps) {
                 if (on) {
 #pragma unroll
@@ -395,7 +426,8 @@ static void plan_sweep(HeadParams& p, int64_t M, int64_t V) {
 // steps, and costs what kChunkCost steps take (fill and drain of the pipeline, the partial tile written and read
 // again).  Measured: 14 x 20 output tiles, K = 152064: 7.19 -> 4.18 ms; 65 x 4 tiles, K = 32000: 1.48 -> 0.90 ms.
 constexpr int kMinChunk = 32, kChunkCost = 40;
-static void plan_product(HeadParams& p, int64_t M, int64_t N, int k_tiles, void* part, size_t part_bytes) {
+static void plan_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes) {
+    const int k_tiles = p.k_tiles;
     p.M = M;
     p.V = (int)N;
     p.row_tiles = (int)((M + kTile - 1) / kTile);
@@ -446,10 +478,11 @@ static bool allow_lds(const void* fn, int lds_bytes) {
 // Clear the arrival counters and launch one sweep (persistent: one workgroup per CU).  A device that does not
 // report 256 compute units (a partition of the chip, another chip) is refused: the sweep would still be
 // correct there, but its workgroups would take turns instead of running side by side.
-template <template <class> class Epi>
+template <class C, template <class> class Epi>
 static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
-    if (!allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<HeadCfg, Epi>), HeadCfg::kLdsBytes)) return TPPO_ERR_LAUNCH;
+    if (!allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes)) return TPPO_ERR_LAUNCH;
+    static_assert(kTile == C::kTileV && kTile == C::kTileT, "the schedule counts in these tiles");
     const int n = arrival_count(p);
     p.arrivals = nullptr;
     if (n > 8 && (size_t)n * sizeof(int32_t) <= arrivals_room) {
@@ -457,7 +490,7 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
         hipLaunchKernelGGL(head_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.arrivals, n);
         if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL((head_mfma_kernel<HeadCfg, Epi>), dim3(kSweepGroups), dim3(HeadCfg::kThreads), HeadCfg::kLdsBytes, s, p);
+    hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(kSweepGroups), dim3(C::kThreads), C::kLdsBytes, s, p);
     return launch_result();
 }
 

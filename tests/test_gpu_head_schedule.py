@@ -40,3 +40,50 @@ def test_logprob_grads_cut_contraction(tp, M, V, H):
     assert np.array_equal(host(again), dh)
     # one fp32 rounding of (2 + dw)
     assert np.abs(host(acc) - 2.0 - dw).max() <= 2.0 ** -23 * (2.0 + np.abs(dw).max())
+
+
+def _padded(a, ld, offset):
+    """The matrix on the GPU with leading dimension `ld`, starting `offset` elements into its allocation, everything
+    around it NaN."""
+    import torch
+    t = dev(a)
+    buf = torch.full((offset + a.shape[0] * ld,), float("nan"), dtype=t.dtype, device="cuda")
+    view = torch.as_strided(buf, t.shape, (ld, 1), offset)
+    view.copy_(t)
+    return view
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("H,pad,offset", [(64, 0, 0),      # whole stages
+                                          (72, 8, 0), (100, 4, 8), (1000, 0, 0),   # a ragged last stage
+                                          (36, 60, 4),     # less than one bf16 stage
+                                          (8, 0, 0), (4, 12, 0),
+                                          (1, 0, 0), (63, 1, 0), (129, 0, 0), (333, 3, 5),   # rows copied to whole chunks
+                                          (128, 8, 3), (96, 1, 0)])   # whole chunks at addresses that are not
+def test_logprobs_any_row_shape(tp, f32, H, pad, offset):
+    M, V, N = 300, 777, 41
+    rng = np.random.default_rng(H + pad)
+    hidden = rng.normal(size=(N, H)).astype(np.float32)
+    w = (rng.normal(size=(V, H)) / np.sqrt(H)).astype(np.float32)
+    if not f32:
+        hidden, w = synth.f32_to_bf16_bits(hidden), synth.f32_to_bf16_bits(w)
+    rows, targets = rng.integers(0, N, size=M), (np.arange(M) * 5 + 1) % V
+    st = tp.new_status("cuda")
+    args = (_padded(hidden, H + pad, offset), _padded(w, H + pad, offset), dev(rows.astype(np.int32)),
+            dev(targets.astype(np.int32)))
+    logp, lse = tp.tppo_token_logprobs(*args, status=st)
+    ref_lp, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    assert int(host(st)[0]) == 0
+    # exact products summed in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
+    assert np.abs(host(logp) - ref_lp).max() <= 1e-5 and np.abs(host(lse) - ref_lse).max() <= 1e-5
+    # the device's token count, and a workspace without room for copies
+    m_dev = dev(np.array([M - 50], np.int64))
+    small = tp._workspace(tp.load().tppo_token_logprobs_workspace_bytes(M, 64, V, tp.TPPO_F32), "cuda")
+    for ws in (None, small):
+        part, _ = tp.tppo_token_logprobs(*args, m_actual=m_dev, workspace=ws, status=st)
+        assert np.abs(host(part)[:M - 50] - ref_lp[:M - 50]).max() <= 1e-5
+    bad = args[2].clone()
+    bad[7] = N
+    part, _ = tp.tppo_token_logprobs(args[0], args[1], bad, args[3], status=st)
+    assert int(host(st)[0]) == tp.STATUS_BAD_ROW and np.isnan(host(part)[7])
+    assert np.abs(np.delete(host(part) - ref_lp, 7)).max() <= 1e-5
