@@ -227,8 +227,7 @@ __device__ __forceinline__ bool poll(const unsigned long long* p, uint32_t tag, 
 uint32_t next_call_tag();
 
 // Enqueue the kernel that builds a plan for (resp_off, done[, keep_len]) in `plan_raw` (plan_bytes_for(cap)
-// bytes) and zeroes its tagged words.  keep_len may be NULL (no set sizes).  n_resp < 0: the kernel takes
-// resp_off[B] for it (a caller whose offsets are still being computed on the stream).
+// bytes) and zeroes its tagged words.  keep_len may be NULL (no set sizes).
 int launch_plan_build(const int32_t* resp_off, const int32_t* keep_len, const int32_t* done, int64_t B,
                       int64_t n_resp, int64_t cap, void* plan_raw, int32_t* status, hipStream_t s);
 

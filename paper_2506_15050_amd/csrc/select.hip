@@ -1,21 +1,28 @@
-// tppo_select: token filter of Sec. 3.2 as a segmented compaction.
-//   kernel 1 (one workgroup per 1024 sequences): per-sequence window / keep lengths, their prefix
-//            sums (resp_off, sel_off), the counts and a list of tiles of the compact
-//            output (<= 1024 kept tokens of one sequence each);
-//   kernel 2 (persistent grid): walks the compact list; a tile's descriptor says
-//            which sequence and which window positions it covers, so every
-//            thread emits (row, target id, response-packed index) for 4
-//            consecutive kept tokens without searching the offset arrays;
-//   and, if the caller wants one, the work plan of the response-packed domain
-//   (plan.h) that tppo_egae* and the loss entry points take, built from the
-//   offsets kernel 1 has just written.
-#include "plan.h"
+// tppo_select: token filter of Sec. 3.2 as a segmented compaction: per-sequence
+// window / keep lengths, their prefix sums (resp_off, sel_off), the counts, then
+// (row, target id, response-packed index) of every kept token and, if the caller
+// wants one, the work plan of the response-packed domain (plan.h) that tppo_egae*
+// and the loss entry points take.
+//   up to kOneLaunchSeqs sequences: ONE launch.  Every workgroup works out all
+//            lengths and prefix sums for itself, in LDS (one sequence per thread),
+//            then plays its part: the small outputs and the plan's list, or a
+//            share of the kept tokens and of the plan's words to zero;
+//   more:    two.  One workgroup per 1024 sequences writes the lengths and prefix
+//            sums and a list of tiles of the compact output (<= 1024 kept tokens of
+//            one sequence each); then the plan's builders and the workgroups that
+//            walk the tile list, side by side.
+// Launches and the chains of dependent loads inside them are what this costs; only beyond some ten million tokens do
+// the bytes written count.  Scan, plan and fill as three launches against now, in a pass over
+// 2.4 M tokens in 512 sequences: 29 -> 12 us; 40 M tokens in 8704 sequences: 111 -> 62 us (278 MB of indices).
+#include "plan_build.h"
 
 namespace tppo {
 
 constexpr int kScanThreads = 1024;
-constexpr int kFillThreads = 256, kFillTpt = kTileTokens / kFillThreads;
-constexpr int kFillMaxGroups = 2048;
+constexpr int kOneLaunchSeqs = kScanThreads;
+constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
+constexpr int kFillMaxGroups = 512;                             // two per CU
+static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");
 
 struct Sums { int win, keep, val, tiles; };     // window / kept / value tokens, tiles of the compact output
 
@@ -82,6 +89,7 @@ __global__ __launch_bounds__(kScanThreads) void select_scan_kernel(
     __syncthreads();
     Sums run = {inc.win - mine.win, inc.keep - mine.keep, inc.val - mine.val, inc.tiles - mine.tiles};
     Sums total = {0, 0, 0, 0};
+#pragma unroll 4
     for (int w = 0; w < kScanThreads / kWave; ++w) {
         if (w < wave) run = add4(run, wave_tot[0][w]);
         run = add4(run, wave_tot[1][w]);
@@ -107,34 +115,201 @@ __global__ __launch_bounds__(kScanThreads) void select_scan_kernel(
     }
 }
 
-__global__ __launch_bounds__(kFillThreads) void select_fill_kernel(
-    const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ ctx_len,
-    const int32_t* __restrict__ input_ids, int n_tok, const int32_t* __restrict__ resp_off,
-    const Tile* __restrict__ tiles, const int32_t* __restrict__ n_tiles,
-    int32_t* __restrict__ sel_rows, int32_t* __restrict__ sel_targets,
-    int32_t* __restrict__ sel_resp_idx, int64_t capacity, int32_t* status) {
+struct FillArgs {
+    const int32_t *cu_seqlens, *ctx_len, *input_ids;
+    int32_t *sel_rows, *sel_targets, *sel_resp_idx;
+    int64_t capacity;
+    int n_tok;
+    int32_t* status;
+};
+
+// Second launch of the large case.  Workgroups 0 .. parts-1 build the plan's list and workgroup `parts` counts its
+// sets (none of these without a plan); the others zero the plan's words and walk the compact tile list, four
+// tiles at a time.
+__global__ __launch_bounds__(kBuildThreads) void select_fill_kernel(FillArgs a, const int32_t* __restrict__ resp_off,
+                                                                    const int32_t* __restrict__ keep_len,
+                                                                    const int32_t* __restrict__ done, int B,
+                                                                    const Tile* __restrict__ tiles,
+                                                                    const int32_t* __restrict__ n_tiles, int parts,
+                                                                    int plan_cap, void* plan_raw) {
+    __shared__ union {
+        BuildLds build;
+        SetLds sets;
+    } s;
+    int worker = blockIdx.x, workers = gridDim.x;
+    if (plan_raw) {
+        const Plan pl = plan_view(plan_raw, plan_cap);
+        if (worker < parts) {
+            build_list(pl, s.build, resp_off, keep_len, done, true, B, resp_off[B], worker, parts, a.status);
+            return;
+        }
+        if (worker == parts) {
+            count_sets(pl, s.sets, resp_off, keep_len, done, B);
+            return;
+        }
+        worker -= parts + 1;
+        workers -= parts + 1;
+        clear_words(pl, worker, workers);
+    }
+    if (!tiles) return;
     const int count = *n_tiles;
-    const int tid = threadIdx.x;
-    for (int w = blockIdx.x; w < count; w += gridDim.x) {
+    const int quarter = threadIdx.x / kQuarter, tid = threadIdx.x % kQuarter;
+    for (int w = worker * 4 + quarter; w < count; w += workers * 4) {
         const Tile t = tiles[w];
         const int i = t.seg, len = t.len(), t0 = t.number() * kTileTokens;
-        const int first_pos = cu_seqlens[i] + ctx_len[i] + t0;      // packed position of the tile's first token
+        const int first_pos = a.cu_seqlens[i] + a.ctx_len[i] + t0;  // packed position of the tile's first token
         const int first_resp = resp_off[i] + t0;
 #pragma unroll
-        for (int q = 0; q < kFillTpt; ++q) {
-            const int k = q * kFillThreads + tid;                    // lane-consecutive: coalesced stores
+        for (int q = 0; q < kTileTokens / kQuarter; ++q) {
+            const int k = q * kQuarter + tid;                        // lane-consecutive: coalesced stores
             const int64_t m = (int64_t)t.start + k;
             if (k < len) {
-                if (m >= capacity) {
-                    if (m == capacity) set_status(status, TPPO_STATUS_CAPACITY);
+                if (m >= a.capacity) {
+                    if (m == a.capacity) set_status(a.status, TPPO_STATUS_CAPACITY);
                 } else {
                     const int pos = first_pos + k;
-                    if (sel_rows) sel_rows[m] = pos - 1;
-                    if (sel_targets) sel_targets[m] = (pos >= 0 && pos < n_tok) ? input_ids[pos] : -1;
-                    if (sel_resp_idx) sel_resp_idx[m] = first_resp + k;
+                    if (a.sel_rows) a.sel_rows[m] = pos - 1;
+                    if (a.sel_targets) a.sel_targets[m] = (pos >= 0 && pos < a.n_tok) ? a.input_ids[pos] : -1;
+                    if (a.sel_resp_idx) a.sel_resp_idx[m] = first_resp + k;
                 }
             }
         }
+    }
+}
+
+// The whole filter in one launch, B <= kOneLaunchSeqs.  Workgroup 0 writes the small outputs and the plan's list;
+// the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
+// sequence a thread finds by bisection of the offsets in LDS.
+typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_some(int32_t* dst, int64_t m, const int (&x)[4], int n) {
+    if (n == 4) {
+        *reinterpret_cast<int4u*>(dst + m) = int4u{x[0], x[1], x[2], x[3]};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < n) dst[m + e] = x[e];
+    }
+}
+
+__global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillArgs a, const int32_t* __restrict__ done, int B,
+                                                                          int tail_drop, int32_t* __restrict__ resp_off,
+                                                                          int32_t* __restrict__ sel_off,
+                                                                          int32_t* __restrict__ keep_len,
+                                                                          int64_t* __restrict__ counts, int plan_cap,
+                                                                          void* plan_raw) {
+    __shared__ int32_t s_resp[kOneLaunchSeqs + 1], s_sel[kOneLaunchSeqs + 1], s_aux[2][kOneLaunchSeqs];
+    __shared__ int s_wave[2][kBuildWaves], s_val[kBuildWaves];
+    __shared__ BuildLds s_build;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool lead = blockIdx.x == 0;                               // (also of a grid of one, which then does everything)
+    const int worker = (int)blockIdx.x - 1, workers = (int)gridDim.x - 1;
+    Sums mine = {0, 0, 0, 0};
+    int first_pos = 0;
+    bool fin = false;
+    if (tid < B) {
+        mine = lengths_of(a.cu_seqlens, a.ctx_len, done, tid, a.n_tok, tail_drop, lead ? a.status : nullptr);
+        first_pos = a.cu_seqlens[tid] + a.ctx_len[tid];
+        fin = done[tid] != 0;
+    }
+    const Plan pl = plan_view(plan_raw, plan_cap);
+    if (plan_raw && !lead) clear_words(pl, worker, workers);         // (while the lengths are on their way)
+    int win = mine.win, keep = mine.keep, val = mine.val;            // inclusive prefix sums (val: only the total matters)
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int w = __shfl_up(win, off), k = __shfl_up(keep, off);
+        if (lane >= off) {
+            win += w;
+            keep += k;
+        }
+        val += __shfl_xor(val, off);
+    }
+    if (lane == kWave - 1) {
+        s_wave[0][wave] = win;
+        s_wave[1][wave] = keep;
+        s_val[wave] = val;
+    }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) {
+        win += s_wave[0][w];
+        keep += s_wave[1][w];
+    }
+    if (tid == 0) s_resp[0] = s_sel[0] = 0;
+    s_resp[tid + 1] = win;
+    s_sel[tid + 1] = keep;
+    s_aux[0][tid] = lead ? mine.keep : first_pos;
+    s_aux[1][tid] = fin;
+    __syncthreads();
+    const int n_kept = s_sel[B];
+    if (lead) {
+        if (tid < B) {
+            keep_len[tid] = mine.keep;
+            resp_off[tid + 1] = win;
+            sel_off[tid + 1] = keep;
+        }
+        if (tid == 0) {
+            resp_off[0] = 0;
+            sel_off[0] = 0;
+            long long n_val = 0;
+            for (int w = 0; w < kBuildWaves; ++w) n_val += s_val[w];
+            counts[0] = n_kept;
+            counts[1] = s_resp[B];
+            counts[2] = n_val;
+            if ((a.sel_rows || a.sel_targets || a.sel_resp_idx) && n_kept > a.capacity)
+                set_status(a.status, TPPO_STATUS_CAPACITY);
+            if (plan_raw) {
+                pl.hdr->n_policy = n_kept;
+                pl.hdr->n_value = n_val;
+                pl.hdr->has_sets = 1;
+            }
+        }
+        if (plan_raw)
+            build_list(pl, s_build, (const int32_t*)s_resp, (const int32_t*)s_aux[0], (const int32_t*)s_aux[1], true, B,
+                       s_resp[B], 0, 1, a.status);
+        return;
+    }
+    if (!a.sel_rows && !a.sel_targets && !a.sel_resp_idx) return;
+    const int64_t n = min((int64_t)n_kept, a.capacity);
+    for (int64_t m = ((int64_t)worker * kBuildThreads + tid) * 4; m < n; m += (int64_t)workers * kBuildThreads * 4) {
+        int lo = 0, hi = B - 1;                                      // the last sequence that begins at or before m
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_sel[mid] <= m) lo = mid; else hi = mid - 1;
+        }
+        const int some = (int)min(n - m, (int64_t)4);
+        int pos[4], resp[4], id[4];
+        const bool run = m + 4 <= s_sel[lo + 1];                     // all four in one sequence
+        if (run) {
+            const int t = (int)m - s_sel[lo];
+            const int p0 = s_aux[0][lo] + t, r0 = s_resp[lo] + t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                pos[e] = p0 + e;
+                resp[e] = r0 + e;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                while (lo < B - 1 && s_sel[lo + 1] <= (int)m + e) ++lo;
+                const int t = (int)m + e - s_sel[lo];
+                pos[e] = s_aux[0][lo] + t;
+                resp[e] = s_resp[lo] + t;
+            }
+        }
+        if (a.sel_targets) {
+            if (run && pos[0] >= 0 && pos[0] <= a.n_tok - 4) {
+                const int4u x = *reinterpret_cast<const int4u*>(a.input_ids + pos[0]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) id[e] = x[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) id[e] = (e < some && pos[e] >= 0 && pos[e] < a.n_tok) ? a.input_ids[pos[e]] : -1;
+            }
+            store_some(a.sel_targets, m, id, some);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pos[e] -= 1;
+        if (a.sel_rows) store_some(a.sel_rows, m, pos, some);
+        if (a.sel_resp_idx) store_some(a.sel_resp_idx, m, resp, some);
     }
 }
 
@@ -170,6 +345,22 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
     if (plan && (!is_aligned(plan, 256) || plan_bytes < plan_bytes_for(plan_cap) || plan_cap > INT32_MAX / 8))
         return TPPO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    FillArgs a = {cu_seqlens, ctx_len, input_ids, nullptr, nullptr, nullptr, capacity, (int)n_tok, status};
+    if (want_fill) {
+        a.sel_rows = sel_rows;
+        a.sel_targets = sel_targets;
+        a.sel_resp_idx = sel_resp_idx;
+    }
+    // enough workgroups that zero or fill to keep every CU busy, each with a few turns on a large batch
+    const int64_t clear = plan ? (plan_words(plan_cap) + kBuildThreads * 8 - 1) / (kBuildThreads * 8) : 0;
+    const int64_t fill = want_fill ? (n_tok + kBuildThreads * 4 - 1) / (kBuildThreads * 4) : 0;
+    const int64_t most = clear > fill ? clear : fill;
+    const int workers = (int)(most < kFillMaxGroups ? most : kFillMaxGroups);
+    if (B <= kOneLaunchSeqs) {
+        hipLaunchKernelGGL(select_one_launch_kernel, dim3(1 + workers), dim3(kBuildThreads), 0, s, a, done, (int)B,
+                           (int)tail_drop, resp_off, sel_off, keep_len, counts, (int)plan_cap, plan);
+        return launch_result();
+    }
     Tile* tiles = want_fill ? static_cast<Tile*>(workspace) : nullptr;
     int32_t* n_tiles = want_fill ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) +
                                                               round_up((size_t)cap64 * sizeof(Tile), 256))
@@ -179,15 +370,9 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
                        done, (int)B, (int)n_tok, (int)tail_drop, parts, resp_off, sel_off, keep_len, counts,
                        tiles, (int)cap64, n_tiles, status);
     if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
-    // n_resp is known on the device only: the builder reads it from the offsets
-    if (plan && launch_plan_build(resp_off, keep_len, done, B, -1, plan_cap, plan, status, s) != TPPO_OK)
-        return TPPO_ERR_LAUNCH;
-    if (want_fill) {
-        const int groups = (int)(cap64 < kFillMaxGroups ? cap64 : kFillMaxGroups);
-        hipLaunchKernelGGL(select_fill_kernel, dim3(groups), dim3(kFillThreads), 0, s, cu_seqlens,
-                           ctx_len, input_ids, (int)n_tok, resp_off, tiles, n_tiles, sel_rows,
-                           sel_targets, sel_resp_idx, capacity, status);
-        if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
-    }
-    return TPPO_OK;
+    const int groups = (plan ? parts + 1 : 0) + workers;             // n_resp is known on the device only
+    if (groups == 0) return TPPO_OK;
+    hipLaunchKernelGGL(select_fill_kernel, dim3(groups), dim3(kBuildThreads), 0, s, a, resp_off, keep_len, done, (int)B,
+                       tiles, n_tiles, parts, (int)plan_cap, plan);
+    return launch_result();
 }
