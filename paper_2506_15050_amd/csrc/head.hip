@@ -2,8 +2,8 @@
 // W_head h fused with log-softmax and the gather of the sampled token's logit
 // (the quantity inside the ratio of Eq. (ppoloss)); logits never reach memory.
 //
-// bf16 path (matrix cores).  The logits of a 256-token x 256-vocabulary tile
-// are accumulated with v_mfma_f32_16x16x32_bf16 (head_tile.h).
+// Matrix-core path.  The logits of a 256-token x 256-vocabulary tile (64 x 128 in
+// calls too small for those) are accumulated with v_mfma_f32_16x16x32_bf16 (head_tile.h).
 // The MFMA "row" operand is the W tile and the "column" operand the gathered
 // hidden rows, so the accumulators a lane holds for one block all belong to ONE
 // token (column lane % 16) and to different vocabulary entries: the running
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kGenThreads) void head_generic_kernel(
 
 // ------------------------------------------------------------------ MFMA path
 // Per-lane running log-softmax state of the kTB token columns a lane owns, and
-// the two steps that use it: folding a finished 256-wide vocabulary tile, and
+// the two steps that use it: folding a finished vocabulary tile, and
 // the final merge across lane halves / waves.
 template <class C>
 struct LaneSoftmax {
@@ -364,14 +364,19 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     typedef HeadCfg<T, false> Whole;
     typedef HeadCfg<T, true> Ragged;
     p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
-    plan_sweep(p, M, V);
-    const int64_t first_tokens = (int64_t)p.first.rows * kTile, rest_tokens = (int64_t)p.rest.rows * kTile;
+    const double large = plan_sweep(p, M, V);
+    const bool small = plan_small(p, M, V, sizeof(T) == 2, large);
+    const int tile = small ? SmallShape::kTileT : kTile;
+    const int64_t first_tokens = (int64_t)p.first.rows * tile, rest_tokens = (int64_t)p.rest.rows * tile;
     const size_t room = arrivals_bytes(M);
     char* ws = static_cast<char*>(workspace);
     p.part_first = reinterpret_cast<float*>(ws + room);
     p.part_rest = p.part_first + 3 * first_tokens * p.first.cols;
-    const int rc = p.H % Whole::kBK == 0 ? launch_sweep<Whole, LaneSoftmax>(p, ws, room, s)
-                                         : launch_sweep<Ragged, LaneSoftmax>(p, ws, room, s);
+    const bool whole = p.H % Whole::kBK == 0;
+    const int rc = small ? (whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, room, s)
+                                  : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, room, s))
+                         : (whole ? launch_sweep<Whole, LaneSoftmax>(p, ws, room, s)
+                                  : launch_sweep<Ragged, LaneSoftmax>(p, ws, room, s));
     if (rc != TPPO_OK) return rc;
     const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
     hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),

@@ -65,7 +65,7 @@ struct HeadParams {
 // and fragments.  fp32 runs four v_mfma_f32_16x16x4_f32 on a pair of 16-byte fragments: MFMA j takes element j of
 // every lane's chunk, i.e. k = j, 4 + j, 8 + j, 12 + j of the 16 -- the same set on both sides, in another order.
 // Its matrix rate is a sixteenth of bf16's, so nothing else matters there (measured: 2064 tokens, H = 1024,
-// V = 32000: 1.2 ms, 110 TFLOP/s of the 154 a large fp32 product reaches here; one token per workgroup with
+// V = 32000: 1.1 ms, 124 TFLOP/s of the 154 a large fp32 product reaches here; one token per workgroup with
 // plain multiply-adds took 77-80 ms).
 //
 // For bf16 the MFMA is v_mfma_f32_16x16x32_bf16: same flops per cycle and same LDS bytes per flop as 32x32x16, but at the
@@ -75,17 +75,18 @@ struct HeadParams {
 // l / 16 of the MFMA's K range.
 // RAGGED: H is not a multiple of a stage, and the chunks of the last one that lie beyond it are fetched as zeros (a
 // variant of its own: the selects cost registers that the plain one does not have to spare).
-template <typename T, bool RAGGED>
+// SMALL: 128 x 64 tiles and workgroups of 2 x 2 wavefronts, three to a CU, for calls that would leave much of the
+// chip idle with the large ones (plan_small has the line between them).
+template <typename T, bool RAGGED, bool SMALL = false>
 struct HeadCfg {
-    static constexpr bool kRagged = RAGGED;
+    static constexpr bool kRagged = RAGGED, kSmall = SMALL;
     static constexpr int kEsz = sizeof(T), kPerChunk = 16 / kEsz;         // elements of a 16-byte chunk
     typedef typename std::conditional<kEsz == 2, bf16x8, f32x4>::type Frag;
     static constexpr int kMI = 16, kGroups = 64 / kMI, kAccElems = 4;
     typedef float Acc __attribute__((__vector_size__(kAccElems * sizeof(float))));
-    static constexpr int kTileV = 256, kTileT = 256, kWavesV = 2, kWavesT = 4, kBK = 128 / kEsz, kStages = 2;
-    // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
-    // a full memory queue
-    static constexpr int kSpread = 32;
+    static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 256;
+    static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
+    static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
     static constexpr int kWaves = kWavesV * kWavesT, kThreads = kWaves * 64;
     static constexpr int kWaveV = kTileV / kWavesV, kWaveT = kTileT / kWavesT;    // wave tile
     static constexpr int kVB = kWaveV / kMI, kTB = kWaveT / kMI;                  // 16 x 16 blocks per wave
@@ -99,6 +100,9 @@ struct HeadCfg {
     static constexpr int kDmaPerStage = kRows / kRowsPerDma;
     static constexpr int kDmaPerWave = kDmaPerStage / kWaves;
     static constexpr int kKSteps = (kChunks / 4) * kVB;
+    // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
+    // a full memory queue
+    static constexpr int kSpread = SMALL ? kKSteps * kMfmaPerStep : 32;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");
     static_assert(kKSteps % 2 == 0, "fragment double buffering assumes an even number of K steps");
@@ -193,13 +197,13 @@ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int all_k_ti
 
 // Epi (the per-lane epilogue) provides
 //   init(p, tok0, m_eff, wt, lane)                          once per task,
-//   fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane)       after each finished tile of 256 W rows; clears acc,
+//   fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane)       after each finished tile of W rows; clears acc,
 //   finish(p, lds_scratch, task, tok0, m_eff, wv, wt, lane, tid)  after the task's tiles (workgroup-wide).
 // what the chunks beyond a ragged H hold, in both operands
 static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
 template <class C, template <class> class Epi>
-__global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(HeadParams p) {
+__global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void head_mfma_kernel(HeadParams p) {
     constexpr int kTileV = C::kTileV, kTileT = C::kTileT, kWaveV = C::kWaveV, kWaveT = C::kWaveT;
     constexpr int kVB = C::kVB, kTB = C::kTB;
     constexpr int kDmaPerWave = C::kDmaPerWave, kKSteps = C::kKSteps;
@@ -213,9 +217,10 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves / 4) void head_mfma_kernel(H
     const int frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    for (int t = xcd * kXcdGroups + slot; t < p.n_tasks; t += kSweepGroups) {
+    const int t_first = C::kSmall ? (int)blockIdx.x : xcd * kXcdGroups + slot, t_step = C::kSmall ? (int)gridDim.x : kSweepGroups;
+    for (int t = t_first; t < p.n_tasks; t += t_step) {
     const int round = t / kSweepGroups;
-    if (round > 0 && p.arrivals)                            // the first round starts aligned
+    if (!C::kSmall && round > 0 && p.arrivals)                            // the first round starts aligned
         align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
     const Task task = task_at(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
@@ -389,7 +394,8 @@ static double rounds_of(int64_t tasks) { return (double)((tasks + kSweepGroups -
 // rounded up: 4 token tiles x 594 W tiles (10 instead of 19 tile times per workgroup; half of each unit's workgroups
 // had no token tile) 2.24 -> 1.25 ms; 54 x 125 tiles 0.79 -> 0.75 ms; 227 x 594 tiles (533 instead of 574 tile
 // times) 48.0 -> 45.6 ms; 248 x 594 (580 instead of 612) 1.3 %: there the busier chip clocks lower.
-static void plan_sweep(HeadParams& p, int64_t M, int64_t V) {
+// Returns the cost.
+static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
     p.M = M;
     p.V = (int)V;
     p.row_tiles = (int)((M + kTile - 1) / kTile);
@@ -418,6 +424,47 @@ static void plan_sweep(HeadParams& p, int64_t M, int64_t V) {
     p.rest_tasks = p.rest.rows * best_cols;
     p.k_chunks = 1;
     p.n_tasks = p.first_tasks + p.rest_tasks;
+    return best;
+}
+
+// The same sweep in 128 x 64 tiles, one workgroup per task, if that is the faster way; true if so.  A small tile is an
+// eighth of a large one's work and takes n / 8 of its time where n share a CU.  fp32, which the matrix cores bound,
+// loses 6 % to the smaller tile; for bf16 the traffic from L2 makes it up to 2.5 times slower per flop, so there it
+// only serves what would leave most of the chip idle.  Measured, large -> small (us):
+//   bf16: 146 tokens x V 1000, H 64: 14.8 -> 10.4;  x V 5000, H 1024: 35.6 -> 18.5;  x V 32000, H 512: 30.0 -> 26.1;
+//         20 x V 152064, H 5120: 478 -> 403.  Where the rule says large: 300 x V 32000, H 512: 29.7 (34.2),
+//         146 x V 50021, H 1024: 42.2 (57.9), 2500 x V 5000, H 1024: 39.3 (47.4), 1000 x V 152064, H 5120: 1297 (2950)
+//   fp32: 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  300 x V 32000, H 1024: 264 -> 210;
+//         2064 x V 32000, H 1024: 1281 -> 1093.  Large: 1000 x V 32000, H 1024: 508 (601)
+typedef HeadCfg<uint16_t, false, true> SmallShape;
+constexpr int kSmallPerCu = SmallShape::kGroupsPerCu;
+constexpr double kSmallPart = (double)SmallShape::kTileV * SmallShape::kTileT / ((double)kTile * kTile);
+static bool plan_small(HeadParams& p, int64_t M, int64_t V, bool bf16, double large_cost) {
+    const int64_t rows = (M + SmallShape::kTileT - 1) / SmallShape::kTileT, vts = (V + SmallShape::kTileV - 1) / SmallShape::kTileV;
+    const double slower = bf16 ? 2.5 : 1.06;
+    double best = large_cost;
+    int64_t best_cols = 0;
+    for (int64_t s = 1; s <= vts && s <= kMaxSplits; ++s) {
+        // (no more partial results than most_triples() has room for)
+        if (s > 4 && rows * s * SmallShape::kTileT > kRestTasks * kTile) break;
+        const int64_t tasks = rows * s, full = tasks / (kSweepGroups * kSmallPerCu), rest = tasks % (kSweepGroups * kSmallPerCu);
+        const double shares = (double)(full * kSmallPerCu) + rounds_of(rest);      // tasks in turn on the busiest CU
+        const double cost = shares * kSmallPart * ((double)((vts + s - 1) / s) + kTaskCost) * slower;
+        if (cost < best - 1e-9) { best = cost; best_cols = s; }
+    }
+    if (best_cols == 0) return false;
+    p.M = M;
+    p.V = (int)V;
+    p.row_tiles = (int)rows;
+    p.vocab_tiles = (int)vts;
+    p.first = {0, 0, 1};
+    p.first_tasks = 0;
+    p.rest = {0, (int)rows, (int)best_cols};
+    p.rest_base = 0;
+    p.rest_tasks = (int)(rows * best_cols);
+    p.k_chunks = 1;
+    p.n_tasks = p.rest_tasks;
+    return true;
 }
 
 // Plain product of M token-role rows and N W-role rows over K = 64 * k_tiles, columns = W-role tiles.  Whole rounds
@@ -481,16 +528,18 @@ static bool allow_lds(const void* fn, int lds_bytes) {
 template <class C, template <class> class Epi>
 static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
-    if (!allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes)) return TPPO_ERR_LAUNCH;
-    static_assert(kTile == C::kTileV && kTile == C::kTileT, "the schedule counts in these tiles");
-    const int n = arrival_count(p);
+    if (C::kLdsBytes > 64 * 1024 && !allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes))
+        return TPPO_ERR_LAUNCH;
+    static_assert(C::kSmall || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
+    const int n = C::kSmall ? 0 : arrival_count(p);
     p.arrivals = nullptr;
     if (n > 8 && (size_t)n * sizeof(int32_t) <= arrivals_room) {
         p.arrivals = static_cast<int32_t*>(arrivals);
         hipLaunchKernelGGL(head_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.arrivals, n);
         if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(kSweepGroups), dim3(C::kThreads), C::kLdsBytes, s, p);
+    hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(C::kSmall ? p.n_tasks : kSweepGroups), dim3(C::kThreads),
+                       C::kLdsBytes, s, p);
     return launch_result();
 }
 

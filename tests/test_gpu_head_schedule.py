@@ -42,6 +42,31 @@ def test_logprob_grads_cut_contraction(tp, M, V, H):
     assert np.abs(host(acc) - 2.0 - dw).max() <= 2.0 ** -23 * (2.0 + np.abs(dw).max())
 
 
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("M,V", [(1, 1), (1, 129), (63, 127), (64, 128), (65, 1000), (130, 5003), (700, 2000)])
+@pytest.mark.parametrize("H", [64, 72, 192])
+def test_logprobs_small_tiles(tp, f32, M, V, H):
+    """Sizes that go to the 128 x 64 tiles: edges of a tile, one task and many."""
+    rng = np.random.default_rng(M + V + H)
+    hidden = rng.normal(size=(90, H)).astype(np.float32)
+    w = (rng.normal(size=(V, H)) / np.sqrt(H)).astype(np.float32)
+    if not f32:
+        hidden, w = synth.f32_to_bf16_bits(hidden), synth.f32_to_bf16_bits(w)
+    rows, targets = rng.integers(0, 90, size=M), (np.arange(M) * 7 + V - 1) % V
+    out = dev(rng.permutation(M + 5)[:M].astype(np.int32))
+    logp, lse = tp.tppo_token_logprobs(dev(hidden), dev(w), dev(rows.astype(np.int32)), dev(targets.astype(np.int32)),
+                                       out_index=out, out_size=M + 5)
+    ref_lp, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    at = host(out)
+    # exact products summed in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
+    assert np.abs(host(logp)[at] - ref_lp).max() <= 1e-5 and np.abs(host(lse)[at] - ref_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("M,V", [(1, 64), (65, 129), (200, 1000), (130, 5003)])
+def test_logprob_grads_small_tiles(tp, M, V):
+    check_logprob_grads(tp, *_bf16_case(M, V, 128, seed=M + V))
+
+
 def _padded(a, ld, offset):
     """The matrix on the GPU with leading dimension `ld`, starting `offset` elements into its allocation, everything
     around it NaN."""
