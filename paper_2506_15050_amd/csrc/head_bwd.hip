@@ -7,8 +7,9 @@
 // The logits are recomputed tile by tile with the forward kernel's sweep, whose
 // epilogue here turns each finished tile into dz and writes it as bf16 for a
 // chunk of tokens at a time; the two products are the same sweep again with a
-// plain store epilogue (both operands K-contiguous: W^T, dZ^T and the gathered
-// Hid^T are made by a tiled transpose).
+// plain store epilogue.  W in the first and dZ in the second have K as their row
+// index and are read that way (K-major operands, head_tile.h); only the gathered
+// Hid^T, H x tokens, is made by a tiled transpose.
 #include "head_tile.h"
 
 namespace tppo {
@@ -236,12 +237,18 @@ static int launch_transpose(const uint16_t* src, int64_t rows, int64_t cols, int
 
 using BwdCfg = HeadCfg<uint16_t, false>;
 
-// out[M, N] (+)= tokens[M, K] . w_role[N, K]^T; `part` is scratch for the tiles whose contraction is cut
+// out[M, N] (+)= tokens[M, K] . w_role[N, K]^T, one of the two K-major; `part` is scratch for the tiles whose
+// contraction is cut.  Transposing W and dZ first (both operands read along K, b128 fragments) moves 2 x 2 bytes per entry
+// of both through memory, 7 to 13 % of the call, and needs their room; the K-major sweep itself is 2 to 6 % slower
+// (twice the LDS instructions for one operand).  Whole call, transposes -> now: 16414 tokens, H = 1024, V = 32000:
+// 3.28 -> 2.91 ms; 3514 tokens, H = 5120, V = 152064: 14.38 -> 13.69 ms.
+template <int KMAJOR>
 static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, void* arrivals,
                           size_t arrivals_room, hipStream_t s) {
     p.k_tiles = p.H / BwdCfg::kBK;
     plan_product(p, M, N, part, part_bytes);
-    if (launch_sweep<BwdCfg, StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK)
+        return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
     hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
     return launch_result();
@@ -251,17 +258,22 @@ constexpr int64_t kBwdChunkDefault = 98304, kBwdChunkMax = 98304;
 
 struct BwdLayout {
     int64_t v_pad, chunk;              // vocabulary padded to 64; tokens per chunk (multiple of 256)
-    size_t off_wt, off_dz, off_dzt, off_hidt, off_arrivals, total;
+    size_t off_dz, off_part, off_hidt, off_arrivals, total;
+    size_t part_bytes;
 };
+
+// Room for the partial tiles of a cut contraction: 512 of them, two rounds, and no more than dZ itself takes.
+constexpr size_t kPartBytes = (size_t)512 * kTile * kTile * sizeof(float);
 
 static BwdLayout bwd_layout(int64_t H, int64_t V, int64_t chunk) {
     BwdLayout L;
     L.v_pad = (V + 63) / 64 * 64;
     L.chunk = chunk;
     size_t o = 0;
-    L.off_wt = o;       o += round_up((size_t)H * L.v_pad * 2, 256);           // W^T   [H, v_pad]
-    L.off_dz = o;       o += round_up((size_t)chunk * L.v_pad * 2, 256);       // dZ    [chunk, v_pad]
-    L.off_dzt = o;      o += round_up((size_t)L.v_pad * chunk * 2, 256);       // dZ^T  [v_pad, chunk]
+    const size_t dz = round_up((size_t)chunk * L.v_pad * 2, 256);
+    L.part_bytes = dz < kPartBytes ? dz : kPartBytes;
+    L.off_dz = o;       o += dz;                                               // dZ    [chunk, v_pad]
+    L.off_part = o;     o += L.part_bytes;
     L.off_hidt = o;     o += round_up((size_t)H * chunk * 2, 256);             // Hid^T [H, chunk]
     L.off_arrivals = o; o += arrivals_bytes(chunk > V ? chunk : V);
     L.total = o;
@@ -303,19 +315,14 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
     if (chunk < 256) return TPPO_ERR_WORKSPACE;
     const BwdLayout L = bwd_layout(H, V, chunk);
     char* ws = static_cast<char*>(workspace);
-    uint16_t* wt = reinterpret_cast<uint16_t*>(ws + L.off_wt);
     uint16_t* dz = reinterpret_cast<uint16_t*>(ws + L.off_dz);
-    uint16_t* dzt = reinterpret_cast<uint16_t*>(ws + L.off_dzt);
     uint16_t* hidt = reinterpret_cast<uint16_t*>(ws + L.off_hidt);
-    void* arrivals = ws + L.off_arrivals;
-    const size_t room = L.total - L.off_arrivals, dz_bytes = (size_t)chunk * L.v_pad * 2;
+    void *arrivals = ws + L.off_arrivals, *part = ws + L.off_part;
+    const size_t room = L.total - L.off_arrivals;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t* hid = static_cast<const uint16_t*>(hidden);
     const uint16_t* w = static_cast<const uint16_t*>(w_head);
 
-    if (grad_hidden) {      // W^T [H, v_pad], K (= vocabulary) contiguous; padding columns are zero
-        if (launch_transpose(w, V, H, ld_w, nullptr, V, wt, L.v_pad, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
-    }
     for (int64_t m0 = 0; m0 < M; m0 += chunk) {
         const int64_t mc = M - m0 < chunk ? M - m0 : chunk;
         const int64_t m_pad = (mc + 63) / 64 * 64;
@@ -333,27 +340,26 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         if ((small ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
                    : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;
-        // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: rows of W^T; K = v_pad)
+        // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: columns of W; K = v_pad)
         if (grad_hidden) {
             HeadParams q = {};
             q.hidden = dz; q.n_rows = mc; q.ld_h = L.v_pad;
-            q.w = wt; q.ld_w = L.v_pad; q.H = (int)L.v_pad;
+            q.w = w; q.ld_w = ld_w; q.H = (int)L.v_pad;
+            q.km_rows = (int)V; q.km_cols = (int)H;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
-            // (dZ^T is not made yet: its place holds the partial tiles)
-            if (launch_product(q, mc, H, dzt, dz_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<1>(q, mc, H, part, L.part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
-        // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: rows of dZ^T; W role: rows of Hid^T; K = m_pad)
+        // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: columns of dZ; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
-            if (launch_transpose(dz, mc, L.v_pad, L.v_pad, nullptr, mc, dzt, m_pad, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
             if (launch_transpose(hid, mc, H, ld_hidden, sel_rows + m0, n_rows, hidt, m_pad, s) != TPPO_OK)
                 return TPPO_ERR_LAUNCH;
             HeadParams q = {};
-            q.hidden = dzt; q.n_rows = V; q.ld_h = m_pad;
+            q.hidden = dz; q.n_rows = mc; q.ld_h = L.v_pad;
             q.w = hidt; q.ld_w = m_pad; q.H = (int)m_pad;
+            q.km_rows = (int)mc; q.km_cols = (int)L.v_pad;
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
-            // (dZ is not needed any more: its place holds the partial tiles)
-            if (launch_product(q, V, H, dz, dz_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<2>(q, V, H, part, L.part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;

@@ -49,6 +49,7 @@ struct HeadParams {
     void* out;                             // tile output
     int64_t ld_out, out_cols;              // leading dimension / columns of `out` that exist
     int accumulate;                        // add to `out` instead of overwriting it
+    int km_rows, km_cols;                  // a K-major operand: K rows that exist (zeros beyond), columns that exist
 };
 
 // The kernel's shape: a kTileV x kTileT (vocabulary x tokens) output tile per workgroup of kWavesV x kWavesT
@@ -77,9 +78,15 @@ struct HeadParams {
 // variant of its own: the selects cost registers that the plain one does not have to spare).
 // SMALL: 128 x 64 tiles and workgroups of 2 x 2 wavefronts, three to a CU, for calls that would leave much of the
 // chip idle with the large ones (plan_small has the line between them).
-template <typename T, bool RAGGED, bool SMALL = false>
+// KMAJOR (bf16, large tiles): one operand lies in memory with K as the ROW index -- 1 the W-role one, 2 the token-role
+// one; element (row r, k) is at base[k * ld + r].  A stage of it is kBK rows of 512 bytes, K row k's 16-byte chunk c in
+// slot c ^ swz_k(k), and ds_read_b64_tr_b16 takes fragments out transposed: 16 lanes read 4 K rows x 16 columns, lane i
+// gets column i's four.  Two of them make the fragment one ds_read_b128 gives of the other layout.
+template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0>
 struct HeadCfg {
     static constexpr bool kRagged = RAGGED, kSmall = SMALL;
+    static constexpr int kKMajor = KMAJOR;
+    static constexpr bool kOneTile = KMAJOR != 0;      // products: a task is one output tile
     static constexpr int kEsz = sizeof(T), kPerChunk = 16 / kEsz;         // elements of a 16-byte chunk
     typedef typename std::conditional<kEsz == 2, bf16x8, f32x4>::type Frag;
     static constexpr int kMI = 16, kGroups = 64 / kMI, kAccElems = 4;
@@ -110,6 +117,12 @@ struct HeadCfg {
     static_assert(kStages == 2 && kSpread <= kKSteps * kMfmaPerStep, "spread issue: at most one stage's worth of MFMAs");
     __device__ static __forceinline__ int swz(int r) { return (r >> 1) & 7; }
     __device__ static __forceinline__ int chunk_off(int r, int c) { return r * kRowBytes + ((c ^ swz(r)) << 4); }
+    // K-major operand: the 32 lanes that a tr read serves at a time cover 8 K rows, {0 .. 3, 8 .. 11} + 4 h (mod 16),
+    // of 32 bytes each; this spreads them over the 8 places of the 256-byte bank window
+    static constexpr int kKRowBytes = 512;
+    __device__ static __forceinline__ int swz_k(int k) { return ((k & 3) | ((k >> 3) & 1) << 2) << 1; }
+    static_assert(KMAJOR == 0 || (kEsz == 2 && !SMALL && !RAGGED && kTileV * kEsz == kKRowBytes && kTileT == kTileV),
+                  "K-major stages are laid out for 256 columns of 2 bytes");
     // row (inside the wave tile's W rows) of accumulator element e of block vb, for lane group g = lane / 16
     __device__ static __forceinline__ int row_in_wave(int vb, int e, int g) { return vb * kMI + g * 4 + e; }
 };
@@ -232,12 +245,29 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const int ld_row0 = wave * kDmaPerWave * C::kRowsPerDma + lane / C::kChunks;   // + q * kRowsPerDma
     const int ld_slot = lane % C::kChunks;
     const char* src[kDmaPerWave];
-    const int k_first = task.k_begin * C::kRowBytes, k_bytes = p.H * C::kEsz;
+    const int k_bytes = p.H * C::kEsz;
     const int64_t ld_w = p.ld_w * C::kEsz, ld_h = p.ld_h * C::kEsz;
-    int issue_vt = vt_begin, issue_kt = 0, issue_stage = 0, issue_kpos = k_first;
+    // this wavefront's transfers are all of one operand
+    constexpr int kVWaves = kTileV / (kDmaPerWave * C::kRowsPerDma);
+    const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
+    const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
+    typedef typename std::conditional<C::kKMajor != 0, int64_t, int>::type KPos;
+    const KPos k_step = k_major ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h)) : (KPos)C::kRowBytes;
+    const KPos k_first = task.k_begin * k_step;
+    int issue_vt = vt_begin, issue_kt = 0, issue_stage = 0;
+    KPos issue_kpos = k_first;
+    int issue_left = p.km_rows - task.k_begin * C::kBK;                 // K rows from the stage to be issued on
     auto point_at_tile = [&](int vt, bool w_only) {
 #pragma unroll
         for (int q = 0; q < kDmaPerWave; ++q) {
+            if (C::kKMajor && k_major) {                                // (columns that do not exist: any others, never stored)
+                const int k = km_row0 + 2 * q, col = ((lane & 31) ^ C::swz_k(k)) * 8;
+                if (C::kKMajor == 1)
+                    src[q] = static_cast<const char*>(p.w) + k * ld_w + (int64_t)min(vt * kTileV + col, p.km_cols - 8) * C::kEsz;
+                else
+                    src[q] = static_cast<const char*>(p.hidden) + k * ld_h + min(tok0 + col, (int64_t)p.km_cols - 8) * C::kEsz;
+                continue;
+            }
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
             const int chunk = (ld_slot ^ C::swz(r)) * 16;
             if (r < kTileV) {
@@ -251,7 +281,15 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             }
         }
     };
+    auto point_at_zeros = [&]() {       // a K-major operand's rows beyond the last K row, in a tile's last stage
+        if (C::kKMajor && k_major && issue_left < C::kBK) {
+#pragma unroll
+            for (int q = 0; q < kDmaPerWave; ++q)
+                if (km_row0 + 2 * q >= issue_left) src[q] = reinterpret_cast<const char*>(&kZeroChunk) - issue_kpos;
+        }
+    };
     point_at_tile(vt_begin, false);
+    point_at_zeros();
     auto issue_one = [&](int q) {
         const unsigned dst = lds_base + issue_stage * C::kStageBytes + wave * kDmaPerWave * 1024;
         const char* from = src[q] + issue_kpos;
@@ -262,14 +300,16 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         dma_16b_per_lane(from, dst + q * 1024);
     };
     auto issue_advance = [&]() {        // next (vocabulary tile, k tile) in sweep order
-        issue_kpos += C::kRowBytes;
+        issue_kpos += k_step;
+        issue_left -= C::kBK;
         issue_stage ^= 1;
-        if (++issue_kt == k_tiles) {
+        if (!C::kOneTile && ++issue_kt == k_tiles) {
             issue_kt = 0;
             issue_kpos = k_first;
             ++issue_vt;
             point_at_tile(min(issue_vt, vt_end - 1), true);
         }
+        point_at_zeros();
     };
     Epi<C> epi;
     epi.init(p, tok0, m_eff, wt, lane);
@@ -286,16 +326,34 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     // kVB + W block; the W block's fragment, K chunks 4 * (step / kVB) + group, and with a K step's first block
     // the token fragments of that K step.
     typename C::Frag fa[2], fb[2][kTB];
+    // the fragment of 16 columns `block` of a K-major operand whose stage begins at LDS byte `at`; first_block: the
+    // wave tile's (its column blocks are the 32-byte pieces first_block ... of a K row, exchanged by the swizzle)
+    auto k_major_frag = [&](int at, int first_block, int block, int k32) {
+        typedef short s4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s4* lds_s4;
+        const int k = frag_grp * 8 + (frag_row >> 2);                   // + 32 k32 + 4 h: neither changes the swizzle
+        const int lane_at = k * C::kKRowBytes + ((2 * first_block + ((frag_row & 3) >> 1)) ^ C::swz_k(k)) * 16 + (frag_row & 1) * 8;
+        const unsigned from = lds_base + at + (lane_at ^ (block * 32)) + k32 * 32 * C::kKRowBytes;
+        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(size_t)from);
+        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(size_t)(from + 4 * C::kKRowBytes));
+        return __builtin_bit_cast(typename C::Frag, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
     auto load_frags = [&](int stage, int step) {
         const unsigned char* st = smem + stage * C::kStageBytes;
         const unsigned char* a_base = st + (wv * kWaveV) * C::kRowBytes;
         const unsigned char* b_base = st + (kTileV + wt * kWaveT) * C::kRowBytes;
         const int k32 = step / kVB, vb = step % kVB, c = k32 * 4 + frag_grp;
-        fa[step & 1] = *reinterpret_cast<const typename C::Frag*>(a_base + C::chunk_off(vb * 16 + frag_row, c));
+        if constexpr (C::kKMajor == 1)
+            fa[step & 1] = k_major_frag(stage * C::kStageBytes, wv * kVB, vb, k32);
+        else
+            fa[step & 1] = *reinterpret_cast<const typename C::Frag*>(a_base + C::chunk_off(vb * 16 + frag_row, c));
         if (vb == 0) {
 #pragma unroll
             for (int tb = 0; tb < kTB; ++tb)
-                fb[k32][tb] = *reinterpret_cast<const typename C::Frag*>(b_base + C::chunk_off(tb * 16 + frag_row, c));
+                if constexpr (C::kKMajor == 2)
+                    fb[k32][tb] = k_major_frag(stage * C::kStageBytes + kTileV * C::kRowBytes, wt * kTB, tb, k32);
+                else
+                    fb[k32][tb] = *reinterpret_cast<const typename C::Frag*>(b_base + C::chunk_off(tb * 16 + frag_row, c));
         }
     };
     // An MFMA step with this wave's transfers of the stage being refilled issued between the MFMAs (`on` is
@@ -359,12 +417,13 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
         mfma_step(kKSteps - 1, 0, refill);
         stage ^= 1;
-        if (++kt == k_tiles) {          // a tile is complete
+        if (!C::kOneTile && ++kt == k_tiles) {          // a tile is complete
             epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
             kt = 0;
             ++vt;
         }
     }
+    if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
     __syncthreads();                    // every fragment read is done before the stages are reused
     epi.finish(p, reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
     __syncthreads();                    // merge buffer is read before the next task's transfers land

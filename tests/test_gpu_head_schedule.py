@@ -112,3 +112,20 @@ def test_logprobs_any_row_shape(tp, f32, H, pad, offset):
     part, _ = tp.tppo_token_logprobs(args[0], args[1], bad, args[3], status=st)
     assert int(host(st)[0]) == tp.STATUS_BAD_ROW and np.isnan(host(part)[7])
     assert np.abs(np.delete(host(part) - ref_lp, 7)).max() <= 1e-5
+
+
+@pytest.mark.parametrize("M,V,H", [(1, 1, 64), (65, 63, 64), (63, 65, 320), (257, 640, 192), (300, 1001, 256)])
+def test_logprob_grads_operands_read_along_their_rows(tp, M, V, H):
+    """W and the logits' derivative are contracted over their row index: row and column counts around a stage and a
+    tile, rows of a larger matrix with NaN in everything around them, and the derivatives' neighbours untouched."""
+    import torch
+    hidden, w, rows, targets, g = _bf16_case(M, V, H, seed=M * 7 + V)
+    _, lse = ofast.token_logprobs(hidden, w, rows, targets)
+    buf = torch.full((V + 2, H), 5.0, device="cuda")
+    dh, dw = tp.tppo_token_logprobs_backward(_padded(hidden, H + 8, 16), _padded(w, H + 24, 8), dev(rows.astype(np.int32)),
+                                             dev(targets.astype(np.int32)), dev(lse.astype(np.float32)),
+                                             dev(g.astype(np.float32)), grad_w=buf[1:V + 1])
+    ref_h, ref_w, abs_h, abs_w = ofast.token_logprob_grads(hidden, w, rows, targets, g, return_abs_bounds=True)
+    assert_within_term_bound(host(dh), ref_h, abs_h, "grad_hidden")
+    assert_within_term_bound(host(dw), ref_w, abs_w, "grad_w")
+    assert (host(buf)[0] == 5.0).all() and (host(buf)[V + 1] == 5.0).all()
