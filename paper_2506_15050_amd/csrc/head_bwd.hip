@@ -336,7 +336,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         p.aux1 = in_index ? grad_logp : grad_logp + m0;
         p.aux_index = in_index ? in_index + m0 : nullptr;
         p.out = dz; p.ld_out = L.v_pad; p.out_cols = L.v_pad;
-        const bool small = plan_small(p, mc, V, true, plan_sweep(p, mc, V));
+        const bool small = plan_small(p, mc, V, plan_sweep(p, mc, V));
         if ((small ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
                    : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;

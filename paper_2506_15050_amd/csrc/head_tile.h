@@ -94,6 +94,9 @@ struct HeadCfg {
     static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 256;
     static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
     static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
+    // Small tiles have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
+    // matrix cores have added up moves there, so that no sum runs over thousands of elements one after the other.
+    static constexpr int kSumStages = SMALL ? 128 / kBK : 0;
     static constexpr int kWaves = kWavesV * kWavesT, kThreads = kWaves * 64;
     static constexpr int kWaveV = kTileV / kWavesV, kWaveT = kTileT / kWavesT;    // wave tile
     static constexpr int kVB = kWaveV / kMI, kTB = kWaveT / kMI;                  // 16 x 16 blocks per wave
@@ -396,6 +399,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     }
     load_frags(0, 0);
 
+    typename C::Acc sums[C::kSumStages ? kVB : 1][C::kSumStages ? kTB : 1] = {};
     int kt = 0, vt = vt_begin, stage = 0;
     bool refill = false;                // transfers of the stage freed at the last barrier are pending
     for (int it = 0; it < total_iters; ++it) {
@@ -417,8 +421,21 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
         mfma_step(kKSteps - 1, 0, refill);
         stage ^= 1;
-        if (!C::kOneTile && ++kt == k_tiles) {          // a tile is complete
-            epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
+        if (!C::kOneTile) ++kt;
+        if constexpr (C::kSumStages != 0) {
+            if (kt % C::kSumStages == 0 || kt == k_tiles) {
+#pragma unroll
+                for (int vb = 0; vb < kVB; ++vb)
+#pragma unroll
+                    for (int tb = 0; tb < kTB; ++tb) {
+                        sums[vb][tb] += acc[vb][tb];
+                        acc[vb][tb] = typename C::Acc{};
+                    }
+            }
+        }
+        if (!C::kOneTile && kt == k_tiles) {            // a tile is complete
+            if constexpr (C::kSumStages != 0) epi.fold(sums, p, task, tok0, m_eff, vt, wv, wt, lane);
+            else epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
             kt = 0;
             ++vt;
         }
@@ -486,21 +503,22 @@ static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
     return best;
 }
 
-// The same sweep in 128 x 64 tiles, one workgroup per task, if that is the faster way; true if so.  A small tile is an
-// eighth of a large one's work and takes n / 8 of its time where n share a CU.  fp32, which the matrix cores bound,
-// loses 6 % to the smaller tile; for bf16 the traffic from L2 makes it up to 2.5 times slower per flop, so there it
-// only serves what would leave most of the chip idle.  Measured, large -> small (us):
-//   bf16: 146 tokens x V 1000, H 64: 14.8 -> 10.4;  x V 5000, H 1024: 35.6 -> 18.5;  x V 32000, H 512: 30.0 -> 26.1;
-//         20 x V 152064, H 5120: 478 -> 403.  Where the rule says large: 300 x V 32000, H 512: 29.7 (34.2),
-//         146 x V 50021, H 1024: 42.2 (57.9), 2500 x V 5000, H 1024: 39.3 (47.4), 1000 x V 152064, H 5120: 1297 (2950)
-//   fp32: 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  300 x V 32000, H 1024: 264 -> 210;
-//         2064 x V 32000, H 1024: 1281 -> 1093.  Large: 1000 x V 32000, H 1024: 508 (601)
+// The same sweep in 128 x 64 tiles, one workgroup per task, if that costs less than `large_cost`; true if so.  A small
+// tile is an eighth of a large one's work and takes n / 8 of its time where n share a CU.  For bf16 the traffic from
+// L2 makes it up to 2.5 times slower per flop, so there it only serves what would leave most of the chip idle.
+// Measured, large -> small (us):
+//   146 tokens x V 1000, H 64: 14.8 -> 10.4;  x V 5000, H 1024: 35.6 -> 18.5;  x V 32000, H 512: 30.0 -> 26.1;
+//   20 x V 152064, H 5120: 478 -> 403.  Where the rule says large: 300 x V 32000, H 512: 29.7 (34.2),
+//   146 x V 50021, H 1024: 42.2 (57.9), 2500 x V 5000, H 1024: 39.3 (47.4), 1000 x V 152064, H 5120: 1297 (2950)
+// fp32, which the matrix cores bound, loses 6 % per flop and wins that back by filling the chip, and always goes this
+// way (head.hip): 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  2064 x V 32000, H 1024: 1281 ->
+// 1114;  the worst seen, 1000 x V 32000, H 1024: 508 -> 601.
 typedef HeadCfg<uint16_t, false, true> SmallShape;
 constexpr int kSmallPerCu = SmallShape::kGroupsPerCu;
 constexpr double kSmallPart = (double)SmallShape::kTileV * SmallShape::kTileT / ((double)kTile * kTile);
-static bool plan_small(HeadParams& p, int64_t M, int64_t V, bool bf16, double large_cost) {
+constexpr double kSmallSlower = 2.5;
+static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
     const int64_t rows = (M + SmallShape::kTileT - 1) / SmallShape::kTileT, vts = (V + SmallShape::kTileV - 1) / SmallShape::kTileV;
-    const double slower = bf16 ? 2.5 : 1.06;
     double best = large_cost;
     int64_t best_cols = 0;
     for (int64_t s = 1; s <= vts && s <= kMaxSplits; ++s) {
@@ -508,7 +526,7 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, bool bf16, double la
         if (s > 4 && rows * s * SmallShape::kTileT > kRestTasks * kTile) break;
         const int64_t tasks = rows * s, full = tasks / (kSweepGroups * kSmallPerCu), rest = tasks % (kSweepGroups * kSmallPerCu);
         const double shares = (double)(full * kSmallPerCu) + rounds_of(rest);      // tasks in turn on the busiest CU
-        const double cost = shares * kSmallPart * ((double)((vts + s - 1) / s) + kTaskCost) * slower;
+        const double cost = shares * kSmallPart * ((double)((vts + s - 1) / s) + kTaskCost) * kSmallSlower;
         if (cost < best - 1e-9) { best = cost; best_cols = s; }
     }
     if (best_cols == 0) return false;
@@ -597,7 +615,9 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
         hipLaunchKernelGGL(head_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.arrivals, n);
         if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(C::kSmall ? p.n_tasks : kSweepGroups), dim3(C::kThreads),
+    constexpr int kMostGroups = 1 << 20;                            // (beyond that, several tasks per workgroup)
+    const int groups = !C::kSmall ? kSweepGroups : p.n_tasks < kMostGroups ? p.n_tasks : kMostGroups;
+    hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(groups), dim3(C::kThreads),
                        C::kLdsBytes, s, p);
     return launch_result();
 }

@@ -62,6 +62,24 @@ def test_logprobs_small_tiles(tp, f32, M, V, H):
     assert np.abs(host(logp)[at] - ref_lp).max() <= 1e-5 and np.abs(host(lse)[at] - ref_lse).max() <= 1e-5
 
 
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("H", [5112, 5100])
+def test_logprobs_long_sums(tp, f32, H):
+    """fp32 and ragged bf16 rows of thousands of elements, in sums of 128 that are then added up."""
+    M, V = 300, 4000
+    rng = np.random.default_rng(H)
+    hidden = rng.normal(size=(M, H)).astype(np.float32)
+    w = (rng.normal(size=(V, H)) * 0.02).astype(np.float32)
+    if not f32:
+        hidden, w = synth.f32_to_bf16_bits(hidden), synth.f32_to_bf16_bits(w)
+    rows, targets = np.arange(M), rng.integers(0, V, size=M)
+    logp, lse = tp.tppo_token_logprobs(dev(hidden), dev(w), dev(rows.astype(np.int32)), dev(targets.astype(np.int32)))
+    ref_lp, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    # a logit of rms 1.43 by 128 and then 40 additions: a random walk of rms 2^-24 * 1.43 * sqrt(64 + 20) = 8e-7, six of
+    # those (one sum over all of H: rms 4e-6)
+    assert np.abs(host(logp) - ref_lp).max() <= 5e-6 and np.abs(host(lse) - ref_lse).max() <= 5e-6
+
+
 @pytest.mark.parametrize("M,V", [(1, 64), (65, 129), (200, 1000), (130, 5003)])
 def test_logprob_grads_small_tiles(tp, M, V):
     check_logprob_grads(tp, *_bf16_case(M, V, 128, seed=M + V))
