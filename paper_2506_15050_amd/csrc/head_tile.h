@@ -145,6 +145,8 @@ __device__ __forceinline__ void dma_16b_per_lane(const void* src, unsigned lds_b
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding)
 constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
 
+constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that waits for LDS reads only
+
 // Schedule.  The launch is persistent: 256 workgroups, one per CU; hardware id b runs on XCD b % 8 (ids go
 // round-robin over the 8 XCDs, each with its own L2).  The work is a list of tasks, 256 to a round, dealt out so
 // that the 32 workgroups of an XCD hold 32 CONSECUTIVE tasks.  A grid of `rows` token tiles x `cols` divisions of
@@ -362,10 +364,13 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     // An MFMA step with this wave's transfers of the stage being refilled issued between the MFMAs (`on` is
     // workgroup-uniform): transfer j follows MFMA number j * kSpread / kDmaPerWave, counted from the barrier that
     // freed the stage (`part`: steps since then).
+    // The scheduling barrier in front keeps the next step's fragment reads ahead of this step's MFMAs; without it the
+    // compiler puts each read right before its use, and half of the steps wait out the LDS latency (1 to 3 % of the
+    // sweep, by card: the clock gives back part of what the shorter schedule gains).
     constexpr int kMfmaPerStep = C::kMfmaPerStep, kSpreadSteps = C::kSpread / kMfmaPerStep;
     auto mfma_step = [&](int step, int part, bool on) {
         const int k32 = step / kVB, vb = step % kVB;
-        if (part < kSpreadSteps) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
             if constexpr (C::kEsz == 2) {
@@ -413,6 +418,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         // publish the next one and fetch its first fragments BEFORE issuing the
         // last MFMAs, so the barrier and the LDS latency hide behind them.
         refill = false;
+        __builtin_amdgcn_s_waitcnt(kLgkm0);     // here, on both paths: behind the branch it would wait for the next stage's too
         if (it + 1 < total_iters) {
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             __syncthreads();            // stage it+1 landed for everyone; everyone left stage it
