@@ -81,17 +81,27 @@ __device__ __forceinline__ float value_term(float v, float vo, float r, float xl
     return value_undefined(d0, d1, vo) ? __builtin_nanf("") : fmaxf(d0 * d0, d1 * d1);
 }
 
-__device__ __forceinline__ double block_sum(double x, double* s_red) {
+// The workgroup's sums of kSums values per thread, in a fixed order and with one pass through LDS for all of them:
+// valid in every thread.  s_red: kSums * (wavefronts of the workgroup) doubles.
+template <int kSums>
+__device__ __forceinline__ void block_sums(double (&x)[kSums], double* s_red) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)(blockDim.x >> 6);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_down(x, off);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) x[q] += __shfl_down(x[q], off);
     __syncthreads();
-    if (lane == 0) s_red[wave] = x;
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) s_red[q * waves + wave] = x[q];
+    }
     __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += s_red[w];
-    return t;   // valid in thread 0
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) {
+        double t = 0.0;
+        for (int w = 0; w < waves; ++w) t += s_red[q * waves + w];
+        x[q] = t;
+    }
 }
 
 // Four consecutive results per access; `n` = how many of the four exist.
@@ -277,7 +287,8 @@ __device__ __forceinline__ bool collect_sums(const unsigned long long* words, ui
     __syncthreads();
     if (!ok) *s_flag = 0;
 #pragma unroll
-    for (int q = 0; q < kSums; ++q) tot[q] = block_sum(acc[q], s_red);
+    for (int q = 0; q < kSums; ++q) tot[q] = acc[q];
+    block_sums(tot, s_red);
     return *s_flag != 0;
 }
 
@@ -299,7 +310,7 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
 }
 
 __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
-    __shared__ double s_red[kLossThreads / kWave];
+    __shared__ double s_red[2 * kLossThreads / kWave];
     __shared__ int s_flag;
     const Plan pl = plan_open(p.plan);
     const int tid = threadIdx.x;
@@ -343,16 +354,15 @@ __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tpp
         pol_acc += (double)pol_t;
         val_acc += (double)val_t;
     }
-    const double ps = block_sum(pol_acc, s_red);
-    const double vs = block_sum(val_acc, s_red);
-    unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
-    if (tid == 0) {
-        publish(mine, p.tag, ps);
-        publish(mine + 2, p.tag, vs);
+    double tot[2] = {pol_acc, val_acc};
+    block_sums(tot, s_red);
+    bool ok = true;
+    if (gridDim.x > 1) {                                           // (a grid of one has them all)
+        unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
+        if (tid < 2) publish(mine + 2 * tid, p.tag, tid == 0 ? tot[0] : tot[1]);
+        if (blockIdx.x != gridDim.x - 1) return;
+        ok = collect_sums<2, 4>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
     }
-    if (blockIdx.x != gridDim.x - 1) return;
-    double tot[2];
-    const bool ok = collect_sums<2, 4>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
     if (tid == 0) {
         if (!ok) {
             set_status(p.status, TPPO_STATUS_TIMEOUT);
@@ -402,7 +412,7 @@ struct GradParams {
 
 __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams gp, tppo_loss_out* __restrict__ out,
                                                                 tppo_loss_stats* __restrict__ stats) {
-    __shared__ double s_red[kLossThreads / kWave];
+    __shared__ double s_red[kGradSums * kLossThreads / kWave];
     __shared__ int s_flag;
     const LossParams& p = gp.fwd;
     const Plan pl = plan_open(p.plan);
@@ -475,16 +485,18 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         val_acc += (double)val_t;
         ratio_acc += (double)ratio_t;
     }
-    const double sums[kGradSums] = {pol_acc, val_acc, ratio_acc, (double)pol_clipped, (double)val_clipped};
-    unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
+    if (gridDim.x == 1 && !out && !stats) return;
+    double tot[kGradSums] = {pol_acc, val_acc, ratio_acc, (double)pol_clipped, (double)val_clipped};
+    block_sums(tot, s_red);
+    bool ok = true;
+    if (gridDim.x > 1) {
+        unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
 #pragma unroll
-    for (int q = 0; q < kGradSums; ++q) {
-        const double t = block_sum(sums[q], s_red);
-        if (tid == 0) publish(mine + 2 * q, p.tag, t);
+        for (int q = 0; q < kGradSums; ++q)
+            if (tid == q) publish(mine + 2 * q, p.tag, tot[q]);
+        if (blockIdx.x != gridDim.x - 1 || (!out && !stats)) return;
+        ok = collect_sums<kGradSums, 2>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
     }
-    if (blockIdx.x != gridDim.x - 1 || (!out && !stats)) return;
-    double tot[kGradSums];
-    const bool ok = collect_sums<kGradSums, 2>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
     if (tid == 0) {
         if (!ok) {
             set_status(p.status, TPPO_STATUS_TIMEOUT);
@@ -509,8 +521,7 @@ template <bool kGrad>
 __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int32_t* __restrict__ resp_off,
                                                         tppo_loss_out* __restrict__ out,
                                                         tppo_loss_stats* __restrict__ stats) {
-    __shared__ double s_red[256 / kWave];
-    __shared__ double s_count[2];
+    __shared__ double s_red[kGradSums * 256 / kWave];
     const LossParams& p = gp.fwd;
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const int tid = threadIdx.x;
@@ -520,13 +531,9 @@ __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int
         if (has_pol) cnt_p += (double)min(max(p.keep_len[i], 0), win);
         if (has_val && p.done[i] != 0) cnt_v += (double)win;
     }
-    const double tp_ = block_sum(cnt_p, s_red), tv_ = block_sum(cnt_v, s_red);
-    if (tid == 0) {
-        s_count[0] = tp_;
-        s_count[1] = tv_;
-    }
-    __syncthreads();
-    const long long np = (long long)s_count[0], nv = (long long)s_count[1];
+    double cnt[2] = {cnt_p, cnt_v};
+    block_sums(cnt, s_red);
+    const long long np = (long long)cnt[0], nv = (long long)cnt[1];
     const long long den_p = gp.policy_denominator > 0 ? gp.policy_denominator : np;
     const long long den_v = gp.value_denominator > 0 ? gp.value_denominator : nv;
     const float pol_coef = den_p > 0 ? -gp.policy_scale / (float)den_p : 0.f;
@@ -564,9 +571,8 @@ __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int
             }
         }
     }
-    double tot[kGradSums];
-#pragma unroll
-    for (int q = 0; q < kGradSums; ++q) tot[q] = block_sum(sums[q], s_red);
+    double (&tot)[kGradSums] = sums;
+    block_sums(tot, s_red);
     if (tid == 0) {
         if (out) write_losses(out, tot[0], tot[1], np, nv);
         if (stats) {
