@@ -33,10 +33,11 @@ namespace tppo {
 constexpr int kLossThreads = TPPO_LOSS_THREADS;
 constexpr int kLossParts = kTileTokens / (4 * kLossThreads);      // a workgroup takes this fraction of a frame, four tokens per thread
 static_assert(kLossParts >= 1 && kLossParts * 4 * kLossThreads == kTileTokens, "whole parts of a frame");
-// Workgroups of the persistent grids, measured on 40 M tokens: the read-only pass is fastest with 8 per CU; the
-// pass that also writes two arrays with 4 per CU (fewer accesses in flight at once, as for a bare elementwise
-// pass of 6 reads and 2 writes).
-constexpr int kLossGroups = 2048, kGradGroups = 1024;
+// Most workgroups of the persistent grids.  Enough of them to keep the memory busy, and no more: the one that collects
+// the sums reads 4 (forward) or 10 words of each.  Measured, us: forward with 2048 / 1024 / 512 workgroups 14.5 / 12.8 /
+// 12.3 on 2.4 M tokens, 30.5 / 28.8 / 28.9 on 10 M, 52.4 / 50.7 / 53.0 on 20 M; with derivatives 2048 / 1024 / 512 take
+// 28 / 21.3 / 21.0 on 2.4 M tokens and 1024 / 512 take 49.3 / 55.9 on 10 M (768: the same up to 20 M, 2 % more on 40 M).
+constexpr int kLossGroups = 1024, kGradGroups = 1024;
 constexpr int kFinishSpin = 1 << 20;
 static_assert(kLossGroups <= kFinishGroups, "the plan holds partial sums for kFinishGroups workgroups");
 
