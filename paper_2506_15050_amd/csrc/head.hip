@@ -95,18 +95,36 @@ __global__ __launch_bounds__(kGenThreads) void head_generic_kernel(
 }
 
 // ------------------------------------------------------------------ MFMA path
+// What a running maximum is held in: logits, or logits * log2(e) (head_tile.h, kLogitMax).  Measured, 32000 logits of
+// rms 1.4 and the sampled one at 8 to 12 / 30 to 35 / 60 to 65, rms error of its log-prob against 64 bits: 1.2e-7 / 2.4e-9 /
+// 0 in logits; 4.2e-7 / 8e-7 / 1.7e-6 in log2, with up to a third of the log-probs positive; the one-token kernel 9.5e-7 /
+// 2.4e-9 / 0.  The extra operation per logit costs ragged bf16 1 % (2512 tokens, H 1000, V 50021: 297.5 -> 300.7 us) and fp32
+// nothing.
+template <bool kLogitMax>
+struct MaxUnits {
+    static constexpr float kLeast = kLogitMax ? kLowest : kNegBig;
+    __device__ static __forceinline__ float of(float z) { return kLogitMax ? z : z * kLog2e; }
+    __device__ static __forceinline__ float log2_term(float z, float max) {
+        return kLogitMax ? (z - max) * kLog2e : fmaf(z, kLog2e, -max);
+    }
+    __device__ static __forceinline__ float log2_ratio(float from, float to) {
+        return kLogitMax ? (from - to) * kLog2e : from - to;
+    }
+};
+
 // Per-lane running log-softmax state of the kTB token columns a lane owns, and
 // the two steps that use it: folding a finished vocabulary tile, and
 // the final merge across lane halves / waves.
 template <class C>
 struct LaneSoftmax {
+    typedef MaxUnits<C::kLogitMax> Units;
     float run_max[C::kTB], run_sum[C::kTB], tgt_logit[C::kTB];
     int tgt[C::kTB];
 
     __device__ __forceinline__ void init(const HeadParams& p, int64_t tok0, int64_t m_eff, int wt, int lane) {
 #pragma unroll
         for (int tb = 0; tb < C::kTB; ++tb) {
-            run_max[tb] = kNegBig;
+            run_max[tb] = Units::kLeast;
             run_sum[tb] = 0.f;
             tgt_logit[tb] = 0.f;
             const int64_t t = tok0 + wt * C::kWaveT + tb * C::kMI + (lane % C::kMI);
@@ -140,18 +158,18 @@ struct LaneSoftmax {
                     mx0 = fmaxf(mx0, acc[vb][tb][e]);
                     mx1 = fmaxf(mx1, acc[vb][tb][e + 1]);
                 }
-            const float new_max = fmaxf(run_max[tb], fmaxf(mx0, mx1) * kLog2e);
+            const float new_max = fmaxf(run_max[tb], Units::of(fmaxf(mx0, mx1)));
             float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll
             for (int vb = 0; vb < kVB; ++vb)
 #pragma unroll
                 for (int e = 0; e < kE; e += 4) {
-                    s0 += __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][e], kLog2e, -new_max));
-                    s1 += __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][e + 1], kLog2e, -new_max));
-                    s2 += __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][e + 2], kLog2e, -new_max));
-                    s3 += __builtin_amdgcn_exp2f(fmaf(acc[vb][tb][e + 3], kLog2e, -new_max));
+                    s0 += __builtin_amdgcn_exp2f(Units::log2_term(acc[vb][tb][e], new_max));
+                    s1 += __builtin_amdgcn_exp2f(Units::log2_term(acc[vb][tb][e + 1], new_max));
+                    s2 += __builtin_amdgcn_exp2f(Units::log2_term(acc[vb][tb][e + 2], new_max));
+                    s3 += __builtin_amdgcn_exp2f(Units::log2_term(acc[vb][tb][e + 3], new_max));
                 }
-            run_sum[tb] = fmaf(run_sum[tb], __builtin_amdgcn_exp2f(run_max[tb] - new_max), (s0 + s1) + (s2 + s3));
+            run_sum[tb] = fmaf(run_sum[tb], __builtin_amdgcn_exp2f(Units::log2_ratio(run_max[tb], new_max)), (s0 + s1) + (s2 + s3));
             run_max[tb] = new_max;
         }
         // target logit: rare (a lane owns kVB * kAccElems of V ids per tile), so only
@@ -200,7 +218,8 @@ struct LaneSoftmax {
                 const float om = __shfl_xor(run_max[tb], off), os = __shfl_xor(run_sum[tb], off);
                 const float ot = __shfl_xor(tgt_logit[tb], off);
                 const float nm = fmaxf(run_max[tb], om);
-                run_sum[tb] = run_sum[tb] * __builtin_amdgcn_exp2f(run_max[tb] - nm) + os * __builtin_amdgcn_exp2f(om - nm);
+                run_sum[tb] = run_sum[tb] * __builtin_amdgcn_exp2f(Units::log2_ratio(run_max[tb], nm)) +
+                              os * __builtin_amdgcn_exp2f(Units::log2_ratio(om, nm));
                 run_max[tb] = nm;
                 tgt_logit[tb] += ot;
             }
@@ -218,12 +237,13 @@ struct LaneSoftmax {
         for (int col = tid; col < kTileT; col += C::kThreads) {
             const int64_t t = tok0 + col;
             if (t >= m_eff) continue;
-            float gm = kNegBig, gs = 0.f, gt = 0.f;
+            float gm = Units::kLeast, gs = 0.f, gt = 0.f;
 #pragma unroll
             for (int q = 0; q < C::kWavesV; ++q) gm = fmaxf(gm, s_merge[(q * 3 + 0) * kTileT + col]);
 #pragma unroll
             for (int q = 0; q < C::kWavesV; ++q) {
-                gs += s_merge[(q * 3 + 1) * kTileT + col] * __builtin_amdgcn_exp2f(s_merge[(q * 3 + 0) * kTileT + col] - gm);
+                gs += s_merge[(q * 3 + 1) * kTileT + col] *
+                      __builtin_amdgcn_exp2f(Units::log2_ratio(s_merge[(q * 3 + 0) * kTileT + col], gm));
                 gt += s_merge[(q * 3 + 2) * kTileT + col];
             }
             const Grid& g = task.rest ? p.rest : p.first;
@@ -246,6 +266,7 @@ struct Partials {
     int first_cols, rest_cols;
 };
 constexpr int kMergeTokens = 32, kMergeLanes = 8;
+template <bool kLogitMax>
 __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel(
     Partials q, int64_t M, const int64_t* __restrict__ m_actual,
     const int32_t* __restrict__ sel_rows, const int32_t* __restrict__ sel_targets, int64_t n_rows,
@@ -255,7 +276,8 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
     const int tok = threadIdx.x % kMergeTokens, sub = threadIdx.x / kMergeTokens;
     const int64_t m = (int64_t)blockIdx.x * kMergeTokens + tok;
     const int64_t m_eff = m_actual ? min(M, *m_actual) : M;
-    float mx = kNegBig, sum = 0.f, tz = 0.f;
+    typedef MaxUnits<kLogitMax> Units;
+    float mx = Units::kLeast, sum = 0.f, tz = 0.f;
     if (m < m_eff) {
         const bool rest = m >= q.first_tokens;
         const float* part = rest ? q.rest + (m - q.first_tokens) : q.first + m;
@@ -267,7 +289,7 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
             const float* at = part + c * stride;
             const float om = at[0], os = at[plane], ot = at[2 * plane];
             const float nm = fmaxf(mx, om);
-            sum = sum * exp2f(mx - nm) + os * exp2f(om - nm);
+            sum = sum * exp2f(Units::log2_ratio(mx, nm)) + os * exp2f(Units::log2_ratio(om, nm));
             mx = nm;
             tz += ot;
         }
@@ -287,18 +309,24 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
         if (lse) lse[o] = __builtin_nanf("");
         return;
     }
-    float gm = kNegBig;
+    float gm = Units::kLeast;
 #pragma unroll
     for (int s = 0; s < kMergeLanes; ++s) gm = fmaxf(gm, s_part[0][s][tok]);
     float gs = 0.f, gt = 0.f;
 #pragma unroll
     for (int s = 0; s < kMergeLanes; ++s) {
-        gs += s_part[1][s][tok] * exp2f(s_part[0][s][tok] - gm);
+        gs += s_part[1][s][tok] * exp2f(Units::log2_ratio(s_part[0][s][tok], gm));
         gt += s_part[2][s][tok];
     }
-    const float l = (gm + log2f(gs)) * kLn2;
-    logp[o] = gt - l;
-    if (lse) lse[o] = l;
+    if (kLogitMax) {                   // gt - gm before the sum's logarithm: a confident token's loses nothing to the size of its logit
+        const float log_sum = logf(gs);
+        logp[o] = (gt - gm) - log_sum;
+        if (lse) lse[o] = gm + log_sum;
+    } else {
+        const float l = (gm + log2f(gs)) * kLn2;
+        logp[o] = gt - l;
+        if (lse) lse[o] = l;
+    }
 }
 
 // Most partial triples a sweep of M tokens can write (plan_sweep: up to 4 columns in the whole rounds, kRestTasks
@@ -365,11 +393,12 @@ static int head_generic(const void* hidden, int64_t n_rows, int64_t H, int64_t l
 constexpr int kLongSumH = 2048;
 template <typename T>
 static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_index, float* logp, float* lse,
-                      int64_t n_rows, const int32_t* sel_rows, void* workspace, int32_t* status, hipStream_t s) {
+                      int64_t n_rows, const int32_t* sel_rows, bool matrix_only, void* workspace, int32_t* status, hipStream_t s) {
     typedef HeadCfg<T, false> Whole;
     typedef HeadCfg<T, true> Ragged;
     p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
-    const bool bf16 = sizeof(T) == 2, whole = p.H % Whole::kBK == 0;
+    // (the ragged variant also takes whole stages: bf16 copies of misaligned rows, which want its exact maximum)
+    const bool bf16 = sizeof(T) == 2, whole = bf16 ? matrix_only : p.H % Whole::kBK == 0;
     const bool only_small = !bf16 || (p.H % Whole::kBK != 0 && p.H > kLongSumH);
     const bool small = plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
     const int tile = small ? SmallShape::kTileT : kTile;
@@ -387,16 +416,20 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     }
     if (rc != TPPO_OK) return rc;
     const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
-    hipLaunchKernelGGL(head_combine_kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),
-                       dim3(kMergeTokens * kMergeLanes), 0, s, q, M, p.m_actual, sel_rows, p.sel_targets, n_rows, (int)V,
-                       out_index, logp, lse, status);
+    auto merge = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)), dim3(kMergeTokens * kMergeLanes),
+                           0, s, q, M, p.m_actual, sel_rows, p.sel_targets, n_rows, (int)V, out_index, logp, lse, status);
+    };
+    if (whole ? Whole::kLogitMax : Ragged::kLogitMax) merge(head_combine_kernel<true>);
+    else merge(head_combine_kernel<false>);
     return launch_result();
 }
 
 // Aligned copies first where the rows need them, then the tiled kernel.
 template <typename T>
 static int head_call(HeadParams& p, int64_t M, int64_t V, const int32_t* out_index, float* logp, float* lse,
-                     void* workspace, size_t tiled_bytes, bool pack_h, bool pack_w, int32_t* status, hipStream_t s) {
+                     void* workspace, size_t tiled_bytes, bool pack_h, bool pack_w, bool matrix_only, int32_t* status,
+                     hipStream_t s) {
     const int64_t n_rows = p.n_rows;
     const int32_t* sel_rows = p.sel_rows;
     const int chunks = (int)(packed_row_bytes(p.H, sizeof(T)) / 16), per_row = chunks * (16 / (int)sizeof(T));
@@ -423,7 +456,7 @@ static int head_call(HeadParams& p, int64_t M, int64_t V, const int32_t* out_ind
         p.sel_rows = nullptr;
     }
     if (pack_w || pack_h) p.H = per_row;                            // (zeros: they change no logit)
-    return head_tiled<T>(p, M, V, out_index, logp, lse, n_rows, sel_rows, workspace, status, s);
+    return head_tiled<T>(p, M, V, out_index, logp, lse, n_rows, sel_rows, matrix_only, workspace, status, s);
 }
 
 }  // namespace tppo
@@ -481,8 +514,8 @@ extern "C" int tppo_token_logprobs(const void* hidden, int64_t n_rows, int64_t H
     p.m_actual = m_actual;
     p.n_rows = n_rows; p.ld_h = ld_hidden; p.ld_w = ld_w;
     p.H = (int)H;
-    return bf16 ? head_call<uint16_t>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, status, s)
-                : head_call<float>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, status, s);
+    return bf16 ? head_call<uint16_t>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, matrix_only, status, s)
+                : head_call<float>(p, M, V, out_index, logp, lse, workspace, tiled, pack_h, pack_w, matrix_only, status, s);
 }
 
 extern "C" int tppo_version(void) { return TPPO_VERSION; }

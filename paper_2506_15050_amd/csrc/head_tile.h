@@ -17,7 +17,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kMaxSplits = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kNegBig = -3.0e38f;    // finite stand-in for -inf (keeps exp2(m - m') NaN-free)
+// finite stand-ins for -inf (they keep exp2(m - m') NaN-free)
+constexpr float kNegBig = -3.0e38f;    // in units of log2
+constexpr float kLowest = -3.402823466e38f;   // in units of the logits: no finite one lies below
 
 // A block of the sweep's work: `rows` token tiles from `row0` on, `cols` divisions of the W-role side each (see
 // "Schedule" below).
@@ -94,6 +96,10 @@ struct HeadCfg {
     static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 256;
     static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
     static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
+    // The log-softmax's running maximum is held in units of the logits, exact, in the variants that took over from the
+    // one-token kernel (fp32, and bf16 rows off a stage or off 16 bytes): the largest term is then exactly 1, as it was
+    // there.  The whole-stage bf16 sweep holds it in units of log2, rounded, one operation per logit less.
+    static constexpr bool kLogitMax = sizeof(T) == 4 || RAGGED;
     // Small tiles have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
     // matrix cores have added up moves there, so that no sum runs over thousands of elements one after the other.
     static constexpr int kSumStages = SMALL ? 128 / kBK : 0;
