@@ -42,3 +42,12 @@ def test_peaked_rows_fp32_and_ragged(tp, f32, M, H, lo, hi):
     tol = 2.0 ** -24 if lo >= 30 else 1.2e-6
     assert np.abs(logp - ref).max() <= tol
     assert np.abs(lse - ref_lse).max() <= 2.0 ** -24 * 2 * hi + tol
+
+
+@pytest.mark.parametrize("M", [60, 1500])                  # small and large tiles
+@pytest.mark.parametrize("lo,hi", [(8, 12), (30, 35), (60, 65)])
+def test_peaked_rows_whole_stages_bf16(tp, M, lo, hi):
+    logp, lse, ref, ref_lse = peaked(tp, False, M, 64, lo, hi)
+    # the maximum is rounded in units of log2, so the largest term is 2^(that rounding): one ulp of exp2 and the rounding
+    # of the sum, 3 x 2^-24 of 1
+    assert np.abs(logp - ref).max() <= (3 * 2.0 ** -24 if lo >= 30 else 1.2e-6)
