@@ -80,6 +80,25 @@ def test_logprobs_long_sums(tp, f32, H):
     assert np.abs(host(logp) - ref_lp).max() <= 5e-6 and np.abs(host(lse) - ref_lse).max() <= 5e-6
 
 
+@pytest.mark.parametrize("H,pad,offset", [(5120, 1, 0), (2112, 8, 3), (5112, 0, 0)])
+def test_logprobs_long_sums_no_worse_than_one_token_at_a_time(tp, H, pad, offset):
+    """bf16 rows that the one-token kernel takes when the workspace is small: with room for copies of W and the kept rows
+    they go to the tiles, and are summed no less exactly there."""
+    M, V = 1500, 8000                                      # 6 token tiles x 32: not too few for the large tiles
+    rng = np.random.default_rng(H)
+    hidden = synth.f32_to_bf16_bits(rng.normal(size=(M, H)).astype(np.float32))
+    w = synth.f32_to_bf16_bits((rng.normal(size=(V, H)) * 0.02).astype(np.float32))
+    rows, targets = np.arange(M), rng.integers(0, V, size=M)
+    args = (_padded(hidden, H + pad, offset), _padded(w, H + pad, offset), dev(rows.astype(np.int32)),
+            dev(targets.astype(np.int32)))
+    ref, _ = ofast.token_logprobs(hidden, w, rows, targets)
+    room = tp.load().tppo_token_logprobs_workspace_bytes(M, H, V, tp.TPPO_BF16) + 2 * (M + V) * (H + 8)
+    rms = [np.sqrt(np.mean((host(tp.tppo_token_logprobs(*args, workspace=tp._workspace(n, "cuda"))[0]) - ref) ** 2))
+           for n in (256, room)]
+    # (an rms over 1500 tokens is good to 2 %; one sum over all of H = 5120 shows 1.3 times the one-token kernel's)
+    assert rms[1] <= 1.1 * rms[0]
+
+
 @pytest.mark.parametrize("M,V", [(1, 64), (65, 129), (200, 1000), (130, 5003)])
 def test_logprob_grads_small_tiles(tp, M, V):
     check_logprob_grads(tp, *_bf16_case(M, V, 128, seed=M + V))
