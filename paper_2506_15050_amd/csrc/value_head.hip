@@ -10,7 +10,7 @@ namespace tppo {
 constexpr int kVhThreads = 256, kVhWaves = kVhThreads / kWave;
 constexpr int kVhMaxH = 16384;
 constexpr int64_t kVhMaxGroups = 1 << 20;         // (more rows than 16 million: several turns per wavefront)
-constexpr int64_t kVhManyRows = 8192;
+constexpr int64_t kVhFewRows = 256 * 3 * 8;
 
 typedef uint32_t vh_chunk __attribute__((ext_vector_type(4)));
 typedef uint32_t vh_weights __attribute__((ext_vector_type(4), aligned(2)));   // w_value may start anywhere
@@ -18,8 +18,7 @@ typedef uint32_t vh_weights __attribute__((ext_vector_type(4), aligned(2)));   /
 // kRows rows per wavefront: one 16-byte load per row and step, two steps in flight, and the weights, which every
 // wavefront of the CU reads and the vector cache holds, fetched once for all of them.  One group of rows per
 // wavefront and no loop over groups: nothing waits for a workgroup's slowest row.
-// Measured, hidden
-// states that no cache holds: 94639 rows of H = 5120, 140 us = 6.9 TB/s; of H = 1024, 30 us = 6.4; 20000 of H = 3584,
+// Measured, hidden states that no cache holds: 94639 rows of H = 5120, 140 us = 6.9 TB/s; of H = 1024, 30 us = 6.4; 20000 of H = 3584,
 // 24 us.  One row per wavefront, two plain loads in flight, the weights as fp32 in LDS and a persistent grid took
 // 221, 52 and 40 us; plain instead of non-temporal loads cost 14 %, one row per wavefront 13 % at H = 1024.
 template <int kRows>
@@ -93,8 +92,9 @@ extern "C" int tppo_value_head(const void* hidden, int64_t n_rows, int64_t H, in
     if (n_rows == 0) return TPPO_ERR_SIZE;
     if (!hidden || !w_value || !v_out) return TPPO_ERR_NULL;
     if (H % 8 != 0 || ld_hidden % 8 != 0 || !is_aligned(hidden, 16)) return TPPO_ERR_PARAM;
-    // Four rows per wavefront where that still gives every CU eight wavefronts; below, two (2000 rows of H = 5120: 7.6
-    // against 9.9 us; 8000 rows: 15.5 against 14.6).
+    // Two rows per wavefront up to three workgroups of eight rows to a CU, where their time jumps; four beyond.  Measured at
+    // H = 5120, two / four, us: 2000 rows 6.8 / 10.1, 6016 rows 11.7 / 12.4, 6144 rows 11.9 / 12.3, 6152 rows 13.7 / 12.4,
+    // 7168 rows 15.2 / 13.6, 8000 rows 15.6 / 14.8; the same line at H = 2048, 3584 and 8192.
     auto go = [&](auto kernel, int per_wave) {
         const int64_t per_group = (int64_t)kVhWaves * per_wave;
         const int64_t want = (M + per_group - 1) / per_group;
@@ -102,7 +102,7 @@ extern "C" int tppo_value_head(const void* hidden, int64_t n_rows, int64_t H, in
                            static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(hidden), n_rows, (int)H, ld_hidden,
                            static_cast<const uint16_t*>(w_value), bias, rows, out_index, M, m_actual, v_out, status);
     };
-    if (M >= kVhManyRows) go(value_head_kernel<4>, 4);
+    if (M > kVhFewRows) go(value_head_kernel<4>, 4);
     else go(value_head_kernel<2>, 2);
     return launch_result();
 }
