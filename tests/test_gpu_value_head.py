@@ -30,3 +30,21 @@ def test_value_head_row_groups(tp, M, H):
     st = tp.new_status("cuda")
     got2 = host(tp.tppo_value_head(dev(hidden), shifted, 0.5, dev(bad), status=st))
     assert int(host(st)[0]) == tp.STATUS_BAD_ROW and np.isnan(got2[M - 1]) and np.array_equal(got2[:M - 1], got[:M - 1])
+
+
+def test_value_head_several_turns(tp):
+    """More rows than one turn of the largest grid takes (2^20 workgroups of 16), the last turn short and with a bad row."""
+    import torch
+    H, N, M = 8, 300, (1 << 24) + 41
+    rng = np.random.default_rng(7)
+    hidden = synth.f32_to_bf16_bits(rng.normal(size=(N, H)).astype(np.float32))
+    w = synth.f32_to_bf16_bits(rng.normal(size=H).astype(np.float32))
+    rows = torch.arange(M, device="cuda", dtype=torch.int32).mul_(7).remainder_(N)
+    rows[M - 3] = -1
+    ref = dev(ofast.value_head(hidden, w, 0.5, np.arange(N)).astype(np.float32))[rows.clamp(min=0).long()]
+    st = tp.new_status("cuda")
+    got = tp.tppo_value_head(dev(hidden), dev(w), 0.5, rows, status=st)
+    assert int(host(st)[0]) == tp.STATUS_BAD_ROW and bool(torch.isnan(got[M - 3]))
+    got[M - 3] = ref[M - 3]
+    # eight products and seven additions in fp32, terms of size 10 at most
+    assert float((got - ref).abs().max()) <= 8 * 2.0 ** -23 * 16
