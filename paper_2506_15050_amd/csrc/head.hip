@@ -388,14 +388,6 @@ static int head_generic(const void* hidden, int64_t n_rows, int64_t H, int64_t l
     return launch_result();
 }
 
-// fp32, and the bf16 rows that the one-token kernel can serve (off a stage or off 16 bytes) with a long H, take the small
-// tiles whatever the size, for the accuracy of their sums: the large ones add up all of H one step after the other, which
-// whole-stage bf16 always did.  Error of the log-probs against 64 bits, weights of 0.02, rms: H = 5112, 300 tokens, fp32
-// 1.8e-6 in large tiles, 5.0e-7 in small ones (6.1e-7 by the one-token kernel); bf16, 1500 tokens, V = 8000, H = 5120
-// misaligned 7.9e-7, 4.8e-7 (6.1e-7).  At H = 2040 bf16 gives 5.6e-7 in large tiles, 6.8e-7 by the one-token kernel.  What
-// that costs, large -> small: 2500 tokens, V = 50000, H = 2104: 0.50 -> 1.09 ms; H = 5112: 1.29 -> 2.83 ms; 16000 tokens,
-// V = 152064, H = 5112: 22.4 -> 110 ms (H = 5120: 17.8 ms).
-constexpr int kLongSumH = 2048;
 template <typename T>
 static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_index, float* logp, float* lse,
                       int64_t n_rows, const int32_t* sel_rows, bool matrix_only, void* workspace, int32_t* status, hipStream_t s) {
@@ -404,8 +396,7 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
     // (the ragged variant also takes whole stages: bf16 copies of misaligned rows, which want its exact maximum)
     const bool bf16 = sizeof(T) == 2, whole = bf16 ? matrix_only : p.H % Whole::kBK == 0;
-    const bool only_small = !bf16 || (!whole && p.H > kLongSumH);
-    const bool small = plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
+    const bool small = plan_logprobs(p, M, V, bf16, whole);
     const int tile = small ? SmallShape::kTileT : kTile;
     const int64_t first_tokens = (int64_t)p.first.rows * tile, rest_tokens = (int64_t)p.rest.rows * tile;
     const size_t room = arrivals_bytes(M);

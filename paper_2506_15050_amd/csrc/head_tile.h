@@ -523,7 +523,7 @@ static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
 //   20 x V 152064, H 5120: 478 -> 403.  Where the rule says large: 300 x V 32000, H 512: 29.7 (34.2),
 //   146 x V 50021, H 1024: 42.2 (57.9), 2500 x V 5000, H 1024: 39.3 (47.4), 1000 x V 152064, H 5120: 1297 (2950)
 // fp32, which the matrix cores bound, loses 6 % per flop and wins that back by filling the chip, and always goes this
-// way (head.hip): 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  2064 x V 32000, H 1024: 1281 ->
+// way (plan_logprobs): 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  2064 x V 32000, H 1024: 1281 ->
 // 1114;  the worst seen, 1000 x V 32000, H 1024: 508 -> 601.
 typedef HeadCfg<uint16_t, false, true> SmallShape;
 constexpr int kSmallPerCu = SmallShape::kGroupsPerCu;
@@ -554,6 +554,20 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
     p.k_chunks = 1;
     p.n_tasks = p.rest_tasks;
     return true;
+}
+
+// fp32, and the bf16 rows that the one-token kernel can serve (off a stage or off 16 bytes) with a long H, take the small
+// tiles whatever the size, for the accuracy of their sums: the large ones add up all of H one step after the other, which
+// whole-stage bf16 always did.  Error of the log-probs against 64 bits, weights of 0.02, rms: H = 5112, 300 tokens, fp32
+// 1.8e-6 in large tiles, 5.0e-7 in small ones (6.1e-7 by the one-token kernel); bf16, 1500 tokens, V = 8000, H = 5120
+// misaligned 7.9e-7, 4.8e-7 (6.1e-7).  At H = 2040 bf16 gives 5.6e-7 in large tiles, 6.8e-7 by the one-token kernel.  What
+// that costs, large -> small: 2500 tokens, V = 50000, H = 2104: 0.50 -> 1.09 ms; H = 5112: 1.29 -> 2.83 ms; 16000 tokens,
+// V = 152064, H = 5112: 22.4 -> 110 ms (H = 5120: 17.8 ms).
+constexpr int kLongSumH = 2048;
+// The forward sweep's schedule; true: in small tiles.  whole: rows of whole stages (bf16: at aligned addresses too).
+static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool whole) {
+    const bool only_small = !bf16 || (!whole && p.H > kLongSumH);
+    return plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
 }
 
 // Plain product of M token-role rows and N W-role rows over K = 64 * k_tiles, columns = W-role tiles.  Whole rounds

@@ -4,17 +4,18 @@ and output tiles of the backward products whose contraction is cut into chunks."
 import numpy as np
 import pytest
 
+from test_head_routes import LARGE_RAGGED, LARGE_WHOLE
 from test_gpu_parity import _bf16_case, assert_within_term_bound, check_logprob_grads, check_logprobs, dev, host, ofast, tp  # noqa: F401
 from paper_2506_15050_amd import synth
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,V,H", [(5, 70000, 64),        # one token tile, as many vocabulary ranges as there may be
-                                   (1030, 3000, 64),      # 5 token tiles against 12 vocabulary tiles
-                                   (16500, 600, 64),      # 65 token tiles, 3 vocabulary tiles: whole rounds and a rest
-                                   (33000, 300, 64),      # whole rounds of 2 columns, one token tile left
-                                   (66000, 200, 64)])     # one vocabulary tile: rounds of 256 token tiles, 2 left
+@pytest.mark.parametrize("M,V,H", [(5, 70000, 64),        # small tiles: one token tile, 183 vocabulary ranges
+                                   (1030, 3000, 64),      # small tiles: 17 token tiles, 12 vocabulary ranges
+                                   (16500, 600, 64),      # large tiles: 65 token tiles, 3 vocabulary tiles
+                                   (33000, 300, 64),      # 129 token tiles, no cut of the vocabulary
+                                   (66000, 200, 64)])     # one vocabulary tile: a round of 256 token tiles, 2 left
 def test_logprobs_schedule_shapes(tp, M, V, H):
     rng = np.random.default_rng(M + V)
     hidden = synth.f32_to_bf16_bits(rng.normal(size=(999, H)).astype(np.float32))
@@ -22,6 +23,26 @@ def test_logprobs_schedule_shapes(tp, M, V, H):
     targets = rng.integers(0, V, size=M)
     targets[:3] = 0, V - 1, min(256, V - 1)
     check_logprobs(tp, hidden, w, rng.integers(0, 999, size=M), targets)
+
+
+@pytest.mark.parametrize("M,V,H", [*LARGE_WHOLE, *LARGE_RAGGED])
+def test_logprobs_large_tiles(tp, M, V, H):
+    """The 256 x 256 tiles at sizes that test_head_routes.py shows to reach them: whole and ragged rows, one token tile
+    and whole rounds with a rest, a vocabulary that ends one entry into a tile."""
+    rng = np.random.default_rng(M + V + H)
+    hidden = synth.f32_to_bf16_bits(rng.normal(size=(301, H)).astype(np.float32))
+    w = synth.f32_to_bf16_bits((rng.normal(size=(V, H)) / np.sqrt(H)).astype(np.float32))
+    rows, targets = rng.integers(0, 301, size=M), (np.arange(M) * 7 + V - 1) % V
+    args = (_padded(hidden, H + (-H % 8), 0), _padded(w, H + (-H % 8), 8), dev(rows.astype(np.int32)),
+            dev(targets.astype(np.int32)))
+    ref, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    few = M - M // 3 - 1                                   # the device's own count: token tiles cut short and left out
+    for n in (M, few):
+        st = tp.new_status("cuda")
+        logp, lse = tp.tppo_token_logprobs(*args, m_actual=dev(np.array([n], np.int64)), status=st)
+        assert int(host(st)[0]) == 0
+        # exact products summed in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
+        assert np.abs(host(logp)[:n] - ref[:n]).max() <= 1e-5 and np.abs(host(lse)[:n] - ref_lse[:n]).max() <= 1e-5
 
 
 @pytest.mark.parametrize("M,V,H", [(300, 20000, 64),      # grad_hidden: 2 output tiles, 313 K steps in chunks

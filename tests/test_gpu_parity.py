@@ -181,11 +181,12 @@ def test_logprobs_tiny_fp32(tp):
 
 def test_logprobs_generic_bf16_odd_shapes(tp):
     rng = np.random.default_rng(0)
-    H, V, N = 72, 333, 40                                 # H not a multiple of 64 -> generic kernel
+    H, V, N = 72, 333, 40                                 # H not a multiple of 64
     hidden = synth.f32_to_bf16_bits(rng.normal(size=(N, H)).astype(np.float32))
     w = synth.f32_to_bf16_bits((0.1 * rng.normal(size=(V, H))).astype(np.float32))
-    rows = rng.integers(0, N, size=57)
-    check_logprobs(tp, hidden, w, rows, rng.integers(0, V, size=57))
+    rows, targets = rng.integers(0, N, size=57), rng.integers(0, V, size=57)
+    check_logprobs(tp, hidden, w, rows, targets)          # tiles
+    check_logprobs(tp, hidden, w, rows, targets, workspace=tp._workspace(256, "cuda"))   # no room for them: generic kernel
 
 
 @pytest.mark.parametrize("M,V,H", [(1, 256, 64), (37, 1000, 128), (300, 1000, 256), (513, 2049, 192),
@@ -246,8 +247,8 @@ def test_logprobs_small_config_full(tp):
 @pytest.mark.parametrize("M,V,H", [(18600, 2048, 64), (21000, 1100, 128), (4200, 9000, 64)])
 def test_logprobs_many_token_tiles_every_output(tp, M, V, H):
     """Many 256-token tiles against a small vocabulary and hidden size, so the oracle can afford
-    every output: the persistent schedule then has several rounds of units per XCD, more than one
-    unit column, a ragged last group of unit rows and a ragged last token tile."""
+    every output: one round of the persistent schedule that several columns share, a last block of
+    fewer than 8 token tiles and a ragged last token tile."""
     rng = np.random.default_rng(M)
     N = M // 3 + 11                                       # rows are revisited, in no order
     hidden = synth.f32_to_bf16_bits(rng.normal(size=(N, H)).astype(np.float32))
@@ -315,18 +316,10 @@ def _stratified_rows(sel, seed):
 
 
 def _split_edge_targets(V, tile=256):
-    """Vocabulary ids on both sides of every boundary between vocabulary splits, for every split count
-    the kernel may choose (a split owns tiles [tiles*s/S, tiles*(s+1)/S) of `tile` ids), and both ends."""
-    tiles = (V + tile - 1) // tile
-    edges = set()
-    for S in (1, 2, 3) + tuple(range(4, 65, 4)):
-        for s in range(1, S):
-            edges.add((tiles * s // S) * tile)
-    ids = {0, V - 1}
-    for e in edges:
-        if 0 < e < V:
-            ids.update((e - 1, e))
-    return np.array(sorted(ids))
+    """Vocabulary ids on both sides of every boundary between tiles, which every cut of the vocabulary
+    falls on, and both ends."""
+    edges = np.arange(tile, V, tile)
+    return np.unique(np.concatenate([[0, V - 1], edges - 1, edges]))
 
 
 @pytest.mark.timeout(1200)
@@ -334,8 +327,8 @@ def _split_edge_targets(V, tile=256):
 def test_logprobs_full_size_stratified(tp, name):
     """Full-size shapes in the launch configuration the benchmark times.  The oracle checks, one by
     one, a stratified sample of the outputs: 16 per 256-token tile (one per accumulator block), each
-    sequence's first and last kept token; a few hundred of the sampled tokens get their target moved
-    onto the edges of the vocabulary splits."""
+    sequence's first and last kept token; some of the sampled tokens get their target moved onto the
+    edges of the vocabulary tiles."""
     import torch
     b = synth.make_batch(name)
     if b["cfg"].get("ids_from_policy"):

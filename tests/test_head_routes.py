@@ -1,0 +1,92 @@
+"""Which tiles and which division of the work the log-prob sweep takes: the rule
+itself (csrc/head_tile.h, host side), run at the sizes that the GPU tests rely
+on to reach a path.  A change of the rule that moves one of them shows here."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+# (tokens, vocabulary, hidden size): (token tiles, columns) of the whole rounds, of the rest
+LARGE_WHOLE = {
+    (200, 152064, 64): ((0, 4), (1, 198)),         # one token tile
+    (130, 131072, 64): ((0, 4), (1, 256)),         # ... against as many vocabulary ranges as there may be
+    (513, 65281, 64): ((0, 4), (3, 256)),          # three tasks per workgroup, a last vocabulary tile of one entry
+    (1024, 40961, 64): ((0, 4), (4, 54)),          # whole token tiles only
+    (17000, 4000, 64): ((64, 4), (3, 16)),         # a whole round and a finely cut rest
+    (33000, 1100, 64): ((64, 4), (65, 3)),         # a whole round and a rest of nearly another, 5 vocabulary tiles
+}
+LARGE_WHOLE_ELSEWHERE = {                          # shapes of other tests
+    (16500, 600, 64): ((0, 2), (65, 3)),           # no whole round although there could be one
+    (33000, 300, 64): ((0, 2), (129, 1)),
+    (66000, 200, 64): ((256, 1), (2, 1)),          # one vocabulary tile: a round of 256 token tiles
+    (18600, 2048, 64): ((0, 4), (73, 3)),
+    (21000, 1100, 128): ((0, 4), (83, 3)),
+    (4200, 9000, 64): ((0, 4), (17, 12)),
+}
+LARGE_RAGGED = {                                   # bf16 rows off a stage of 64
+    (300, 20000, 72): ((0, 4), (2, 79)),
+    (700, 30000, 8): ((0, 4), (3, 59)),            # a stage that is mostly zeros
+    (2500, 9000, 1000): ((0, 4), (10, 18)),
+    (300, 20000, 333): ((0, 4), (2, 79)),          # rows copied to 336
+    (18600, 2048, 200): ((0, 4), (73, 3)),
+    (17000, 4000, 136): ((64, 4), (3, 16)),
+    (33000, 1100, 72): ((64, 4), (65, 3)),
+}
+SMALL_WHOLE = {
+    (5, 70000, 64): (1, 183),
+    (1030, 3000, 64): (17, 12),
+    (1, 256, 64): (1, 2), (37, 1000, 128): (1, 8), (300, 1000, 256): (5, 8), (513, 2049, 192): (9, 17),
+    (256, 512, 64): (4, 4), (700, 5000, 1024): (11, 20),
+}
+SMALL_RAGGED = {
+    (57, 333, 72): (1, 3),
+    (1500, 8000, 5120): (24, 21),                  # long rows at misaligned addresses, whatever the size
+    (16000, 152064, 5112): (250, 1),
+}
+SMALL_FP32 = {(2064, 32000, 1024): (33, 23), (300, 32000, 64): (5, 50)}
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "head_tile.h"
+namespace tppo { int device_compute_units() { return 256; } }
+int main(int argc, char** argv) {
+    for (int i = 1; i + 4 < argc; i += 5) {
+        tppo::HeadParams p = {};
+        p.H = (atoi(argv[i + 2]) + 7) / 8 * 8;
+        const bool small = tppo::plan_logprobs(p, atol(argv[i]), atol(argv[i + 1]), atoi(argv[i + 3]), atoi(argv[i + 4]));
+        printf("%d %d %d %d %d\n", small, p.first_tasks ? p.first.rows : 0, p.first.cols, p.rest.rows, p.rest.cols);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    at = tmp_path_factory.mktemp("routes")
+    (at / "routes.hip").write_text(PROGRAM)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(at / "routes.hip"), "-o", str(at / "routes")],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+    def run(shapes, bf16, whole):
+        args = [str(x) for s in shapes for x in (*s, int(bf16), int(whole))]
+        out = subprocess.run([str(at / "routes"), *args], check=True, stdout=subprocess.PIPE, text=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return run
+
+
+@pytest.mark.parametrize("table,whole", [(LARGE_WHOLE, True), (LARGE_WHOLE_ELSEWHERE, True), (LARGE_RAGGED, False)])
+def test_large_tiles(rule, table, whole):
+    got = {s: ((f_rows, f_cols), (r_rows, r_cols)) if not small else "small"
+           for s, (small, f_rows, f_cols, r_rows, r_cols) in zip(table, rule(table, True, whole))}
+    assert got == table
+
+
+@pytest.mark.parametrize("table,bf16,whole", [(SMALL_WHOLE, True, True), (SMALL_RAGGED, True, False), (SMALL_FP32, False, True)])
+def test_small_tiles(rule, table, bf16, whole):
+    got = {s: (rows, cols) if small else "large" for s, (small, _, _, rows, cols) in zip(table, rule(table, bf16, whole))}
+    assert got == table
