@@ -3,14 +3,15 @@
 // (the quantity inside the ratio of Eq. (ppoloss)); logits never reach memory.
 //
 // Matrix-core path.  The logits of a 256-token x 256-vocabulary tile (64 x 128 in
-// calls too small for those) are accumulated with v_mfma_f32_16x16x32_bf16 (head_tile.h).
+// calls too small for those, in fp32 and for long ragged rows) are accumulated with
+// v_mfma_f32_16x16x32_bf16 or 16x16x4_f32 (head_tile.h).
 // The MFMA "row" operand is the W tile and the "column" operand the gathered
 // hidden rows, so the accumulators a lane holds for one block all belong to ONE
 // token (column lane % 16) and to different vocabulary entries: the running
 // maximum, the running sum of exponentials and the target logit of a token
 // live in that lane's registers across all vocabulary tiles of the sweep, with
 // no cross-lane traffic until the very end.  The work is (token tiles) x
-// (vocabulary splits), handed to a persistent grid (head_tile.h); each pair
+// (vocabulary splits), dealt out by the schedule of head_tile.h; each pair
 // sweeps its share of vocabulary tiles and writes one (max, sumexp, target
 // logit) triple per token; a small kernel merges the splits into logp and lse.
 //

@@ -21,7 +21,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
-// Epilogue 1: a finished 256 (vocabulary) x 256 (token) tile of logits becomes
+// Epilogue 1: a finished tile of logits (vocabulary x tokens) becomes
 // dz, row t of out[.., ld_out].  A lane owns one token column per block, and of
 // each block of 16 vocabulary entries the 4 of its lane group; two blocks' worth is
 // exchanged between the four lane groups of a token so that each holds 8
@@ -112,8 +112,8 @@ struct DzEpilogue {
     __device__ __forceinline__ void finish(const HeadParams&, float*, const Task&, int64_t, int64_t, int, int, int, int) {}
 };
 
-// Epilogue 2: plain store of the fp32 tile, out[t, v] (+)= acc -- the sweep as an
-// "NT" product out[T, V] = tokens[T, K] . w_role[V, K]^T.  A tile that holds one chunk of the contraction goes
+// Epilogue 2: plain store of the fp32 tile, out[t, v] (+)= acc -- the sweep as the
+// product out[T, V] = tokens[T, K] . w_role[V, K]^T.  A tile that holds one chunk of the contraction goes
 // whole into its place among the partial tiles.
 template <class C>
 struct StoreEpilogue {

@@ -1,8 +1,10 @@
-// Machinery shared by the LM-head kernels: the persistent, XCD-aware sweep of
-// 256 x 256 MFMA tiles (W-role rows x token-role rows, K contiguous in both
-// operands) with a pluggable per-lane epilogue.  The forward pass plugs in the
-// online log-softmax; the backward pass plugs in the softmax-derivative writer
-// and a plain tile store (which makes the same sweep an "NT" GEMM).
+// Machinery shared by the LM-head kernels: the XCD-aware sweep of MFMA tiles
+// (W-role rows x token-role rows) with a pluggable per-lane epilogue, as 256 x 256
+// tiles on a persistent grid or, where those leave the chip idle, 128 x 64 tiles
+// with a workgroup per task.  K is contiguous in both operands, or the row index of
+// one (KMAJOR).  The forward pass plugs in the online log-softmax; the backward
+// pass plugs in the softmax-derivative writer and a plain tile store, which makes
+// the sweep a matrix product.
 #pragma once
 #include <atomic>
 #include <type_traits>
@@ -153,7 +155,7 @@ constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4
 
 constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that waits for LDS reads only
 
-// Schedule.  The launch is persistent: 256 workgroups, one per CU; hardware id b runs on XCD b % 8 (ids go
+// Schedule.  The launch of the large tiles is persistent: 256 workgroups, one per CU; hardware id b runs on XCD b % 8 (ids go
 // round-robin over the 8 XCDs, each with its own L2).  The work is a list of tasks, 256 to a round, dealt out so
 // that the 32 workgroups of an XCD hold 32 CONSECUTIVE tasks.  A grid of `rows` token tiles x `cols` divisions of
 // the W-role side is listed in blocks of 8 rows, column by column: an XCD's 32 tasks are 8 token tiles x 4
@@ -171,6 +173,7 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 //                               into k_chunks of the contraction, whose partial tiles a second kernel adds up.
 // Workgroups of an XCD re-align at every round boundary with an arrival counter.  That wait is only a hint for
 // the caches: it is bounded and falls through, and nothing depends on it.
+// Small tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
 constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
 constexpr int kAlignSpins = 4096;
 __device__ __forceinline__ void align_round(int32_t* arrivals, int expected) {
@@ -625,9 +628,10 @@ static bool allow_lds(const void* fn, int lds_bytes) {
     return true;
 }
 
-// Clear the arrival counters and launch one sweep (persistent: one workgroup per CU).  A device that does not
-// report 256 compute units (a partition of the chip, another chip) is refused: the sweep would still be
-// correct there, but its workgroups would take turns instead of running side by side.
+// Launch one sweep: large tiles one workgroup per CU, with their arrival counters cleared first if there is more than
+// one round; small tiles one workgroup per task.  A device that does not report 256 compute units (a partition of
+// the chip, another chip) is refused: the sweep would still be correct there, but its workgroups would take turns
+// instead of running side by side.
 template <class C, template <class> class Epi>
 static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
