@@ -87,16 +87,16 @@ def _ptr(t):
     return None if t is None else t.data_ptr()          # the argument types turn it into a pointer
 
 
-# torch's way to a raw stream handle has a private name; a torch without it gets the public way, a Stream object that
-# costs 2.8 us to make (the smallest calls are bound by what happens here)
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+# The current stream of the current device.  torch's way to the raw handle has private names; a torch without them gets
+# the public way, a Stream object that costs 2.8 us to make (the smallest calls are bound by what happens here).
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
-
-def _stream():
-    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it."""
-    if _raw_stream is None:
+    def _stream():
+        return _raw_stream(_device())
+else:
+    def _stream():
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev_i32(t):
