@@ -96,11 +96,7 @@ __global__ __launch_bounds__(kGenThreads) void head_generic_kernel(
 }
 
 // ------------------------------------------------------------------ MFMA path
-// What a running maximum is held in: logits, or logits * log2(e) (head_tile.h, kLogitMax).  Measured, 32000 logits of
-// rms 1.4 and the sampled one at 8 to 12 / 30 to 35 / 60 to 65, rms error of its log-prob against 64 bits: 1.2e-7 / 2.4e-9 /
-// 0 in logits; 4.2e-7 / 8e-7 / 1.7e-6 in log2, with up to a third of the log-probs positive; the one-token kernel 9.5e-7 /
-// 2.4e-9 / 0.  The extra operation per logit costs ragged bf16 1 % (2512 tokens, H 1000, V 50021: 297.5 -> 300.7 us) and fp32
-// nothing.
+// What a running maximum is held in: logits, or logits * log2(e) (head_tile.h, kLogitMax).
 template <bool kLogitMax>
 struct MaxUnits {
     static constexpr float kLeast = kLogitMax ? kLowest : kNegBig;
@@ -319,16 +315,21 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
         gs += s_part[1][s][tok] * exp2f(Units::log2_ratio(s_part[0][s][tok], gm));
         gt += s_part[2][s][tok];
     }
-    if (kLogitMax) {                   // gt - gm before the sum's logarithm: a confident token's loses nothing to the size of its logit
+    // The log-prob is put together before anything is rounded at the size of the logits: gt - lse would lose half an ulp of
+    // them.  32000 logits of rms 1.4 and the sampled one at 8 to 12 / 30 to 35 / 60 to 65, rms error against 64 bits: 1.1e-7 /
+    // 2.4e-9 / 0 in logits, 1.8e-7 / 2.5e-9 / 0 in log2, 9.5e-7 / 2.4e-9 / 0 by the one-token kernel; by gt - lse from log2
+    // 4.2e-7 / 8e-7 / 1.7e-6, up to a third of them positive.
+    if (kLogitMax) {
         const float log_sum = logf(gs);
         logp[o] = (gt - gm) - log_sum;
         if (lse) lse[o] = gm + log_sum;
     } else {
-        // The rounding of gm is in the sum's terms, so it has to meet the sampled logit's before anything else is rounded:
-        // gt - lse loses half an ulp of the logit (rms 1.7e-6 at 60 to 65, with positive log-probs; this way 3e-8).
-        const float log_sum = log2f(gs);
-        logp[o] = (fmaf(gt, kLog2e, -gm) - log_sum) * kLn2;
-        if (lse) lse[o] = (gm + log_sum) * kLn2;
+        const float log_sum = log2f(gs), l = (gm + log_sum) * kLn2, d = fmaf(gt, kLog2e, -gm);
+        float lp = (d - log_sum) * kLn2;
+        if (gt * kLog2e == gm) lp = logf(__builtin_amdgcn_exp2f(d) / gs);   // the largest: gs holds this very term, so 1 is 1
+        else if (!isfinite(d)) lp = gt - l;                                 // (gt * log2(e) out of range)
+        logp[o] = lp;
+        if (lse) lse[o] = l;
     }
 }
 
@@ -395,9 +396,7 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     typedef HeadCfg<T, false> Whole;
     typedef HeadCfg<T, true> Ragged;
     p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
-    // (the ragged variant also takes whole stages: bf16 copies of misaligned rows, which want its exact maximum)
-    const bool bf16 = sizeof(T) == 2, whole = bf16 ? matrix_only : p.H % Whole::kBK == 0;
-    const bool small = plan_logprobs(p, M, V, bf16, whole);
+    const bool whole = p.H % Whole::kBK == 0, small = plan_logprobs(p, M, V, sizeof(T) == 2, matrix_only);
     const int tile = small ? SmallShape::kTileT : kTile;
     const int64_t first_tokens = (int64_t)p.first.rows * tile, rest_tokens = (int64_t)p.rest.rows * tile;
     const size_t room = arrivals_bytes(M);
@@ -413,12 +412,9 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     }
     if (rc != TPPO_OK) return rc;
     const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};
-    auto merge = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)), dim3(kMergeTokens * kMergeLanes),
-                           0, s, q, M, p.m_actual, sel_rows, p.sel_targets, n_rows, (int)V, out_index, logp, lse, status);
-    };
-    if (whole ? Whole::kLogitMax : Ragged::kLogitMax) merge(head_combine_kernel<true>);
-    else merge(head_combine_kernel<false>);
+    hipLaunchKernelGGL(head_combine_kernel<Whole::kLogitMax>, dim3((unsigned)((M + kMergeTokens - 1) / kMergeTokens)),
+                       dim3(kMergeTokens * kMergeLanes), 0, s, q, M, p.m_actual, sel_rows, p.sel_targets, n_rows, (int)V,
+                       out_index, logp, lse, status);
     return launch_result();
 }
 

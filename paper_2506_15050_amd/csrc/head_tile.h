@@ -98,10 +98,10 @@ struct HeadCfg {
     static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 256;
     static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
     static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
-    // The log-softmax's running maximum is held in units of the logits, exact, in the variants that took over from the
-    // one-token kernel (fp32, and bf16 rows off a stage or off 16 bytes): the largest term is then exactly 1, as it was
-    // there.  The whole-stage bf16 sweep holds it in units of log2, rounded, one operation per logit less.
-    static constexpr bool kLogitMax = sizeof(T) == 4 || RAGGED;
+    // The log-softmax's running maximum is held in logits in fp32, whose sweep the matrix cores bound: no finite logit is out
+    // of its range.  In bf16 it is held in units of log2, rounded, one operation per logit less (ragged rows: 1 % at H = 1000,
+    // 5 % at H = 72), and the merge takes that rounding back out (head.hip).
+    static constexpr bool kLogitMax = sizeof(T) == 4;
     // Small tiles have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
     // matrix cores have added up moves there, so that no sum runs over thousands of elements one after the other.
     static constexpr int kSumStages = SMALL ? 128 / kBK : 0;
@@ -567,9 +567,9 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
 // that costs, large -> small: 2500 tokens, V = 50000, H = 2104: 0.50 -> 1.09 ms; H = 5112: 1.29 -> 2.83 ms; 16000 tokens,
 // V = 152064, H = 5112: 22.4 -> 110 ms (H = 5120: 17.8 ms).
 constexpr int kLongSumH = 2048;
-// The forward sweep's schedule; true: in small tiles.  whole: rows of whole stages (bf16: at aligned addresses too).
-static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool whole) {
-    const bool only_small = !bf16 || (!whole && p.H > kLongSumH);
+// The forward sweep's schedule; true: in small tiles.  matrix_only: bf16 rows of whole stages at aligned addresses.
+static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool matrix_only) {
+    const bool only_small = !bf16 || (!matrix_only && p.H > kLongSumH);
     return plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
 }
 
