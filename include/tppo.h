@@ -168,6 +168,9 @@ int tppo_plan_build(const int32_t* resp_off, const int32_t* keep_len, const int3
  *      first; where it has no room for that (the size function below cannot
  *      see base pointers and leading dimensions) or an fp32 call has no
  *      workspace, a generic kernel is used, a hundred times slower.
+ *      bf16 rows off 64 elements or off 16 bytes with H > 2048 run in smaller
+ *      tiles, for the accuracy of their sums: two to five times slower than
+ *      aligned rows of whole 64s on large batches.
  *      fp32, and bf16 with H % 64 != 0, leading dimensions not multiples of 8
  *      or base pointers not 16-byte aligned: H <= 16320, beyond that
  *      TPPO_ERR_SIZE;
