@@ -238,14 +238,15 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int64_t m_eff = p.m_actual ? min(p.M, *p.m_actual) : p.M;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wv = wave / C::kWavesT, wt = wave % C::kWavesT;
-    const int frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     const int t_first = C::kSmall ? (int)blockIdx.x : xcd * kXcdGroups + slot, t_step = C::kSmall ? (int)gridDim.x : kSweepGroups;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
+    const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const int round = t / kSweepGroups;
     if (!C::kSmall && round > 0 && p.arrivals)                            // the first round starts aligned
         align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
