@@ -3,7 +3,7 @@
 // (the quantity inside the ratio of Eq. (ppoloss)); logits never reach memory.
 //
 // Matrix-core path.  The logits of a 256-token x 256-vocabulary tile (64 x 128 in
-// calls too small for those, in fp32 and for long ragged rows) are accumulated with
+// calls too small for those, in fp32 and for long ragged rows; 64 to 192 x 256 in between) are accumulated with
 // v_mfma_f32_16x16x32_bf16 or 16x16x4_f32 (head_tile.h).
 // The MFMA "row" operand is the W tile and the "column" operand the gathered
 // hidden rows, so the accumulators a lane holds for one block all belong to ONE
@@ -131,19 +131,19 @@ struct LaneSoftmax {
 
     // acc holds logits: lane owns column lane % 16 of block tb; entry e of block vb
     // is vocabulary id v_wave + row_in_wave(vb, e, lane / 16).  Clears acc.
-    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task&,
-                                         int64_t, int64_t, int vt, int wv, int, int lane) {
+    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams&, const Task& task,
+                                         int64_t, int64_t, int v0, int wv, int, int lane) {
         constexpr int kVB = C::kVB, kTB = C::kTB, kE = C::kAccElems;
-        const int grp = lane / C::kMI, V = p.V;
-        const int v_wave = vt * C::kTileV + wv * C::kWaveV;
-        if (vt * C::kTileV + C::kTileV > V) {                       // ragged last tile: mask ids >= V
+        const int grp = lane / C::kMI;
+        const int v_wave = v0 + wv * C::kWaveV;
+        if (v0 + C::kTileV > task.v_end) {                          // ragged last tile: mask ids beyond the task's
 #pragma unroll
             for (int vb = 0; vb < kVB; ++vb)
 #pragma unroll
                 for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
                     for (int e = 0; e < kE; ++e)
-                        if (v_wave + C::row_in_wave(vb, e, grp) >= V) acc[vb][tb][e] = -INFINITY;
+                        if (v_wave + C::row_in_wave(vb, e, grp) >= task.v_end) acc[vb][tb][e] = -INFINITY;
         }
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
@@ -172,17 +172,18 @@ struct LaneSoftmax {
         // target logit: rare (a lane owns kVB * kAccElems of V ids per tile), so only
         // waves in which some lane hits take the register-select path.  Row r of
         // a block belongs to lane group (r / 4) % kGroups, element (r / (4 kGroups)) * 4 + r % 4.
+        const int in_tile = min(C::kWaveV, task.v_end - v_wave);    // (a sampled id beyond it is another task's)
         bool hit = false;
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
             const int d = tgt[tb] - v_wave;
-            hit |= d >= 0 && d < C::kWaveV && ((d >> 2) % C::kGroups) == grp;
+            hit |= d >= 0 && d < in_tile && ((d >> 2) % C::kGroups) == grp;
         }
         if (__any(hit)) {
 #pragma unroll
             for (int tb = 0; tb < kTB; ++tb) {
                 const int d = tgt[tb] - v_wave;
-                if (d >= 0 && d < C::kWaveV && ((d >> 2) % C::kGroups) == grp) {
+                if (d >= 0 && d < in_tile && ((d >> 2) % C::kGroups) == grp) {
                     const int vb_t = d / C::kMI, r = d % C::kMI;
                     const int e_t = (r / (4 * C::kGroups)) * 4 + (r & 3);
                     float z = 0.f;
@@ -396,15 +397,19 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     typedef HeadCfg<T, false> Whole;
     typedef HeadCfg<T, true> Ragged;
     p.k_tiles = (p.H + Whole::kBK - 1) / Whole::kBK;
-    const bool whole = p.H % Whole::kBK == 0, small = plan_logprobs(p, M, V, sizeof(T) == 2, matrix_only);
-    const int tile = small ? SmallShape::kTileT : kTile;
+    const bool whole = p.H % Whole::kBK == 0;
+    const bool small = plan_logprobs(p, M, V, sizeof(T) == 2, matrix_only);
+    const int narrow = sizeof(T) == 2 ? plan_narrow(p, M, V, small) : 0;
+    const int tile = narrow ? 64 * narrow : small ? SmallShape::kTileT : kTile;
     const int64_t first_tokens = (int64_t)p.first.rows * tile, rest_tokens = (int64_t)p.rest.rows * tile;
     const size_t room = arrivals_bytes(M);
     char* ws = static_cast<char*>(workspace);
     p.part_first = reinterpret_cast<float*>(ws + room);
     p.part_rest = p.part_first + 3 * first_tokens * p.first.cols;
     int rc = TPPO_ERR_LAUNCH;
-    if (small) {
+    if (narrow) {
+        rc = whole ? launch_narrow<false, LaneSoftmax>(narrow, p, s) : launch_narrow<true, LaneSoftmax>(narrow, p, s);
+    } else if (small) {
         rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, room, s)
                    : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, room, s);
     } else if constexpr (sizeof(T) == 2) {

@@ -53,19 +53,20 @@ struct DzEpilogue {
         }
     }
 
-    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task&,
-                                         int64_t tok0, int64_t m_eff, int vt, int wv, int wt, int lane) {
+    __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task& task,
+                                         int64_t tok0, int64_t m_eff, int v0, int wv, int wt, int lane) {
         constexpr int kVB = C::kVB, kTB = C::kTB, kE = C::kAccElems;
-        const int grp = lane / C::kMI, v_wave = vt * C::kTileV + wv * C::kWaveV;
+        const int grp = lane / C::kMI, v_wave = v0 + wv * C::kWaveV;
+        const int stored = task.v_end == p.V ? (int)p.out_cols : task.v_end;    // columns up to here are this task's
         uint16_t* out = static_cast<uint16_t*>(p.out);
-        if (vt * C::kTileV + C::kTileV > p.V) {                     // ragged last tile: no entry there, dz = 0
+        if (v0 + C::kTileV > task.v_end) {                          // ragged last tile: no entry there, dz = 0
 #pragma unroll
             for (int vb = 0; vb < kVB; ++vb)
 #pragma unroll
                 for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
                     for (int e = 0; e < kE; ++e)
-                        if (v_wave + C::row_in_wave(vb, e, grp) >= p.V) acc[vb][tb][e] = -INFINITY;
+                        if (v_wave + C::row_in_wave(vb, e, grp) >= task.v_end) acc[vb][tb][e] = -INFINITY;
         }
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
@@ -97,8 +98,8 @@ struct DzEpilogue {
                     a[j] = quarter[0];
                     b[j] = quarter[1];
                 }
-                const int v0 = v_wave + vb * C::kMI + grp * 8;
-                if (t < m_eff && v0 < p.out_cols) *reinterpret_cast<uint4*>(row + v0) = make_uint4(a[0], a[1], b[0], b[1]);
+                const int v = v_wave + vb * C::kMI + grp * 8;
+                if (t < m_eff && v < stored) *reinterpret_cast<uint4*>(row + v) = make_uint4(a[0], a[1], b[0], b[1]);
             }
         }
 #pragma unroll
@@ -120,9 +121,9 @@ struct StoreEpilogue {
     __device__ __forceinline__ void init(const HeadParams&, int64_t, int64_t, int, int) {}
 
     __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task& task,
-                                         int64_t tok0, int64_t m_eff, int vt, int wv, int wt, int lane) {
+                                         int64_t tok0, int64_t m_eff, int v_tile, int wv, int wt, int lane) {
         const bool partial = task.rest && p.k_chunks > 1;
-        const int v_lane = (partial ? 0 : vt * C::kTileV) + wv * C::kWaveV + (lane / C::kMI) * 4;
+        const int v_lane = (partial ? 0 : v_tile) + wv * C::kWaveV + (lane / C::kMI) * 4;
         float* out = partial ? p.part_rest + (int64_t)task.part * (C::kTileV * C::kTileT) - tok0 * C::kTileV
                              : static_cast<float*>(p.out);
         const int64_t ld_out = partial ? C::kTileV : p.ld_out, out_cols = partial ? C::kTileV : p.out_cols;
@@ -337,8 +338,10 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         p.aux_index = in_index ? in_index + m0 : nullptr;
         p.out = dz; p.ld_out = L.v_pad; p.out_cols = L.v_pad;
         const bool small = plan_small(p, mc, V, plan_sweep(p, mc, V));
-        if ((small ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
-                   : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
+        const int narrow = plan_narrow(p, mc, V, small);
+        if ((narrow  ? launch_narrow<false, DzEpilogue>(narrow, p, s)
+             : small ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
+                     : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: columns of W; K = v_pad)
         if (grad_hidden) {

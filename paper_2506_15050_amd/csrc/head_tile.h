@@ -36,7 +36,8 @@ struct HeadParams {
     const int32_t* sel_targets;
     const int64_t* m_actual;
     int64_t n_rows, ld_h, ld_w, M;
-    int H, V, row_tiles, vocab_tiles;
+    int H, V, row_tiles;
+    int vocab_tiles, v_unit;           // what the columns of a grid divide: so many tiles (or parts of one) of v_unit rows
     int k_tiles;                       // K stages: H / kBK, rounded up
     // schedule
     Grid first, rest;                  // tasks 0 .. first_tasks - 1 come from `first`, the others from `rest`
@@ -82,11 +83,13 @@ struct HeadParams {
 // variant of its own: the selects cost registers that the plain one does not have to spare).
 // SMALL: 128 x 64 tiles and workgroups of 2 x 2 wavefronts, three to a CU, for calls that would leave much of the
 // chip idle with the large ones (plan_small has the line between them).
+// TOKEN_BLOCKS < 4 (bf16): narrow tiles, 256 x 64 TOKEN_BLOCKS, and a workgroup per task too: the large tile's workgroup and
+// W rows, for calls of some tens to some hundreds of tokens (plan_narrow).
 // KMAJOR (bf16, large tiles): one operand lies in memory with K as the ROW index -- 1 the W-role one, 2 the token-role
 // one; element (row r, k) is at base[k * ld + r].  A stage of it is kBK rows of 512 bytes, K row k's 16-byte chunk c in
 // slot c ^ swz_k(k), and ds_read_b64_tr_b16 takes fragments out transposed: 16 lanes read 4 K rows x 16 columns, lane i
 // gets column i's four.  Two of them make the fragment one ds_read_b128 gives of the other layout.
-template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0>
+template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0, int TOKEN_BLOCKS = 4>
 struct HeadCfg {
     static constexpr bool kRagged = RAGGED, kSmall = SMALL;
     static constexpr int kKMajor = KMAJOR;
@@ -95,16 +98,17 @@ struct HeadCfg {
     typedef typename std::conditional<kEsz == 2, bf16x8, f32x4>::type Frag;
     static constexpr int kMI = 16, kGroups = 64 / kMI, kAccElems = 4;
     typedef float Acc __attribute__((__vector_size__(kAccElems * sizeof(float))));
-    static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 256;
+    static constexpr bool kNarrow = TOKEN_BLOCKS != 4;
+    static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 64 * TOKEN_BLOCKS;
     static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
-    static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
+    static constexpr int kGroupsPerCu = SMALL ? 3 : TOKEN_BLOCKS == 1 ? 2 : 1;
     // The log-softmax's running maximum is held in logits in fp32, whose sweep the matrix cores bound: no finite logit is out
     // of its range.  In bf16 it is held in units of log2, rounded, one operation per logit less (ragged rows: 1 % at H = 1000,
     // 5 % at H = 72), and the merge takes that rounding back out (head.hip).
     static constexpr bool kLogitMax = sizeof(T) == 4;
-    // Small tiles have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
+    // Small tiles and narrow ones of up to 128 tokens have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
     // matrix cores have added up moves there, so that no sum runs over thousands of elements one after the other.
-    static constexpr int kSumStages = SMALL ? 128 / kBK : 0;
+    static constexpr int kSumStages = SMALL || TOKEN_BLOCKS <= 2 ? 128 / kBK : 0;
     static constexpr int kWaves = kWavesV * kWavesT, kThreads = kWaves * 64;
     static constexpr int kWaveV = kTileV / kWavesV, kWaveT = kTileT / kWavesT;    // wave tile
     static constexpr int kVB = kWaveV / kMI, kTB = kWaveT / kMI;                  // 16 x 16 blocks per wave
@@ -120,7 +124,7 @@ struct HeadCfg {
     static constexpr int kKSteps = (kChunks / 4) * kVB;
     // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
     // a full memory queue
-    static constexpr int kSpread = SMALL ? kKSteps * kMfmaPerStep : 32;
+    static constexpr int kSpread = SMALL ? kKSteps * kMfmaPerStep : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");
     static_assert(kKSteps % 2 == 0, "fragment double buffering assumes an even number of K steps");
@@ -173,7 +177,7 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 //                               into k_chunks of the contraction, whose partial tiles a second kernel adds up.
 // Workgroups of an XCD re-align at every round boundary with an arrival counter.  That wait is only a hint for
 // the caches: it is bounded and falls through, and nothing depends on it.
-// Small tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
+// Small and narrow tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
 constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
 constexpr int kAlignSpins = 4096;
 __device__ __forceinline__ void align_round(int32_t* arrivals, int expected) {
@@ -189,7 +193,7 @@ __device__ __forceinline__ void align_round(int32_t* arrivals, int expected) {
 
 struct Task {
     int row, col;                      // token tile, column of its grid
-    int vt_begin, vt_end;              // tiles of W-role rows
+    int v_begin, v_end;                // W-role rows; tiles of kTileV from v_begin on
     int k_begin, k_tiles;              // K range in steps of kBK
     int rest;                          // which grid: 0 first, 1 rest
     int part;                          // rest: index of the partial tile (chunk * rest_tasks + task)
@@ -217,14 +221,14 @@ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int all_k_ti
     const int height = min(kRowBlock, g.rows - block * kRowBlock);
     x.col = in_block / height;
     x.row = g.row0 + block * kRowBlock + in_block - x.col * height;
-    x.vt_begin = (int)((int64_t)p.vocab_tiles * x.col / g.cols);
-    x.vt_end = (int)((int64_t)p.vocab_tiles * (x.col + 1) / g.cols);
+    x.v_begin = (int)((int64_t)p.vocab_tiles * x.col / g.cols) * p.v_unit;
+    x.v_end = min(p.V, (int)((int64_t)p.vocab_tiles * (x.col + 1) / g.cols) * p.v_unit);
     return x;
 }
 
 // Epi (the per-lane epilogue) provides
 //   init(p, tok0, m_eff, wt, lane)                          once per task,
-//   fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane)       after each finished tile of W rows; clears acc,
+//   fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane)       after each finished tile of W rows; clears acc,
 //   finish(p, lds_scratch, task, tok0, m_eff, wv, wt, lane, tid)  after the task's tiles (workgroup-wide).
 // what the chunks beyond a ragged H hold, in both operands
 static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
@@ -242,19 +246,20 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const int wv = wave / C::kWavesT, wt = wave % C::kWavesT;
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    const int t_first = C::kSmall ? (int)blockIdx.x : xcd * kXcdGroups + slot, t_step = C::kSmall ? (int)gridDim.x : kSweepGroups;
+    constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
+    const int t_first = C::kSmall ? (int)blockIdx.x : xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
     const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const int round = t / kSweepGroups;
-    if (!C::kSmall && round > 0 && p.arrivals)                            // the first round starts aligned
+    if (kPersistent && round > 0 && p.arrivals)                            // the first round starts aligned
         align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
     const Task task = task_at(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
     if (tok0 >= m_eff) continue;                            // uniform over the workgroup
-    const int vt_begin = task.vt_begin, vt_end = task.vt_end, k_tiles = task.k_tiles;
-    const int total_iters = (vt_end - vt_begin) * k_tiles;
+    const int v_end = task.v_end, k_tiles = task.k_tiles;
+    const int total_iters = (v_end - task.v_begin + kTileV - 1) / kTileV * k_tiles;
 
     // ---- loader role: transfers wave*kDmaPerWave + q, each kRowsPerDma staged rows
     const int ld_row0 = wave * kDmaPerWave * C::kRowsPerDma + lane / C::kChunks;   // + q * kRowsPerDma
@@ -263,22 +268,22 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const int k_bytes = p.H * C::kEsz;
     const int64_t ld_w = p.ld_w * C::kEsz, ld_h = p.ld_h * C::kEsz;
     // this wavefront's transfers are all of one operand
-    constexpr int kVWaves = kTileV / (kDmaPerWave * C::kRowsPerDma);
+    constexpr int kVWaves = C::kKMajor ? kTileV / (kDmaPerWave * C::kRowsPerDma) : 1;
     const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
     const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
     typedef typename std::conditional<C::kKMajor != 0, int64_t, int>::type KPos;
     const KPos k_step = k_major ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h)) : (KPos)C::kRowBytes;
     const KPos k_first = task.k_begin * k_step;
-    int issue_vt = vt_begin, issue_kt = 0, issue_stage = 0;
+    int issue_v = task.v_begin, issue_kt = 0, issue_stage = 0;
     KPos issue_kpos = k_first;
     int issue_left = p.km_rows - task.k_begin * C::kBK;                 // K rows from the stage to be issued on
-    auto point_at_tile = [&](int vt, bool w_only) {
+    auto point_at_tile = [&](int v0, bool w_only) {
 #pragma unroll
         for (int q = 0; q < kDmaPerWave; ++q) {
             if (C::kKMajor && k_major) {                                // (columns that do not exist: any others, never stored)
                 const int k = km_row0 + 2 * q, col = ((lane & 31) ^ C::swz_k(k)) * 8;
                 if (C::kKMajor == 1)
-                    src[q] = static_cast<const char*>(p.w) + k * ld_w + (int64_t)min(vt * kTileV + col, p.km_cols - 8) * C::kEsz;
+                    src[q] = static_cast<const char*>(p.w) + k * ld_w + (int64_t)min(v0 + col, p.km_cols - 8) * C::kEsz;
                 else
                     src[q] = static_cast<const char*>(p.hidden) + k * ld_h + min(tok0 + col, (int64_t)p.km_cols - 8) * C::kEsz;
                 continue;
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
             const int chunk = (ld_slot ^ C::swz(r)) * 16;
             if (r < kTileV) {
-                const int64_t v = min((int64_t)vt * kTileV + r, (int64_t)p.V - 1);
+                const int64_t v = min(v0 + r, v_end - 1);
                 src[q] = static_cast<const char*>(p.w) + v * ld_w + chunk;
             } else if (!w_only) {
                 const int64_t t = min(tok0 + (r - kTileV), m_eff - 1);
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
                 if (km_row0 + 2 * q >= issue_left) src[q] = reinterpret_cast<const char*>(&kZeroChunk) - issue_kpos;
         }
     };
-    point_at_tile(vt_begin, false);
+    point_at_tile(task.v_begin, false);
     point_at_zeros();
     auto issue_one = [&](int q) {
         const unsigned dst = lds_base + issue_stage * C::kStageBytes + wave * kDmaPerWave * 1024;
@@ -321,8 +326,8 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         if (!C::kOneTile && ++issue_kt == k_tiles) {
             issue_kt = 0;
             issue_kpos = k_first;
-            ++issue_vt;
-            point_at_tile(min(issue_vt, vt_end - 1), true);
+            issue_v += kTileV;
+            point_at_tile(issue_v, true);
         }
         point_at_zeros();
     };
@@ -415,7 +420,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     load_frags(0, 0);
 
     typename C::Acc sums[C::kSumStages ? kVB : 1][C::kSumStages ? kTB : 1] = {};
-    int kt = 0, vt = vt_begin, stage = 0;
+    int kt = 0, v0 = task.v_begin, stage = 0;
     bool refill = false;                // transfers of the stage freed at the last barrier are pending
     for (int it = 0; it < total_iters; ++it) {
 #pragma unroll
@@ -450,13 +455,13 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             }
         }
         if (!C::kOneTile && kt == k_tiles) {            // a tile is complete
-            if constexpr (C::kSumStages != 0) epi.fold(sums, p, task, tok0, m_eff, vt, wv, wt, lane);
-            else epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
+            if constexpr (C::kSumStages != 0) epi.fold(sums, p, task, tok0, m_eff, v0, wv, wt, lane);
+            else epi.fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane);
             kt = 0;
-            ++vt;
+            v0 += kTileV;
         }
     }
-    if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, vt, wv, wt, lane);
+    if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane);
     __syncthreads();                    // every fragment read is done before the stages are reused
     epi.finish(p, reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
     __syncthreads();                    // merge buffer is read before the next task's transfers land
@@ -492,6 +497,7 @@ static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
     p.V = (int)V;
     p.row_tiles = (int)((M + kTile - 1) / kTile);
     p.vocab_tiles = (int)((V + kTile - 1) / kTile);
+    p.v_unit = kTile;
     const int rows = p.row_tiles, vts = p.vocab_tiles;
     int first_cols = vts < 4 ? (vts == 3 ? 2 : vts) : 4;            // 1, 2 or 4: a whole number of token tiles per round
     const int per_round = kSweepGroups / first_cols, most = rows / per_round;
@@ -550,6 +556,7 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
     p.V = (int)V;
     p.row_tiles = (int)rows;
     p.vocab_tiles = (int)vts;
+    p.v_unit = SmallShape::kTileV;
     p.first = {0, 0, 1};
     p.first_tasks = 0;
     p.rest = {0, (int)rows, (int)best_cols};
@@ -574,6 +581,65 @@ static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool m
     return plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
 }
 
+// The same sweep in narrow tiles, 256 W rows x 64 n tokens, n = 1 .. 3, where that ends sooner than the division that
+// plan_logprobs made in `p`: a few hundred tokens are most of one large tile or several, rounded up, and in small tiles a
+// workgroup waits out the latency of every stage.  Columns are ranges of W rows in units of 64 here, so that a call with
+// fewer tiles than CUs still spreads W evenly.  Returns n, with `p` set, or 0.
+// The times of a stage, a tile and a task on a CU (us; two columns: a W that the caches hold, and one that comes from HBM) are
+// fits to 364 sizes (20 .. 1300 tokens, V 1500 .. 152064, H 128 .. 5120; 17 % rms), and the narrow division has to be 5 % better
+// by them.  Over those sizes, old division -> narrow where the rule takes it, us a call:
+//   100 tokens x V 152064, H 5120: 792 -> 401;  300 x V 152064, H 5120: 657 -> 617;  20 x V 152064, H 5120: 424 -> 354;
+//   150 x V 32000, H 1024: 45.9 -> 28.3;  500 x V 12000, H 1024: 44.4 -> 25.4;  900 x V 5000, H 2048: 75.8 -> 39.7;
+//   1300 x V 12000, H 5120: 243 -> 169.  Where it leaves the old one: 942 x V 152064, H 5120: 1268 (n = 3: 1382);
+//   60 x V 32000, H 5120: 96.7 (n = 1: 124);  400 x V 32000, H 1024: 38.1 (n = 3: 49.7).  Below 320 of K it gains nothing.
+// fp32 keeps the small tiles (its matrix rate bounds it), and what small tiles served is not given to n = 3, whose sums run over
+// all of K: no sum gets longer.
+constexpr int kNarrowStages = 5;
+constexpr double kNarrowGain = 0.95;
+constexpr int64_t kCachedW = 128 << 20;            // bytes of W that a pass can expect to find in the 256 MB cache
+struct ShapeTime {
+    double stage[2], tile, task;
+};
+constexpr ShapeTime kShapeTime[5] = {              // [n]; 0: small tiles, 4: large ones
+    {{0.65, 1.0}, 1.2, 4.0}, {{0.75, 1.45}, 3.0, 5.0}, {{0.95, 1.62}, 3.0, 6.0}, {{1.0, 1.5}, 3.5, 7.0}, {{1.3, 1.65}, 4.5, 8.0}};
+static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
+    if (p.k_tiles < kNarrowStages) return 0;
+    const bool from_hbm = V * p.H * 2 > kCachedW;
+    auto time_of = [&](int n, double rounds, double tiles) {
+        const ShapeTime& t = kShapeTime[n];
+        return rounds * (t.task + tiles * (p.k_tiles * t.stage[from_hbm] + t.tile));
+    };
+    auto in_parts = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    double best;
+    if (small) {
+        best = time_of(0, (double)in_parts(p.rest_tasks, kSweepGroups * kSmallPerCu), (double)in_parts(p.vocab_tiles, p.rest.cols));
+    } else {
+        best = time_of(4, rounds_of(p.rest_tasks), (double)in_parts(p.vocab_tiles, p.rest.cols));
+        best += time_of(4, rounds_of(p.first_tasks), (double)in_parts(p.vocab_tiles, p.first.cols));
+    }
+    best *= kNarrowGain;
+    constexpr int kUnit = 64;
+    const int64_t units = in_parts(V, kUnit);
+    int best_n = 0;
+    int64_t best_cols = 0;
+    for (int n = 1; n <= (small ? 2 : 3); ++n) {
+        const int64_t rows = in_parts(M, 64 * n);
+        for (int64_t s = 1; s <= units && rows * s <= kRestTasks && rows * s * 64 * n <= kRestTasks * kTile; ++s) {
+            const double t = time_of(n, rounds_of(rows * s), (double)in_parts(in_parts(units, s) * kUnit, kTile));
+            if (t < best - 1e-9) { best = t; best_n = n; best_cols = s; }
+        }
+    }
+    if (best_n == 0) return 0;
+    p.row_tiles = (int)in_parts(M, 64 * best_n);
+    p.vocab_tiles = (int)units;
+    p.v_unit = kUnit;
+    p.first = {0, 0, 1};
+    p.first_tasks = 0;
+    p.rest = {0, p.row_tiles, (int)best_cols};
+    p.rest_tasks = p.n_tasks = p.row_tiles * (int)best_cols;
+    return best_n;
+}
+
 // Plain product of M token-role rows and N W-role rows over K = 64 * k_tiles, columns = W-role tiles.  Whole rounds
 // of 256 output tiles first; of the tiles that remain, fewer than a round, each is cut into k_chunks of the
 // contraction if that ends sooner.  part_bytes: room for the partial tiles.  A chunk keeps at least kMinChunk
@@ -586,6 +652,7 @@ static void plan_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t
     p.V = (int)N;
     p.row_tiles = (int)((M + kTile - 1) / kTile);
     p.vocab_tiles = (int)((N + kTile - 1) / kTile);
+    p.v_unit = kTile;
     p.first = p.rest = {0, p.row_tiles, p.vocab_tiles};
     const int64_t tiles = (int64_t)p.row_tiles * p.vocab_tiles;
     p.first_tasks = (int)(tiles / kSweepGroups * kSweepGroups);
@@ -611,7 +678,7 @@ static size_t arrivals_bytes(int64_t M) { return round_up((size_t)(M / kTile + 6
 
 // A kernel that wants more than 64 KiB of LDS has to be told so once per device.
 static bool allow_lds(const void* fn, int lds_bytes) {
-    constexpr int kMaxDevices = 64, kMaxKernels = 8;
+    constexpr int kMaxDevices = 64, kMaxKernels = 16;
     static std::atomic<const void*> done[kMaxDevices][kMaxKernels];
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) return false;
@@ -630,7 +697,7 @@ static bool allow_lds(const void* fn, int lds_bytes) {
 }
 
 // Launch one sweep: large tiles one workgroup per CU, with their arrival counters cleared first if there is more than
-// one round; small tiles one workgroup per task.  A device that does not report 256 compute units (a partition of
+// one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A device that does not report 256 compute units (a partition of
 // the chip, another chip) is refused: the sweep would still be correct there, but its workgroups would take turns
 // instead of running side by side.
 template <class C, template <class> class Epi>
@@ -638,8 +705,8 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
     if (C::kLdsBytes > 64 * 1024 && !allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes))
         return TPPO_ERR_LAUNCH;
-    static_assert(C::kSmall || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
-    const int n = C::kSmall ? 0 : arrival_count(p);
+    static_assert(C::kSmall || C::kNarrow || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
+    const int n = C::kSmall || C::kNarrow ? 0 : arrival_count(p);
     p.arrivals = nullptr;
     if (n > 8 && (size_t)n * sizeof(int32_t) <= arrivals_room) {
         p.arrivals = static_cast<int32_t*>(arrivals);
@@ -647,10 +714,18 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
         if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
     }
     constexpr int kMostGroups = 1 << 20;                            // (beyond that, several tasks per workgroup)
-    const int groups = !C::kSmall ? kSweepGroups : p.n_tasks < kMostGroups ? p.n_tasks : kMostGroups;
+    const int tasks = C::kSmall ? p.n_tasks : (p.n_tasks + 7) / 8 * 8;
+    const int groups = !C::kSmall && !C::kNarrow ? kSweepGroups : tasks < kMostGroups ? tasks : kMostGroups;
     hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(groups), dim3(C::kThreads),
                        C::kLdsBytes, s, p);
     return launch_result();
+}
+
+template <bool RAGGED, template <class> class Epi>
+static int launch_narrow(int n, HeadParams& p, hipStream_t s) {
+    return n == 1   ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 1>, Epi>(p, nullptr, 0, s)
+           : n == 2 ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 2>, Epi>(p, nullptr, 0, s)
+                    : launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 3>, Epi>(p, nullptr, 0, s);
 }
 
 }  // namespace tppo

@@ -1,0 +1,100 @@
+"""Log-prob sweeps in narrow tiles (256 W rows x 64, 128 or 192 tokens): which calls take them (the rule itself,
+csrc/head_tile.h, run on the host) and their results at the edges of tiles, of W ranges and of the last K stage."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from test_gpu_parity import _bf16_case, check_logprob_grads, dev, host, ofast, tp  # noqa: F401
+from test_head_routes import HIPCC, ROOT
+from paper_2506_15050_amd import synth
+
+# (tokens, vocabulary, hidden size): (64-token blocks of a tile, W ranges)
+NARROW = {
+    (65, 30011, 1024): (1, 118),                   # one token beyond a tile, W ranges of three and of four units
+    (385, 5000, 832): (1, 20),
+    (2500, 1011, 640): (1, 4),                     # 40 token tiles
+    (257, 20033, 1024): (2, 79),
+    (500, 12000, 320): (2, 47),                    # the shortest K
+    (1025, 7001, 704): (2, 28),
+    (900, 20001, 576): (3, 40),
+    (1300, 12007, 576): (3, 24),                   # ranges of two tiles, the second short
+}
+NARROW_RAGGED = {
+    (385, 5000, 840): (1, 20),
+    (1300, 4003, 2120): (2, 16),                   # too long for one sum over K
+    (450, 9000, 329): (2, 36),                     # rows copied to 336
+    (1300, 12007, 584): (3, 24),
+    (2500, 9000, 1000): (3, 18),
+}
+NOT = [(500, 12000, 256), (942, 152064, 5120), (60, 32000, 5120), (400, 32000, 1024), (15000, 32000, 1024)]
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "head_tile.h"
+namespace tppo { int device_compute_units() { return 256; } }
+int main(int argc, char** argv) {
+    for (int i = 1; i + 2 < argc; i += 3) {
+        tppo::HeadParams p = {};
+        p.H = (atoi(argv[i + 2]) + 7) / 8 * 8;
+        p.k_tiles = (p.H + 63) / 64;
+        const long M = atol(argv[i]), V = atol(argv[i + 1]);
+        const bool small = tppo::plan_logprobs(p, M, V, true, p.H % 64 == 0);
+        const int n = tppo::plan_narrow(p, M, V, small);
+        printf("%d %d %d %d\n", n, p.rest.cols, n == 0 || p.rest.rows == (M + 64 * n - 1) / (64 * n), p.n_tasks);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    at = tmp_path_factory.mktemp("narrow")
+    (at / "narrow.hip").write_text(PROGRAM)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(at / "narrow.hip"), "-o", str(at / "narrow")],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+    def run(shapes):
+        out = subprocess.run([str(at / "narrow"), *(str(x) for s in shapes for x in s)], check=True, stdout=subprocess.PIPE,
+                             text=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return run
+
+
+def test_which_calls(rule):
+    for table in (NARROW, NARROW_RAGGED):
+        got = dict(zip(table, rule(table)))
+        assert {s: g[:2] for s, g in got.items()} == table
+        # every token has a tile, and the partial results stay within what a workspace holds
+        assert all(g[2] and g[3] <= 1024 and g[3] * 64 * g[0] <= 1024 * 256 for g in got.values())
+    assert [g[0] for g in rule(NOT)] == [0] * len(NOT)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,V,H", [*NARROW, *NARROW_RAGGED])
+def test_logprobs(tp, M, V, H):
+    rng = np.random.default_rng(M + V + H)
+    hidden = synth.f32_to_bf16_bits(rng.normal(size=(301, H)).astype(np.float32))
+    w = synth.f32_to_bf16_bits((rng.normal(size=(V, H)) / np.sqrt(H)).astype(np.float32))
+    rows, targets = rng.integers(0, 301, size=M), (np.arange(M) * 7 + V - 1) % V
+    firsts = np.arange(64, V, 64)[: M // 2]                # sampled tokens on both sides of where a range of W may begin
+    targets[: len(firsts)], targets[M - len(firsts):] = firsts, firsts - 1
+    out = dev(rng.permutation(M + 5)[:M].astype(np.int32))
+    args = (dev(hidden), dev(w), dev(rows.astype(np.int32)), dev(targets.astype(np.int32)))
+    ref, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    at = host(out)
+    for n in (M, M - M // 3 - 1):                          # the device's own count: token tiles cut short and left out
+        st = tp.new_status("cuda")
+        logp, lse = tp.tppo_token_logprobs(*args, m_actual=dev(np.array([n], np.int64)), out_index=out, out_size=M + 5, status=st)
+        assert int(host(st)[0]) == 0
+        # exact products summed in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
+        assert np.abs(host(logp)[at][:n] - ref[:n]).max() <= 1e-5 and np.abs(host(lse)[at][:n] - ref_lse[:n]).max() <= 1e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,V,H", [(385, 5000, 832), (500, 12000, 320), (1300, 12007, 576)])
+def test_grads(tp, M, V, H):
+    check_logprob_grads(tp, *_bf16_case(M, V, H, seed=M + V))
