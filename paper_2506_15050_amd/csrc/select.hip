@@ -20,6 +20,7 @@ namespace tppo {
 
 constexpr int kScanThreads = 1024;
 constexpr int kOneLaunchSeqs = kScanThreads;
+constexpr int kListParts = 2;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
 constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
 constexpr int kFillMaxGroups = 512;                             // two per CU
 static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");
@@ -177,8 +178,8 @@ __global__ __launch_bounds__(kBuildThreads) void select_fill_kernel(FillArgs a, 
     }
 }
 
-// The whole filter in one launch, B <= kOneLaunchSeqs.  Workgroup 0 writes the small outputs and the plan's list;
-// the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
+// The whole filter in one launch, B <= kOneLaunchSeqs.  Workgroups 0 .. parts - 1 write the plan's list, the first of them also
+// the small outputs; the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
 // sequence a thread finds by bisection of the offsets in LDS.
 typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void store_some(int32_t* dst, int64_t m, const int (&x)[4], int n) {
@@ -195,19 +196,19 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
                                                                           int tail_drop, int32_t* __restrict__ resp_off,
                                                                           int32_t* __restrict__ sel_off,
                                                                           int32_t* __restrict__ keep_len,
-                                                                          int64_t* __restrict__ counts, int plan_cap,
+                                                                          int64_t* __restrict__ counts, int parts, int plan_cap,
                                                                           void* plan_raw) {
     __shared__ int32_t s_resp[kOneLaunchSeqs + 1], s_sel[kOneLaunchSeqs + 1], s_aux[2][kOneLaunchSeqs];
     __shared__ int s_wave[2][kBuildWaves], s_val[kBuildWaves];
     __shared__ BuildLds s_build;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool lead = blockIdx.x == 0;                               // (also of a grid of one, which then does everything)
-    const int worker = (int)blockIdx.x - 1, workers = (int)gridDim.x - 1;
+    const bool lead = (int)blockIdx.x < parts, first = blockIdx.x == 0;
+    const int worker = (int)blockIdx.x - parts, workers = (int)gridDim.x - parts;
     Sums mine = {0, 0, 0, 0};
     int first_pos = 0;
     bool fin = false;
     if (tid < B) {
-        mine = lengths_of(a.cu_seqlens, a.ctx_len, done, tid, a.n_tok, tail_drop, lead ? a.status : nullptr);
+        mine = lengths_of(a.cu_seqlens, a.ctx_len, done, tid, a.n_tok, tail_drop, first ? a.status : nullptr);
         first_pos = a.cu_seqlens[tid] + a.ctx_len[tid];
         fin = done[tid] != 0;
     }
@@ -241,12 +242,12 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
     __syncthreads();
     const int n_kept = s_sel[B];
     if (lead) {
-        if (tid < B) {
+        if (first && tid < B) {
             keep_len[tid] = mine.keep;
             resp_off[tid + 1] = win;
             sel_off[tid + 1] = keep;
         }
-        if (tid == 0) {
+        if (first && tid == 0) {
             resp_off[0] = 0;
             sel_off[0] = 0;
             long long n_val = 0;
@@ -263,8 +264,8 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
             }
         }
         if (plan_raw)
-            build_list(pl, s_build, (const int32_t*)s_resp, (const int32_t*)s_aux[0], (const int32_t*)s_aux[1], true, B,
-                       s_resp[B], 0, 1, a.status);
+            build_list_by_level(pl, s_build, (const int32_t*)s_resp, (const int32_t*)s_aux[0], (const int32_t*)s_aux[1], B,
+                                s_resp[B], (int)blockIdx.x, parts, a.status);
         return;
     }
     if (!a.sel_rows && !a.sel_targets && !a.sel_resp_idx) return;
@@ -357,8 +358,9 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
     const int64_t most = clear > fill ? clear : fill;
     const int workers = (int)(most < kFillMaxGroups ? most : kFillMaxGroups);
     if (B <= kOneLaunchSeqs) {
-        hipLaunchKernelGGL(select_one_launch_kernel, dim3(1 + workers), dim3(kBuildThreads), 0, s, a, done, (int)B,
-                           (int)tail_drop, resp_off, sel_off, keep_len, counts, (int)plan_cap, plan);
+        const int parts = plan && B > 2 * kWave ? kListParts : 1;
+        hipLaunchKernelGGL(select_one_launch_kernel, dim3(parts + workers), dim3(kBuildThreads), 0, s, a, done, (int)B,
+                           (int)tail_drop, resp_off, sel_off, keep_len, counts, parts, (int)plan_cap, plan);
         return launch_result();
     }
     Tile* tiles = want_fill ? static_cast<Tile*>(workspace) : nullptr;
