@@ -1,16 +1,20 @@
-"""Thin ctypes binding of libtppo.so (see include/tppo.h for the contract).
+"""Thin binding of libtppo.so (see include/tppo.h for the contract): ctypes, and for the calls of a training step a native
+half (csrc/marshal.cpp), which checks, allocates and calls in a third of the time.
 
 Argument marshalling only: every step of the path runs in the HIP kernels.
 PyTorch provides device memory and the current HIP stream.  There is no CPU
 fallback: if the shared library is missing, every call raises.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtppo.so")
+NATIVE_PATH = os.path.join(_HERE, "_marshal.so")
 
 TPPO_F32, TPPO_BF16 = 0, 1
 ERRORS = {-1: "TPPO_ERR_NULL", -2: "TPPO_ERR_SIZE", -3: "TPPO_ERR_PARAM", -4: "TPPO_ERR_DTYPE",
@@ -78,6 +82,23 @@ def load():
     return _lib
 
 
+_native_module = None
+
+
+def _native():
+    """The native half of the binding (built with the library)."""
+    global _native_module
+    if _native_module is None:
+        load()
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(f"{NATIVE_PATH} is missing: build it with "
+                               "`python -m paper_2506_15050_amd.build`; there is no fallback path")
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", NATIVE_PATH)
+        _native_module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+        loader.exec_module(_native_module)
+    return _native_module
+
+
 def _check(rc, what):
     if rc != 0:
         raise RuntimeError(f"{what} failed: {ERRORS.get(rc, rc)}")
@@ -123,35 +144,38 @@ def tppo_select(cu_seqlens, ctx_len, done, input_ids, tail_drop, capacity=None, 
     sel_rows, sel_targets, sel_resp_idx (capacity-sized) and counts (int64[3] =
     M, n_resp, N_val); with ``want_plan`` (or a ``plan`` buffer) also ``plan``, the
     work plan that tppo_egae* and the loss calls take."""
-    lib = load()
-    dev = cu_seqlens.device
+    native = _native()
     B = ctx_len.numel()
     if input_ids is not None:
         n_tok = input_ids.numel()
     assert n_tok is not None, "n_tok is required when input_ids is None"
     cap = n_tok if capacity is None else int(capacity)
-    out = dict(resp_off=torch.empty(B + 1, dtype=torch.int32, device=dev),
-               sel_off=torch.empty(B + 1, dtype=torch.int32, device=dev),
-               keep_len=torch.empty(B, dtype=torch.int32, device=dev),
-               counts=torch.empty(3, dtype=torch.int64, device=dev))
+    kinds, sizes = "iiil", [B + 1, B + 1, B, 3]
     if want_indices:
-        for k in ("sel_rows", "sel_targets", "sel_resp_idx"):
-            out[k] = torch.empty(cap, dtype=torch.int32, device=dev)
-        if input_ids is None:
-            out["sel_targets"] = None
-    ws = workspace
-    if ws is None and want_indices:
-        ws = _workspace(lib.tppo_select_workspace_bytes(B, max(cap, n_tok)), dev)
+        kinds += "iii" if input_ids is not None else "ii"
+        sizes += [cap] * (len(kinds) - 4)
+    if workspace is None and want_indices:
+        kinds += "b"
+        sizes.append(max(native.select_workspace_bytes(B, max(cap, n_tok)), 256))
     if plan is None and want_plan:
-        plan = _workspace(lib.tppo_plan_bytes(n_tok, B), dev)
+        kinds += "b"
+        sizes.append(max(native.plan_bytes(n_tok, B), 256))
+    made = iter(native.empties(cu_seqlens, kinds, *sizes))
+    resp_off, sel_off, keep_len, counts = next(made), next(made), next(made), next(made)
+    out = dict(resp_off=resp_off, sel_off=sel_off, keep_len=keep_len, counts=counts)
+    rows = targets = resp_idx = None
+    ws = workspace
+    if want_indices:
+        rows, resp_idx = next(made), next(made)
+        targets = next(made) if input_ids is not None else None
+        out.update(sel_rows=rows, sel_targets=targets, sel_resp_idx=resp_idx)
+        if ws is None:
+            ws = next(made)
+    if plan is None and want_plan:
+        plan = next(made)
     out["plan"] = plan
-    rc = lib.tppo_select(_ptr(_dev_i32(cu_seqlens)), _ptr(_dev_i32(ctx_len)), _ptr(_dev_i32(done)),
-                         _ptr(input_ids), B, n_tok, int(tail_drop),
-                         _ptr(out["resp_off"]), _ptr(out["sel_off"]), _ptr(out["keep_len"]),
-                         _ptr(out.get("sel_rows")), _ptr(out.get("sel_targets")),
-                         _ptr(out.get("sel_resp_idx")), cap, _ptr(out["counts"]), _ptr(ws),
-                         0 if ws is None else ws.numel(), _ptr(plan), 0 if plan is None else plan.numel(),
-                         _ptr(status), _stream())
+    rc = native.select(cu_seqlens, ctx_len, done, input_ids, B, n_tok, int(tail_drop), resp_off, sel_off, keep_len, rows,
+                       targets, resp_idx, cap, counts, ws, plan, status, _stream())
     _check(rc, "tppo_select")
     return out
 
@@ -180,15 +204,14 @@ def tppo_token_logprobs(hidden, w_head, sel_rows, sel_targets, M=None, m_actual=
     V = w_head.shape[0]
     M = sel_rows.numel() if M is None else int(M)
     n_out = M if out_size is None else int(out_size)
-    logp = torch.empty(n_out, dtype=torch.float32, device=hidden.device)
-    lse = torch.empty(n_out, dtype=torch.float32, device=hidden.device) if want_lse else None
+    native = _native()
+    made = native.empties(hidden, "ff" if want_lse else "f", *([n_out] * (2 if want_lse else 1)))
+    logp, lse = made if want_lse else (made[0], None)
     ws = workspace
     if ws is None:
         ws = _workspace(lib.tppo_token_logprobs_workspace_bytes(M, H, V, dt), hidden.device)
-    rc = lib.tppo_token_logprobs(_ptr(hidden), n_rows, H, hidden.stride(0), _ptr(w_head), V,
-                                 w_head.stride(0), dt, _ptr(_dev_i32(sel_rows)),
-                                 _ptr(_dev_i32(sel_targets)), M, _ptr(m_actual), _ptr(out_index),
-                                 _ptr(logp), _ptr(lse), _ptr(ws), ws.numel(), _ptr(status), _stream())
+    rc = native.token_logprobs(hidden, n_rows, H, hidden.stride(0), w_head, V, w_head.stride(0), dt, sel_rows, sel_targets, M,
+                               m_actual, out_index, logp, lse, ws, status, _stream())
     _check(rc, "tppo_token_logprobs")
     return logp, lse
 
@@ -207,10 +230,8 @@ def tppo_egae(rewards, values, resp_off, done, gamma, lam, bootstrap=None, statu
     n_resp, B = rewards.numel(), done.numel()
     adv, ret = out if out is not None else (torch.empty_like(rewards), torch.empty_like(rewards))
     ws = _scratch(lib.tppo_egae_workspace_bytes, n_resp, B, workspace, plan, rewards.device)
-    rc = lib.tppo_egae(_ptr(_dev_f32(rewards)), _ptr(_dev_f32(values)), _ptr(_dev_i32(resp_off)),
-                       _ptr(_dev_i32(done)), _ptr(bootstrap), B, n_resp, float(gamma), float(lam),
-                       _ptr(adv), _ptr(ret), _ptr(ws), 0 if ws is None else ws.numel(), _ptr(plan),
-                       _ptr(status), _stream())
+    rc = _native().egae(rewards, values, resp_off, done, bootstrap, B, n_resp, float(gamma), float(lam), adv, ret, ws, plan,
+                        status, _stream())
     _check(rc, "tppo_egae")
     return adv, ret
 
@@ -236,10 +257,8 @@ def tppo_egae_terminal(terminal_reward, values, resp_off, done, gamma, lam, boot
     n_resp, B = values.numel(), done.numel()
     adv, ret = out if out is not None else (torch.empty_like(values), torch.empty_like(values))
     ws = _scratch(lib.tppo_egae_workspace_bytes, n_resp, B, workspace, plan, values.device)
-    rc = lib.tppo_egae_terminal(_ptr(_dev_f32(terminal_reward)), _ptr(_dev_f32(values)),
-                                _ptr(_dev_i32(resp_off)), _ptr(_dev_i32(done)), _ptr(bootstrap), B, n_resp,
-                                float(gamma), float(lam), _ptr(adv), _ptr(ret), _ptr(ws),
-                                0 if ws is None else ws.numel(), _ptr(plan), _ptr(status), _stream())
+    rc = _native().egae_terminal(terminal_reward, values, resp_off, done, bootstrap, B, n_resp, float(gamma), float(lam), adv,
+                                 ret, ws, plan, status, _stream())
     _check(rc, "tppo_egae_terminal")
     return adv, ret
 
@@ -260,11 +279,8 @@ def tppo_ppo_losses(logp_new, logp_old, adv, v_new, v_old, ret, resp_off, keep_l
     n_resp = (logp_new if logp_new is not None else v_new).numel()
     res = torch.empty(ctypes.sizeof(LossOut), dtype=torch.uint8, device=dev) if out is None else out
     ws = _scratch(lib.tppo_ppo_losses_workspace_bytes, n_resp, B, workspace, plan, dev)
-    rc = lib.tppo_ppo_losses(_ptr(logp_new), _ptr(logp_old), _ptr(adv), _ptr(v_new), _ptr(v_old),
-                             _ptr(ret), _ptr(_dev_i32(resp_off)), _ptr(_dev_i32(keep_len)),
-                             _ptr(_dev_i32(done)), B, n_resp, float(eps_low), float(eps_high),
-                             float(xi_low), float(xi_high), _ptr(res), _ptr(ws),
-                             0 if ws is None else ws.numel(), _ptr(plan), _ptr(status), _stream())
+    rc = _native().ppo_losses(logp_new, logp_old, adv, v_new, v_old, ret, resp_off, keep_len, done, B, n_resp, float(eps_low),
+                              float(eps_high), float(xi_low), float(xi_high), res, ws, plan, status, _stream())
     _check(rc, "tppo_ppo_losses")
     return res
 
@@ -316,9 +332,8 @@ def tppo_value_head(hidden, w_value, bias=0.0, rows=None, M=None, m_actual=None,
         M = n_rows if rows is None else rows.numel()
     n_out = int(M) if out_size is None else int(out_size)
     v = torch.empty(n_out, dtype=torch.float32, device=hidden.device) if out is None else out
-    rc = lib.tppo_value_head(_ptr(hidden), n_rows, H, hidden.stride(0), _ptr(w_value), float(bias), TPPO_BF16,
-                             _ptr(rows), _ptr(out_index), int(M), _ptr(m_actual), _ptr(v), _ptr(status),
-                             _stream())
+    rc = _native().value_head(hidden, n_rows, H, hidden.stride(0), w_value, float(bias), TPPO_BF16, rows, out_index, int(M),
+                              m_actual, v, status, _stream())
     _check(rc, "tppo_value_head")
     return v
 
@@ -391,12 +406,10 @@ def tppo_ppo_losses_backward(logp_new, logp_old, adv, v_new, v_old, ret, resp_of
     res = torch.empty(ctypes.sizeof(LossOut), dtype=torch.uint8, device=dev) if out is None else out
     st = torch.empty(ctypes.sizeof(LossStats), dtype=torch.uint8, device=dev) if stats is None else stats
     ws = _scratch(lib.tppo_ppo_losses_backward_workspace_bytes, n_resp, B, workspace, plan, dev)
-    rc = lib.tppo_ppo_losses_backward(
-        _ptr(logp_new), _ptr(logp_old), _ptr(adv), _ptr(v_new), _ptr(v_old), _ptr(ret),
-        _ptr(_dev_i32(resp_off)), _ptr(_dev_i32(keep_len)), _ptr(_dev_i32(done)), B, n_resp,
-        float(eps_low), float(eps_high), float(xi_low), float(xi_high), float(policy_scale),
-        float(value_scale), int(policy_denominator), int(value_denominator), _ptr(g_lp), _ptr(g_v),
-        _ptr(res), _ptr(st), _ptr(ws), 0 if ws is None else ws.numel(), _ptr(plan), _ptr(status), _stream())
+    rc = _native().ppo_losses_backward(
+        logp_new, logp_old, adv, v_new, v_old, ret, resp_off, keep_len, done, B, n_resp, float(eps_low), float(eps_high),
+        float(xi_low), float(xi_high), float(policy_scale), float(value_scale), int(policy_denominator),
+        int(value_denominator), g_lp, g_v, res, st, ws, plan, status, _stream())
     _check(rc, "tppo_ppo_losses_backward")
     return g_lp, g_v, res, st
 

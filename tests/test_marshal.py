@@ -1,0 +1,53 @@
+"""The binding's native half: what it refuses, and the buffers it makes (no GPU work here)."""
+import os
+
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def native():
+    from paper_2506_15050_amd import binding, build
+    if not (os.path.exists(binding.LIB_PATH) and os.path.exists(binding.NATIVE_PATH)):
+        build.build()
+    return binding._native()
+
+
+def test_empties(native):
+    made = native.empties(torch.zeros(1), "ilfb", 3, 0, 5, 7)
+    assert [t.dtype for t in made] == [torch.int32, torch.int64, torch.float32, torch.uint8]
+    assert [tuple(t.shape) for t in made] == [(3,), (0,), (5,), (7,)] and len({t.data_ptr() for t in made if t.numel()}) == 3
+    for bad, error in (((torch.zeros(1), "i", -3), RuntimeError), ((torch.zeros(1), "ii", 3), TypeError),
+                       ((None, "i", 3), TypeError), ((torch.zeros(1), "i", "3"), TypeError)):
+        with pytest.raises(error):
+            native.empties(*bad)
+
+
+@pytest.mark.parametrize("args,error", [
+    ([], TypeError),                                                        # count
+    ([torch.zeros(3)] * 15, AssertionError),                                # not on the device
+    ([None] * 15, AssertionError),                                          # no tensor where one is required
+])
+def test_refusals(native, args, error):
+    with pytest.raises(error):
+        native.egae(*args)
+
+
+def test_codes_and_pointers_reach_the_entry_point(native):
+    # all pointers NULL: the entry point's own codes, by what it looks at first
+    args = [None, 1, 8, 8, None, 0.0, 1, None, None, 3, None, None, None, 0]
+    assert native.value_head(*args) == -1                                   # NULL
+    assert native.value_head(*args[:9], -3, *args[10:]) == -2               # size
+    assert native.value_head(*args[:9], 0, *args[10:]) == 0                 # nothing to do
+    with pytest.raises(AttributeError):
+        native.value_head("hidden", *args[1:])
+    with pytest.raises(TypeError):
+        native.value_head(*args[:13], "stream")
+
+
+def test_sizes(native):
+    from paper_2506_15050_amd import binding
+    lib = binding.load()
+    for n, B in ((0, 0), (1, 1), (1000, 3), (2_400_000, 512)):
+        assert native.plan_bytes(n, B) == lib.tppo_plan_bytes(n, B)
+        assert native.select_workspace_bytes(B, n) == lib.tppo_select_workspace_bytes(B, n)
