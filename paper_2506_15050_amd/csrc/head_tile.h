@@ -101,7 +101,7 @@ struct HeadCfg {
     static constexpr bool kNarrow = TOKEN_BLOCKS != 4;
     static constexpr int kTileV = SMALL ? 128 : 256, kTileT = SMALL ? 64 : 64 * TOKEN_BLOCKS;
     static constexpr int kWavesV = 2, kWavesT = SMALL ? 2 : 4, kBK = 128 / kEsz, kStages = 2;
-    static constexpr int kGroupsPerCu = SMALL ? 3 : TOKEN_BLOCKS == 1 ? 2 : 1;
+    static constexpr int kGroupsPerCu = SMALL ? 3 : 1;
     // The log-softmax's running maximum is held in logits in fp32, whose sweep the matrix cores bound: no finite logit is out
     // of its range.  In bf16 it is held in units of log2, rounded, one operation per logit less (ragged rows: 1 % at H = 1000,
     // 5 % at H = 72), and the merge takes that rounding back out (head.hip).
@@ -117,7 +117,9 @@ struct HeadCfg {
     static constexpr int kRowBytes = kBK * kEsz, kChunks = kRowBytes / 16;
     static constexpr int kRows = kTileV + kTileT;
     static constexpr int kStageBytes = kRows * kRowBytes;
-    static constexpr int kLdsBytes = kStages * kStageBytes;
+    // W's lines are brought into L2 ahead of their transfers (head_mfma_kernel, prefetch)
+    static constexpr bool kPrefetch = kEsz == 2 && !SMALL && (RAGGED || kNarrow);
+    static constexpr int kLdsBytes = kStages * kStageBytes + (kPrefetch ? 256 : 0);
     static constexpr int kRowsPerDma = 1024 / kRowBytes;                  // one wave-wide 16 B/lane transfer
     static constexpr int kDmaPerStage = kRows / kRowsPerDma;
     static constexpr int kDmaPerWave = kDmaPerStage / kWaves;
@@ -149,6 +151,14 @@ struct HeadCfg {
 // before the workgroup barrier that publishes the stage.
 __device__ __forceinline__ void dma_16b_per_lane(const void* src, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_base), "v"(src)
+                 : "memory", "m0");
+}
+
+// The same with 4 bytes a lane, 256 bytes in all.
+__device__ __forceinline__ void dma_4b_per_lane(const void* src, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
                  :
                  : "s"(lds_base), "v"(src)
                  : "memory", "m0");
@@ -331,6 +341,48 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
         point_at_zeros();
     };
+    // ---- Prefetch.  A stage's transfers go out in the first half of the stage before and are waited for at its end: time
+    // enough for what lies in L2, hardly for a miss.  So kAhead stages before its transfers the 256 rows' lines of a stage of W
+    // are touched, 64 by each of four wavefronts, with a transfer of 4 bytes a lane into a corner of LDS that nobody reads (a
+    // load would hold registers until it returns).  Where workgroups of the XCD share the W tile (their token tiles
+    // follow each other), each touches its part.  It is the last transfer that a wavefront has under way at a barrier, so
+    // it is the one that may still be: the counter counts in order.
+    // Measured with W in HBM, us a call: 2516 tokens x V 50021, H 1000: 270 -> 247;  300 x V 152064, H 5120: 604 -> 555;
+    // 900 x V 20001, H 576: 38.0 -> 34.4;  100 x V 20000, H 4096: 87.1 -> 65.8;  20 x V 152064, H 5120: 352 -> 343.  With W in a
+    // cache it costs 2 .. 5 % (a pass over other tensors between two calls, as in a training step, leaves little of W there).
+    // One stage ahead takes 271 us for the first, four 608 for the second.  Whole stages in large tiles lose by it (H = 3584:
+    // 6 %): all token tiles sweep the same W there, which is in a cache as it is, and the requests are a quarter more.
+    constexpr int kAhead = 2;
+    const Grid& grid = task.rest ? p.rest : p.first;
+    const bool prefetches = C::kPrefetch && wave >= 4 &&
+                            ((wave ^ (task.row - grid.row0)) & (grid.rows >= 4 ? 3 : grid.rows >= 2 ? 1 : 0)) == 0;
+    const char* ahead = nullptr;
+    int ahead_v = task.v_begin, ahead_kt = 0;
+    auto point_ahead = [&]() {
+        ahead = static_cast<const char*>(p.w) + min(ahead_v + (wave & 3) * 64 + lane, v_end - 1) * ld_w;
+    };
+    auto prefetch_advance = [&]() {
+        ahead += C::kRowBytes;
+        if (++ahead_kt == k_tiles) {
+            ahead_kt = 0;
+            ahead_v += kTileV;
+            point_ahead();
+        }
+    };
+    auto prefetch = [&]() {
+        if (C::kPrefetch && prefetches) {
+            dma_4b_per_lane(ahead, lds_base + C::kStages * C::kStageBytes);
+            prefetch_advance();
+        }
+    };
+    auto wait_for_stage = [&]() {
+        if (C::kPrefetch && prefetches) __builtin_amdgcn_s_waitcnt(vmcnt_imm(1));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    };
+    if (C::kPrefetch && prefetches) {
+        point_ahead();
+        for (int i = 0; i < 1 + kAhead; ++i) prefetch_advance();
+    }
     Epi<C> epi;
     epi.init(p, tok0, m_eff, wt, lane);
 
@@ -416,6 +468,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
 #pragma unroll
         for (int q = 0; q < kDmaPerWave; ++q) issue_one(q);
         issue_advance();
+        prefetch();
     }
     load_frags(0, 0);
 
@@ -427,7 +480,10 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         for (int ks = 0; ks + 1 < kKSteps; ++ks) {
             load_frags(stage, ks + 1);
             mfma_step(ks, ks + 1, refill);
-            if (ks + 2 == kSpreadSteps && refill) issue_advance();
+            if (ks + 2 == kSpreadSteps && refill) {
+                issue_advance();
+                prefetch();
+            }
         }
         // The stage's last fragments are in registers.  Hand the stage back,
         // publish the next one and fetch its first fragments BEFORE issuing the
@@ -435,7 +491,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         refill = false;
         __builtin_amdgcn_s_waitcnt(kLgkm0);     // here, on both paths: behind the branch it would wait for the next stage's too
         if (it + 1 < total_iters) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            wait_for_stage();
             __syncthreads();            // stage it+1 landed for everyone; everyone left stage it
             refill = it + 2 < total_iters;
             load_frags(stage ^ 1, 0);
@@ -462,6 +518,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
     }
     if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane);
+    if (C::kPrefetch) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));         // (this workgroup's LDS is somebody else's after its end)
     __syncthreads();                    // every fragment read is done before the stages are reused
     epi.finish(p, reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
     __syncthreads();                    // merge buffer is read before the next task's transfers land
@@ -587,11 +644,12 @@ static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool m
 // fewer tiles than CUs still spreads W evenly.  Returns n, with `p` set, or 0.
 // The times of a stage, a tile and a task on a CU (us; two columns: a W that the caches hold, and one that comes from HBM) are
 // fits to 364 sizes (20 .. 1300 tokens, V 1500 .. 152064, H 128 .. 5120; 17 % rms), and the narrow division has to be 5 % better
-// by them.  Over those sizes, old division -> narrow where the rule takes it, us a call:
-//   100 tokens x V 152064, H 5120: 792 -> 401;  300 x V 152064, H 5120: 657 -> 617;  20 x V 152064, H 5120: 424 -> 354;
-//   150 x V 32000, H 1024: 45.9 -> 28.3;  500 x V 12000, H 1024: 44.4 -> 25.4;  900 x V 5000, H 2048: 75.8 -> 39.7;
-//   1300 x V 12000, H 5120: 243 -> 169.  Where it leaves the old one: 942 x V 152064, H 5120: 1268 (n = 3: 1382);
-//   60 x V 32000, H 5120: 96.7 (n = 1: 124);  400 x V 32000, H 1024: 38.1 (n = 3: 49.7).  Below 320 of K it gains nothing.
+// by them.  Over 300 of those sizes (H from 320), W in HBM: taken by 132, 1.42 times as fast in the geometric mean, 3 % slower at
+// the worst (1300 x V 32000, H 2048: 160 -> 165), and the choice costs 1.1 % more than the best division of each.
+// Old division -> narrow, us a call:  100 tokens x V 152064, H 5120: 792 -> 387;  300: 666 -> 573;  20: 423 -> 343;
+//   190 x V 32000, H 1024: 57.7 -> 31.1;  500 x V 12000, H 1024: 54.5 -> 27.6;  900 x V 5000, H 2048: 95.1 -> 45.5;
+//   1300 x V 12000, H 5120: 246 -> 176.  Where it leaves the old one: 900 x V 152064, H 5120: 1266 (n = 3: 1277);
+//   60 x V 32000, H 5120: 97.9 (n = 1: 113).  Below 320 of K it gains nothing.
 // fp32 keeps the small tiles (its matrix rate bounds it), and what small tiles served is not given to n = 3, whose sums run over
 // all of K: no sum gets longer.
 constexpr int kNarrowStages = 5;
