@@ -31,9 +31,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // sampled token and the ragged last tile are rare branches.  Measured: 16414
 // tokens, H = 1024, V = 32000, the whole backward call 3.33 -> 3.21 ms against
 // per-entry selects, rounding in integer steps and 8-byte stores.  (Non-temporal
-// stores: 2 % faster there, 1 % slower at H = 5120.)
+// stores: 3 % faster at H = 512, as fast there, 4 % slower at 4096 tokens, V = 152064, 2 % at H = 3584.)
 template <class C>
 struct DzEpilogue {
+    static constexpr bool kPrefetch = false;
     float lse2[C::kTB], g[C::kTB];
     int tgt[C::kTB];
 
@@ -113,11 +114,23 @@ struct DzEpilogue {
     __device__ __forceinline__ void finish(const HeadParams&, float*, const Task&, int64_t, int64_t, int, int, int, int) {}
 };
 
+// The same in large tiles up to this H, where the sweep brings W's lines into L2 ahead (head_mfma_kernel): between two tiles
+// each workgroup stores 128 KB of dz, on an XCD as much as its L2 holds, and the next tile's W is gone from there; with a
+// longer H the stores are rarer, and the requests cost more than they give.  The whole backward call, us:
+// H 512, 32768 tokens x V 12000: 1284 -> 1246;  H 576, 4096 x 32000: 574 -> 561;  H 1024, 16414 x 32000: 2816 -> 2758;
+// H 1536: 4198 -> 4133;  H 2048, 8206 x 32000: 2697 -> 2724, 1300 x 152064: 2609 -> 2581;  H 3584, 8206 x 32000: 4680 -> 4731.
+constexpr int kPrefetchH = 1536;
+template <class C>
+struct DzAheadEpilogue : DzEpilogue<C> {
+    static constexpr bool kPrefetch = true;
+};
+
 // Epilogue 2: plain store of the fp32 tile, out[t, v] (+)= acc -- the sweep as the
 // product out[T, V] = tokens[T, K] . w_role[V, K]^T.  A tile that holds one chunk of the contraction goes
 // whole into its place among the partial tiles.
 template <class C>
 struct StoreEpilogue {
+    static constexpr bool kPrefetch = false;
     __device__ __forceinline__ void init(const HeadParams&, int64_t, int64_t, int, int) {}
 
     __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task& task,
@@ -339,9 +352,10 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         p.out = dz; p.ld_out = L.v_pad; p.out_cols = L.v_pad;
         const bool small = plan_small(p, mc, V, plan_sweep(p, mc, V));
         const int narrow = plan_narrow(p, mc, V, small);
-        if ((narrow  ? launch_narrow<false, DzEpilogue>(narrow, p, s)
-             : small ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
-                     : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
+        if ((narrow            ? launch_narrow<false, DzEpilogue>(narrow, p, s)
+             : small           ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
+             : H <= kPrefetchH ? launch_sweep<BwdCfg, DzAheadEpilogue>(p, arrivals, room, s)
+                               : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: columns of W; K = v_pad)
         if (grad_hidden) {

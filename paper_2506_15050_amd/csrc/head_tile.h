@@ -106,8 +106,9 @@ struct HeadCfg {
     // of its range.  In bf16 it is held in units of log2, rounded, one operation per logit less (ragged rows: 1 % at H = 1000,
     // 5 % at H = 72), and the merge takes that rounding back out (head.hip).
     static constexpr bool kLogitMax = sizeof(T) == 4;
-    // Small tiles and narrow ones of up to 128 tokens have registers for a second set of accumulators: every kSumStages stages (128 elements of K) what the
-    // matrix cores have added up moves there, so that no sum runs over thousands of elements one after the other.
+    // Small tiles and narrow ones of up to 128 tokens have registers for a second set of accumulators: every kSumStages stages
+    // (128 elements of K) what the matrix cores have added up moves there, so that no sum runs over thousands of elements one
+    // after the other.
     static constexpr int kSumStages = SMALL || TOKEN_BLOCKS <= 2 ? 128 / kBK : 0;
     static constexpr int kWaves = kWavesV * kWavesT, kThreads = kWaves * 64;
     static constexpr int kWaveV = kTileV / kWavesV, kWaveT = kTileT / kWavesT;    // wave tile
@@ -119,7 +120,7 @@ struct HeadCfg {
     static constexpr int kStageBytes = kRows * kRowBytes;
     // W's lines are brought into L2 ahead of their transfers (head_mfma_kernel, prefetch)
     static constexpr bool kPrefetch = kEsz == 2 && !SMALL && (RAGGED || kNarrow);
-    static constexpr int kLdsBytes = kStages * kStageBytes + (kPrefetch ? 256 : 0);
+    static constexpr int kLdsBytes = kStages * kStageBytes + (kEsz == 2 && !SMALL ? 256 : 0);
     static constexpr int kRowsPerDma = 1024 / kRowBytes;                  // one wave-wide 16 B/lane transfer
     static constexpr int kDmaPerStage = kRows / kRowsPerDma;
     static constexpr int kDmaPerWave = kDmaPerStage / kWaves;
@@ -351,10 +352,12 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     // 900 x V 20001, H 576: 38.0 -> 34.4;  100 x V 20000, H 4096: 87.1 -> 65.8;  20 x V 152064, H 5120: 352 -> 343.  With W in a
     // cache it costs 2 .. 5 % (a pass over other tensors between two calls, as in a training step, leaves little of W there).
     // One stage ahead takes 271 us for the first, four 608 for the second.  Whole stages in large tiles lose by it (H = 3584:
-    // 6 %): all token tiles sweep the same W there, which is in a cache as it is, and the requests are a quarter more.
+    // 6 %, 1024: 3 %): all token tiles sweep the same W there, which is in a cache as it is, and the requests are a quarter
+    // more.  Unless the epilogue's stores drive W out of L2 (DzAheadEpilogue).
     constexpr int kAhead = 2;
+    constexpr bool kPrefetch = C::kPrefetch || Epi<C>::kPrefetch;
     const Grid& grid = task.rest ? p.rest : p.first;
-    const bool prefetches = C::kPrefetch && wave >= 4 &&
+    const bool prefetches = kPrefetch && wave >= 4 &&
                             ((wave ^ (task.row - grid.row0)) & (grid.rows >= 4 ? 3 : grid.rows >= 2 ? 1 : 0)) == 0;
     const char* ahead = nullptr;
     int ahead_v = task.v_begin, ahead_kt = 0;
@@ -370,16 +373,16 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
     };
     auto prefetch = [&]() {
-        if (C::kPrefetch && prefetches) {
+        if (kPrefetch && prefetches) {
             dma_4b_per_lane(ahead, lds_base + C::kStages * C::kStageBytes);
             prefetch_advance();
         }
     };
     auto wait_for_stage = [&]() {
-        if (C::kPrefetch && prefetches) __builtin_amdgcn_s_waitcnt(vmcnt_imm(1));
+        if (kPrefetch && prefetches) __builtin_amdgcn_s_waitcnt(vmcnt_imm(1));
         else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     };
-    if (C::kPrefetch && prefetches) {
+    if (kPrefetch && prefetches) {
         point_ahead();
         for (int i = 0; i < 1 + kAhead; ++i) prefetch_advance();
     }
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
         }
     }
     if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane);
-    if (C::kPrefetch) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));         // (this workgroup's LDS is somebody else's after its end)
+    if (kPrefetch) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));            // (this workgroup's LDS is somebody else's after its end)
     __syncthreads();                    // every fragment read is done before the stages are reused
     epi.finish(p, reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
     __syncthreads();                    // merge buffer is read before the next task's transfers land
@@ -755,9 +758,9 @@ static bool allow_lds(const void* fn, int lds_bytes) {
 }
 
 // Launch one sweep: large tiles one workgroup per CU, with their arrival counters cleared first if there is more than
-// one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A device that does not report 256 compute units (a partition of
-// the chip, another chip) is refused: the sweep would still be correct there, but its workgroups would take turns
-// instead of running side by side.
+// one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A
+// device that does not report 256 compute units (a partition of the chip, another chip) is refused: the sweep would still be
+// correct there, but its workgroups would take turns instead of running side by side.
 template <class C, template <class> class Epi>
 static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;

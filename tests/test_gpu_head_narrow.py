@@ -98,3 +98,11 @@ def test_logprobs(tp, M, V, H):
 @pytest.mark.parametrize("M,V,H", [(385, 5000, 832), (500, 12000, 320), (1300, 12007, 576)])
 def test_grads(tp, M, V, H):
     check_logprob_grads(tp, *_bf16_case(M, V, H, seed=M + V))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,V,H", [(250, 60001, 64), (512, 33000, 64), (700, 33000, 64), (1100, 9001, 192), (8100, 2047, 1536)])
+def test_grads_large_tiles_prefetch(tp, M, V, H):
+    """The derivative's large tiles up to H = 1536, one, two, three and more token tiles beside each other, one and
+    several stages, a short last tile of W: the lines brought in ahead end with W, and with the task."""
+    check_logprob_grads(tp, *_bf16_case(M, V, H, seed=M + V))
