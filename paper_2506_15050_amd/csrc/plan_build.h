@@ -244,10 +244,12 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
 }
 
 // The same list for up to kBuildThreads sequences whose offsets, kept lengths and flags lie in LDS, so that any wavefront can
-// look at all of them: wavefronts take levels of groups of 64 sequences, one ballot and one store a lane each, and where a few long sequences are most of the batch, a sequence's tiles beyond the sorted levels go out
-// 64 at a time.  A lane that walks down its own sequence's levels takes as long as the longest has tiles.  The whole
-// filter, us, so -> now: 40 sequences of up to 88 tiles 15.9 -> 9.5; 93 of up to 7 7.1 -> 6.3; 512 of up to 21 12.7 -> 11.1 with two
-// workgroups that share the (level, group) pairs (13.7 with one); 900 of one or two 6.9 -> 7.1.
+// look at all of them: wavefronts take levels of groups of 64 sequences, one ballot and one store a lane each, and where a
+// few long sequences are most of the batch, a sequence's tiles beyond the sorted levels go out 64 at a time.  A lane that
+// walks down its own sequence's levels takes as long as the longest has tiles.  The whole filter, us, so -> now:
+// 40 sequences of up to 88 tiles 15.9 -> 9.5; 93 of up to 7 7.1 -> 6.3; beyond 128 sequences several workgroups share the
+// (level, group) pairs, with two -> with four: 512 of up to 20 11.9 -> 10.5 -> 10.2; 900 of up to 40 24.5 -> 20.3 -> 19.6;
+// 700 of up to 6, which the lanes' own walk serves as well, 11.9 -> 12.6 -> 12.2.
 template <class Ints>
 __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s, Ints resp_off, Ints keep_len, Ints done, int B,
                                                     int n_resp, int part, int parts, int32_t* status) {

@@ -13,14 +13,14 @@
 //            walk the tile list, side by side.
 // Launches and the chains of dependent loads inside them are what this costs; only beyond some ten million tokens do
 // the bytes written count.  Scan, plan and fill as three launches against now, in a pass over
-// 2.4 M tokens in 512 sequences: 29 -> 12 us; 40 M tokens in 8704 sequences: 111 -> 62 us (278 MB of indices).
+// 2.4 M tokens in 512 sequences: 29 -> 11 us; 40 M tokens in 8704 sequences: 111 -> 62 us (278 MB of indices).
 #include "plan_build.h"
 
 namespace tppo {
 
 constexpr int kScanThreads = 1024;
 constexpr int kOneLaunchSeqs = kScanThreads;
-constexpr int kListParts = 2;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
+constexpr int kListParts = 4;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
 constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
 constexpr int kFillMaxGroups = 512;                             // two per CU
 static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");

@@ -1,4 +1,4 @@
-"""The plan's list where its levels are shared out: groups of 64 sequences around a whole number of them, one and two
+"""The plan's list where its levels are shared out: groups of 64 sequences around a whole number of them, one and four
 workgroups, sequences of more tiles than the sorted levels."""
 import pytest
 
