@@ -5,9 +5,8 @@
 // C entry points' own business.
 #include <Python.h>
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
-
-#include <exception>
 
 #include "tppo.h"
 
@@ -74,17 +73,17 @@ class Args {
     PyObject* const* at_;
 };
 
+// What torch raises passes as from its own functions: an allocation that fails is torch.OutOfMemoryError, an exception of a
+// Python dispatch mode is that exception.
 template <class F>
 PyObject* guarded(F&& f) {
+    HANDLE_TH_ERRORS
     try {
         return f();
     } catch (const Raised&) {
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-    } catch (...) {
-        PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+        return nullptr;
     }
-    return nullptr;
+    END_HANDLE_TH_ERRORS
 }
 
 // the call itself, with the interpreter free for other threads as it is under ctypes

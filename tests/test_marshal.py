@@ -51,3 +51,24 @@ def test_sizes(native):
     for n, B in ((0, 0), (1, 1), (1000, 3), (2_400_000, 512)):
         assert native.plan_bytes(n, B) == lib.tppo_plan_bytes(n, B)
         assert native.select_workspace_bytes(B, n) == lib.tppo_select_workspace_bytes(B, n)
+
+
+def test_allocations_raise_what_torch_raises(native):
+    from torch.utils._python_dispatch import TorchDispatchMode
+    like = torch.zeros(1)
+
+    class Mode(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise KeyError("a mode's own exception")
+    with Mode():
+        for make in (lambda: torch.empty(3), lambda: native.empties(like, "i", 3)):
+            with pytest.raises(KeyError):
+                make()
+
+
+@pytest.mark.gpu
+def test_out_of_memory_is_torchs_own(native):
+    like = torch.zeros(1, device="cuda")
+    for make in (lambda: torch.empty(1 << 46, dtype=torch.uint8, device="cuda"), lambda: native.empties(like, "b", 1 << 46)):
+        with pytest.raises(torch.OutOfMemoryError):
+            make()
