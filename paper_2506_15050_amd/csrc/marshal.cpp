@@ -86,13 +86,25 @@ PyObject* guarded(F&& f) {
     END_HANDLE_TH_ERRORS
 }
 
-// the call itself, with the interpreter free for other threads as it is under ctypes
+// other Python threads run while one of these lives
+class NoInterpreter {
+  public:
+    NoInterpreter() : state_(PyEval_SaveThread()) {}
+    ~NoInterpreter() { PyEval_RestoreThread(state_); }
+    NoInterpreter(const NoInterpreter&) = delete;
+
+  private:
+    PyThreadState* state_;
+};
+
+// the call itself, with the interpreter free as it is under ctypes
 template <class F>
 PyObject* status_of(F&& call) {
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
+    {
+        NoInterpreter other_threads_run;
+        rc = call();
+    }
     return PyLong_FromLong(rc);
 }
 
@@ -225,7 +237,9 @@ PyObject* plan_bytes(Args& x) {
 }
 
 // empties(like, kinds, n0, n1, ...): one-dimensional uninitialised tensors on `like`'s device, kinds[i] in "ilfb" (int32, int64,
-// float32, bytes)
+// float32, bytes).  The interpreter is free meanwhile, as it is in torch.empty: an allocator that has to ask the driver, or that
+// waits for another thread's call into it, must not hold up the other Python threads.
+constexpr Py_ssize_t kMostBuffers = 16;
 PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         if (n < 2 || !THPVariable_Check(args[0])) raise(PyExc_TypeError, "empties(tensor, kinds, sizes...)");
@@ -234,20 +248,29 @@ PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (!kinds) throw Raised{};
         if (count != n - 2) raise(PyExc_TypeError, "a size for each kind");
         const auto on = at::TensorOptions().device(THPVariable_Unpack(args[0]).device());
+        int64_t sizes[kMostBuffers];
+        at::Tensor made[kMostBuffers];
+        if (count > kMostBuffers) raise(PyExc_TypeError, "too many buffers");
+        for (Py_ssize_t i = 0; i < count; ++i) {
+            sizes[i] = PyLong_AsLongLong(args[2 + i]);
+            if (sizes[i] == -1 && PyErr_Occurred()) throw Raised{};
+        }
+        {
+            NoInterpreter other_threads_run;
+            for (Py_ssize_t i = 0; i < count; ++i) {
+                const auto type = kinds[i] == 'i' ? at::kInt : kinds[i] == 'l' ? at::kLong : kinds[i] == 'f' ? at::kFloat : at::kByte;
+                made[i] = at::empty({sizes[i]}, on.dtype(type));
+            }
+        }
         PyObject* out = PyTuple_New(count);
         if (!out) throw Raised{};
-        try {
-            for (Py_ssize_t i = 0; i < count; ++i) {
-                const int64_t size = PyLong_AsLongLong(args[2 + i]);
-                if (size == -1 && PyErr_Occurred()) throw Raised{};
-                const auto type = kinds[i] == 'i' ? at::kInt : kinds[i] == 'l' ? at::kLong : kinds[i] == 'f' ? at::kFloat : at::kByte;
-                PyObject* t = THPVariable_Wrap(at::empty({size}, on.dtype(type)));
-                if (!t) throw Raised{};
-                PyTuple_SET_ITEM(out, i, t);
+        for (Py_ssize_t i = 0; i < count; ++i) {
+            PyObject* t = THPVariable_Wrap(made[i]);
+            if (!t) {
+                Py_DECREF(out);
+                throw Raised{};
             }
-        } catch (...) {
-            Py_DECREF(out);
-            throw;
+            PyTuple_SET_ITEM(out, i, t);
         }
         return out;
     });

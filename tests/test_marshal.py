@@ -66,6 +66,36 @@ def test_allocations_raise_what_torch_raises(native):
                 make()
 
 
+def test_other_threads_run_during_allocations(native):
+    """torch's filling of fresh memory under deterministic algorithms makes an allocation last: the longest time in which
+    another thread got nowhere is well below it."""
+    import threading
+    import time
+    like, stop, gaps = torch.zeros(1), threading.Event(), [0.0]
+
+    def watch():
+        last = time.perf_counter()
+        while not stop.is_set():
+            time.sleep(0.001)
+            now = time.perf_counter()
+            gaps[0], last = max(gaps[0], now - last), now
+    was, threads = torch.are_deterministic_algorithms_enabled(), torch.get_num_threads()
+    torch.use_deterministic_algorithms(True)
+    torch.set_num_threads(1)
+    watcher = threading.Thread(target=watch)
+    try:
+        watcher.start()
+        begin = time.perf_counter()
+        native.empties(like, "b", 1 << 30)
+        took = time.perf_counter() - begin
+    finally:
+        stop.set()
+        watcher.join()
+        torch.use_deterministic_algorithms(was)
+        torch.set_num_threads(threads)
+    assert took > 0.05 and gaps[0] < took / 2, (took, gaps[0])
+
+
 @pytest.mark.gpu
 def test_out_of_memory_is_torchs_own(native):
     like = torch.zeros(1, device="cuda")
