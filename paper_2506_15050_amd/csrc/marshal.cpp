@@ -5,6 +5,8 @@
 // C entry points' own business.
 #include <Python.h>
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Device.h>
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -19,21 +21,35 @@ struct Raised {};                                                   // a Python 
     throw Raised{};
 }
 
+// a new reference, or the exception that is there instead
+class Held {
+  public:
+    explicit Held(PyObject* o) : o_(o) {
+        if (!o) throw Raised{};
+    }
+    ~Held() { Py_DECREF(o_); }
+    Held(const Held&) = delete;
+    PyObject* get() const { return o_; }
+
+  private:
+    PyObject* o_;
+};
+
 // The arguments of one call, in order.
 class Args {
   public:
     Args(PyObject* const* args, Py_ssize_t n, Py_ssize_t want) : at_(args) {
         if (n != want) raise(PyExc_TypeError, "wrong number of arguments");
     }
-    // a tensor's memory; None: NULL
+    // a tensor's memory; None: NULL.  Anything but a plain tensor is asked through Python, where a subclass or another
+    // library's array has its own say.
     void* any() {
         PyObject* o = *at_++;
         if (o == Py_None) return nullptr;
-        if (THPVariable_Check(o)) return THPVariable_Unpack(o).data_ptr();
-        PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);
-        if (!p) throw Raised{};
-        void* v = PyLong_AsVoidPtr(p);
-        Py_DECREF(p);
+        if (THPVariable_CheckExact(o)) return THPVariable_Unpack(o).data_ptr();
+        const Held p(PyObject_CallMethod(o, "data_ptr", nullptr));
+        if (p.get() == Py_None) return nullptr;
+        void* v = PyLong_AsVoidPtr(p.get());
         if (PyErr_Occurred()) throw Raised{};
         return v;
     }
@@ -45,7 +61,14 @@ class Args {
     void* buffer(size_t& bytes) {
         bytes = 0;
         PyObject* o = *at_;
-        if (o != Py_None && THPVariable_Check(o)) bytes = (size_t)THPVariable_Unpack(o).numel();
+        if (o == Py_None) return any();
+        if (THPVariable_CheckExact(o)) {
+            bytes = (size_t)THPVariable_Unpack(o).numel();
+        } else {
+            const Held n(PyObject_CallMethod(o, "numel", nullptr));
+            bytes = (size_t)PyLong_AsUnsignedLongLongMask(n.get());
+            if (PyErr_Occurred()) throw Raised{};
+        }
         return any();
     }
     int64_t i64() {
@@ -63,12 +86,24 @@ class Args {
 
   private:
     void* checked(at::ScalarType type) {
-        PyObject* o = *at_++;
-        if (!THPVariable_Check(o)) raise(PyExc_AssertionError, "a tensor is required");
-        const at::Tensor& t = THPVariable_Unpack(o);
-        if (!t.is_cuda() || t.scalar_type() != type || !t.is_contiguous())
-            raise(PyExc_AssertionError, "a contiguous device tensor of the documented type is required");
-        return t.data_ptr();
+        PyObject* o = *at_;
+        if (o == Py_None) raise(PyExc_AssertionError, "a tensor is required");
+        bool good;
+        if (THPVariable_CheckExact(o)) {
+            const at::Tensor& t = THPVariable_Unpack(o);
+            good = t.is_cuda() && t.scalar_type() == type && t.is_contiguous();
+        } else {
+            const Held cuda(PyObject_GetAttrString(o, "is_cuda")), dtype(PyObject_GetAttrString(o, "dtype"));
+            const Held dense(PyObject_CallMethod(o, "is_contiguous", nullptr));
+            good = truth(PyObject_IsTrue(cuda.get())) && truth(PyObject_IsTrue(dense.get())) &&
+                   truth(PyObject_RichCompareBool(dtype.get(), reinterpret_cast<PyObject*>(torch::getTHPDtype(type)), Py_EQ));
+        }
+        if (!good) raise(PyExc_AssertionError, "a contiguous device tensor of the documented type is required");
+        return any();
+    }
+    static bool truth(int answer) {
+        if (answer < 0) throw Raised{};
+        return answer != 0;
     }
     PyObject* const* at_;
 };
@@ -240,14 +275,20 @@ PyObject* plan_bytes(Args& x) {
 // float32, bytes).  The interpreter is free meanwhile, as it is in torch.empty: an allocator that has to ask the driver, or that
 // waits for another thread's call into it, must not hold up the other Python threads.
 constexpr Py_ssize_t kMostBuffers = 16;
+at::Device device_of(PyObject* like) {
+    if (THPVariable_CheckExact(like)) return THPVariable_Unpack(like).device();
+    const Held device(PyObject_GetAttrString(like, "device"));
+    if (!THPDevice_Check(device.get())) raise(PyExc_TypeError, "a torch.device is required");
+    return reinterpret_cast<THPDevice*>(device.get())->device;
+}
 PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
-        if (n < 2 || !THPVariable_Check(args[0])) raise(PyExc_TypeError, "empties(tensor, kinds, sizes...)");
+        if (n < 2 || args[0] == Py_None) raise(PyExc_TypeError, "empties(tensor, kinds, sizes...)");
         Py_ssize_t count = 0;
         const char* kinds = PyUnicode_AsUTF8AndSize(args[1], &count);
         if (!kinds) throw Raised{};
         if (count != n - 2) raise(PyExc_TypeError, "a size for each kind");
-        const auto on = at::TensorOptions().device(THPVariable_Unpack(args[0]).device());
+        const auto on = at::TensorOptions().device(device_of(args[0]));
         int64_t sizes[kMostBuffers];
         at::Tensor made[kMostBuffers];
         if (count > kMostBuffers) raise(PyExc_TypeError, "too many buffers");

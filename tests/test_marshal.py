@@ -96,6 +96,61 @@ def test_other_threads_run_during_allocations(native):
     assert took > 0.05 and gaps[0] < took / 2, (took, gaps[0])
 
 
+class Array:
+    """Another library's array: what the entry points need of a tensor, and no torch.Tensor."""
+    def __init__(self, at=0, n=0, dtype=torch.float32, is_cuda=True, dense=True):
+        self.at, self.n, self.dtype, self.is_cuda, self.dense = at, n, dtype, is_cuda, dense
+
+    def data_ptr(self):
+        return self.at
+
+    def numel(self):
+        return self.n
+
+    def is_contiguous(self):
+        return self.dense
+
+
+def test_arrays_that_are_no_tensors(native):
+    def egae(rewards):
+        ints = Array(dtype=torch.int32)
+        return native.egae(rewards, Array(), ints, ints, None, 1, 1, 1.0, 1.0, None, None, None, None, None, 0)
+    assert egae(Array()) == -1                                              # taken, and its pointer is NULL
+    for bad in (Array(dtype=torch.int32), Array(is_cuda=False), Array(dense=False)):
+        with pytest.raises(AssertionError):
+            egae(bad)
+    with pytest.raises(AttributeError):
+        egae(3.0)
+
+
+def test_a_subclass_has_its_say(native):
+    says = {torch.Tensor.data_ptr: 0, torch.Tensor.is_cuda.__get__: True}
+
+    class Elsewhere(torch.Tensor):
+        @classmethod
+        def __torch_function__(cls, func, types, args=(), kwargs=None):
+            return says[func] if func in says else super().__torch_function__(func, types, args, kwargs or {})
+    f32, i32 = (torch.zeros(3, dtype=t).as_subclass(Elsewhere) for t in (torch.float32, torch.int32))
+    assert native.egae(f32, f32, i32, i32, None, 1, 1, 1.0, 1.0, None, None, None, None, None, 0) == -1      # NULL, as it says
+
+
+@pytest.mark.gpu
+def test_buffers_that_are_no_tensors(native):
+    from paper_2506_15050_amd import binding as tp
+    i32 = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    cu, ctx, done, n_tok = i32(0, 9, 20), i32(2, 3), i32(1, 0), 20
+    plain = tp.tppo_select(cu, ctx, done, None, 1, n_tok=n_tok, want_plan=True)
+    keep = [torch.zeros(1 << 16, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    ws, plan = (Array(t.data_ptr(), t.numel()) for t in keep)
+    again = tp.tppo_select(cu, ctx, done, None, 1, n_tok=n_tok, workspace=ws, plan=plan)
+    kept = int(plain["counts"][0])
+    assert again["counts"].tolist() == plain["counts"].tolist() == [7 + 8 - 1, 15, 7]
+    assert again["sel_rows"][:kept].tolist() == plain["sel_rows"][:kept].tolist()
+    for short in (dict(workspace=Array(keep[0].data_ptr(), 16)), dict(plan=Array(keep[1].data_ptr(), 16))):
+        with pytest.raises(RuntimeError, match="WORKSPACE"):
+            tp.tppo_select(cu, ctx, done, None, 1, n_tok=n_tok, **short)
+
+
 @pytest.mark.gpu
 def test_out_of_memory_is_torchs_own(native):
     like = torch.zeros(1, device="cuda")
