@@ -1,8 +1,8 @@
 // Python side of the C ABI (tppo.h), native: turns a call's tensors into pointers, allocates its results, and calls.  The
 // smallest passes are bound by what happens here, once a call: through ctypes and torch's Python functions a token filter
 // with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 12.4, 9.0, 4.5 and 4.2.
-// Everything that is checked here was checked in Python before, with the same exceptions; sizes, ranges and NULLs are the
-// C entry points' own business.
+// What is taken and what is refused is what ctypes and the binding's own assertions take and refuse; sizes, ranges and NULLs are
+// the C entry points' own business.
 #include <Python.h>
 #include <ATen/ops/empty.h>
 #include <torch/csrc/Device.h>
@@ -72,9 +72,10 @@ class Args {
         return any();
     }
     int64_t i64() {
-        const long long v = PyLong_AsLongLong(*at_++);
-        if (v == -1 && PyErr_Occurred()) throw Raised{};
-        return v;
+        PyObject* o = *at_++;
+        const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+        if (v == ~0ull && PyErr_Occurred()) refuse(o);
+        return (int64_t)v;
     }
     int32_t i32() { return (int32_t)i64(); }
     float f32() {
@@ -82,9 +83,20 @@ class Args {
         if (v == -1.0 && PyErr_Occurred()) throw Raised{};
         return (float)v;
     }
-    void* stream() { return reinterpret_cast<void*>((uintptr_t)i64()); }
+    void* stream() {
+        void* s = PyLong_AsVoidPtr(*at_++);
+        if (PyErr_Occurred()) throw Raised{};
+        return s;
+    }
 
   private:
+    // what is no whole number: ctypes' own exception
+    [[noreturn]] static void refuse(PyObject* o) {
+        PyErr_Clear();
+        const Held ctypes(PyImport_ImportModule("ctypes")), error(PyObject_GetAttrString(ctypes.get(), "ArgumentError"));
+        PyErr_Format(error.get(), "int expected instead of %.200s instance", Py_TYPE(o)->tp_name);
+        throw Raised{};
+    }
     void* checked(at::ScalarType type) {
         PyObject* o = *at_;
         if (o == Py_None) raise(PyExc_AssertionError, "a tensor is required");

@@ -1,6 +1,8 @@
 """The binding's native half: what it refuses, and the buffers it makes (no GPU work here)."""
+import ctypes
 import os
 
+import numpy as np
 import pytest
 import torch
 
@@ -132,6 +134,18 @@ def test_a_subclass_has_its_say(native):
             return says[func] if func in says else super().__torch_function__(func, types, args, kwargs or {})
     f32, i32 = (torch.zeros(3, dtype=t).as_subclass(Elsewhere) for t in (torch.float32, torch.int32))
     assert native.egae(f32, f32, i32, i32, None, 1, 1, 1.0, 1.0, None, None, None, None, None, 0) == -1      # NULL, as it says
+
+
+@pytest.mark.parametrize("make", [lambda: np.int64(5), lambda: torch.tensor(5), lambda: (1 << 64) + 5, lambda: 5.0, lambda: "5"])
+def test_numbers(native, make):
+    """Whole numbers are taken and refused as by ctypes."""
+    from paper_2506_15050_amd import binding
+    for plan_bytes in (binding.load().tppo_plan_bytes, native.plan_bytes):
+        if isinstance(make(), (float, str)):
+            with pytest.raises(ctypes.ArgumentError):
+                plan_bytes(make(), 1)
+        else:
+            assert plan_bytes(make(), 1) == plan_bytes(5, 1)
 
 
 @pytest.mark.gpu
