@@ -6,6 +6,7 @@
 // pass plugs in the softmax-derivative writer and a plain tile store, which makes
 // the sweep a matrix product.
 #pragma once
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -654,7 +655,7 @@ static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool m
 //   1300 x V 12000, H 5120: 246 -> 176.  Where it leaves the old one: 900 x V 152064, H 5120: 1266 (n = 3: 1277);
 //   60 x V 32000, H 5120: 97.9 (n = 1: 113).  Below 320 of K it gains nothing.
 // fp32 keeps the small tiles (its matrix rate bounds it), and what small tiles served is not given to n = 3, whose sums run over
-// all of K: no sum gets longer.
+// all of K: no sum gets longer.  Looked up on every call, on the host: 0.1 us (every number of ranges tried: up to 8).
 constexpr int kNarrowStages = 5;
 constexpr double kNarrowGain = 0.95;
 constexpr int64_t kCachedW = 128 << 20;            // bytes of W that a pass can expect to find in the 256 MB cache
@@ -663,9 +664,10 @@ struct ShapeTime {
 };
 constexpr ShapeTime kShapeTime[5] = {              // [n]; 0: small tiles, 4: large ones
     {{0.65, 1.0}, 1.2, 4.0}, {{0.75, 1.45}, 3.0, 5.0}, {{0.95, 1.62}, 3.0, 6.0}, {{1.0, 1.5}, 3.5, 7.0}, {{1.3, 1.65}, 4.5, 8.0}};
+static bool w_from_hbm(const HeadParams& p, int64_t, int64_t V) { return V * p.H * 2 > kCachedW; }
 static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
     if (p.k_tiles < kNarrowStages) return 0;
-    const bool from_hbm = V * p.H * 2 > kCachedW;
+    const bool from_hbm = w_from_hbm(p, M, V);
     auto time_of = [&](int n, double rounds, double tiles) {
         const ShapeTime& t = kShapeTime[n];
         return rounds * (t.task + tiles * (p.k_tiles * t.stage[from_hbm] + t.tile));
@@ -684,9 +686,14 @@ static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
     int best_n = 0;
     int64_t best_cols = 0;
     for (int n = 1; n <= (small ? 2 : 3); ++n) {
-        const int64_t rows = in_parts(M, 64 * n);
-        for (int64_t s = 1; s <= units && rows * s <= kRestTasks && rows * s * 64 * n <= kRestTasks * kTile; ++s) {
-            const double t = time_of(n, rounds_of(rows * s), (double)in_parts(in_parts(units, s) * kUnit, kTile));
+        // Of the divisions that take r rounds of workgroups the finest ends soonest, and the coarsest of those with its
+        // tiles per range ends with it.
+        const int64_t rows = in_parts(M, 64 * n), most = std::min({units, kRestTasks / rows, kRestTasks * kTile / (rows * 64 * n)});
+        for (int64_t r = 1; r <= (int64_t)rounds_of(rows * most); ++r) {
+            const int64_t finest = std::min(most, r * kSweepGroups / rows);
+            if (finest == 0) continue;
+            const int64_t tiles = in_parts(in_parts(units, finest) * kUnit, kTile), s = in_parts(units, tiles * (kTile / kUnit));
+            const double t = time_of(n, rounds_of(rows * s), (double)tiles);
             if (t < best - 1e-9) { best = t; best_n = n; best_cols = s; }
         }
     }

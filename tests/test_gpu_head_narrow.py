@@ -49,16 +49,85 @@ int main(int argc, char** argv) {
 """
 
 
+# the rule's model with every number of ranges tried, over random calls; prints how many are divided otherwise and the time both take
+SEARCH = r"""
+#include <chrono>
+#include <cmath>
+#include <cstdio>
+#include <random>
+#include "head_tile.h"
+namespace tppo {
+int device_compute_units() { return 256; }
+static int search(const HeadParams& p, int64_t M, int64_t V, bool small, int64_t& cols) {
+    cols = 0;
+    if (p.k_tiles < kNarrowStages) return 0;
+    auto parts = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    auto time_of = [&](int n, double rounds, double tiles) {
+        const ShapeTime& t = kShapeTime[n];
+        return rounds * (t.task + tiles * (p.k_tiles * t.stage[w_from_hbm(p, M, V)] + t.tile));
+    };
+    double best;
+    if (small) {
+        best = time_of(0, (double)parts(p.rest_tasks, kSweepGroups * kSmallPerCu), (double)parts(p.vocab_tiles, p.rest.cols));
+    } else {
+        best = time_of(4, rounds_of(p.rest_tasks), (double)parts(p.vocab_tiles, p.rest.cols)) +
+               time_of(4, rounds_of(p.first_tasks), (double)parts(p.vocab_tiles, p.first.cols));
+    }
+    best *= kNarrowGain;
+    int found = 0;
+    for (int n = 1; n <= (small ? 2 : 3); ++n) {
+        const int64_t rows = parts(M, 64 * n), units = parts(V, 64);
+        for (int64_t s = 1; s <= units && rows * s <= kRestTasks && rows * s * 64 * n <= kRestTasks * kTile; ++s) {
+            const double t = time_of(n, rounds_of(rows * s), (double)parts(parts(units, s) * 64, kTile));
+            if (t < best - 1e-9) { best = t; found = n; cols = s; }
+        }
+    }
+    return found;
+}
+}
+int main() {
+    using namespace tppo;
+    using std::chrono::steady_clock;
+    std::mt19937_64 bits(7);
+    auto between = [&](double a, double b) { return std::lround(a * std::pow(b / a, (bits() >> 11) * 0x1p-53)); };
+    int otherwise = 0, taken = 0;
+    double times[2] = {0, 0};
+    for (int i = 0; i < 20000; ++i) {
+        const long M = between(1, 200000), V = between(1, 152064), H = between(8, 5200);
+        HeadParams p = {};
+        p.H = (int)(H + 7) / 8 * 8;
+        p.k_tiles = (p.H + 63) / 64;
+        const bool small = plan_logprobs(p, M, V, true, p.H % 64 == 0);
+        int64_t cols;
+        const auto t0 = steady_clock::now();
+        const int want = search(p, M, V, small, cols);
+        const auto t1 = steady_clock::now();
+        const int n = plan_narrow(p, M, V, small);
+        const auto t2 = steady_clock::now();
+        times[0] += std::chrono::duration<double>(t1 - t0).count();
+        times[1] += std::chrono::duration<double>(t2 - t1).count();
+        otherwise += n != want || (n && p.rest.cols != cols);
+        taken += n != 0;
+    }
+    printf("%d %d %g %g\n", otherwise, taken, times[0], times[1]);
+}
+"""
+
+
+def compiled(at, program):
+    at.with_suffix(".hip").write_text(program)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(at.with_suffix(".hip")), "-o", str(at)],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    return str(at)
+
+
 @pytest.fixture(scope="module")
 def rule(tmp_path_factory):
-    at = tmp_path_factory.mktemp("narrow")
-    (at / "narrow.hip").write_text(PROGRAM)
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
-                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(at / "narrow.hip"), "-o", str(at / "narrow")],
-                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    program = compiled(tmp_path_factory.mktemp("narrow") / "narrow", PROGRAM)
 
     def run(shapes):
-        out = subprocess.run([str(at / "narrow"), *(str(x) for s in shapes for x in s)], check=True, stdout=subprocess.PIPE,
+        out = subprocess.run([program, *(str(x) for s in shapes for x in s)], check=True, stdout=subprocess.PIPE,
                              text=True).stdout
         return [tuple(map(int, line.split())) for line in out.splitlines()]
     return run
@@ -71,6 +140,13 @@ def test_which_calls(rule):
         # every token has a tile, and the partial results stay within what a workspace holds
         assert all(g[2] and g[3] <= 1024 and g[3] * 64 * g[0] <= 1024 * 256 for g in got.values())
     assert [g[0] for g in rule(NOT)] == [0] * len(NOT)
+
+
+def test_the_rule_looks_at_few_divisions(tmp_path):
+    """It finds what trying every number of ranges finds, in a fraction of the time (each call pays for it on the host)."""
+    out = subprocess.run([compiled(tmp_path / "search", SEARCH)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+    otherwise, taken, every, rule_itself = int(out[0]), int(out[1]), float(out[2]), float(out[3])
+    assert otherwise == 0 and taken > 500 and rule_itself < every / 2
 
 
 @pytest.mark.gpu
