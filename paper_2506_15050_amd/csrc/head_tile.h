@@ -656,6 +656,15 @@ static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool m
 //   60 x V 32000, H 5120: 97.9 (n = 1: 113).  Below 320 of K it gains nothing.
 // fp32 keeps the small tiles (its matrix rate bounds it), and what small tiles served is not given to n = 3, whose sums run over
 // all of K: no sum gets longer.  Looked up on every call, on the host: 0.1 us (every number of ranges tried: up to 8).
+// Against large tiles the fit holds up to some thousands of tokens (60 sizes of 1300 .. 10000, V from 1000 on: 1.28 times as fast in
+// the geometric mean, 1 % slower at the worst); beyond, the division has to be 13 % better by it, and the token rows that
+// 256 workgroups sweep at once have to stay in the cache, where every W tile reads them again.  Both sides, us, large -> narrow:
+// 16080 x V 1301, H 448: 34.1 -> 32.4;  83412 x 1459, H 320: 146 -> 110;  89178 x 2279, H 1920: 787 -> 739.  By the gain alone refused:
+// 9617 x 13530, H 4416: 902 (976);  181148 x 5306, H 1272: 2509 (2745);  98233 x 2697, H 888: 522 (526);  by the rows (409 and 378 MB):
+// 45819 x 2169, H 4672: 938 (1099);  81560 x 1053, H 4032: 871 (962).  Small tiles, which long rows at misaligned addresses take
+// whatever the size, lose to narrow ones at any (plan_logprobs).
+constexpr int64_t kFittedTokens = 8192, kCachedTokens = 192 << 20;
+constexpr double kFarGain = 0.87;
 constexpr int kNarrowStages = 5;
 constexpr double kNarrowGain = 0.95;
 constexpr int64_t kCachedW = 128 << 20;            // bytes of W that a pass can expect to find in the 256 MB cache
@@ -664,10 +673,9 @@ struct ShapeTime {
 };
 constexpr ShapeTime kShapeTime[5] = {              // [n]; 0: small tiles, 4: large ones
     {{0.65, 1.0}, 1.2, 4.0}, {{0.75, 1.45}, 3.0, 5.0}, {{0.95, 1.62}, 3.0, 6.0}, {{1.0, 1.5}, 3.5, 7.0}, {{1.3, 1.65}, 4.5, 8.0}};
-static bool w_from_hbm(const HeadParams& p, int64_t, int64_t V) { return V * p.H * 2 > kCachedW; }
 static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
     if (p.k_tiles < kNarrowStages) return 0;
-    const bool from_hbm = w_from_hbm(p, M, V);
+    const bool from_hbm = V * p.H * 2 > kCachedW;
     auto time_of = [&](int n, double rounds, double tiles) {
         const ShapeTime& t = kShapeTime[n];
         return rounds * (t.task + tiles * (p.k_tiles * t.stage[from_hbm] + t.tile));
@@ -680,7 +688,7 @@ static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
         best = time_of(4, rounds_of(p.rest_tasks), (double)in_parts(p.vocab_tiles, p.rest.cols));
         best += time_of(4, rounds_of(p.first_tasks), (double)in_parts(p.vocab_tiles, p.first.cols));
     }
-    best *= kNarrowGain;
+    best *= small || M <= kFittedTokens ? kNarrowGain : kFarGain;
     constexpr int kUnit = 64;
     const int64_t units = in_parts(V, kUnit);
     int best_n = 0;
@@ -698,6 +706,8 @@ static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
         }
     }
     if (best_n == 0) return 0;
+    const int64_t rows_at_once = std::min(in_parts(M, 64 * best_n), std::max(kSweepGroups / best_cols, (int64_t)1));
+    if (!small && rows_at_once * 64 * best_n * p.H * 2 > kCachedTokens) return 0;
     p.row_tiles = (int)in_parts(M, 64 * best_n);
     p.vocab_tiles = (int)units;
     p.v_unit = kUnit;

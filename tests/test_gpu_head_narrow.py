@@ -19,6 +19,7 @@ NARROW = {
     (500, 12000, 320): (2, 47),                    # the shortest K
     (1025, 7001, 704): (2, 28),
     (900, 20001, 576): (3, 40),
+    (16080, 1301, 448): (3, 3),                    # many tokens
     (1300, 12007, 576): (3, 24),                   # ranges of two tiles, the second short
 }
 NARROW_RAGGED = {
@@ -28,7 +29,9 @@ NARROW_RAGGED = {
     (1300, 12007, 584): (3, 24),
     (2500, 9000, 1000): (3, 18),
 }
-NOT = [(500, 12000, 256), (942, 152064, 5120), (60, 32000, 5120), (400, 32000, 1024), (15000, 32000, 1024)]
+NOT = [(500, 12000, 256), (942, 152064, 5120), (60, 32000, 5120), (400, 32000, 1024), (15000, 32000, 1024),
+       (9617, 13530, 4416), (181148, 5306, 1272),      # many tokens: too little gained by the model
+       (45819, 2169, 4672), (81560, 1053, 4032)]       # ... or more token rows at once than the cache holds
 
 PROGRAM = r"""
 #include <cstdio>
@@ -64,7 +67,7 @@ static int search(const HeadParams& p, int64_t M, int64_t V, bool small, int64_t
     auto parts = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     auto time_of = [&](int n, double rounds, double tiles) {
         const ShapeTime& t = kShapeTime[n];
-        return rounds * (t.task + tiles * (p.k_tiles * t.stage[w_from_hbm(p, M, V)] + t.tile));
+        return rounds * (t.task + tiles * (p.k_tiles * t.stage[V * p.H * 2 > kCachedW] + t.tile));
     };
     double best;
     if (small) {
@@ -73,7 +76,7 @@ static int search(const HeadParams& p, int64_t M, int64_t V, bool small, int64_t
         best = time_of(4, rounds_of(p.rest_tasks), (double)parts(p.vocab_tiles, p.rest.cols)) +
                time_of(4, rounds_of(p.first_tasks), (double)parts(p.vocab_tiles, p.first.cols));
     }
-    best *= kNarrowGain;
+    best *= small || M <= kFittedTokens ? kNarrowGain : kFarGain;
     int found = 0;
     for (int n = 1; n <= (small ? 2 : 3); ++n) {
         const int64_t rows = parts(M, 64 * n), units = parts(V, 64);
@@ -82,7 +85,9 @@ static int search(const HeadParams& p, int64_t M, int64_t V, bool small, int64_t
             if (t < best - 1e-9) { best = t; found = n; cols = s; }
         }
     }
-    return found;
+    if (found == 0 || small) return found;
+    const int64_t at_once = std::min(parts(M, 64 * found), std::max(kSweepGroups / cols, (int64_t)1)) * 64 * found;
+    return at_once * p.H * 2 > kCachedTokens ? 0 : found;
 }
 }
 int main() {
