@@ -9,7 +9,8 @@
 // frames) knows its share of both sets from two comparisons.  Only a thread at
 // or beyond a sequence boundary inside the frame looks into the offset arrays.
 // No mask array is read, and a thread with no member of a set issues no loads
-// for that set.
+// for that set (but for the first frame's policy arrays in the pass that writes
+// derivatives, loss_load_policy).
 //
 // One launch per call.  A persistent grid walks the frames; a thread issues all loads of its share of a
 // frame at once (non-temporal 16-byte accesses, consecutive lanes on consecutive 16 bytes, no branch and no wait
@@ -222,11 +223,15 @@ __device__ __forceinline__ void loss_load(LossRegs& x, const LossParams& p, cons
     }
 }
 
-// The same before the plan is known, for a workgroup's first frame: whatever set a token turns out to be in.  The plan's header,
-// the frame's descriptor and the tokens are then one round trip and not three, which is what a call on a batch of a
-// turn or two is made of.  Measured, us: losses 9.1 -> 8.4 and derivatives 12.4 -> 11.5 on 280 K tokens, 9.8 -> 8.7 and 14.0 -> 12.8 on
-// 490 K; no change from 2 M tokens on.
-__device__ __forceinline__ void loss_load_any(LossRegs& x, const LossParams& p, int tid) {
+// The policy arrays' part of it before the plan is known, for a workgroup's first frame in the pass that writes derivatives: all
+// but the dropped tails are policy tokens, so little of it is asked for in vain, and the plan's header, the frame's descriptor
+// and these tokens are one round trip instead of three.  The value arrays follow the descriptor: a finished sequence is
+// what they need.  Derivatives alone, us, after the descriptor -> so, at a tenth / half / nine tenths of finished sequences:
+// 280 K tokens 10.5 / 10.9 / 11.0 -> 10.3 / 10.9 / 10.9;  490 K 11.6 / 12.1 / 12.4 -> 10.9 / 11.5 / 11.7;  1 M 16.6 / 18.1 / 18.1 -> 15.7 /
+// 17.2 / 17.1;  4 M 25.8 / 28.6 / 31.3 -> 24.8 / 27.8 / 30.5.  All six arrays early: 17.3 at 1 M and a tenth, 26.5 at 4 M.  The pass that
+// only sums gains nothing by it (1 M: 9.5 / 11.0 / 11.4 -> 9.4 / 10.8 / 11.2, 2.3 M: 15.1 / 16.0 / 17.7 -> 14.9 / 16.8 / 18.7) and waits
+// for the descriptor.
+__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, int tid) {
     const float4u zero = {0.f, 0.f, 0.f, 0.f};
     const int at = min((int)blockIdx.x * (4 * kLossThreads) + 4 * tid, p.n_resp - 4);
     x.ln = x.lo = x.a = x.v = x.vo = x.r = zero;
@@ -235,7 +240,10 @@ __device__ __forceinline__ void loss_load_any(LossRegs& x, const LossParams& p, 
         x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
         x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
     }
-    if (p.v_new) {
+}
+__device__ __forceinline__ void loss_load_value(LossRegs& x, const LossParams& p, const TokenSets& ts) {
+    const int at = min(ts.first, p.n_resp - 4);
+    if (ts.val != 0) {
         x.v = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_new + at));
         x.vo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_old + at));
         x.r = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.ret + at));
@@ -333,10 +341,8 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
 __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
     __shared__ double s_red[2 * kLossThreads / kWave];
     __shared__ int s_flag;
-    const int tid = threadIdx.x;
-    LossRegs cur;
-    loss_load_any(cur, p, tid);
     const Plan pl = plan_open(p.plan);
+    const int tid = threadIdx.x;
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const bool plan_ok = pl.hdr->B == p.B && pl.hdr->n_resp == p.n_resp && pl.hdr->has_sets != 0 &&
                          pl.cap >= p.n_resp / kTileTokens + p.B + 1;
@@ -356,7 +362,8 @@ __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tpp
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
-        if (f != (int)blockIdx.x) loss_load(cur, p, ts);
+        LossRegs cur;
+        loss_load(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
         if (ts.pol != 0) {
@@ -439,7 +446,7 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
     const LossParams& p = gp.fwd;
     const int tid = threadIdx.x;
     LossRegs cur;
-    loss_load_any(cur, p, tid);
+    loss_load_policy(cur, p, tid);
     const Plan pl = plan_open(p.plan);
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const bool plan_ok = pl.hdr->B == p.B && pl.hdr->n_resp == p.n_resp && pl.hdr->has_sets != 0 &&
@@ -467,6 +474,7 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
         if (f != (int)blockIdx.x) loss_load(cur, p, ts);
+        else loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
         if (has_pol && ts.n_tok > 0) {
