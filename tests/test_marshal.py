@@ -154,7 +154,7 @@ def test_buffers_that_are_no_tensors(native):
     i32 = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
     cu, ctx, done, n_tok = i32(0, 9, 20), i32(2, 3), i32(1, 0), 20
     plain = tp.tppo_select(cu, ctx, done, None, 1, n_tok=n_tok, want_plan=True)
-    keep = [torch.zeros(1 << 16, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    keep = [torch.zeros(1 << 22, dtype=torch.uint8, device="cuda") for _ in range(2)]
     ws, plan = (Array(t.data_ptr(), t.numel()) for t in keep)
     again = tp.tppo_select(cu, ctx, done, None, 1, n_tok=n_tok, workspace=ws, plan=plan)
     kept = int(plain["counts"][0])
