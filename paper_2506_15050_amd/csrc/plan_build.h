@@ -246,10 +246,11 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
 // The same list for up to kBuildThreads sequences whose offsets, kept lengths and flags lie in LDS, so that any wavefront can
 // look at all of them: wavefronts take levels of groups of 64 sequences, one ballot and one store a lane each, and where a
 // few long sequences are most of the batch, a sequence's tiles beyond the sorted levels go out 64 at a time.  A lane that
-// walks down its own sequence's levels takes as long as the longest has tiles.  The whole filter, us, so -> now:
-// 40 sequences of up to 88 tiles 15.9 -> 9.5; 93 of up to 7 7.1 -> 6.3; beyond 128 sequences several workgroups share the
-// (level, group) pairs, with two -> with four: 512 of up to 20 11.9 -> 10.5 -> 10.2; 900 of up to 40 24.5 -> 20.3 -> 19.6;
-// 700 of up to 6, which the lanes' own walk serves as well, 11.9 -> 12.6 -> 12.2.
+// walks down its own sequence's levels takes as long as the longest has tiles.  The whole filter, us, by the lanes' walk -> so:
+// 40 sequences of up to 88 tiles 15.9 -> 9.5; 93 of up to 7 7.1 -> 6.3; beyond 128 sequences eight workgroups share the
+// (level, group) pairs: 200 of up to 4 6.5 -> 5.7; 512 of up to 20 11.7 -> 10.0; 900 of up to 40 23.7 -> 16.7; 700 of up to 6 11.5 ->
+// 11.5, where four workgroups take 11.7, and 11.9 if they count and place tiles beyond the sorted levels that no sequence
+// has and leave other workgroups without a place on the chip (select.hip).
 template <class Ints>
 __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s, Ints resp_off, Ints keep_len, Ints done, int B,
                                                     int n_resp, int part, int parts, int32_t* status) {
@@ -261,17 +262,20 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
         len = i < B ? window_of(resp_off, i, n_resp, lo, st) : 0;
         return window_tiles(lo, len);
     };
-    int counter = 0;                                                // lane l: group `wave`'s tiles of level l
+    int counter = 0, deepest = 0;                                   // lane l: group `wave`'s tiles of level l
     if (wave < groups) {
-        const int tiles = tiles_at(wave * kWave + lane, part == 0 ? status : nullptr), deepest = min(wave_max(tiles), kLevels);
-        for (int l = 0; l < deepest; ++l) {
+        const int tiles = tiles_at(wave * kWave + lane, part == 0 ? status : nullptr);
+        deepest = wave_max(tiles);
+        for (int l = 0; l < min(deepest, kLevels); ++l) {
             const int c = __popcll(__ballot(tiles > l));
             counter = lane == l ? c : counter;
         }
-        int extra = max(tiles - kLevels, 0);                        // tiles beyond the sorted levels
+        if (deepest > kLevels) {                                    // tiles beyond the sorted levels
+            int extra = max(tiles - kLevels, 0);
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) extra += __shfl_xor(extra, off);
-        counter = lane == kLevels ? extra : counter;
+            for (int off = 1; off < kWave; off <<= 1) extra += __shfl_xor(extra, off);
+            counter = lane == kLevels ? extra : counter;
+        }
     }
     if (lane <= kLevels) s.count[0][wave][lane] = counter;
     __syncthreads();
@@ -293,8 +297,8 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
             }
             if (lane == kLevels) s.total = at;
         }
-        const int deepest = __popcll(__ballot(mine > 0));
-        if (lane == 0) s.levels = deepest;
+        const int levels = __popcll(__ballot(mine > 0));
+        if (lane == 0) s.levels = levels;
     }
     __syncthreads();
     for (int task = part * kBuildWaves + wave, n = s.levels * groups; task < n; task += parts * kBuildWaves) {
@@ -310,7 +314,7 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
             note_frame(pl, d, lo, len, true, keep_len[i], done[i] != 0, next);
         }
     }
-    if (wave < groups && part == parts - 1) {                       // a sequence's deeper tiles stay together
+    if (deepest > kLevels && part == parts - 1) {                       // a sequence's deeper tiles stay together
         const int i = wave * kWave + lane, tiles = tiles_at(i, nullptr), extra = max(tiles - kLevels, 0);
         int inc = extra;
 #pragma unroll

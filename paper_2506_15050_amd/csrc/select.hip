@@ -20,7 +20,7 @@ namespace tppo {
 
 constexpr int kScanThreads = 1024;
 constexpr int kOneLaunchSeqs = kScanThreads;
-constexpr int kListParts = 4;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
+constexpr int kListParts = 8;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
 constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
 constexpr int kFillMaxGroups = 512;                             // two per CU
 static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");
@@ -314,6 +314,11 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
     }
 }
 
+// The one launch's grid.  Its workers and the list's workgroups are on the chip together: one beyond the kFillMaxGroups places
+// waits until another has ended and goes through the whole chain, metadata to prefix sums, after it.
+static int list_parts(bool plan, int64_t B) { return plan && B > 2 * kWave ? kListParts : 1; }
+static int one_launch_workers(int64_t most, int parts) { return (int)(most < kFillMaxGroups - parts ? most : kFillMaxGroups - parts); }
+
 }  // namespace tppo
 
 extern "C" size_t tppo_select_workspace_bytes(int64_t B, int64_t capacity) {
@@ -356,9 +361,8 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
     const int64_t clear = plan ? (plan_words(plan_cap) + kBuildThreads * 8 - 1) / (kBuildThreads * 8) : 0;
     const int64_t fill = want_fill ? (n_tok + kBuildThreads * 4 - 1) / (kBuildThreads * 4) : 0;
     const int64_t most = clear > fill ? clear : fill;
-    const int workers = (int)(most < kFillMaxGroups ? most : kFillMaxGroups);
     if (B <= kOneLaunchSeqs) {
-        const int parts = plan && B > 2 * kWave ? kListParts : 1;
+        const int parts = list_parts(plan != nullptr, B), workers = one_launch_workers(most, parts);
         hipLaunchKernelGGL(select_one_launch_kernel, dim3(parts + workers), dim3(kBuildThreads), 0, s, a, done, (int)B,
                            (int)tail_drop, resp_off, sel_off, keep_len, counts, parts, (int)plan_cap, plan);
         return launch_result();
@@ -367,7 +371,7 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
     int32_t* n_tiles = want_fill ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) +
                                                               round_up((size_t)cap64 * sizeof(Tile), 256))
                                  : nullptr;
-    const int parts = build_parts(B);
+    const int parts = build_parts(B), workers = (int)(most < kFillMaxGroups ? most : kFillMaxGroups);
     hipLaunchKernelGGL(select_scan_kernel, dim3(parts), dim3(kScanThreads), 0, s, cu_seqlens, ctx_len,
                        done, (int)B, (int)n_tok, (int)tail_drop, parts, resp_off, sel_off, keep_len, counts,
                        tiles, (int)cap64, n_tiles, status);
