@@ -114,12 +114,7 @@ struct DzEpilogue {
     __device__ __forceinline__ void finish(const HeadParams&, float*, const Task&, int64_t, int64_t, int, int, int, int) {}
 };
 
-// The same in large tiles up to this H, where the sweep brings W's lines into L2 ahead (head_mfma_kernel): between two tiles
-// each workgroup stores 128 KB of dz, on an XCD as much as its L2 holds, and the next tile's W is gone from there; with a
-// longer H the stores are rarer, and the requests cost more than they give.  The whole backward call, us:
-// H 512, 32768 tokens x V 12000: 1284 -> 1246;  H 576, 4096 x 32000: 574 -> 561;  H 1024, 16414 x 32000: 2816 -> 2758;
-// H 1536: 4198 -> 4133;  H 2048, 8206 x 32000: 2697 -> 2724, 1300 x 152064: 2609 -> 2581;  H 3584, 8206 x 32000: 4680 -> 4731.
-constexpr int kPrefetchH = 1536;
+// The same in large tiles up to H = kPrefetchH, with W's lines brought ahead.
 template <class C>
 struct DzAheadEpilogue : DzEpilogue<C> {
     static constexpr bool kPrefetch = true;

@@ -718,6 +718,13 @@ static int plan_narrow(HeadParams& p, int64_t M, int64_t V, bool small) {
     return best_n;
 }
 
+// The derivative's sweep in large tiles brings W's lines into L2 ahead (head_mfma_kernel) up to this H: between two tiles
+// each workgroup stores 128 KB of dz, on an XCD as much as its L2 holds, and the next tile's W is gone from there; with a
+// longer H the stores are rarer, and the requests cost more than they give.  The whole backward call, us:
+// H 512, 32768 tokens x V 12000: 1284 -> 1246;  H 576, 4096 x 32000: 574 -> 561;  H 1024, 16414 x 32000: 2816 -> 2758;
+// H 1536: 4198 -> 4133;  H 2048, 8206 x 32000: 2697 -> 2724, 1300 x 152064: 2609 -> 2581;  H 3584, 8206 x 32000: 4680 -> 4731.
+constexpr int kPrefetchH = 1536;
+
 // Plain product of M token-role rows and N W-role rows over K = 64 * k_tiles, columns = W-role tiles.  Whole rounds
 // of 256 output tiles first; of the tiles that remain, fewer than a round, each is cut into k_chunks of the
 // contraction if that ends sooner.  part_bytes: room for the partial tiles.  A chunk keeps at least kMinChunk

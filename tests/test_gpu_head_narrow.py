@@ -14,6 +14,7 @@ from paper_2506_15050_amd import synth
 NARROW = {
     (65, 30011, 1024): (1, 118),                   # one token beyond a tile, W ranges of three and of four units
     (385, 5000, 832): (1, 20),
+    (700, 5000, 1024): (1, 20),
     (2500, 1011, 640): (1, 4),                     # 40 token tiles
     (257, 20033, 1024): (2, 79),
     (500, 12000, 320): (2, 47),                    # the shortest K
@@ -26,9 +27,14 @@ NARROW_RAGGED = {
     (385, 5000, 840): (1, 20),
     (1300, 4003, 2120): (2, 16),                   # too long for one sum over K
     (450, 9000, 329): (2, 36),                     # rows copied to 336
+    (300, 20000, 333): (2, 79),
     (1300, 12007, 584): (3, 24),
     (2500, 9000, 1000): (3, 18),
 }
+NARROW_TOO = {(16000, 152064, 5112): (2, 2), (20, 152064, 5120): (1, 198)}      # (too large for a test's oracle)
+# the derivative's large tiles, where they bring W's lines ahead: one, two, three and more token tiles beside each other, one and
+# several stages, a short last tile of W
+LARGE_AHEAD = [(250, 60001, 64), (512, 33000, 64), (700, 33000, 64), (1100, 9001, 192), (8100, 2047, 1536)]
 NOT = [(500, 12000, 256), (942, 152064, 5120), (60, 32000, 5120), (400, 32000, 1024), (15000, 32000, 1024),
        (9617, 13530, 4416), (181148, 5306, 1272),      # many tokens: too little gained by the model
        (45819, 2169, 4672), (81560, 1053, 4032)]       # ... or more token rows at once than the cache holds
@@ -46,7 +52,8 @@ int main(int argc, char** argv) {
         const long M = atol(argv[i]), V = atol(argv[i + 1]);
         const bool small = tppo::plan_logprobs(p, M, V, true, p.H % 64 == 0);
         const int n = tppo::plan_narrow(p, M, V, small);
-        printf("%d %d %d %d\n", n, p.rest.cols, n == 0 || p.rest.rows == (M + 64 * n - 1) / (64 * n), p.n_tasks);
+        const bool ahead = !small && n == 0 && p.H <= tppo::kPrefetchH;
+        printf("%d %d %d %d %d\n", n, p.rest.cols, n == 0 || p.rest.rows == (M + 64 * n - 1) / (64 * n), p.n_tasks, ahead);
     }
 }
 """
@@ -139,12 +146,13 @@ def rule(tmp_path_factory):
 
 
 def test_which_calls(rule):
-    for table in (NARROW, NARROW_RAGGED):
+    for table in (NARROW, NARROW_RAGGED, NARROW_TOO):
         got = dict(zip(table, rule(table)))
         assert {s: g[:2] for s, g in got.items()} == table
         # every token has a tile, and the partial results stay within what a workspace holds
         assert all(g[2] and g[3] <= 1024 and g[3] * 64 * g[0] <= 1024 * 256 for g in got.values())
     assert [g[0] for g in rule(NOT)] == [0] * len(NOT)
+    assert all(g[4] for g in rule(LARGE_AHEAD))
 
 
 def test_the_rule_looks_at_few_divisions(tmp_path):
@@ -182,8 +190,7 @@ def test_grads(tp, M, V, H):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,V,H", [(250, 60001, 64), (512, 33000, 64), (700, 33000, 64), (1100, 9001, 192), (8100, 2047, 1536)])
+@pytest.mark.parametrize("M,V,H", LARGE_AHEAD)
 def test_grads_large_tiles_prefetch(tp, M, V, H):
-    """The derivative's large tiles up to H = 1536, one, two, three and more token tiles beside each other, one and
-    several stages, a short last tile of W: the lines brought in ahead end with W, and with the task."""
+    """The lines brought in ahead end with W, and with the task."""
     check_logprob_grads(tp, *_bf16_case(M, V, H, seed=M + V))

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,V,H", [(5, 70000, 64),        # small tiles: one token tile, 183 vocabulary ranges
                                    (1030, 3000, 64),      # small tiles: 17 token tiles, 12 vocabulary ranges
+                                   (64, 32000, 1024), (20, 1500, 320),      # small tiles, 16 and 5 K stages
                                    (16500, 600, 64),      # large tiles: 65 token tiles, 3 vocabulary tiles
                                    (33000, 300, 64),      # 129 token tiles, no cut of the vocabulary
                                    (66000, 200, 64)])     # one vocabulary tile: a round of 256 token tiles, 2 left

@@ -1,6 +1,7 @@
-"""Which tiles and which division of the work the log-prob sweep takes: the rule
-itself (csrc/head_tile.h, host side), run at the sizes that the GPU tests rely
-on to reach a path.  A change of the rule that moves one of them shows here."""
+"""Which tiles and which division of the work the log-prob sweep takes: the rules
+themselves (csrc/head_tile.h, host side) in the order in which a call asks them,
+run at the sizes that the GPU tests rely on to reach a path.  A change of a rule
+that moves one of them shows here.  (Narrow tiles: test_gpu_head_narrow.py.)"""
 import os
 import subprocess
 
@@ -17,6 +18,7 @@ LARGE_WHOLE = {
     (1024, 40961, 64): ((0, 4), (4, 54)),          # whole token tiles only
     (17000, 4000, 64): ((64, 4), (3, 16)),         # a whole round and a finely cut rest
     (33000, 1100, 64): ((64, 4), (65, 3)),         # a whole round and a rest of nearly another, 5 vocabulary tiles
+    (1000, 32000, 1024): ((0, 4), (4, 63)),        # K stages enough for narrow tiles, which gain too little here
 }
 LARGE_WHOLE_ELSEWHERE = {                          # shapes of other tests
     (16500, 600, 64): ((0, 2), (65, 3)),           # no whole round although there could be one
@@ -29,8 +31,10 @@ LARGE_WHOLE_ELSEWHERE = {                          # shapes of other tests
 LARGE_RAGGED = {                                   # bf16 rows off a stage of 64
     (300, 20000, 72): ((0, 4), (2, 79)),
     (700, 30000, 8): ((0, 4), (3, 59)),            # a stage that is mostly zeros
-    (2500, 9000, 1000): ((0, 4), (10, 18)),
-    (300, 20000, 333): ((0, 4), (2, 79)),          # rows copied to 336
+    (300, 20000, 203): ((0, 4), (2, 79)),          # rows copied to 208
+    (1000, 32000, 1000): ((0, 4), (4, 63)),        # 16 K stages
+    (600, 60000, 1013): ((0, 4), (3, 79)),         # ... of rows copied to 1016
+    (17000, 4000, 392): ((64, 4), (3, 16)),        # 7 stages, whole rounds and a rest
     (18600, 2048, 200): ((0, 4), (73, 3)),
     (17000, 4000, 136): ((64, 4), (3, 16)),
     (33000, 1100, 72): ((64, 4), (65, 3)),
@@ -39,12 +43,13 @@ SMALL_WHOLE = {
     (5, 70000, 64): (1, 183),
     (1030, 3000, 64): (17, 12),
     (1, 256, 64): (1, 2), (37, 1000, 128): (1, 8), (300, 1000, 256): (5, 8), (513, 2049, 192): (9, 17),
-    (256, 512, 64): (4, 4), (700, 5000, 1024): (11, 20),
+    (256, 512, 64): (4, 4),
+    (64, 32000, 1024): (1, 250), (20, 1500, 320): (1, 12),       # K stages enough for narrow tiles
 }
 SMALL_RAGGED = {
     (57, 333, 72): (1, 3),
     (1500, 8000, 5120): (24, 21),                  # long rows at misaligned addresses, whatever the size
-    (16000, 152064, 5112): (250, 1),
+    (1500, 8000, 2112): (24, 21), (300, 4000, 5112): (5, 32), (300, 4000, 5100): (5, 32),
 }
 SMALL_FP32 = {(2064, 32000, 1024): (33, 23), (300, 32000, 64): (5, 50)}
 
@@ -57,8 +62,11 @@ int main(int argc, char** argv) {
     for (int i = 1; i + 4 < argc; i += 5) {
         tppo::HeadParams p = {};
         p.H = (atoi(argv[i + 2]) + 7) / 8 * 8;
-        const bool small = tppo::plan_logprobs(p, atol(argv[i]), atol(argv[i + 1]), atoi(argv[i + 3]), atoi(argv[i + 4]));
-        printf("%d %d %d %d %d\n", small, p.first_tasks ? p.first.rows : 0, p.first.cols, p.rest.rows, p.rest.cols);
+        const long M = atol(argv[i]), V = atol(argv[i + 1]);
+        const bool bf16 = atoi(argv[i + 3]), small = tppo::plan_logprobs(p, M, V, bf16, atoi(argv[i + 4]));
+        p.k_tiles = (p.H + 63) / 64;
+        const int narrow = bf16 ? tppo::plan_narrow(p, M, V, small) : 0;
+        printf("%d %d %d %d %d\n", narrow ? 2 : small, p.first_tasks ? p.first.rows : 0, p.first.cols, p.rest.rows, p.rest.cols);
     }
 }
 """
@@ -81,12 +89,12 @@ def rule(tmp_path_factory):
 
 @pytest.mark.parametrize("table,whole", [(LARGE_WHOLE, True), (LARGE_WHOLE_ELSEWHERE, True), (LARGE_RAGGED, False)])
 def test_large_tiles(rule, table, whole):
-    got = {s: ((f_rows, f_cols), (r_rows, r_cols)) if not small else "small"
-           for s, (small, f_rows, f_cols, r_rows, r_cols) in zip(table, rule(table, True, whole))}
+    got = {s: ((f_rows, f_cols), (r_rows, r_cols)) if tiles == 0 else tiles
+           for s, (tiles, f_rows, f_cols, r_rows, r_cols) in zip(table, rule(table, True, whole))}
     assert got == table
 
 
 @pytest.mark.parametrize("table,bf16,whole", [(SMALL_WHOLE, True, True), (SMALL_RAGGED, True, False), (SMALL_FP32, False, True)])
 def test_small_tiles(rule, table, bf16, whole):
-    got = {s: (rows, cols) if small else "large" for s, (small, _, _, rows, cols) in zip(table, rule(table, bf16, whole))}
+    got = {s: (rows, cols) if tiles == 1 else tiles for s, (tiles, _, _, rows, cols) in zip(table, rule(table, bf16, whole))}
     assert got == table
