@@ -10,7 +10,7 @@
 // or beyond a sequence boundary inside the frame looks into the offset arrays.
 // No mask array is read, and a thread with no member of a set issues no loads
 // for that set (but for the first frame's policy arrays in the pass that writes
-// derivatives, loss_load_policy).
+// derivatives, loss_load_ahead).
 //
 // One launch per call.  A persistent grid walks the frames; a thread issues all loads of its share of a
 // frame at once (non-temporal 16-byte accesses, consecutive lanes on consecutive 16 bytes, no branch and no wait
@@ -202,40 +202,14 @@ __device__ __forceinline__ FrameDesc checked_frame(FrameDesc d, const LossParams
     return d;
 }
 
-// Issue the loads of a thread's four tokens.  Consecutive lanes on consecutive 16 bytes (the access shape that
+// Issue the loads of a thread's four tokens, one set's arrays each.  Consecutive lanes on consecutive 16 bytes (the access shape that
 // streams at full rate), non-temporal.  Nothing is loaded for a set none of the four is in; with 1..3 members
 // the 16 bytes are loaded whole -- the surplus elements are never used -- so that no branch and no wait
 // separates the loads and all of them are in flight together; the one thread that would read past the END OF
 // THE ARRAY reads the array's last 16 bytes instead (see unshift).  Needs n_resp >= 4.
-__device__ __forceinline__ void loss_load(LossRegs& x, const LossParams& p, const TokenSets& ts) {
-    const float4u zero = {0.f, 0.f, 0.f, 0.f};
+__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, const TokenSets& ts) {
     const int at = min(ts.first, p.n_resp - 4);
-    x.ln = x.lo = x.a = x.v = x.vo = x.r = zero;
     if (ts.pol != 0) {
-        x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
-        x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
-        x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
-    }
-    if (ts.val != 0) {
-        x.v = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_new + at));
-        x.vo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_old + at));
-        x.r = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.ret + at));
-    }
-}
-
-// The policy arrays' part of it before the plan is known, for a workgroup's first frame in the pass that writes derivatives: all
-// but the dropped tails are policy tokens, so little of it is asked for in vain, and the plan's header, the frame's descriptor
-// and these tokens are one round trip instead of three.  The value arrays follow the descriptor: a finished sequence is
-// what they need.  Derivatives alone, us, after the descriptor -> so, at a tenth / half / nine tenths of finished sequences:
-// 280 K tokens 10.5 / 10.9 / 11.0 -> 10.3 / 10.9 / 10.9;  490 K 11.6 / 12.1 / 12.4 -> 10.9 / 11.5 / 11.7;  1 M 16.6 / 18.1 / 18.1 -> 15.7 /
-// 17.2 / 17.1;  4 M 25.8 / 28.6 / 31.3 -> 24.8 / 27.8 / 30.5.  All six arrays early: 17.3 at 1 M and a tenth, 26.5 at 4 M.  The pass that
-// only sums gains nothing by it (1 M: 9.5 / 11.0 / 11.4 -> 9.4 / 10.8 / 11.2, 2.3 M: 15.1 / 16.0 / 17.7 -> 14.9 / 16.8 / 18.7) and waits
-// for the descriptor.
-__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, int tid) {
-    const float4u zero = {0.f, 0.f, 0.f, 0.f};
-    const int at = min((int)blockIdx.x * (4 * kLossThreads) + 4 * tid, p.n_resp - 4);
-    x.ln = x.lo = x.a = x.v = x.vo = x.r = zero;
-    if (p.logp_new) {
         x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
         x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
         x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
@@ -247,6 +221,23 @@ __device__ __forceinline__ void loss_load_value(LossRegs& x, const LossParams& p
         x.v = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_new + at));
         x.vo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_old + at));
         x.r = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.ret + at));
+    }
+}
+
+// The policy arrays' part of it before the plan is known, for a workgroup's first frame in the pass that writes derivatives: all
+// but the dropped tails are policy tokens, so little of it is asked for in vain, and the plan's header, the frame's descriptor
+// and these tokens are one round trip instead of three.  The value arrays follow the descriptor: a finished sequence is
+// what they need.  Derivatives alone, us, after the descriptor -> so, at a tenth / three tenths / nine tenths of finished sequences:
+// 100 K tokens 9.2 / 9.1 / 9.4 -> 9.0 / 9.1 / 9.4;  490 K 11.5 / 11.8 / 12.5 -> 11.2 / 11.5 / 11.9;  1 M 16.6 / 17.3 / 18.0 -> 15.7 / 16.8 /
+// 17.4;  4 M 25.8 / 27.2 / 31.0 -> 25.7 / 26.7 / 30.8.  All six arrays early: 17.3 / 17.4 / 17.3 at 1 M, 26.8 / 28.0 / 30.7 at 4 M.  The
+// pass that only sums gains nothing by it (1 M, a tenth / half / nine tenths: 9.5 / 11.0 / 11.4 -> 9.4 / 10.8 / 11.2, 2.3 M: 15.1 / 16.0 /
+// 17.7 -> 14.9 / 16.8 / 18.7) and waits for the descriptor.
+__device__ __forceinline__ void loss_load_ahead(LossRegs& x, const LossParams& p, int tid) {
+    const int at = min((int)blockIdx.x * (4 * kLossThreads) + 4 * tid, p.n_resp - 4);
+    if (p.logp_new) {
+        x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
+        x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
+        x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
     }
 }
 
@@ -362,8 +353,9 @@ __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tpp
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
-        LossRegs cur;
-        loss_load(cur, p, ts);
+        LossRegs cur = {};
+        loss_load_policy(cur, p, ts);
+        loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
         if (ts.pol != 0) {
@@ -445,8 +437,8 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
     __shared__ int s_flag;
     const LossParams& p = gp.fwd;
     const int tid = threadIdx.x;
-    LossRegs cur;
-    loss_load_policy(cur, p, tid);
+    LossRegs cur = {};
+    loss_load_ahead(cur, p, tid);
     const Plan pl = plan_open(p.plan);
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const bool plan_ok = pl.hdr->B == p.B && pl.hdr->n_resp == p.n_resp && pl.hdr->has_sets != 0 &&
@@ -473,8 +465,8 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
-        if (f != (int)blockIdx.x) loss_load(cur, p, ts);
-        else loss_load_value(cur, p, ts);
+        if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
+        loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
         if (has_pol && ts.n_tok > 0) {
