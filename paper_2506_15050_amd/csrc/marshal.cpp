@@ -1,6 +1,6 @@
 // Python side of the C ABI (tppo.h), native: turns a call's tensors into pointers, allocates its results, and calls.  The
 // smallest passes are bound by what happens here, once a call: through ctypes and torch's Python functions a token filter
-// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 12.4, 9.0, 4.5 and 4.2.
+// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 12.6, 9.1, 4.2 and 4.0.
 // What is taken and what is refused is what ctypes and the binding's own assertions take and refuse; sizes, ranges and NULLs are
 // the C entry points' own business.
 #include <Python.h>
@@ -9,6 +9,8 @@
 #include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
 
 #include "tppo.h"
 
@@ -124,13 +126,13 @@ class Args {
 // Python dispatch mode is that exception.
 template <class F>
 PyObject* guarded(F&& f) {
-    HANDLE_TH_ERRORS
     try {
         return f();
     } catch (const Raised&) {
-        return nullptr;
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());
     }
-    END_HANDLE_TH_ERRORS
+    return nullptr;
 }
 
 // other Python threads run while one of these lives
@@ -294,7 +296,8 @@ at::Device device_of(PyObject* like) {
     return reinterpret_cast<THPDevice*>(device.get())->device;
 }
 PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    return guarded([&]() -> PyObject* {
+    HANDLE_TH_ERRORS                                                // (the allocator's warnings are Python's)
+    try {
         if (n < 2 || args[0] == Py_None) raise(PyExc_TypeError, "empties(tensor, kinds, sizes...)");
         Py_ssize_t count = 0;
         const char* kinds = PyUnicode_AsUTF8AndSize(args[1], &count);
@@ -326,7 +329,10 @@ PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
             PyTuple_SET_ITEM(out, i, t);
         }
         return out;
-    });
+    } catch (const Raised&) {
+        return nullptr;
+    }
+    END_HANDLE_TH_ERRORS
 }
 
 template <PyObject* (*f)(PyObject*, PyObject* const*, Py_ssize_t)>
