@@ -1,8 +1,8 @@
 // Machinery shared by the LM-head kernels: the XCD-aware sweep of MFMA tiles
 // (W-role rows x token-role rows) with a pluggable per-lane epilogue, as 256 x 256
-// tiles on a persistent grid or, where those leave the chip idle, 128 x 64 tiles
-// with a workgroup per task.  K is contiguous in both operands, or the row index of
-// one (KMAJOR).  The forward pass plugs in the online log-softmax; the backward
+// tiles on a persistent grid or, where those leave the chip idle, with a workgroup
+// per task, as 256 x 64, 128 or 192 tiles (narrow) or 128 x 64 ones (small).  K is
+// contiguous in both operands, or the row index of one (KMAJOR).  The forward pass plugs in the online log-softmax; the backward
 // pass plugs in the softmax-derivative writer and a plain tile store, which makes
 // the sweep a matrix product.
 #pragma once
@@ -350,8 +350,13 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     // follow each other), each touches its part.  It is the last transfer that a wavefront has under way at a barrier, so
     // it is the one that may still be: the counter counts in order.
     // Measured with W in HBM, us a call: 2516 tokens x V 50021, H 1000: 270 -> 247;  300 x V 152064, H 5120: 604 -> 555;
-    // 900 x V 20001, H 576: 38.0 -> 34.4;  100 x V 20000, H 4096: 87.1 -> 65.8;  20 x V 152064, H 5120: 352 -> 343.  With W in a
-    // cache it costs 2 .. 5 % (a pass over other tensors between two calls, as in a training step, leaves little of W there).
+    // 900 x V 20001, H 576: 38.0 -> 34.4;  100 x V 20000, H 4096: 87.1 -> 65.8;  20 x V 152064, H 5120: 352 -> 343.  Where W is in a
+    // cache it costs: in calls one after the other on the same W 2 .. 3 % of ragged sweeps in large tiles (2516 x V 50021, H 1000:
+    // 234 -> 240) and up to 10 % of narrow ones (1300 x V 12000, H 1024: 45.5 -> 50.0), and with W in HBM where all of it
+    // stays in L2 from its first token tile on (8000 x V 1500, H 1000: 35.0 -> 36.5) or a row is two stages long (300 x V 20000, H 72:
+    // 17.6 -> 19.1).  It stays on all the same: a pass over other tensors between two calls, as in a training step, leaves
+    // little of W in a cache, and no call tells.  The touches add 5 % to the requests to L2 where four token tiles share them and
+    // 39 % where one has them all, and none to the misses.
     // One stage ahead takes 271 us for the first, four 608 for the second.  Whole stages in large tiles lose by it (H = 3584:
     // 6 %, 1024: 3 %): all token tiles sweep the same W there, which is in a cache as it is, and the requests are a quarter
     // more.  Unless the epilogue's stores drive W out of L2 (DzAheadEpilogue).
@@ -586,13 +591,15 @@ static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
     return best;
 }
 
-// The same sweep in 128 x 64 tiles, one workgroup per task, if that costs less than `large_cost`; true if so.  A small
-// tile is an eighth of a large one's work and takes n / 8 of its time where n share a CU.  For bf16 the traffic from
-// L2 makes it up to 2.5 times slower per flop, so there it only serves what would leave most of the chip idle.
+// The same sweep in 128 x 64 tiles, one workgroup per task, if that costs less than `large_cost`; true if so (in bf16 plan_narrow
+// looks at it again, whichever it is, where K is 320 or more).  A small tile is an eighth of a large one's work and takes n / 8
+// of its time where n share a CU.  For bf16 the traffic from L2 makes it up to 2.5 times slower per flop, so there it only
+// serves what would leave most of the chip idle.
 // Measured, large -> small (us):
-//   146 tokens x V 1000, H 64: 14.8 -> 10.4;  x V 5000, H 1024: 35.6 -> 18.5;  x V 32000, H 512: 30.0 -> 26.1;
-//   20 x V 152064, H 5120: 478 -> 403.  Where the rule says large: 300 x V 32000, H 512: 29.7 (34.2),
-//   146 x V 50021, H 1024: 42.2 (57.9), 2500 x V 5000, H 1024: 39.3 (47.4), 1000 x V 152064, H 5120: 1297 (2950)
+//   146 tokens x V 1000, H 64: 14.8 -> 10.4;  x V 5000, H 1024: 35.6 -> 18.5;  x V 32000, H 512: 30.0 -> 26.1 (narrow now);
+//   20 x V 152064, H 5120: 478 -> 403 (narrow now).  Where the rule says large: 2500 x V 5000, H 1024: 39.3 (47.4),
+//   1000 x V 152064, H 5120: 1297 (2950), and of those that are narrow now 300 x V 32000, H 512: 29.7 (34.2),
+//   146 x V 50021, H 1024: 42.2 (57.9)
 // fp32, which the matrix cores bound, loses 6 % per flop and wins that back by filling the chip, and always goes this
 // way (plan_logprobs): 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  2064 x V 32000, H 1024: 1281 ->
 // 1114;  the worst seen, 1000 x V 32000, H 1024: 508 -> 601.
@@ -629,12 +636,12 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
 }
 
 // fp32, and the bf16 rows that the one-token kernel can serve (off a stage or off 16 bytes) with a long H, take the small
-// tiles whatever the size, for the accuracy of their sums: the large ones add up all of H one step after the other, which
-// whole-stage bf16 always did.  Error of the log-probs against 64 bits, weights of 0.02, rms: H = 5112, 300 tokens, fp32
-// 1.8e-6 in large tiles, 5.0e-7 in small ones (6.1e-7 by the one-token kernel); bf16, 1500 tokens, V = 8000, H = 5120
-// misaligned 7.9e-7, 4.8e-7 (6.1e-7).  At H = 2040 bf16 gives 5.6e-7 in large tiles, 6.8e-7 by the one-token kernel.  What
-// that costs, large -> small: 2500 tokens, V = 50000, H = 2104: 0.50 -> 1.09 ms; H = 5112: 1.29 -> 2.83 ms; 16000 tokens,
-// V = 152064, H = 5112: 22.4 -> 110 ms (H = 5120: 17.8 ms).
+// tiles whatever the size (bf16: or narrow ones of up to 128 tokens, plan_narrow, which sum as they do), for the accuracy of
+// their sums: the large ones add up all of H one step after the other, which whole-stage bf16 always did.  Error of the
+// log-probs against 64 bits, weights of 0.02, rms: H = 5112, 300 tokens, fp32 1.8e-6 in large tiles, 5.0e-7 in small ones (6.1e-7 by
+// the one-token kernel); bf16, 1500 tokens, V = 8000, H = 5120 misaligned 7.9e-7, 4.8e-7 (6.1e-7).  At H = 2040 bf16 gives 5.6e-7 in
+// large tiles, 6.8e-7 by the one-token kernel.  What that costs, large -> small: 2500 tokens, V = 50000, H = 2104: 0.50 -> 1.09 ms;
+// H = 5112: 1.29 -> 2.83 ms; large -> narrow: 16000 tokens, V = 152064, H = 5112: 22.4 -> 38.9 ms (small 108; H = 5120: 17.8 ms).
 constexpr int kLongSumH = 2048;
 // The forward sweep's schedule; true: in small tiles.  matrix_only: bf16 rows of whole stages at aligned addresses.
 static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool matrix_only) {
