@@ -22,10 +22,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 // Epilogue 1: a finished tile of logits (vocabulary x tokens) becomes
-// dz, row t of out[.., ld_out].  A lane owns one token column per block, and of
+// dz, row t of `out`, which is ld_out wide and lies in blocks (head_tile.h, block_at).  A lane owns one token column per block, and of
 // each block of 16 vocabulary entries the 4 of its lane group; two blocks' worth is
 // exchanged between the four lane groups of a token so that each holds 8
-// consecutive entries: 16-byte stores, 64 bytes of a row side by side.
+// consecutive entries: 16-byte stores, 64 bytes of a block's row side by side.
 // This runs once per tile with every matrix core idle, so its instructions count:
 // per entry one fma, one exp2, one multiply, half a conversion, half a swap; the
 // sampled token and the ragged last tile are rare branches.  Measured: 16414
@@ -59,7 +59,7 @@ struct DzEpilogue {
         constexpr int kVB = C::kVB, kTB = C::kTB, kE = C::kAccElems;
         const int grp = lane / C::kMI, v_wave = v0 + wv * C::kWaveV;
         const int stored = task.v_end == p.V ? (int)p.out_cols : task.v_end;    // columns up to here are this task's
-        uint16_t* out = static_cast<uint16_t*>(p.out);
+        char* out = static_cast<char*>(p.out);
         if (v0 + C::kTileV > task.v_end) {                          // ragged last tile: no entry there, dz = 0
 #pragma unroll
             for (int vb = 0; vb < kVB; ++vb)
@@ -85,7 +85,7 @@ struct DzEpilogue {
                     for (int e = 0; e < kE; ++e) acc[vb][tb][e] -= d == vb * C::kMI + e ? 1.f : 0.f;
             }
             const int64_t t = tok0 + wt * C::kWaveT + tb * C::kMI + (lane % C::kMI);
-            uint16_t* row = out + t * p.ld_out;
+            char* row = out + C::block_at(t, v_wave, p.ld_out);
 #pragma unroll
             for (int vb = 0; vb < kVB; vb += 2) {
                 uint32_t a[2], b[2];                                // groups 0-3 of block vb, of block vb + 1
@@ -100,7 +100,7 @@ struct DzEpilogue {
                     b[j] = quarter[1];
                 }
                 const int v = v_wave + vb * C::kMI + grp * 8;
-                if (t < m_eff && v < stored) *reinterpret_cast<uint4*>(row + v) = make_uint4(a[0], a[1], b[0], b[1]);
+                if (t < m_eff && v < stored) *reinterpret_cast<uint4*>(row + C::block_at(0, vb * C::kMI + grp * 8, 0)) = make_uint4(a[0], a[1], b[0], b[1]);
             }
         }
 #pragma unroll
@@ -281,7 +281,7 @@ static BwdLayout bwd_layout(int64_t H, int64_t V, int64_t chunk) {
     size_t o = 0;
     const size_t dz = round_up((size_t)chunk * L.v_pad * 2, 256);
     L.part_bytes = dz < kPartBytes ? dz : kPartBytes;
-    L.off_dz = o;       o += dz;                                               // dZ    [chunk, v_pad]
+    L.off_dz = o;       o += dz;                                               // dZ    [chunk, v_pad] in blocks
     L.off_part = o;     o += L.part_bytes;
     L.off_hidt = o;     o += round_up((size_t)H * chunk * 2, 256);             // Hid^T [H, chunk]
     L.off_arrivals = o; o += arrivals_bytes(chunk > V ? chunk : V);

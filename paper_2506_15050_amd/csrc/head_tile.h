@@ -142,6 +142,15 @@ struct HeadCfg {
     __device__ static __forceinline__ int swz_k(int k) { return ((k & 3) | ((k >> 3) & 1) << 2) << 1; }
     static_assert(KMAJOR == 0 || (kEsz == 2 && !SMALL && !RAGGED && kTileV * kEsz == kKRowBytes && kTileT == kTileV),
                   "K-major stages are laid out for 256 columns of 2 bytes");
+    // dZ lies in blocks of 64 rows x 64 columns, 8 KB each, a row of blocks after the other: a stage of the first product (256
+    // rows x 64 of K) is four blocks, one of the second (64 of K x 256 columns) four that follow each other, and both walk on
+    // by whole blocks, where rows of V entries gave 128 or 512 bytes of each of 256 or 64 rows.  First product, dZ row by row ->
+    // in blocks, us: 16414 tokens x V 32000, H 1024: 889 -> 854;  3514 x 152064, H 5120: 4251 -> 4220; the second and the stores: the same.
+    // Byte of element (r, c), `cols` columns in all, a multiple of 64:
+    static constexpr int kBlockBytes = 64 * 64 * 2;
+    __device__ static __forceinline__ int64_t block_at(int64_t r, int64_t c, int64_t cols) {
+        return ((r >> 6) * (cols >> 6) + (c >> 6)) * kBlockBytes + (r & 63) * 128 + (c & 63) * 2;
+    }
     // row (inside the wave tile's W rows) of accumulator element e of block vb, for lane group g = lane / 16
     __device__ static __forceinline__ int row_in_wave(int vb, int e, int g) { return vb * kMI + g * 4 + e; }
 };
@@ -284,7 +293,9 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
     const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
     typedef typename std::conditional<C::kKMajor != 0, int64_t, int>::type KPos;
-    const KPos k_step = k_major ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h)) : (KPos)C::kRowBytes;
+    const KPos k_step = k_major                            ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h))
+                        : C::kKMajor == 1 && wave >= kVWaves ? (KPos)C::kBlockBytes
+                                                             : (KPos)C::kRowBytes;
     const KPos k_first = task.k_begin * k_step;
     int issue_v = task.v_begin, issue_kt = 0, issue_stage = 0;
     KPos issue_kpos = k_first;
@@ -297,7 +308,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
                 if (C::kKMajor == 1)
                     src[q] = static_cast<const char*>(p.w) + k * ld_w + (int64_t)min(v0 + col, p.km_cols - 8) * C::kEsz;
                 else
-                    src[q] = static_cast<const char*>(p.hidden) + k * ld_h + min(tok0 + col, (int64_t)p.km_cols - 8) * C::kEsz;
+                    src[q] = static_cast<const char*>(p.hidden) + C::block_at(k, min(tok0 + col, (int64_t)p.km_cols - 8), p.ld_h);
                 continue;
             }
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
@@ -307,6 +318,10 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
                 src[q] = static_cast<const char*>(p.w) + v * ld_w + chunk;
             } else if (!w_only) {
                 const int64_t t = min(tok0 + (r - kTileV), m_eff - 1);
+                if (C::kKMajor == 1) {
+                    src[q] = static_cast<const char*>(p.hidden) + C::block_at(t, 0, p.ld_h) + chunk;
+                    continue;
+                }
                 int64_t row = p.sel_rows ? (int64_t)p.sel_rows[t] : t;      // no list: rows in order
                 row = min(max(row, (int64_t)0), p.n_rows - 1);
                 src[q] = static_cast<const char*>(p.hidden) + row * ld_h + chunk;
