@@ -373,9 +373,9 @@ int tppo_ppo_losses_backward(const float* logp_new, const float* logp_old, const
  * status is not written by this call (bad rows and targets were reported by
  * the forward pass; rows are clamped, a bad target matches no column).
  * workspace: tppo_token_logprobs_backward_workspace_bytes(M, ...) holds dZ
- *      for min(M, 98304) tokens at once (about 2 (V + H) bytes per token and
- *      134 MB: 25 GB for the 77 000 kept tokens of the 32B-shaped head) and is
- *      the fastest.  The call works with any workspace that
+ *      for min(M, 98304) tokens at once (about 2 (V + H) bytes per token and up
+ *      to 134 MB for the partial sums of a cut contraction: 25 GB for the 77 000
+ *      kept tokens of the 32B-shaped head) and is the fastest.  The call works with any workspace that
  *      holds 256 tokens (the size the same function returns for M = 256): it
  *      then goes through chunks of as many tokens, a multiple of 256, as the
  *      workspace holds, more slowly (fewer tiles per sweep, grad_w re-read and

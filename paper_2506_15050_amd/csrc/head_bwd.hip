@@ -134,7 +134,7 @@ struct StoreEpilogue {
         const int v_lane = (partial ? 0 : v_tile) + wv * C::kWaveV + (lane / C::kMI) * 4;
         float* out = partial ? p.part_rest + (int64_t)task.part * (C::kTileV * C::kTileT) - tok0 * C::kTileV
                              : static_cast<float*>(p.out);
-        const int64_t ld_out = partial ? C::kTileV : p.ld_out, out_cols = partial ? C::kTileV : p.out_cols;
+        const int64_t ld_out = partial ? C::kTileV : p.ld_out, out_cols = p.out_cols - (partial ? v_tile : 0);
         const bool accumulate = p.accumulate && !partial;
 #pragma unroll
         for (int tb = 0; tb < C::kTB; ++tb) {
@@ -168,8 +168,9 @@ struct StoreEpilogue {
 };
 
 // The output tiles whose contraction was cut: out (+)= the sum of their partial tiles, in chunk order.  One
-// workgroup per 16 rows of a tile, a float4 per thread and row.
-constexpr int kSumRows = 16;
+// workgroup per 4 rows of a tile, a float4 per thread (16 rows, four to a thread: 10.0 us for 4 tiles in 15 chunks; now 8.2 for
+// 4 in 32).
+constexpr int kSumRows = 4;
 __global__ __launch_bounds__(256) void sum_chunks_kernel(HeadParams p) {
     const int id = blockIdx.x / (kTile / kSumRows), r0 = blockIdx.x % (kTile / kSumRows) * kSumRows;
     const Task task = task_at(p, p.first_tasks + id, 1);
@@ -267,11 +268,11 @@ constexpr int64_t kBwdChunkDefault = 98304, kBwdChunkMax = 98304;
 
 struct BwdLayout {
     int64_t v_pad, chunk;              // vocabulary padded to 64; tokens per chunk (multiple of 256)
-    size_t off_dz, off_part, off_hidt, off_arrivals, total;
-    size_t part_bytes;
+    size_t off_dz, off_hidt, off_arrivals, off_part, total;
 };
 
-// Room for the partial tiles of a cut contraction: 512 of them, two rounds, and no more than dZ itself takes.
+// Room for the partial tiles of a cut contraction: 512 of them, two rounds, at most.  The least that a call is content with is
+// as much as dZ takes; what a workspace has beyond that is used as well.
 constexpr size_t kPartBytes = (size_t)512 * kTile * kTile * sizeof(float);
 
 static BwdLayout bwd_layout(int64_t H, int64_t V, int64_t chunk) {
@@ -280,13 +281,24 @@ static BwdLayout bwd_layout(int64_t H, int64_t V, int64_t chunk) {
     L.chunk = chunk;
     size_t o = 0;
     const size_t dz = round_up((size_t)chunk * L.v_pad * 2, 256);
-    L.part_bytes = dz < kPartBytes ? dz : kPartBytes;
     L.off_dz = o;       o += dz;                                               // dZ    [chunk, v_pad] in blocks
-    L.off_part = o;     o += L.part_bytes;
     L.off_hidt = o;     o += round_up((size_t)H * chunk * 2, 256);             // Hid^T [H, chunk]
     L.off_arrivals = o; o += arrivals_bytes(chunk > V ? chunk : V);
+    L.off_part = o;     o += dz < kPartBytes ? dz : kPartBytes;
     L.total = o;
     return L;
+}
+
+// what the two products of such a chunk would cut into, given room
+static size_t wanted_part_bytes(const BwdLayout& L, int64_t H, int64_t V) {
+    size_t most = 0;
+    for (int product = 0; product < 2; ++product) {
+        HeadParams p = {};
+        p.k_tiles = (int)((product == 0 ? L.v_pad : L.chunk) / BwdCfg::kBK);
+        plan_product(p, product == 0 ? L.chunk : V, H, nullptr, kPartBytes);
+        if (p.k_chunks > 1) most = std::max(most, (size_t)p.k_chunks * p.rest_tasks * kTile * kTile * sizeof(float));
+    }
+    return most;
 }
 
 }  // namespace tppo
@@ -295,7 +307,8 @@ extern "C" size_t tppo_token_logprobs_backward_workspace_bytes(int64_t M, int64_
     using namespace tppo;
     if (M <= 0 || H <= 0 || V <= 0 || dt != TPPO_BF16) return 256;
     const int64_t m_round = (M + 255) / 256 * 256;
-    return bwd_layout(H, V, m_round < kBwdChunkDefault ? m_round : kBwdChunkDefault).total;
+    const BwdLayout L = bwd_layout(H, V, m_round < kBwdChunkDefault ? m_round : kBwdChunkDefault);
+    return std::max(L.total, L.off_part + wanted_part_bytes(L, H, V));
 }
 
 extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden,
@@ -327,7 +340,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
     uint16_t* dz = reinterpret_cast<uint16_t*>(ws + L.off_dz);
     uint16_t* hidt = reinterpret_cast<uint16_t*>(ws + L.off_hidt);
     void *arrivals = ws + L.off_arrivals, *part = ws + L.off_part;
-    const size_t room = L.total - L.off_arrivals;
+    const size_t room = L.off_part - L.off_arrivals, part_bytes = std::min(kPartBytes, workspace_bytes - L.off_part);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t* hid = static_cast<const uint16_t*>(hidden);
     const uint16_t* w = static_cast<const uint16_t*>(w_head);
@@ -359,7 +372,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.w = w; q.ld_w = ld_w; q.H = (int)L.v_pad;
             q.km_rows = (int)V; q.km_cols = (int)H;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
-            if (launch_product<1>(q, mc, H, part, L.part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<1>(q, mc, H, part, part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
         // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: columns of dZ; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
@@ -371,7 +384,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.km_rows = (int)mc; q.km_cols = (int)L.v_pad;
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
-            if (launch_product<2>(q, V, H, part, L.part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<2>(q, V, H, part, part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;

@@ -749,10 +749,17 @@ constexpr int kPrefetchH = 1536;
 
 // Plain product of M token-role rows and N W-role rows over K = 64 * k_tiles, columns = W-role tiles.  Whole rounds
 // of 256 output tiles first; of the tiles that remain, fewer than a round, each is cut into k_chunks of the
-// contraction if that ends sooner.  part_bytes: room for the partial tiles.  A chunk keeps at least kMinChunk
-// steps, and costs what kChunkCost steps take (fill and drain of the pipeline, the partial tile written and read
-// again).  Measured: 14 x 20 output tiles, K = 152064: 7.19 -> 4.18 ms; 65 x 4 tiles, K = 32000: 1.48 -> 0.90 ms.
-constexpr int kMinChunk = 32, kChunkCost = 40;
+// contraction if that ends sooner.  part_bytes: room for the partial tiles.  In stages: a round of tasks costs kTaskStages besides
+// its stages (fill, store, drain), the kernel that adds up the chunks kAddStages, a partial tile kPartStages (written and read
+// again, for the most part in the caches).  Measured, us a call with one output, uncut -> cut (chunks), W out of the caches:
+//   V 5000 x H 128, 900 tokens: d/dh 114 -> 42 (64), d/dW 49 -> 43 (12);  20000 x 512, 400: 389 -> 58 (64);  8000 x 256, 2000: 177 -> 59
+//   (31), 80 -> 62 (8);  35637 x 832, 699: 718 -> 131 (21);  3681 x 3520, 1406: 180 -> 140 (3);  21481 x 64, 3631: 426 -> 97 (17), 125 -> 98 (3);
+//   12000 x 2048, 3000: 424 -> 298 (5), 304 -> 289 (2);  32000 x 1024, 16414: 2306 -> 1765 (64).  Cut in vain, two rounds instead of one:
+//   9050 x 1088, 1732: d/dW 99 (131 in 2);  2439 x 4224, 471: 104 (135 in 2).
+// Contractions of fewer than kLeastCut stages stay whole: their results do not depend on the room (one tile over 17 stages, all
+// there is to gain: 35 -> 26).
+constexpr double kTaskStages = 6, kAddStages = 6.5, kPartStages = 0.03;
+constexpr int kLeastCut = 24;
 static void plan_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes) {
     const int k_tiles = p.k_tiles;
     p.M = M;
@@ -766,11 +773,12 @@ static void plan_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t
     p.rest_base = p.first_tasks;
     p.rest_tasks = (int)(tiles - p.first_tasks);
     p.k_chunks = 1;
-    if (p.rest_tasks > 0) {
-        double best = (double)k_tiles;
-        for (int c = 2; c <= kMaxSplits && c * kMinChunk <= k_tiles; ++c) {
-            if ((size_t)c * p.rest_tasks * kTile * kTile * sizeof(float) > part_bytes) break;
-            const double cost = rounds_of((int64_t)p.rest_tasks * c) * ((double)((k_tiles + c - 1) / c) + kChunkCost);
+    if (p.rest_tasks > 0 && k_tiles >= kLeastCut) {
+        double best = (double)k_tiles + kTaskStages;
+        for (int c = 2; c <= kMaxSplits && c <= k_tiles; ++c) {
+            const int64_t tasks = (int64_t)c * p.rest_tasks;
+            if ((size_t)tasks * kTile * kTile * sizeof(float) > part_bytes) break;
+            const double cost = rounds_of(tasks) * ((double)((k_tiles + c - 1) / c) + kTaskStages) + kAddStages + kPartStages * (double)tasks;
             if (cost < best) { best = cost; p.k_chunks = c; }
         }
     }

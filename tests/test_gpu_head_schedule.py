@@ -64,6 +64,22 @@ def test_logprob_grads_cut_contraction(tp, M, V, H):
     assert np.abs(host(acc) - 2.0 - dw).max() <= 2.0 ** -23 * (2.0 + np.abs(dw).max())
 
 
+@pytest.mark.parametrize("M,V,H", [(40, 1472, 64),        # grad_hidden: 23 K steps, whole; a quarter of a tile's columns
+                                   (40, 1473, 64),        # ... 24 steps, in chunks of one or two
+                                   (1473, 300, 320),      # grad_w: 24 K steps of tokens, a short second column of tiles
+                                   (1600, 4200, 704)])    # both, 7 x 3 and 17 x 3 output tiles
+def test_logprob_grads_short_contractions(tp, M, V, H):
+    """Contractions around the shortest that is cut, with all the room for partial tiles that the call wants and with the
+    least workspace that it takes."""
+    case = _bf16_case(M, V, H, seed=M + V)
+    check_logprob_grads(tp, *case)
+    wanted = tp.load().tppo_token_logprobs_backward_workspace_bytes(M, H, V, tp.TPPO_BF16)
+    rows = (M + 255) // 256 * 256 * 2
+    least = rows * ((V + 63) // 64 * 64) * 2 + rows * H + 65536            # dZ, as much again, Hid^T, a little
+    assert least < wanted + 65536
+    check_logprob_grads(tp, *case, workspace=tp._workspace(min(least, wanted), "cuda"))
+
+
 @pytest.mark.parametrize("f32", [False, True])
 @pytest.mark.parametrize("M,V", [(1, 1), (1, 129), (63, 127), (64, 128), (65, 1000), (130, 5003), (700, 2000)])
 @pytest.mark.parametrize("H", [64, 72, 192])

@@ -1,0 +1,49 @@
+"""How the backward pass's products divide their output tiles (csrc/head_tile.h, plan_product, run on the host): every K
+step of every tile belongs to exactly one task, and the partial tiles fit their room."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "head_tile.h"
+namespace tppo { int device_compute_units() { return 256; } }
+using namespace tppo;
+static int check(long M, long N, int k_tiles, size_t room) {
+    HeadParams p = {};
+    p.k_tiles = k_tiles;
+    plan_product(p, M, N, nullptr, room);
+    const long tiles = (M + 255) / 256 * ((N + 255) / 256);
+    bool good = p.first_tasks % 256 == 0 && p.first_tasks + p.rest_tasks == tiles && p.rest_tasks < 256 &&
+                p.n_tasks == p.first_tasks + p.rest_tasks * p.k_chunks && p.k_chunks >= 1 && p.k_chunks <= k_tiles;
+    if (p.k_chunks > 1) good = good && k_tiles >= 24 && (size_t)p.rest_tasks * p.k_chunks * 256 * 256 * 4 <= room;
+    int at = 0;
+    for (int c = 0; c < p.k_chunks; ++c) {                          // (the kernel's own division)
+        const int begin = (int)((int64_t)k_tiles * c / p.k_chunks), end = (int)((int64_t)k_tiles * (c + 1) / p.k_chunks);
+        good = good && begin == at && end > begin;
+        at = end;
+    }
+    if (!(good && at == k_tiles)) printf("M %ld N %ld k %d room %zu: first %d rest %d chunks %d\n", M, N, k_tiles, room,
+                                         p.first_tasks, p.rest_tasks, p.k_chunks);
+    return p.k_chunks > 1;
+}
+int main() {
+    const long sizes[] = {1, 63, 256, 257, 700, 2049, 9000, 33000, 152064};
+    const int depths[] = {1, 2, 23, 24, 25, 64, 257, 500, 2376};
+    int cut = 0;
+    for (long M : sizes) for (long N : {64l, 320l, 1024l, 5120l, 5184l}) for (int k : depths)
+        for (size_t room : {(size_t)0, (size_t)1 << 18, (size_t)5 << 18, (size_t)1 << 27}) cut += check(M, N, k, room);
+    printf("cut %d\n", cut > 50);
+}
+"""
+
+
+def test_every_step_in_one_task(tmp_path):
+    (tmp_path / "plan.hip").write_text(PROGRAM)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(tmp_path / "plan.hip"), "-o", str(tmp_path / "plan")],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    assert subprocess.run([str(tmp_path / "plan")], check=True, stdout=subprocess.PIPE, text=True).stdout.split("\n") == ["cut 1", ""]
