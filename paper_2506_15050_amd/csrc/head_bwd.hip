@@ -253,11 +253,10 @@ using BwdCfg = HeadCfg<uint16_t, false>;
 // (twice the LDS instructions for one operand).  Whole call, transposes -> now: 16414 tokens, H = 1024, V = 32000:
 // 3.28 -> 2.91 ms; 3514 tokens, H = 5120, V = 152064: 14.38 -> 13.69 ms.
 template <int KMAJOR>
-static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, void* arrivals,
-                          size_t arrivals_room, hipStream_t s) {
+static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, hipStream_t s) {
     p.k_tiles = p.H / BwdCfg::kBK;
     plan_product(p, M, N, part, part_bytes);
-    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, arrivals, arrivals_room, s) != TPPO_OK)
+    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, 0, s) != TPPO_OK)
         return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
     hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
@@ -372,7 +371,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.w = w; q.ld_w = ld_w; q.H = (int)L.v_pad;
             q.km_rows = (int)V; q.km_cols = (int)H;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
-            if (launch_product<1>(q, mc, H, part, part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<1>(q, mc, H, part, part_bytes, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
         // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: columns of dZ; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
@@ -384,7 +383,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.km_rows = (int)mc; q.km_cols = (int)L.v_pad;
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
-            if (launch_product<2>(q, V, H, part, part_bytes, arrivals, room, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<2>(q, V, H, part, part_bytes, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;

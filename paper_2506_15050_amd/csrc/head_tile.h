@@ -197,7 +197,10 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 //   plain products:             a column is one tile of W-role rows; `rest` is the last output tiles, each cut
 //                               into k_chunks of the contraction, whose partial tiles a second kernel adds up.
 // Workgroups of an XCD re-align at every round boundary with an arrival counter.  That wait is only a hint for
-// the caches: it is bounded and falls through, and nothing depends on it.
+// the caches: it is bounded and falls through, and nothing depends on it.  Plain products go without: their workgroups would
+// store 64 MB of output tiles all at the same time, and a contraction of some stages is short against that.  Second product, waiting
+// for each other -> not, us: V 46863 x H 3520, 185 tokens: 205 -> 170;  54900 x 1728, 61: 96 -> 78;  54342 x 1664, 1722: 355 -> 325;
+// 152064 x 5120, 3514: 4605 -> 4504;  first products: the same.
 // Small and narrow tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
 constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
 constexpr int kAlignSpins = 4096;
@@ -274,7 +277,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
     const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const int round = t / kSweepGroups;
-    if (kPersistent && round > 0 && p.arrivals)                            // the first round starts aligned
+    if (kPersistent && !C::kOneTile && round > 0 && p.arrivals)            // the first round starts aligned
         align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
     const Task task = task_at(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
@@ -821,7 +824,7 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
     if (C::kLdsBytes > 64 * 1024 && !allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes))
         return TPPO_ERR_LAUNCH;
     static_assert(C::kSmall || C::kNarrow || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
-    const int n = C::kSmall || C::kNarrow ? 0 : arrival_count(p);
+    const int n = C::kSmall || C::kNarrow || C::kOneTile ? 0 : arrival_count(p);
     p.arrivals = nullptr;
     if (n > 8 && (size_t)n * sizeof(int32_t) <= arrivals_room) {
         p.arrivals = static_cast<int32_t*>(arrivals);
