@@ -138,13 +138,16 @@ struct LaneSoftmax {
         const int grp = lane / C::kMI;
         const int v_wave = v0 + wv * C::kWaveV;
         if (v0 + C::kTileV > task.v_end) {                          // ragged last tile: mask ids beyond the task's
+            int left = task.v_end - v_wave - C::row_in_wave(0, 0, grp);
 #pragma unroll
-            for (int vb = 0; vb < kVB; ++vb)
+            for (int vb = 0; vb < kVB; ++vb) {
+                asm volatile("" : "+v"(left));                      // (one block's masks at a time: the scalar registers are full)
 #pragma unroll
                 for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
                     for (int e = 0; e < kE; ++e)
-                        if (v_wave + C::row_in_wave(vb, e, grp) >= task.v_end) acc[vb][tb][e] = -INFINITY;
+                        if (C::row_in_wave(vb, e, 0) >= left) acc[vb][tb][e] = -INFINITY;
+            }
         }
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
@@ -411,10 +414,10 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     if (narrow) {
         rc = whole ? launch_narrow<false, LaneSoftmax>(narrow, p, s) : launch_narrow<true, LaneSoftmax>(narrow, p, s);
     } else if (small) {
-        rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, room, s)
-                   : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, room, s);
+        rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, s)
+                   : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, s);
     } else if constexpr (sizeof(T) == 2) {
-        rc = whole ? launch_sweep<Whole, LaneSoftmax>(p, ws, room, s) : launch_sweep<Ragged, LaneSoftmax>(p, ws, room, s);
+        rc = whole ? launch_sweep<Whole, LaneSoftmax>(p, ws, s) : launch_sweep<Ragged, LaneSoftmax>(p, ws, s);
     }
     if (rc != TPPO_OK) return rc;
     const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};

@@ -61,13 +61,16 @@ struct DzEpilogue {
         const int stored = task.v_end == p.V ? (int)p.out_cols : task.v_end;    // columns up to here are this task's
         char* out = static_cast<char*>(p.out);
         if (v0 + C::kTileV > task.v_end) {                          // ragged last tile: no entry there, dz = 0
+            int left = task.v_end - v_wave - C::row_in_wave(0, 0, grp);
 #pragma unroll
-            for (int vb = 0; vb < kVB; ++vb)
+            for (int vb = 0; vb < kVB; ++vb) {
+                asm volatile("" : "+v"(left));                      // (one block's masks at a time: the scalar registers are full)
 #pragma unroll
                 for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
                     for (int e = 0; e < kE; ++e)
-                        if (v_wave + C::row_in_wave(vb, e, grp) >= task.v_end) acc[vb][tb][e] = -INFINITY;
+                        if (C::row_in_wave(vb, e, 0) >= left) acc[vb][tb][e] = -INFINITY;
+            }
         }
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
@@ -256,7 +259,7 @@ template <int KMAJOR>
 static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, hipStream_t s) {
     p.k_tiles = p.H / BwdCfg::kBK;
     plan_product(p, M, N, part, part_bytes);
-    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, 0, s) != TPPO_OK)
+    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, s) != TPPO_OK)
         return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
     hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
@@ -339,7 +342,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
     uint16_t* dz = reinterpret_cast<uint16_t*>(ws + L.off_dz);
     uint16_t* hidt = reinterpret_cast<uint16_t*>(ws + L.off_hidt);
     void *arrivals = ws + L.off_arrivals, *part = ws + L.off_part;
-    const size_t room = L.off_part - L.off_arrivals, part_bytes = std::min(kPartBytes, workspace_bytes - L.off_part);
+    const size_t part_bytes = std::min(kPartBytes, workspace_bytes - L.off_part);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t* hid = static_cast<const uint16_t*>(hidden);
     const uint16_t* w = static_cast<const uint16_t*>(w_head);
@@ -360,9 +363,9 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         const bool small = plan_small(p, mc, V, plan_sweep(p, mc, V));
         const int narrow = plan_narrow(p, mc, V, small);
         if ((narrow            ? launch_narrow<false, DzEpilogue>(narrow, p, s)
-             : small           ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, room, s)
-             : H <= kPrefetchH ? launch_sweep<BwdCfg, DzAheadEpilogue>(p, arrivals, room, s)
-                               : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, room, s)) != TPPO_OK)
+             : small           ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, s)
+             : H <= kPrefetchH ? launch_sweep<BwdCfg, DzAheadEpilogue>(p, arrivals, s)
+                               : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: columns of W; K = v_pad)
         if (grad_hidden) {

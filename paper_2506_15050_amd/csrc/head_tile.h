@@ -44,7 +44,7 @@ struct HeadParams {
     Grid first, rest;                  // tasks 0 .. first_tasks - 1 come from `first`, the others from `rest`
     int first_tasks, rest_base, rest_tasks, k_chunks;
     int n_tasks;                       // first_tasks + rest_tasks * k_chunks
-    int32_t* arrivals;                 // [rounds * 8] zeroed before the launch; NULL: one round, nothing to align
+    int32_t* arrivals;                 // [256] the round each workgroup has come to; NULL: one round, nothing to align
     // partial results: of the log-softmax ([3][cols][tokens of the grid] per grid: max in the log2 domain, sumexp,
     // target logit), or of the tiles whose contraction is cut into k_chunks ([chunk][task][256 x 256])
     float *part_first, *part_rest;
@@ -196,7 +196,7 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 //                               more vocabulary splits.
 //   plain products:             a column is one tile of W-role rows; `rest` is the last output tiles, each cut
 //                               into k_chunks of the contraction, whose partial tiles a second kernel adds up.
-// Workgroups of an XCD re-align at every round boundary with an arrival counter.  That wait is only a hint for
+// Workgroups of an XCD re-align at every round boundary.  That wait is only a hint for
 // the caches: it is bounded and falls through, and nothing depends on it.  Plain products go without: their workgroups would
 // store 64 MB of output tiles all at the same time, and a contraction of some stages is short against that.  Second product, waiting
 // for each other -> not, us: V 46863 x H 3520, 185 tokens: 205 -> 170;  54900 x 1728, 61: 96 -> 78;  54342 x 1664, 1722: 355 -> 325;
@@ -204,11 +204,20 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 // Small and narrow tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
 constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
 constexpr int kAlignSpins = 4096;
-__device__ __forceinline__ void align_round(int32_t* arrivals, int expected) {
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Every workgroup says in a word of its own which round it has come to (0 when it starts) and waits for the words of its
+// XCD's workgroups that have a task in that round.  Nothing has to be cleared before the launch, as counters had to be: 20000 tokens
+// x V 4000, H 320: 84 -> 76 us; 13640 x 32000, H 1024: 4.6 us of a launch less.  Without any re-alignment H = 5120 loses 8 % on 77528
+// tokens x V 152064 (1.7 times the misses in L2), H = 3584 1 %.
+__device__ __forceinline__ void arrive(int32_t* rounds, int xcd, int slot, int round) {
+    if (threadIdx.x == 0) __hip_atomic_store(rounds + xcd * kXcdGroups + slot, round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void align_round(int32_t* rounds, int xcd, int slot, int round, int expected) {
+    arrive(rounds, xcd, slot, round);
+    if (threadIdx.x < kWave) {
+        const int other = min((int)threadIdx.x, expected - 1);
         for (int spin = 0; spin < kAlignSpins; ++spin) {
-            if (__hip_atomic_load(arrivals, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= expected) break;
+            const int at = __hip_atomic_load(rounds + xcd * kXcdGroups + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__all(at >= round)) break;
             __builtin_amdgcn_s_sleep(8);
         }
     }
@@ -271,6 +280,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
+    if (kPersistent && !C::kOneTile && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
     const int t_first = C::kSmall ? (int)blockIdx.x : xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
     int tid = threadIdx.x;
@@ -278,7 +288,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const int round = t / kSweepGroups;
     if (kPersistent && !C::kOneTile && round > 0 && p.arrivals)            // the first round starts aligned
-        align_round(p.arrivals + round * 8 + xcd, min(kXcdGroups, p.n_tasks - (t - slot)));
+        align_round(p.arrivals, xcd, slot, round, min(kXcdGroups, p.n_tasks - (t - slot)));
     const Task task = task_at(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
     if (tok0 >= m_eff) continue;                            // uniform over the workgroup
@@ -316,7 +326,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             }
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
             const int chunk = (ld_slot ^ C::swz(r)) * 16;
-            if (r < kTileV) {
+            if ((wave * kDmaPerWave + q) * C::kRowsPerDma < kTileV) {      // (the same for all lanes)
                 const int64_t v = min(v0 + r, v_end - 1);
                 src[q] = static_cast<const char*>(p.w) + v * ld_w + chunk;
             } else if (!w_only) {
@@ -552,11 +562,6 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     }
 }
 
-static __global__ __launch_bounds__(256) void head_clear_kernel(int32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 // ---- host side of the schedule
 constexpr int kTile = 256;                         // both sides of an output tile
 
@@ -789,10 +794,9 @@ static void plan_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t
     p.n_tasks = p.first_tasks + p.rest_tasks * p.k_chunks;
 }
 
-// Arrival counters: 8 per round.  With more rounds than this there is room for (no workload comes near), the
-// rounds are not re-aligned.
-static int arrival_count(const HeadParams& p) { return (p.n_tasks + kSweepGroups - 1) / kSweepGroups * 8; }
+// Room for them, a multiple of 256.  (It grew with M, and a workspace for many tokens has to serve fewer.)
 static size_t arrivals_bytes(int64_t M) { return round_up((size_t)(M / kTile + 64) * 16, 256); }
+static_assert(64 * 16 >= kSweepGroups * sizeof(int32_t), "a word for every workgroup");
 
 // A kernel that wants more than 64 KiB of LDS has to be told so once per device.
 static bool allow_lds(const void* fn, int lds_bytes) {
@@ -814,23 +818,16 @@ static bool allow_lds(const void* fn, int lds_bytes) {
     return true;
 }
 
-// Launch one sweep: large tiles one workgroup per CU, with their arrival counters cleared first if there is more than
-// one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A
+// Launch one sweep: large tiles one workgroup per CU, which re-align if there is more than one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A
 // device that does not report 256 compute units (a partition of the chip, another chip) is refused: the sweep would still be
 // correct there, but its workgroups would take turns instead of running side by side.
 template <class C, template <class> class Epi>
-static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hipStream_t s) {
+static int launch_sweep(HeadParams& p, void* arrivals, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
     if (C::kLdsBytes > 64 * 1024 && !allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes))
         return TPPO_ERR_LAUNCH;
     static_assert(C::kSmall || C::kNarrow || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
-    const int n = C::kSmall || C::kNarrow || C::kOneTile ? 0 : arrival_count(p);
-    p.arrivals = nullptr;
-    if (n > 8 && (size_t)n * sizeof(int32_t) <= arrivals_room) {
-        p.arrivals = static_cast<int32_t*>(arrivals);
-        hipLaunchKernelGGL(head_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.arrivals, n);
-        if (launch_result() != TPPO_OK) return TPPO_ERR_LAUNCH;
-    }
+    p.arrivals = !C::kSmall && !C::kNarrow && !C::kOneTile && p.n_tasks > kSweepGroups ? static_cast<int32_t*>(arrivals) : nullptr;
     constexpr int kMostGroups = 1 << 20;                            // (beyond that, several tasks per workgroup)
     const int tasks = C::kSmall ? p.n_tasks : (p.n_tasks + 7) / 8 * 8;
     const int groups = !C::kSmall && !C::kNarrow ? kSweepGroups : tasks < kMostGroups ? tasks : kMostGroups;
@@ -841,9 +838,9 @@ static int launch_sweep(HeadParams& p, void* arrivals, size_t arrivals_room, hip
 
 template <bool RAGGED, template <class> class Epi>
 static int launch_narrow(int n, HeadParams& p, hipStream_t s) {
-    return n == 1   ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 1>, Epi>(p, nullptr, 0, s)
-           : n == 2 ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 2>, Epi>(p, nullptr, 0, s)
-                    : launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 3>, Epi>(p, nullptr, 0, s);
+    return n == 1   ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 1>, Epi>(p, nullptr, s)
+           : n == 2 ? launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 2>, Epi>(p, nullptr, s)
+                    : launch_sweep<HeadCfg<uint16_t, RAGGED, false, 0, 3>, Epi>(p, nullptr, s);
 }
 
 }  // namespace tppo
