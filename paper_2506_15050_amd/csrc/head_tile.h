@@ -157,19 +157,20 @@ struct HeadCfg {
 
 // One wave-wide global -> LDS transfer without a register round trip: lane l's
 // 16 bytes at `src` land at LDS byte address lds_base + 16*l (lds_base is
-// wave-uniform and goes through M0).  Written as inline assembly so that the
+// wave-uniform and goes through M0; `lds_offset` is a constant that is added; the transfer may not follow the write of M0 at
+// once).  Written as inline assembly so that the
 // transfer stays asynchronous: completion is awaited by hand (vmcnt) right
 // before the workgroup barrier that publishes the stage.
-__device__ __forceinline__ void dma_16b_per_lane(const void* src, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+__device__ __forceinline__ void dma_16b_per_lane(const void* src, unsigned lds_base, int lds_offset) {
+    asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                  :
-                 : "s"(lds_base), "v"(src)
-                 : "memory", "m0");
+                 : "s"(lds_base), "v"(src), "i"(lds_offset)
+                 : "memory", "m0", "scc");
 }
 
 // The same with 4 bytes a lane, 256 bytes in all.
 __device__ __forceinline__ void dma_4b_per_lane(const void* src, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
                  :
                  : "s"(lds_base), "v"(src)
                  : "memory", "m0");
@@ -305,12 +306,17 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     constexpr int kVWaves = C::kKMajor ? kTileV / (kDmaPerWave * C::kRowsPerDma) : 1;
     const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
     const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
-    typedef typename std::conditional<C::kKMajor != 0, int64_t, int>::type KPos;
+    typedef typename std::conditional<C::kKMajor != 0, int64_t, unsigned>::type KPos;
     const KPos k_step = k_major                            ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h))
                         : C::kKMajor == 1 && wave >= kVWaves ? (KPos)C::kBlockBytes
                                                              : (KPos)C::kRowBytes;
     const KPos k_first = task.k_begin * k_step;
-    int issue_v = task.v_begin, issue_kt = 0, issue_stage = 0;
+    int issue_v = task.v_begin, issue_kt = 0;
+    // Where this wavefront's transfers land, in one stage and the other in turn: one scalar register, and one scalar instruction a
+    // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 77528 tokens x V 152064,
+    // H 5120: 70.15 -> 69.6 ms;  942 x 152064: 1262 -> 1251 us;  2516 x 50021, H 1000: 248.5 -> 243.6;  fp32, 2064 x 32000, H 1024: 1112 -> 1103.)
+    const unsigned dst_first = lds_base + wave * kDmaPerWave * 1024;
+    unsigned issue_dst = dst_first;
     KPos issue_kpos = k_first;
     int issue_left = p.km_rows - task.k_begin * C::kBK;                 // K rows from the stage to be issued on
     auto point_at_tile = [&](int v0, bool w_only) {
@@ -351,18 +357,17 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     point_at_tile(task.v_begin, false);
     point_at_zeros();
     auto issue_one = [&](int q) {
-        const unsigned dst = lds_base + issue_stage * C::kStageBytes + wave * kDmaPerWave * 1024;
         const char* from = src[q] + issue_kpos;
-        if (C::kRagged && issue_kpos + C::kRowBytes > k_bytes) {    // (uniform) the last stage
+        if (C::kRagged && (int)issue_kpos + C::kRowBytes > k_bytes) {    // (uniform) the last stage
             const int chunk = (ld_slot ^ C::swz(ld_row0 + q * C::kRowsPerDma)) * 16;
-            if (issue_kpos + chunk >= k_bytes) from = reinterpret_cast<const char*>(&kZeroChunk);
+            if ((int)issue_kpos + chunk >= k_bytes) from = reinterpret_cast<const char*>(&kZeroChunk);
         }
-        dma_16b_per_lane(from, dst + q * 1024);
+        dma_16b_per_lane(from, issue_dst, q * 1024);
     };
     auto issue_advance = [&]() {        // next (vocabulary tile, k tile) in sweep order
         issue_kpos += k_step;
         issue_left -= C::kBK;
-        issue_stage ^= 1;
+        issue_dst = 2 * dst_first + C::kStageBytes - issue_dst;
         if (!C::kOneTile && ++issue_kt == k_tiles) {
             issue_kt = 0;
             issue_kpos = k_first;
