@@ -356,12 +356,28 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     };
     point_at_tile(task.v_begin, false);
     point_at_zeros();
+    // Ragged rows: the lanes whose chunk of a tile's last stage lies beyond H, the same ones in every other transfer, take zeros
+    // for it.  `zeros`: those lanes if the stage to be issued is a last one.  Masks and two selects a transfer; a branch for the last
+    // stage at every one of them took, us: 2516 tokens x V 50021, H 1000: 233 (now 224.5);  4000 x 9000, H 520: 62.5 (59.4);  900 x 12000,
+    // H 2040: 80.5 (77.5);  12000 x 9000, H 136: 78.9 (75.4);  300 x 20000, H 72: 23.2 (23.7).
+    const int last_kpos = (p.k_tiles - 1) * C::kRowBytes;
+    uint64_t beyond[2] = {}, zeros[2] = {};
+    const char* zero_chunk = reinterpret_cast<const char*>(&kZeroChunk);
+    auto find_zeros = [&]() {
+        if constexpr (C::kRagged) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) zeros[i] = (int)issue_kpos == last_kpos ? beyond[i] : 0;
+        }
+    };
+    if constexpr (C::kRagged) {
+        asm volatile("" : "+v"(zero_chunk));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) beyond[i] = __ballot(last_kpos + (ld_slot ^ C::swz(ld_row0 + i * C::kRowsPerDma)) * 16 >= k_bytes);
+        find_zeros();
+    }
     auto issue_one = [&](int q) {
         const char* from = src[q] + issue_kpos;
-        if (C::kRagged && (int)issue_kpos + C::kRowBytes > k_bytes) {    // (uniform) the last stage
-            const int chunk = (ld_slot ^ C::swz(ld_row0 + q * C::kRowsPerDma)) * 16;
-            if ((int)issue_kpos + chunk >= k_bytes) from = reinterpret_cast<const char*>(&kZeroChunk);
-        }
+        if (C::kRagged) from = __builtin_amdgcn_inverse_ballot_w64(zeros[q & 1]) ? zero_chunk : from;
         dma_16b_per_lane(from, issue_dst, q * 1024);
     };
     auto issue_advance = [&]() {        // next (vocabulary tile, k tile) in sweep order
@@ -375,6 +391,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             point_at_tile(issue_v, true);
         }
         point_at_zeros();
+        find_zeros();
     };
     // ---- Prefetch.  A stage's transfers go out in the first half of the stage before and are waited for at its end: time
     // enough for what lies in L2, hardly for a miss.  So kAhead stages before its transfers the 256 rows' lines of a stage of W
