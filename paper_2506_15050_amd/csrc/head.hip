@@ -414,8 +414,13 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     if (narrow) {
         rc = whole ? launch_narrow<false, LaneSoftmax>(narrow, p, s) : launch_narrow<true, LaneSoftmax>(narrow, p, s);
     } else if (small) {
-        rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, s)
-                   : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, s);
+        constexpr bool kFew = sizeof(T) == 4;
+        if (p.n_tasks <= 2 * kSweepGroups)
+            rc = whole ? launch_sweep<HeadCfg<T, false, true, 0, 4, kFew>, LaneSoftmax>(p, ws, s)
+                       : launch_sweep<HeadCfg<T, true, true, 0, 4, kFew>, LaneSoftmax>(p, ws, s);
+        else
+            rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, s)
+                       : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, s);
     } else if constexpr (sizeof(T) == 2) {
         rc = whole ? launch_sweep<Whole, LaneSoftmax>(p, ws, s) : launch_sweep<Ragged, LaneSoftmax>(p, ws, s);
     }

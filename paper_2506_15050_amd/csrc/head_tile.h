@@ -86,11 +86,15 @@ struct HeadParams {
 // chip idle with the large ones (plan_small has the line between them).
 // TOKEN_BLOCKS < 4 (bf16): narrow tiles, 256 x 64 TOKEN_BLOCKS, and a workgroup per task too: the large tile's workgroup and
 // W rows, for calls of some tens to some hundreds of tokens (plan_narrow).
+// FEW (small tiles): no more than two workgroups to a CU, whose stages' transfers go out early: spread over the whole stage the
+// last ones are waited for in vain where no third workgroup computes meanwhile.  fp32, us, late -> early, one workgroup to a CU:
+// 1600 tokens x V 32000, H 1024: 1184 -> 955;  4000 x 5000, H 2048: 939 -> 761;  two: 2064 x 45000, H 1024: 1647 -> 1604;  three: 2064 x
+// 32000: 1101 (1109);  3300 x 32000: 1788 (1807).
 // KMAJOR (bf16, large tiles): one operand lies in memory with K as the ROW index -- 1 the W-role one, 2 the token-role
 // one; element (row r, k) is at base[k * ld + r].  A stage of it is kBK rows of 512 bytes, K row k's 16-byte chunk c in
 // slot c ^ swz_k(k), and ds_read_b64_tr_b16 takes fragments out transposed: 16 lanes read 4 K rows x 16 columns, lane i
 // gets column i's four.  Two of them make the fragment one ds_read_b128 gives of the other layout.
-template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0, int TOKEN_BLOCKS = 4>
+template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0, int TOKEN_BLOCKS = 4, bool FEW = false>
 struct HeadCfg {
     static constexpr bool kRagged = RAGGED, kSmall = SMALL;
     static constexpr int kKMajor = KMAJOR;
@@ -128,7 +132,7 @@ struct HeadCfg {
     static constexpr int kKSteps = (kChunks / 4) * kVB;
     // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
     // a full memory queue
-    static constexpr int kSpread = SMALL ? kKSteps * kMfmaPerStep : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
+    static constexpr int kSpread = FEW ? 8 : SMALL ? kKSteps * kMfmaPerStep : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");
     static_assert(kKSteps % 2 == 0, "fragment double buffering assumes an even number of K steps");
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
 
     constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
     if (kPersistent && !C::kOneTile && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
-    const int t_first = C::kSmall ? (int)blockIdx.x : xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
+    const int t_first = xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
@@ -647,12 +651,16 @@ static double plan_sweep(HeadParams& p, int64_t M, int64_t V) {
 //   146 x V 50021, H 1024: 42.2 (57.9)
 // fp32, which the matrix cores bound, loses 6 % per flop and wins that back by filling the chip, and always goes this
 // way (plan_logprobs): 146 x V 1000, H 64: 28.6 -> 11.0;  500 x V 5000, H 1024: 262 -> 78;  2064 x V 32000, H 1024: 1281 ->
-// 1114;  the worst seen, 1000 x V 32000, H 1024: 508 -> 601.
+// 1114;  the worst seen, 1000 x V 32000, H 1024: 508 -> 561.
 typedef HeadCfg<uint16_t, false, true> SmallShape;
 constexpr int kSmallPerCu = SmallShape::kGroupsPerCu;
 constexpr double kSmallPart = (double)SmallShape::kTileV * SmallShape::kTileT / ((double)kTile * kTile);
 constexpr double kSmallSlower = 2.5;
-static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
+// What n workgroups that share a CU take for a tile each, in units of a workgroup among three: a CU's only one waits out latencies.  fp32,
+// us: 1600 tokens x V 32000, H 1024, 250 tasks of 25 tiles: 955;  1250 of 5: 840;  203 x 15261, H 2240, 240 of 2: 189;  480 of 1: 162.
+// (bf16's factor above holds whatever n.)
+constexpr double kShareF32[kSmallPerCu + 1] = {0, 1.16, 2.04, 3};
+static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost, bool f32 = false) {
     const int64_t rows = (M + SmallShape::kTileT - 1) / SmallShape::kTileT, vts = (V + SmallShape::kTileV - 1) / SmallShape::kTileV;
     double best = large_cost;
     int64_t best_cols = 0;
@@ -660,7 +668,8 @@ static bool plan_small(HeadParams& p, int64_t M, int64_t V, double large_cost) {
         // (no more partial results than most_triples() has room for)
         if (s > 4 && rows * s * SmallShape::kTileT > kRestTasks * kTile) break;
         const int64_t tasks = rows * s, full = tasks / (kSweepGroups * kSmallPerCu), rest = tasks % (kSweepGroups * kSmallPerCu);
-        const double shares = (double)(full * kSmallPerCu) + rounds_of(rest);      // tasks in turn on the busiest CU
+        const double last = rounds_of(rest);
+        const double shares = (double)(full * kSmallPerCu) + (f32 ? kShareF32[(int)last] : last);      // tasks in turn on the busiest CU
         const double cost = shares * kSmallPart * ((double)((vts + s - 1) / s) + kTaskCost) * kSmallSlower;
         if (cost < best - 1e-9) { best = cost; best_cols = s; }
     }
@@ -691,7 +700,7 @@ constexpr int kLongSumH = 2048;
 // The forward sweep's schedule; true: in small tiles.  matrix_only: bf16 rows of whole stages at aligned addresses.
 static bool plan_logprobs(HeadParams& p, int64_t M, int64_t V, bool bf16, bool matrix_only) {
     const bool only_small = !bf16 || (!matrix_only && p.H > kLongSumH);
-    return plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V));
+    return plan_small(p, M, V, only_small ? 1e300 : plan_sweep(p, M, V), !bf16);
 }
 
 // The same sweep in narrow tiles, 256 W rows x 64 n tokens, n = 1 .. 3, where that ends sooner than the division that
@@ -840,9 +849,11 @@ static bool allow_lds(const void* fn, int lds_bytes) {
     return true;
 }
 
-// Launch one sweep: large tiles one workgroup per CU, which re-align if there is more than one round; small and narrow tiles one workgroup per task (narrow: as many for every XCD, which takes consecutive tasks).  A
-// device that does not report 256 compute units (a partition of the chip, another chip) is refused: the sweep would still be
-// correct there, but its workgroups would take turns instead of running side by side.
+// Launch one sweep: large tiles one workgroup per CU, which re-align if there is more than one round; small and narrow tiles one
+// workgroup per task, as many for every XCD, which takes consecutive tasks (small tiles dealt out one by one, us: fp32, 2064
+// tokens x V 32000, H 1024: 1214, so: 1147; bf16, 1500 x 8000, H 5112: 322, 306).  A device that does not report 256 compute
+// units (a partition of the chip, another chip) is refused: the sweep would still be correct there, but its workgroups would
+// take turns instead of running side by side.
 template <class C, template <class> class Epi>
 static int launch_sweep(HeadParams& p, void* arrivals, hipStream_t s) {
     if (device_compute_units() != kSweepGroups) return TPPO_ERR_LAUNCH;
@@ -851,7 +862,7 @@ static int launch_sweep(HeadParams& p, void* arrivals, hipStream_t s) {
     static_assert(C::kSmall || C::kNarrow || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
     p.arrivals = !C::kSmall && !C::kNarrow && !C::kOneTile && p.n_tasks > kSweepGroups ? static_cast<int32_t*>(arrivals) : nullptr;
     constexpr int kMostGroups = 1 << 20;                            // (beyond that, several tasks per workgroup)
-    const int tasks = C::kSmall ? p.n_tasks : (p.n_tasks + 7) / 8 * 8;
+    const int tasks = (p.n_tasks + 7) / 8 * 8;
     const int groups = !C::kSmall && !C::kNarrow ? kSweepGroups : tasks < kMostGroups ? tasks : kMostGroups;
     hipLaunchKernelGGL((head_mfma_kernel<C, Epi>), dim3(groups), dim3(C::kThreads),
                        C::kLdsBytes, s, p);

@@ -4,7 +4,7 @@ and output tiles of the backward products whose contraction is cut into chunks."
 import numpy as np
 import pytest
 
-from test_head_routes import LARGE_RAGGED, LARGE_WHOLE
+from test_head_routes import FP32_FEW, FP32_MANY, LARGE_RAGGED, LARGE_WHOLE
 from test_gpu_parity import _bf16_case, assert_within_term_bound, check_logprob_grads, check_logprobs, dev, host, ofast, tp  # noqa: F401
 from paper_2506_15050_amd import synth
 
@@ -98,6 +98,19 @@ def test_logprobs_small_tiles(tp, f32, M, V, H):
     at = host(out)
     # exact products summed in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
     assert np.abs(host(logp)[at] - ref_lp).max() <= 1e-5 and np.abs(host(lse)[at] - ref_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("M,V,H", [*FP32_FEW, *FP32_MANY])
+def test_logprobs_fp32_tasks(tp, M, V, H):
+    """fp32 with up to two workgroups to a CU and with three: whole and ragged rows, tasks of one tile and of several."""
+    rng = np.random.default_rng(M + V + H)
+    hidden = rng.normal(size=(90, H)).astype(np.float32)
+    w = (rng.normal(size=(V, H)) / np.sqrt(H)).astype(np.float32)
+    rows, targets = rng.integers(0, 90, size=M), (np.arange(M) * 7 + V - 1) % V
+    logp, lse = tp.tppo_token_logprobs(dev(hidden), dev(w), dev(rows.astype(np.int32)), dev(targets.astype(np.int32)))
+    ref_lp, ref_lse = ofast.token_logprobs(hidden, w, rows, targets)
+    # products and sums in fp32 over H and V, logits of size about 5: a few times 2^-24 * 8
+    assert np.abs(host(logp) - ref_lp).max() <= 1e-5 and np.abs(host(lse) - ref_lse).max() <= 1e-5
 
 
 @pytest.mark.parametrize("f32", [False, True])

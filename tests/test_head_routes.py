@@ -53,6 +53,10 @@ SMALL_RAGGED = {
 }
 SMALL_FP32 = {(2064, 32000, 1024): (33, 23), (300, 32000, 64): (5, 50)}
 
+# fp32 in small tiles, (token tiles, columns): up to 512 tasks, two workgroups to a CU, and more
+FP32_FEW = {(1500, 9000, 72): (24, 18), (2100, 3000, 64): (33, 12), (203, 15261, 64): (4, 120)}
+FP32_MANY = {(1400, 4097, 64): (22, 33), (1400, 4097, 72): (22, 33), (520, 8300, 64): (9, 65)}
+
 PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
@@ -98,3 +102,9 @@ def test_large_tiles(rule, table, whole):
 def test_small_tiles(rule, table, bf16, whole):
     got = {s: (rows, cols) if tiles == 1 else tiles for s, (tiles, _, _, rows, cols) in zip(table, rule(table, bf16, whole))}
     assert got == table
+
+
+def test_fp32_tasks(rule):
+    for table, few in ((FP32_FEW, True), (FP32_MANY, False)):
+        for s, (rows, cols) in table.items():
+            assert rule([s], False, s[2] % 32 == 0) == [(1, 0, 1, rows, cols)] and (rows * cols <= 512) == few
