@@ -6,8 +6,8 @@
 // the arrays in aligned frames of 1024 tokens (plan.h), four consecutive tokens
 // per thread: a frame's descriptor names the sequence of its first token, and
 // a thread whose four tokens lie inside that sequence (all threads of most
-// frames) knows its share of both sets from two comparisons.  Only a thread at
-// or beyond a sequence boundary inside the frame looks into the offset arrays.
+// frames) knows its share of both sets from two comparisons.  Of a frame of more than
+// two sequences the workgroup fetches the others' metadata into LDS.
 // No mask array is read, and a thread with no member of a set issues no loads
 // for that set (but for the first frame's policy arrays in the pass that writes
 // derivatives, loss_load_ahead).
@@ -131,6 +131,30 @@ struct TokenSets {
     int first, n_tok, pol, val;
 };
 
+// The metadata of the sequences that follow the two a frame's descriptor knows, one per thread of the workgroup: one round trip, in
+// which the policy arrays come too.  Every thread behind the second boundary looking for itself, token by token and from the
+// fourth sequence on by bisection in memory, took, us: 3.0 M tokens in 6008 sequences losses 24.4 (now 16.3), derivatives 32.7 (23.7);
+// 3.4 M in 2703: 24.0 (18.6), 32.0 (26.5);  8.1 M in 3260: 34.4 (28.7), 46.7 (42.6);  4400 in 100: 9.2 (8.4), 10.8 (10.3).  A sequence's
+// four words are one read of LDS: as four arrays, read token by token, 19.0 and 26.5 at 3.0 M.
+struct MoreSeqs {
+    int4 seq[kLossThreads];                      // a sequence's first token, its end, the end of its policy tokens, finished
+    int in_frame[kLossThreads / kWave];          // how many of a wavefront's begin before the frame's end
+};
+struct SeqMeta {
+    int lo, hi, keep, fin;
+};
+__device__ __forceinline__ SeqMeta load_meta(const LossParams& p, int i) {
+    const int at = min(i, p.B - 1);
+    return SeqMeta{p.resp_off[at], p.resp_off[at + 1], p.keep_len[at], p.done[at]};
+}
+// (`more`: another one than the last time, which other threads may still look at)
+__device__ __forceinline__ void keep_meta(MoreSeqs& more, const SeqMeta& x, bool exists, int frame_end, int tid) {
+    const uint64_t in_frame = __ballot(exists && x.lo < frame_end);
+    if ((tid & 63) == 0) more.in_frame[tid >> 6] = __popcll(in_frame);
+    more.seq[tid] = make_int4(x.lo, x.hi, x.lo + min(max(x.keep, 0), x.hi - x.lo), x.fin);
+    __syncthreads();
+}
+
 // The sets of the tokens at or beyond `end` of sequence `seg` (the last one the frame's descriptor knows):
 // token by token, moving on to the sequence that holds the token -- normally the next one, whose four
 // metadata words are asked for together; past empty sequences by bisection of the offsets, so the work is
@@ -168,7 +192,42 @@ __device__ __forceinline__ void walk_sets(const LossParams& p, int seg, int end,
     }
 }
 
-__device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, int item, int tid,
+// The same, looked up in what the workgroup has fetched of the sequences behind `seg`: the first one that ends beyond a
+// thread's first token by bisection, the others from there on.  Only tokens beyond all of them walk on.
+__device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& more, int seg, int end, TokenSets& ts) {
+    int count = 0;
+#pragma unroll
+    for (int w = 0; w < kLossThreads / kWave; ++w) count += more.in_frame[w];
+    const int from = max(ts.first, end);
+    int j = 0, above = count;
+    while (j < above) {
+        const int m = (j + above) >> 1;
+        if (more.seq[m].y <= from) j = m + 1; else above = m;
+    }
+    int4 x = more.seq[min(j, kLossThreads - 1)];
+    for (int e = 0; e < ts.n_tok; ++e) {
+        const int q = ts.first + e;
+        if (q < end) continue;                                     // a token the descriptor covered
+        while (j < count && x.y <= q) {
+            ++j;
+            x = more.seq[min(j, kLossThreads - 1)];
+        }
+        if (j == count) {
+            if (count == kLossThreads && seg + count < p.B - 1) walk_sets(p, seg + count, x.y, ts);
+            break;
+        }
+        if (q < x.x) continue;                                     // no sequence holds q
+        ts.pol |= q < x.z ? 1 << e : 0;
+        ts.val |= x.w != 0 ? 1 << e : 0;
+    }
+}
+
+// A frame with tokens behind the two sequences its descriptor knows: the same for the whole workgroup.
+__device__ __forceinline__ bool has_more(const LossParams& p, const FrameDesc& d, int item) {
+    return d.end2 < min((item + 1) * (4 * kLossThreads), p.n_resp) && d.seg2 + 1 < p.B;
+}
+
+__device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, const MoreSeqs& more, int item, int tid,
                                                 bool has_pol, bool has_val) {
     TokenSets ts;
     ts.first = item * (4 * kLossThreads) + 4 * tid;                // item: part item % kLossParts of frame item / kLossParts
@@ -185,7 +244,7 @@ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, const Frame
             ts.pol |= ((in1 && q < d.pol_end) || (in2 && q < d.pol_end2)) ? 1 << e : 0;
             ts.val |= ((in1 && d.fin != 0) || (in2 && d.fin2 != 0)) ? 1 << e : 0;
         }
-        if (ts.first + ts.n_tok > d.end2) walk_sets(p, d.seg2, d.end2, ts);
+        if (ts.first + ts.n_tok > d.end2 && d.seg2 + 1 < p.B) more_sets(p, more, d.seg2, d.end2, ts);
     }
     ts.pol = (has_pol && ts.n_tok > 0) ? ts.pol & ((1 << ts.n_tok) - 1) : 0;
     ts.val = (has_val && ts.n_tok > 0) ? ts.val & ((1 << ts.n_tok) - 1) : 0;
@@ -207,9 +266,9 @@ __device__ __forceinline__ FrameDesc checked_frame(FrameDesc d, const LossParams
 // the 16 bytes are loaded whole -- the surplus elements are never used -- so that no branch and no wait
 // separates the loads and all of them are in flight together; the one thread that would read past the END OF
 // THE ARRAY reads the array's last 16 bytes instead (see unshift).  Needs n_resp >= 4.
-__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, const TokenSets& ts) {
-    const int at = min(ts.first, p.n_resp - 4);
-    if (ts.pol != 0) {
+__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, int first, bool any) {
+    const int at = min(first, p.n_resp - 4);
+    if (any) {
         x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
         x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
         x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
@@ -329,9 +388,10 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
     out->n_policy = out->n_value = 0;
 }
 
-__global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
+__global__ __launch_bounds__(kLossThreads, 6) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
     __shared__ double s_red[2 * kLossThreads / kWave];
     __shared__ int s_flag;
+    __shared__ MoreSeqs s_more[2];
     const Plan pl = plan_open(p.plan);
     const int tid = threadIdx.x;
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
@@ -348,13 +408,21 @@ __global__ __launch_bounds__(kLossThreads, 8) void loss_kernel(LossParams p, tpp
 
     double pol_acc = 0.0, val_acc = 0.0;
     FrameDesc ahead = {};
+    int which = 0;                                                 // of s_more
     if ((int)blockIdx.x < count) ahead = load_frame(pl.frames + blockIdx.x / kLossParts);
     for (int f = blockIdx.x; f < count; f += gridDim.x) {
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
-        const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
+        const bool more = has_more(p, d, f);
         LossRegs cur = {};
-        loss_load_policy(cur, p, ts);
+        if (more) {
+            const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
+            loss_load_policy(cur, p, f * (4 * kLossThreads) + 4 * tid, has_pol);      // (nearly all of them are in the set)
+            which ^= 1;
+            keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
+        }
+        const TokenSets ts = token_sets(p, d, s_more[which], f, tid, has_pol, has_val);
+        if (!more) loss_load_policy(cur, p, ts.first, ts.pol != 0);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
@@ -435,6 +503,7 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
                                                                 tppo_loss_stats* __restrict__ stats) {
     __shared__ double s_red[kGradSums * kLossThreads / kWave];
     __shared__ int s_flag;
+    __shared__ MoreSeqs s_more[2];
     const LossParams& p = gp.fwd;
     const int tid = threadIdx.x;
     LossRegs cur = {};
@@ -460,12 +529,20 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
     double pol_acc = 0.0, val_acc = 0.0, ratio_acc = 0.0;
     int pol_clipped = 0, val_clipped = 0;
     FrameDesc ahead = {};
+    int which = 0;                                                 // of s_more
     if ((int)blockIdx.x < count) ahead = load_frame(pl.frames + blockIdx.x / kLossParts);
     for (int f = blockIdx.x; f < count; f += gridDim.x) {
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
-        const TokenSets ts = token_sets(p, d, f, tid, has_pol, has_val);
-        if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
+        const bool more = has_more(p, d, f), first = f == (int)blockIdx.x;
+        if (more) {
+            const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
+            if (!first) loss_load_policy(cur, p, f * (4 * kLossThreads) + 4 * tid, has_pol);
+            which ^= 1;
+            keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
+        }
+        const TokenSets ts = token_sets(p, d, s_more[which], f, tid, has_pol, has_val);
+        if (!more && !first) loss_load_policy(cur, p, ts.first, ts.pol != 0);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
