@@ -20,6 +20,9 @@ namespace tppo {
 
 constexpr int kScanThreads = 1024;
 constexpr int kOneLaunchSeqs = kScanThreads;
+// Sequences before its range whose metadata a thread of the scan asks for at a time.  One by one each is a round trip: the scan of
+// 8704 sequences, us, with 1 / 4 / 8: 12.0 / 10.4 / 9.8 (0.3 of each from keeping the thread's own sequence in registers).
+constexpr int kScanAhead = 8;
 constexpr int kListParts = 8;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
 constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
 constexpr int kFillMaxGroups = 512;                             // two per CU
@@ -41,17 +44,21 @@ __device__ __forceinline__ Sums shfl_xor4(Sums a, int off) {
 
 static inline int64_t select_max_tiles(int64_t capacity, int64_t B) { return capacity / kTileTokens + B + 1; }
 
-// window / keep lengths of sequence i (a bad layout counts as an empty window and sets the status bit)
-__device__ __forceinline__ Sums lengths_of(const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ ctx_len,
-                                           const int32_t* __restrict__ done, int i, int n_tok, int tail_drop,
-                                           int32_t* status) {
-    const int lo = cu_seqlens[i], hi = cu_seqlens[i + 1], ctx = ctx_len[i];
-    int win = hi - lo - ctx;
-    if (ctx < 1 || win < 0 || lo < 0 || hi > n_tok) {
+struct SeqWords { int lo, hi, ctx, done; };      // a sequence's metadata as it stands in memory
+
+__device__ __forceinline__ SeqWords words_of(const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ ctx_len,
+                                             const int32_t* __restrict__ done, int i) {
+    return {cu_seqlens[i], cu_seqlens[i + 1], ctx_len[i], done[i]};
+}
+
+// window / keep lengths of a sequence (a bad layout counts as an empty window and sets the status bit)
+__device__ __forceinline__ Sums lengths_of(SeqWords x, int n_tok, int tail_drop, int32_t* status) {
+    int win = x.hi - x.lo - x.ctx;
+    if (x.ctx < 1 || win < 0 || x.lo < 0 || x.hi > n_tok) {
         if (status) set_status(status, TPPO_STATUS_BAD_LAYOUT);
         win = 0;
     }
-    const bool fin = done[i] != 0;
+    const bool fin = x.done != 0;
     const int keep = fin ? win : max(win - tail_drop, 0);
     return {win, keep, fin ? win : 0, tiles_of(keep)};
 }
@@ -75,9 +82,17 @@ __global__ __launch_bounds__(kScanThreads) void select_scan_kernel(
     const int per = (p_end - p_begin + kScanThreads - 1) / kScanThreads;
     const int i_begin = min(p_begin + tid * per, p_end), i_end = min(i_begin + per, p_end);
     Sums mine = {0, 0, 0, 0}, ahead = {0, 0, 0, 0};
-    for (int i = tid; i < p_begin; i += kScanThreads)
-        ahead = add4(ahead, lengths_of(cu_seqlens, ctx_len, done, i, n_tok, tail_drop, nullptr));
-    for (int i = i_begin; i < i_end; ++i) mine = add4(mine, lengths_of(cu_seqlens, ctx_len, done, i, n_tok, tail_drop, status));
+    const SeqWords first = words_of(cu_seqlens, ctx_len, done, min(i_begin, B - 1));
+    for (int i0 = tid; i0 < p_begin; i0 += kScanAhead * kScanThreads) {
+        SeqWords x[kScanAhead];
+#pragma unroll
+        for (int k = 0; k < kScanAhead; ++k) x[k] = words_of(cu_seqlens, ctx_len, done, min(i0 + k * kScanThreads, p_begin - 1));
+#pragma unroll
+        for (int k = 0; k < kScanAhead; ++k)
+            if (i0 + k * kScanThreads < p_begin) ahead = add4(ahead, lengths_of(x[k], n_tok, tail_drop, nullptr));
+    }
+    for (int i = i_begin; i < i_end; ++i)
+        mine = add4(mine, lengths_of(i == i_begin ? first : words_of(cu_seqlens, ctx_len, done, i), n_tok, tail_drop, status));
     Sums inc = mine;
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
@@ -101,7 +116,7 @@ __global__ __launch_bounds__(kScanThreads) void select_scan_kernel(
         sel_off[0] = 0;
     }
     for (int i = i_begin; i < i_end; ++i) {
-        const Sums x = lengths_of(cu_seqlens, ctx_len, done, i, n_tok, tail_drop, nullptr);
+        const Sums x = lengths_of(i == i_begin ? first : words_of(cu_seqlens, ctx_len, done, i), n_tok, tail_drop, nullptr);
         keep_len[i] = x.keep;
         if (tiles) emit_tiles(tiles, tile_cap, run.tiles, i, run.keep, x.keep);       // compact domain
         run = add4(run, x);
@@ -208,7 +223,7 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
     int first_pos = 0;
     bool fin = false;
     if (tid < B) {
-        mine = lengths_of(a.cu_seqlens, a.ctx_len, done, tid, a.n_tok, tail_drop, first ? a.status : nullptr);
+        mine = lengths_of(words_of(a.cu_seqlens, a.ctx_len, done, tid), a.n_tok, tail_drop, first ? a.status : nullptr);
         first_pos = a.cu_seqlens[tid] + a.ctx_len[tid];
         fin = done[tid] != 0;
     }
