@@ -176,7 +176,7 @@ struct StoreEpilogue {
 constexpr int kSumRows = 4;
 __global__ __launch_bounds__(256) void sum_chunks_kernel(HeadParams p) {
     const int id = blockIdx.x / (kTile / kSumRows), r0 = blockIdx.x % (kTile / kSumRows) * kSumRows;
-    const Task task = task_at(p, p.first_tasks + id, 1);
+    const Task task = task_at<true>(p, p.first_tasks + id, 1);
     const int64_t t0 = (int64_t)task.row * kTile + r0;
     const int v = (threadIdx.x & 63) * 4, i = threadIdx.x >> 6;
     const int64_t v0 = (int64_t)task.col * kTile + v;
