@@ -211,7 +211,7 @@ constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
 constexpr int kAlignSpins = 4096;
 // Every workgroup says in a word of its own which round it has come to (0 when it starts) and waits for the words of its
 // XCD's workgroups that have a task in that round.  Nothing has to be cleared before the launch, as counters had to be: 20000 tokens
-// x V 4000, H 320: 84 -> 76 us; 13640 x 32000, H 1024: 4.6 us of a launch less.  Without any re-alignment H = 5120 loses 8 % on 77528
+// x V 4000, H 320: 84 -> 76 us; 13640 x 32000, H 1024: 4.6 us of a launch less.  Without any re-alignment H = 5120 loses 8 % on 63263
 // tokens x V 152064 (1.7 times the misses in L2), H = 3584 1 %.
 __device__ __forceinline__ void arrive(int32_t* rounds, int xcd, int slot, int round) {
     if (threadIdx.x == 0) __hip_atomic_store(rounds + xcd * kXcdGroups + slot, round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const KPos k_first = task.k_begin * k_step;
     int issue_v = task.v_begin, issue_kt = 0;
     // Where this wavefront's transfers land, in one stage and the other in turn: one scalar register, and one scalar instruction a
-    // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 77528 tokens x V 152064,
+    // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 63263 tokens x V 152064,
     // H 5120: 70.15 -> 69.6 ms;  942 x 152064: 1262 -> 1251 us;  2516 x 50021, H 1000: 248.5 -> 243.6;  fp32, 2064 x 32000, H 1024: 1112 -> 1103.)
     const unsigned dst_first = lds_base + wave * kDmaPerWave * 1024;
     unsigned issue_dst = dst_first;
