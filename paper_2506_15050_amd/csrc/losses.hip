@@ -143,15 +143,18 @@ struct MoreSeqs {
 struct SeqMeta {
     int lo, hi, keep, fin;
 };
-__device__ __forceinline__ SeqMeta load_meta(const LossParams& p, int i) {
+__host__ __device__ __forceinline__ SeqMeta load_meta(const LossParams& p, int i) {
     const int at = min(i, p.B - 1);
     return SeqMeta{p.resp_off[at], p.resp_off[at + 1], p.keep_len[at], p.done[at]};
+}
+__host__ __device__ __forceinline__ int4 kept_words(const SeqMeta& x) {
+    return make_int4(x.lo, x.hi, x.lo + min(max(x.keep, 0), x.hi - x.lo), x.fin);
 }
 // (`more`: another one than the last time, which other threads may still look at)
 __device__ __forceinline__ void keep_meta(MoreSeqs& more, const SeqMeta& x, bool exists, int frame_end, int tid) {
     const uint64_t in_frame = __ballot(exists && x.lo < frame_end);
     if ((tid & 63) == 0) more.in_frame[tid >> 6] = __popcll(in_frame);
-    more.seq[tid] = make_int4(x.lo, x.hi, x.lo + min(max(x.keep, 0), x.hi - x.lo), x.fin);
+    more.seq[tid] = kept_words(x);
     __syncthreads();
 }
 
@@ -160,7 +163,7 @@ __device__ __forceinline__ void keep_meta(MoreSeqs& more, const SeqMeta& x, bool
 // metadata words are asked for together; past empty sequences by bisection of the offsets, so the work is
 // bounded whatever the layout.  Offsets that are not a layout (decreasing, beyond the arrays) put a token in
 // no set; they cannot make an access leave the arrays.
-__device__ __forceinline__ void walk_sets(const LossParams& p, int seg, int end, TokenSets& ts) {
+__host__ __device__ __forceinline__ void walk_sets(const LossParams& p, int seg, int end, TokenSets& ts) {
     int pol_end = end;
     bool fin = false, inside = false;
     for (int e = 0; e < ts.n_tok; ++e) {
@@ -194,14 +197,14 @@ __device__ __forceinline__ void walk_sets(const LossParams& p, int seg, int end,
 
 // The same, looked up in what the workgroup has fetched of the sequences behind `seg`: the first one that ends beyond a
 // thread's first token by bisection, the others from there on.  Only tokens beyond all of them walk on.
-__device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& more, int seg, int end, TokenSets& ts) {
+__host__ __device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& more, int seg, int end, TokenSets& ts) {
     int count = 0;
 #pragma unroll
     for (int w = 0; w < kLossThreads / kWave; ++w) count += more.in_frame[w];
     const int from = max(ts.first, end);
     int j = 0, above = count;
     while (j < above) {
-        const int m = (j + above) >> 1;
+        const int m = j + ((above - j) >> 1);
         if (more.seq[m].y <= from) j = m + 1; else above = m;
     }
     int4 x = more.seq[min(j, kLossThreads - 1)];
@@ -222,13 +225,14 @@ __device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& m
     }
 }
 
-// A frame with tokens behind the two sequences its descriptor knows: the same for the whole workgroup.
-__device__ __forceinline__ bool has_more(const LossParams& p, const FrameDesc& d, int item) {
+// A frame with tokens behind the two sequences its descriptor knows: the same for the whole workgroup, which has `seqs` filled
+// then and only then.
+__host__ __device__ __forceinline__ bool has_more(const LossParams& p, const FrameDesc& d, int item) {
     return d.end2 < min((item + 1) * (4 * kLossThreads), p.n_resp) && d.seg2 + 1 < p.B;
 }
 
-__device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, const MoreSeqs& more, int item, int tid,
-                                                bool has_pol, bool has_val) {
+__host__ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, bool more, const MoreSeqs& seqs,
+                                                         int item, int tid, bool has_pol, bool has_val) {
     TokenSets ts;
     ts.first = item * (4 * kLossThreads) + 4 * tid;                // item: part item % kLossParts of frame item / kLossParts
     ts.n_tok = min(max(p.n_resp - ts.first, 0), 4);
@@ -244,7 +248,8 @@ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, const Frame
             ts.pol |= ((in1 && q < d.pol_end) || (in2 && q < d.pol_end2)) ? 1 << e : 0;
             ts.val |= ((in1 && d.fin != 0) || (in2 && d.fin2 != 0)) ? 1 << e : 0;
         }
-        if (ts.first + ts.n_tok > d.end2 && d.seg2 + 1 < p.B) more_sets(p, more, d.seg2, d.end2, ts);
+        // (a thread beyond the end of the arrays has no token to look for)
+        if (more && ts.n_tok > 0 && ts.first + ts.n_tok > d.end2) more_sets(p, seqs, d.seg2, d.end2, ts);
     }
     ts.pol = (has_pol && ts.n_tok > 0) ? ts.pol & ((1 << ts.n_tok) - 1) : 0;
     ts.val = (has_val && ts.n_tok > 0) ? ts.val & ((1 << ts.n_tok) - 1) : 0;
@@ -421,7 +426,7 @@ __global__ __launch_bounds__(kLossThreads, 6) void loss_kernel(LossParams p, tpp
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets(p, d, s_more[which], f, tid, has_pol, has_val);
+        const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
         if (!more) loss_load_policy(cur, p, ts.first, ts.pol != 0);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets(p, d, s_more[which], f, tid, has_pol, has_val);
+        const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
         if (!more && !first) loss_load_policy(cur, p, ts.first, ts.pol != 0);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);

@@ -24,7 +24,7 @@ __device__ __forceinline__ int window_of(Ints resp_off, int i, int n_resp, int& 
 // aligned arrays), which is worth 10-15 % to a streaming kernel on this chip -- a wavefront's 1 KiB access
 // that straddles 128-byte lines costs an extra line each time.  The price is up to one more (short) tile per
 // sequence.
-__device__ __forceinline__ int window_tiles(int lo, int len) {
+__host__ __device__ __forceinline__ int window_tiles(int lo, int len) {
     return len > 0 ? ((lo + len - 1) / kTileTokens) - (lo / kTileTokens) + 1 : 0;
 }
 
@@ -43,8 +43,8 @@ struct NextSeq {
     int seg, end, pol_end, fin;
 };
 template <class Ints>
-__device__ __forceinline__ NextSeq next_sequence(int seg, int lo, int end, Ints resp_off, Ints keep_len, Ints done,
-                                                 bool sets, int B, int n_resp) {
+__host__ __device__ __forceinline__ NextSeq next_sequence(int seg, int lo, int end, Ints resp_off, Ints keep_len, Ints done,
+                                                          bool sets, int B, int n_resp) {
     NextSeq x = {seg, end, end, 0};
     const int frame = (end - 1) & ~(kTileTokens - 1);
     if (frame < lo || end >= frame + kTileTokens || end >= n_resp) return x;
@@ -61,8 +61,8 @@ __device__ __forceinline__ NextSeq next_sequence(int seg, int lo, int end, Ints 
 }
 
 // The tile that begins a frame describes the frame.
-__device__ __forceinline__ void note_frame(const Plan& pl, const Tile& d, int lo, int len, bool sets, int keep, bool fin,
-                                           const NextSeq& next) {
+__host__ __device__ __forceinline__ void note_frame(const Plan& pl, const Tile& d, int lo, int len, bool sets, int keep, bool fin,
+                                                    const NextSeq& next) {
     if ((d.start & (kTileTokens - 1)) != 0) return;
     const int f = d.start / kTileTokens;
     if (f >= pl.cap) return;
@@ -77,7 +77,7 @@ __device__ __forceinline__ void note_frame(const Plan& pl, const Tile& d, int lo
     pl.frames[f] = x;
 }
 
-__device__ __forceinline__ Tile make_tile(int seg, int lo, int len, int tiles, int after) {
+__host__ __device__ __forceinline__ Tile make_tile(int seg, int lo, int len, int tiles, int after) {
     const int c = tiles - 1 - after;
     const int block = lo / kTileTokens + c;                             // which aligned block of the arrays
     const int first = max(lo, block * kTileTokens), last = min(lo + len, (block + 1) * kTileTokens);
