@@ -131,11 +131,16 @@ struct TokenSets {
     int first, n_tok, pol, val;
 };
 
-// The metadata of the sequences that follow the two a frame's descriptor knows, one per thread of the workgroup: one round trip, in
-// which the policy arrays come too.  Every thread behind the second boundary looking for itself, token by token and from the
-// fourth sequence on by bisection in memory, took, us: 3.0 M tokens in 6008 sequences losses 24.4 (now 16.3), derivatives 32.7 (23.7);
-// 3.4 M in 2703: 24.0 (18.6), 32.0 (26.5);  8.1 M in 3260: 34.4 (28.7), 46.7 (42.6);  4400 in 100: 9.2 (8.4), 10.8 (10.3).  A sequence's
+// The metadata of the sequences that follow the two a frame's descriptor knows, one per thread of the workgroup: one round
+// trip.  Every thread behind the second boundary looking for itself, token by token and from the fourth sequence on by
+// bisection in memory, took, us: 3.0 M tokens in 6008 sequences losses 23.0 (now 16.1), derivatives 31.9 (23.7);  3.4 M in
+// 2703: 18.9 (16.3), 28.0 (23.6);  8.2 M in 3260: 32.2 (27.8), 47.1 (44.4);  4600 in 100: 8.4 (8.0), 10.8 (10.6).  A sequence's
 // four words are one read of LDS: as four arrays, read token by token, 19.0 and 26.5 at 3.0 M.
+// The policy arrays wait for the lookup: short unfinished sequences keep few tokens or none.  Asked for by every thread beside the
+// metadata instead, with 0.2 / 0.5 / 0.8 / 1 of 3.0 M tokens in windows of 64 .. 512 kept: losses 15.9 / 16.8 / 17.1 / 17.0 (now
+// 14.9 / 16.0 / 16.7 / 17.4), derivatives 23.9 / 25.2 / 25.6 / 26.0 (22.7 / 23.7 / 24.1 / 24.9); the three layouts above 16.0, 16.2,
+// 28.1 and 24.2, 24.1, 44.7; a batch of 942 tokens, no such frame among them, 4.4 (4.3), after the other kernels of a scoring
+// pass 5.6 (5.1).
 struct MoreSeqs {
     int4 seq[kLossThreads];                      // a sequence's first token, its end, the end of its policy tokens, finished
     int in_frame[kLossThreads / kWave];          // how many of a wavefront's begin before the frame's end
@@ -271,9 +276,9 @@ __device__ __forceinline__ FrameDesc checked_frame(FrameDesc d, const LossParams
 // the 16 bytes are loaded whole -- the surplus elements are never used -- so that no branch and no wait
 // separates the loads and all of them are in flight together; the one thread that would read past the END OF
 // THE ARRAY reads the array's last 16 bytes instead (see unshift).  Needs n_resp >= 4.
-__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, int first, bool any) {
-    const int at = min(first, p.n_resp - 4);
-    if (any) {
+__device__ __forceinline__ void loss_load_policy(LossRegs& x, const LossParams& p, const TokenSets& ts) {
+    const int at = min(ts.first, p.n_resp - 4);
+    if (ts.pol != 0) {
         x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
         x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
         x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
@@ -422,12 +427,11 @@ __global__ __launch_bounds__(kLossThreads, 6) void loss_kernel(LossParams p, tpp
         LossRegs cur = {};
         if (more) {
             const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
-            loss_load_policy(cur, p, f * (4 * kLossThreads) + 4 * tid, has_pol);      // (nearly all of them are in the set)
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
         const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
-        if (!more) loss_load_policy(cur, p, ts.first, ts.pol != 0);
+        loss_load_policy(cur, p, ts);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
@@ -539,15 +543,14 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
     for (int f = blockIdx.x; f < count; f += gridDim.x) {
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
-        const bool more = has_more(p, d, f), first = f == (int)blockIdx.x;
+        const bool more = has_more(p, d, f);
         if (more) {
             const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
-            if (!first) loss_load_policy(cur, p, f * (4 * kLossThreads) + 4 * tid, has_pol);
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
         const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
-        if (!more && !first) loss_load_policy(cur, p, ts.first, ts.pol != 0);
+        if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
