@@ -318,18 +318,19 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     constexpr int kVWaves = C::kKMajor ? kTileV / (kDmaPerWave * C::kRowsPerDma) : 1;
     const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
     const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
-    typedef typename std::conditional<C::kKMajor != 0, int64_t, unsigned>::type KPos;
-    const KPos k_step = k_major                            ? (KPos)(C::kBK * (C::kKMajor == 1 ? ld_w : ld_h))
-                        : C::kKMajor == 1 && wave >= kVWaves ? (KPos)C::kBlockBytes
-                                                             : (KPos)C::kRowBytes;
-    const KPos k_first = task.k_begin * k_step;
+    // (64 bits throughout: a transfer adds its stage's offset to an address, and 32 are extended every time.  Calls, us, 32 -> 64: 6254
+    // tokens x V 1373, H 64: 18.8 -> 17.9;  177 x 44067, H 128: 22.2 -> 21.3;  942 x 152064, H 5120: 1289 -> 1281.)
+    const int64_t k_step = k_major                            ? C::kBK * (C::kKMajor == 1 ? ld_w : ld_h)
+                           : C::kKMajor == 1 && wave >= kVWaves ? C::kBlockBytes
+                                                                : C::kRowBytes;
+    const int64_t k_first = task.k_begin * k_step;
     int issue_v = task.v_begin, issue_kt = 0;
     // Where this wavefront's transfers land, in one stage and the other in turn: one scalar register, and one scalar instruction a
     // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 63263 tokens x V 152064,
     // H 5120: 70.15 -> 69.6 ms;  942 x 152064: 1262 -> 1251 us;  2516 x 50021, H 1000: 248.5 -> 243.6;  fp32, 2064 x 32000, H 1024: 1112 -> 1103.)
     const unsigned dst_first = lds_base + wave * kDmaPerWave * 1024;
     unsigned issue_dst = dst_first;
-    KPos issue_kpos = k_first;
+    int64_t issue_kpos = k_first;
     int issue_left = p.km_rows - task.k_begin * C::kBK;                 // K rows from the stage to be issued on
     auto point_at_tile = [&](int v0, bool w_only) {
 #pragma unroll
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     auto find_zeros = [&]() {
         if constexpr (C::kRagged) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) zeros[i] = (int)issue_kpos == last_kpos ? beyond[i] : 0;
+            for (int i = 0; i < 2; ++i) zeros[i] = issue_kpos == last_kpos ? beyond[i] : 0;
         }
     };
     if constexpr (C::kRagged) {
