@@ -374,12 +374,19 @@ int tppo_ppo_losses_backward(const float* logp_new, const float* logp_old, const
  * the forward pass; rows are clamped, a bad target matches no column).
  * workspace: tppo_token_logprobs_backward_workspace_bytes(M, ...) holds dZ
  *      for min(M, 98304) tokens at once (about 2 (V + H) bytes per token and up
- *      to 134 MB for the partial sums of a cut contraction: 25 GB for the 77 000
- *      kept tokens of the 32B-shaped head) and is the fastest.  The call works with any workspace that
- *      holds 256 tokens (the size the same function returns for M = 256): it
- *      then goes through chunks of as many tokens, a multiple of 256, as the
- *      workspace holds, more slowly (fewer tiles per sweep, grad_w re-read and
- *      re-written per chunk); smaller than that -> TPPO_ERR_WORKSPACE.
+ *      to 134 MB for the partial sums of a cut contraction, which in calls of
+ *      few tokens is most of it: 25 GB for the 77 000 kept tokens of the
+ *      32B-shaped head, 66 MB for 225 tokens of V = 11194, H = 2304) and is the
+ *      fastest; with more the results are the same bits.  The call works with
+ *      any workspace that holds 256 tokens (the size the same function returns
+ *      for M = 256 is enough; dZ takes 512 bytes per entry of the vocabulary
+ *      padded to 64, the partial sums as much again but no more than 134 MB,
+ *      the transposed hidden rows 512 H): it then goes through chunks of as many
+ *      tokens, a multiple of 256, as the workspace holds, more slowly (fewer
+ *      tiles per sweep, grad_w re-read and re-written per chunk); smaller than
+ *      that -> TPPO_ERR_WORKSPACE.  Below the recommended size the workspace
+ *      also decides into how many partial sums, fp32 each, a contraction is
+ *      cut, and with it how grad_hidden and grad_w are rounded.
  */
 size_t tppo_token_logprobs_backward_workspace_bytes(int64_t M, int64_t H, int64_t V, tppo_dtype dt);
 int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden,

@@ -250,15 +250,13 @@ static int launch_transpose(const uint16_t* src, int64_t rows, int64_t cols, int
 
 using BwdCfg = HeadCfg<uint16_t, false>;
 
-// out[M, N] (+)= tokens[M, K] . w_role[N, K]^T, one of the two K-major; `part` is scratch for the tiles whose
-// contraction is cut.  Transposing W and dZ first (both operands read along K, b128 fragments) moves 2 x 2 bytes per entry
-// of both through memory, 7 to 13 % of the call, and needs their room; the K-major sweep itself is 2 to 6 % slower
-// (twice the LDS instructions for one operand).  Whole call, transposes -> now: 16414 tokens, H = 1024, V = 32000:
-// 3.28 -> 2.91 ms; 3514 tokens, H = 5120, V = 152064: 14.38 -> 13.69 ms.
+// out[M, N] (+)= tokens[M, K] . w_role[N, K]^T, one of the two K-major, divided by plan_bwd_product.
+// Transposing W and dZ first (both operands read along K, b128 fragments) moves 2 x 2 bytes per entry of both through
+// memory, 7 to 13 % of the call, and needs their room; the K-major sweep itself is 2 to 6 % slower (twice the LDS
+// instructions for one operand).  Whole call, transposes -> now: 16414 tokens, H = 1024, V = 32000: 3.28 -> 2.91 ms; 3514
+// tokens, H = 5120, V = 152064: 14.38 -> 13.69 ms.
 template <int KMAJOR>
-static int launch_product(HeadParams& p, int64_t M, int64_t N, void* part, size_t part_bytes, hipStream_t s) {
-    p.k_tiles = p.H / BwdCfg::kBK;
-    plan_product(p, M, N, part, part_bytes);
+static int launch_product(HeadParams& p, hipStream_t s) {
     if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, s) != TPPO_OK)
         return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
@@ -291,15 +289,21 @@ static BwdLayout bwd_layout(int64_t H, int64_t V, int64_t chunk) {
     return L;
 }
 
-// what the two products of such a chunk would cut into, given room
-static size_t wanted_part_bytes(const BwdLayout& L, int64_t H, int64_t V) {
+// The two products of `mc` tokens: 0, dZ . W for grad_hidden; 1, dZ^T . Hid for grad_w.
+static void plan_bwd_product(HeadParams& p, int product, int64_t mc, int64_t H, int64_t V, void* part, size_t part_bytes) {
+    p.k_tiles = (int)(((product == 0 ? V : mc) + BwdCfg::kBK - 1) / BwdCfg::kBK);
+    plan_product(p, product == 0 ? mc : V, H, part, part_bytes);
+}
+
+// What the products of the call's chunks cut into, given room: with as much, or more, they are divided one and the same way.
+static size_t wanted_part_bytes(int64_t M, int64_t chunk, int64_t H, int64_t V) {
     size_t most = 0;
-    for (int product = 0; product < 2; ++product) {
-        HeadParams p = {};
-        p.k_tiles = (int)((product == 0 ? L.v_pad : L.chunk) / BwdCfg::kBK);
-        plan_product(p, product == 0 ? L.chunk : V, H, nullptr, kPartBytes);
-        if (p.k_chunks > 1) most = std::max(most, (size_t)p.k_chunks * p.rest_tasks * kTile * kTile * sizeof(float));
-    }
+    for (int64_t mc : {std::min(M, chunk), M % chunk})
+        for (int product = 0; product < 2 && mc > 0; ++product) {
+            HeadParams p = {};
+            plan_bwd_product(p, product, mc, H, V, nullptr, kPartBytes);
+            if (p.k_chunks > 1) most = std::max(most, (size_t)p.k_chunks * p.rest_tasks * kTile * kTile * sizeof(float));
+        }
     return most;
 }
 
@@ -310,7 +314,7 @@ extern "C" size_t tppo_token_logprobs_backward_workspace_bytes(int64_t M, int64_
     if (M <= 0 || H <= 0 || V <= 0 || dt != TPPO_BF16) return 256;
     const int64_t m_round = (M + 255) / 256 * 256;
     const BwdLayout L = bwd_layout(H, V, m_round < kBwdChunkDefault ? m_round : kBwdChunkDefault);
-    return std::max(L.total, L.off_part + wanted_part_bytes(L, H, V));
+    return std::max(L.total, L.off_part + wanted_part_bytes(M, L.chunk, H, V));
 }
 
 extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, int64_t H, int64_t ld_hidden,
@@ -374,7 +378,8 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.w = w; q.ld_w = ld_w; q.H = (int)L.v_pad;
             q.km_rows = (int)V; q.km_cols = (int)H;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
-            if (launch_product<1>(q, mc, H, part, part_bytes, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            plan_bwd_product(q, 0, mc, H, V, part, part_bytes);
+            if (launch_product<1>(q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
         // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: columns of dZ; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
@@ -386,7 +391,8 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.km_rows = (int)mc; q.km_cols = (int)L.v_pad;
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
-            if (launch_product<2>(q, V, H, part, part_bytes, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            plan_bwd_product(q, 1, mc, H, V, part, part_bytes);
+            if (launch_product<2>(q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;

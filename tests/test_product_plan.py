@@ -1,5 +1,6 @@
 """How the backward pass's products divide their output tiles (csrc/head_tile.h, plan_product, run on the host): every K
-step of every tile belongs to exactly one task, and the partial tiles fit their room."""
+step of every tile belongs to exactly one task, the partial tiles fit their room, and room beyond the recommended
+workspace's changes nothing."""
 import os
 import subprocess
 
@@ -41,9 +42,49 @@ int main() {
 """
 
 
-def test_every_step_in_one_task(tmp_path):
-    (tmp_path / "plan.hip").write_text(PROGRAM)
+ROOM = r"""
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include "head_bwd.hip"
+namespace tppo { int device_compute_units() { return 256; } }
+using namespace tppo;
+int main() {
+    srand48(7);
+    int cut = 0;
+    for (int i = 0; i < 10000; ++i) {
+        const int64_t M = 1 + (int64_t)exp(drand48() * log(i % 10 ? 2e4 : 3e5)), V = 1 + (int64_t)exp(drand48() * log(1.6e5));
+        const int64_t H = 64 * (1 + lrand48() % 80);
+        const size_t asked = tppo_token_logprobs_backward_workspace_bytes(M, H, V, TPPO_BF16);
+        const BwdLayout L = bwd_layout(H, V, std::min((M + 255) / 256 * 256, kBwdChunkDefault));
+        const size_t room = std::min(kPartBytes, asked - L.off_part);
+        bool good = asked >= L.total;
+        for (int64_t m0 = 0; m0 < M; m0 += L.chunk)
+            for (int product = 0; product < 2; ++product) {
+                HeadParams p = {}, q = {};
+                plan_bwd_product(p, product, std::min(M - m0, L.chunk), H, V, nullptr, room);
+                plan_bwd_product(q, product, std::min(M - m0, L.chunk), H, V, nullptr, kPartBytes);
+                good = good && p.k_chunks == q.k_chunks;
+                cut += p.k_chunks > 1;
+            }
+        if (!good) printf("M %ld V %ld H %ld\n", (long)M, (long)V, (long)H);
+    }
+    printf("cut %d\n", cut > 1000);
+}
+"""
+
+
+def check(tmp_path, program):
+    (tmp_path / "plan.hip").write_text(program)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(tmp_path / "plan.hip"), "-o", str(tmp_path / "plan")],
                    check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     assert subprocess.run([str(tmp_path / "plan")], check=True, stdout=subprocess.PIPE, text=True).stdout.split("\n") == ["cut 1", ""]
+
+
+def test_every_step_in_one_task(tmp_path):
+    check(tmp_path, PROGRAM)
+
+
+def test_more_room_divides_no_other_way(tmp_path):
+    check(tmp_path, ROOM)
