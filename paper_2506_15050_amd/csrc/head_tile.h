@@ -238,7 +238,7 @@ struct Task {
 };
 
 template <bool ONE_TILE>
-__device__ __forceinline__ Task task_at(const HeadParams& p, int t, int all_k_tiles) {
+__host__ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int all_k_tiles) {
     Task x;
     x.rest = t >= p.first_tasks;
     Grid g = p.first;

@@ -69,15 +69,19 @@ def test_logprob_grads_cut_contraction(tp, M, V, H):
                                    (1473, 300, 320),      # grad_w: 24 K steps of tokens, a short second column of tiles
                                    (1600, 4200, 704)])    # both, 7 x 3 and 17 x 3 output tiles
 def test_logprob_grads_short_contractions(tp, M, V, H):
-    """Contractions around the shortest that is cut, with all the room for partial tiles that the call wants and with the
-    least workspace that it takes."""
+    """Contractions around the shortest that is cut, with all the room for partial tiles that the call wants, with the
+    least workspace that holds all tokens, and, in chunks, with the least that the call takes."""
     case = _bf16_case(M, V, H, seed=M + V)
     check_logprob_grads(tp, *case)
     wanted = tp.load().tppo_token_logprobs_backward_workspace_bytes(M, H, V, tp.TPPO_BF16)
-    rows = (M + 255) // 256 * 256 * 2
-    least = rows * ((V + 63) // 64 * 64) * 2 + rows * H + 65536            # dZ, as much again, Hid^T, a little
-    assert least < wanted + 65536
-    check_logprob_grads(tp, *case, workspace=tp._workspace(min(least, wanted), "cuda"))
+
+    def least(tokens):                                      # dZ, as much again, Hid^T, the sweep's words
+        return 2 * tokens * 2 * ((V + 63) // 64 * 64) + 2 * tokens * H + ((max(tokens, V) // 256 + 64) * 16 + 255) // 256 * 256
+    assert least((M + 255) // 256 * 256) <= wanted
+    for nbytes in {least((M + 255) // 256 * 256), least(256)}:
+        check_logprob_grads(tp, *case, workspace=tp._workspace(nbytes, "cuda"))
+    with pytest.raises(RuntimeError):
+        check_logprob_grads(tp, *case, workspace=tp._workspace(least(256) - 256, "cuda"))
 
 
 @pytest.mark.parametrize("f32", [False, True])

@@ -10,6 +10,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 #include "head_tile.h"
 namespace tppo { int device_compute_units() { return 256; } }
 using namespace tppo;
@@ -21,13 +22,24 @@ static int check(long M, long N, int k_tiles, size_t room) {
     bool good = p.first_tasks % 256 == 0 && p.first_tasks + p.rest_tasks == tiles && p.rest_tasks < 256 &&
                 p.n_tasks == p.first_tasks + p.rest_tasks * p.k_chunks && p.k_chunks >= 1 && p.k_chunks <= k_tiles;
     if (p.k_chunks > 1) good = good && k_tiles >= 24 && (size_t)p.rest_tasks * p.k_chunks * 256 * 256 * 4 <= room;
-    int at = 0;
-    for (int c = 0; c < p.k_chunks; ++c) {                          // (the kernel's own division)
-        const int begin = (int)((int64_t)k_tiles * c / p.k_chunks), end = (int)((int64_t)k_tiles * (c + 1) / p.k_chunks);
-        good = good && begin == at && end > begin;
-        at = end;
+    // the kernels' own tasks: a tile's steps follow each other, in chunk order and without a gap, and a partial tile lies where
+    // the adding kernel looks for it, under the output tile that it is of
+    std::vector<int> at(tiles, 0);
+    for (int t = 0; good && t < p.n_tasks; ++t) {
+        const Task x = task_at<true>(p, t, k_tiles);
+        const long rows = (M + 255) / 256, tile = x.col * rows + x.row;
+        good = x.row >= 0 && x.row < rows && tile >= 0 && tile < tiles && x.k_begin == at[tile] && x.k_tiles > 0 &&
+               x.v_begin == x.col * 256 && x.v_end == std::min(N, x.v_begin + 256l);
+        if (!good) break;
+        at[tile] = x.k_begin + x.k_tiles;
+        if (x.rest) {
+            const int id = x.part % p.rest_tasks;
+            const Task sum = task_at<true>(p, p.first_tasks + id, 1);
+            good = good && x.part == t - p.first_tasks && x.part < p.rest_tasks * p.k_chunks && sum.row == x.row && sum.col == x.col;
+        }
     }
-    if (!(good && at == k_tiles)) printf("M %ld N %ld k %d room %zu: first %d rest %d chunks %d\n", M, N, k_tiles, room,
+    for (long i = 0; i < tiles; ++i) good = good && at[i] == k_tiles;
+    if (!good) printf("M %ld N %ld k %d room %zu: first %d rest %d chunks %d\n", M, N, k_tiles, room,
                                          p.first_tasks, p.rest_tasks, p.k_chunks);
     return p.k_chunks > 1;
 }
