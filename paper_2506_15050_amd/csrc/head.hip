@@ -414,8 +414,8 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
     if (narrow) {
         rc = whole ? launch_narrow<false, LaneSoftmax>(narrow, p, s) : launch_narrow<true, LaneSoftmax>(narrow, p, s);
     } else if (small) {
-        constexpr bool kFew = sizeof(T) == 4;
-        if (p.n_tasks <= 2 * kSweepGroups)
+        constexpr bool kFew = sizeof(T) == 4;                       // (HeadCfg: measured in fp32)
+        if (kFew && p.n_tasks <= 2 * kSweepGroups)
             rc = whole ? launch_sweep<HeadCfg<T, false, true, 0, 4, kFew>, LaneSoftmax>(p, ws, s)
                        : launch_sweep<HeadCfg<T, true, true, 0, 4, kFew>, LaneSoftmax>(p, ws, s);
         else

@@ -22,8 +22,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 // Epilogue 1: a finished tile of logits (vocabulary x tokens) becomes
-// dz, row t of `out`, which is ld_out wide and lies in blocks (head_tile.h, block_at).  A lane owns one token column per block, and of
-// each block of 16 vocabulary entries the 4 of its lane group; two blocks' worth is
+// dz, row t of `out`, which is ld_out wide and lies in blocks (head_tile.h,
+// block_at).  A lane owns one token column per block, and of each block of 16
+// vocabulary entries the 4 of its lane group; two blocks' worth is
 // exchanged between the four lane groups of a token so that each holds 8
 // consecutive entries: 16-byte stores, 64 bytes of a block's row side by side.
 // This runs once per tile with every matrix core idle, so its instructions count:
@@ -103,7 +104,8 @@ struct DzEpilogue {
                     b[j] = quarter[1];
                 }
                 const int v = v_wave + vb * C::kMI + grp * 8;
-                if (t < m_eff && v < stored) *reinterpret_cast<uint4*>(row + C::block_at(0, vb * C::kMI + grp * 8, 0)) = make_uint4(a[0], a[1], b[0], b[1]);
+                if (t < m_eff && v < stored)
+                    *reinterpret_cast<uint4*>(row + C::block_at(0, vb * C::kMI + grp * 8, 0)) = make_uint4(a[0], a[1], b[0], b[1]);
             }
         }
 #pragma unroll
@@ -173,29 +175,28 @@ struct StoreEpilogue {
 // The output tiles whose contraction was cut: out (+)= the sum of their partial tiles, in chunk order.  One
 // workgroup per 4 rows of a tile, a float4 per thread (16 rows, four to a thread: 10.0 us for 4 tiles in 15 chunks; now 8.2 for
 // 4 in 32).
-constexpr int kSumRows = 4;
-__global__ __launch_bounds__(256) void sum_chunks_kernel(HeadParams p) {
+constexpr int kSumRows = 4;                        // one for each wavefront, a float4 for each lane
+static_assert(kTile % kSumRows == 0 && kTile == 4 * kWave, "a workgroup covers whole rows of a tile");
+__global__ __launch_bounds__(kSumRows * kWave) void sum_chunks_kernel(HeadParams p) {
     const int id = blockIdx.x / (kTile / kSumRows), r0 = blockIdx.x % (kTile / kSumRows) * kSumRows;
     const Task task = task_at<true>(p, p.first_tasks + id, 1);
     const int64_t t0 = (int64_t)task.row * kTile + r0;
-    const int v = (threadIdx.x & 63) * 4, i = threadIdx.x >> 6;
+    const int v = (threadIdx.x & 63) * 4, r = threadIdx.x >> 6;
     const int64_t v0 = (int64_t)task.col * kTile + v;
-    if (v0 >= p.out_cols) return;
-    for (int r = i; r < kSumRows && t0 + r < p.M; r += 4) {
-        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float* at = p.part_rest + (int64_t)id * (kTile * kTile) + (r0 + r) * kTile + v;
+    if (v0 >= p.out_cols || t0 + r >= p.M) return;
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float* at = p.part_rest + (int64_t)id * (kTile * kTile) + (r0 + r) * kTile + v;
 #pragma unroll 4
-        for (int c = 0; c < p.k_chunks; ++c) {
-            const float4 x = *reinterpret_cast<const float4*>(at + (int64_t)c * p.rest_tasks * (kTile * kTile));
-            sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
-        }
-        float4* dst = reinterpret_cast<float4*>(static_cast<float*>(p.out) + (t0 + r) * p.ld_out + v0);
-        if (p.accumulate) {
-            const float4 old = *dst;
-            sum.x += old.x; sum.y += old.y; sum.z += old.z; sum.w += old.w;
-        }
-        *dst = sum;
+    for (int c = 0; c < p.k_chunks; ++c) {
+        const float4 x = *reinterpret_cast<const float4*>(at + (int64_t)c * p.rest_tasks * (kTile * kTile));
+        sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
     }
+    float4* dst = reinterpret_cast<float4*>(static_cast<float*>(p.out) + (t0 + r) * p.ld_out + v0);
+    if (p.accumulate) {
+        const float4 old = *dst;
+        sum.x += old.x; sum.y += old.y; sum.z += old.z; sum.w += old.w;
+    }
+    *dst = sum;
 }
 
 // dst[c, r] = src[index ? index[r] : r, c] for r < rows (0 for rows <= r < the
@@ -260,7 +261,7 @@ static int launch_product(HeadParams& p, hipStream_t s) {
     if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, s) != TPPO_OK)
         return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
-    hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(kSumRows * kWave), 0, s, p);
     return launch_result();
 }
 

@@ -161,9 +161,9 @@ struct HeadCfg {
 
 // One wave-wide global -> LDS transfer without a register round trip: lane l's
 // 16 bytes at `src` land at LDS byte address lds_base + 16*l (lds_base is
-// wave-uniform and goes through M0; `lds_offset` is a constant that is added; the transfer may not follow the write of M0 at
-// once).  Written as inline assembly so that the
-// transfer stays asynchronous: completion is awaited by hand (vmcnt) right
+// wave-uniform and goes through M0; `lds_offset` is a constant that is added; the
+// transfer may not follow the write of M0 at once).  Written as inline assembly so
+// that the transfer stays asynchronous: completion is awaited by hand (vmcnt) right
 // before the workgroup barrier that publishes the stage.
 __device__ __forceinline__ void dma_16b_per_lane(const void* src, unsigned lds_base, int lds_offset) {
     asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
@@ -318,16 +318,17 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     constexpr int kVWaves = C::kKMajor ? kTileV / (kDmaPerWave * C::kRowsPerDma) : 1;
     const bool k_major = (C::kKMajor == 1 && wave < kVWaves) || (C::kKMajor == 2 && wave >= kVWaves);
     const int km_row0 = (wave & (kVWaves - 1)) * kDmaPerWave * 2 + (lane >> 5);          // + q * 2: K row in the stage
-    // (64 bits throughout: a transfer adds its stage's offset to an address, and 32 are extended every time.  Calls, us, 32 -> 64: 6254
-    // tokens x V 1373, H 64: 18.8 -> 17.9;  177 x 44067, H 128: 22.2 -> 21.3;  942 x 152064, H 5120: 1289 -> 1281.)
+    // (64 bits throughout: a transfer adds its stage's offset to an address, and 32 are extended every time.  Calls, us, 32 -> 64:
+    // 6254 tokens x V 1373, H 64: 18.8 -> 17.9;  177 x 44067, H 128: 22.2 -> 21.3;  942 x 152064, H 5120: 1289 -> 1281.)
     const int64_t k_step = k_major                            ? C::kBK * (C::kKMajor == 1 ? ld_w : ld_h)
                            : C::kKMajor == 1 && wave >= kVWaves ? C::kBlockBytes
                                                                 : C::kRowBytes;
     const int64_t k_first = task.k_begin * k_step;
     int issue_v = task.v_begin, issue_kt = 0;
     // Where this wavefront's transfers land, in one stage and the other in turn: one scalar register, and one scalar instruction a
-    // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 63263 tokens x V 152064,
-    // H 5120: 70.15 -> 69.6 ms;  942 x 152064: 1262 -> 1251 us;  2516 x 50021, H 1000: 248.5 -> 243.6;  fp32, 2064 x 32000, H 1024: 1112 -> 1103.)
+    // transfer.  (A place for each transfer held eight, some of them spilled and read back by every stage: 63263 tokens x
+    // V 152064, H 5120: 70.3 -> 68.7 ms;  942 x 152064: 1313 -> 1279 us;  16000 x 32000, H 1024: 829 -> 806;  2516 x 50021, H 1000:
+    // 242 -> 240;  fp32, 2064 x 32000, H 1024: 1113 -> 1106.)
     const unsigned dst_first = lds_base + wave * kDmaPerWave * 1024;
     unsigned issue_dst = dst_first;
     int64_t issue_kpos = k_first;
@@ -340,7 +341,8 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
                 if (C::kKMajor == 1)
                     src[q] = static_cast<const char*>(p.w) + k * ld_w + (int64_t)min(v0 + col, p.km_cols - 8) * C::kEsz;
                 else
-                    src[q] = static_cast<const char*>(p.hidden) + C::block_at(k, min(tok0 + col, (int64_t)p.km_cols - 8), p.ld_h);
+                    src[q] = static_cast<const char*>(p.hidden) +
+                             C::block_at(k, min(tok0 + col, (int64_t)p.km_cols - 8), p.ld_h);
                 continue;
             }
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
@@ -371,8 +373,8 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     point_at_zeros();
     // Ragged rows: the lanes whose chunk of a tile's last stage lies beyond H, the same ones in every other transfer, take zeros
     // for it.  `zeros`: those lanes if the stage to be issued is a last one.  Masks and two selects a transfer; a branch for the last
-    // stage at every one of them took, us: 2516 tokens x V 50021, H 1000: 233 (now 224.5);  4000 x 9000, H 520: 62.5 (59.4);  900 x 12000,
-    // H 2040: 80.5 (77.5);  12000 x 9000, H 136: 78.9 (75.4);  300 x 20000, H 72: 23.2 (23.7).
+    // stage at every one of them took, us: 2516 tokens x V 50021, H 1000: 260 (now 245);  4000 x 9000, H 520: 60.6 (57);  900 x 12000,
+    // H 2040: 79.4 (77.5);  12000 x 9000, H 136: 78.7 (75.1);  300 x 20000, H 72: 20.8 (20.2).
     const int last_kpos = (p.k_tiles - 1) * C::kRowBytes;
     uint64_t beyond[2] = {}, zeros[2] = {};
     const char* zero_chunk = reinterpret_cast<const char*>(&kZeroChunk);
@@ -799,11 +801,13 @@ constexpr int kPrefetchH = 1536;
 // of 256 output tiles first; of the tiles that remain, fewer than a round, each is cut into k_chunks of the
 // contraction if that ends sooner.  part_bytes: room for the partial tiles.  In stages: a round of tasks costs kTaskStages besides
 // its stages (fill, store, drain), the kernel that adds up the chunks kAddStages, a partial tile kPartStages (written and read
-// again, for the most part in the caches).  Measured, us a call with one output, uncut -> cut (chunks), W out of the caches:
-//   V 5000 x H 128, 900 tokens: d/dh 114 -> 42 (64), d/dW 49 -> 43 (12);  20000 x 512, 400: 389 -> 58 (64);  8000 x 256, 2000: 177 -> 59
-//   (31), 80 -> 62 (8);  35637 x 832, 699: 718 -> 131 (21);  3681 x 3520, 1406: 180 -> 140 (3);  21481 x 64, 3631: 426 -> 97 (17), 125 -> 98 (3);
-//   12000 x 2048, 3000: 424 -> 298 (5), 304 -> 289 (2);  32000 x 1024, 16414: 2306 -> 1765 (64).  Cut in vain, two rounds instead of one:
-//   9050 x 1088, 1732: d/dW 99 (131 in 2);  2439 x 4224, 471: 104 (135 in 2).
+// again, for the most part in the caches).  Kernel times of a call with one output, us, uncut -> as the rule has it (chunks),
+// out of the caches:
+//   V 5000 x H 128, 900 tokens: d/dh 112 -> 38 (27);  20000 x 512, 400: 380 -> 56 (53);  8000 x 256, 2000: 174 -> 54 (25), d/dW
+//   81 -> 62 (8);  35637 x 832, 699: 690 -> 126 (21);  3681 x 3520, 1406: 178 -> 138 (3);  21481 x 64, 3631: 419 -> 85 (17),
+//   127 -> 89 (3);  12000 x 2048, 3000: 419 -> 295 (5), 303 -> 285 (2);  32000 x 1024, 16414: 2322 -> 1793 (63).
+// Whole by the rule, and for comparison in 2: two rounds instead of one, 9050 x 1088, 1732: d/dW 102 (128);  2439 x 4224, 471:
+// 98 (126);  under kLeastCut, 5000 x 128, 900: 46.4 (45.8).
 // Contractions of fewer than kLeastCut stages stay whole: their results do not depend on the room (one tile over 17 stages, all
 // there is to gain: 35 -> 26).
 constexpr double kTaskStages = 6, kAddStages = 6.5, kPartStages = 0.03;

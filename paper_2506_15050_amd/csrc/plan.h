@@ -82,8 +82,8 @@ struct PlanHeader {
 
 // What is known about frame f (tokens f * kTileTokens ...) without looking at the offset arrays: the sequence
 // that holds its first token and, when that one ends inside the frame, the sequence that follows it there.
-// Tokens of the frame at or beyond `end2` (a third sequence: only after one of fewer than kTileTokens
-// tokens) are looked up in the offset arrays.
+// Of the sequences that hold tokens of the frame at or beyond `end2` (a third one: only after one of fewer than
+// kTileTokens tokens) the loss kernels fetch the metadata, 256 at a time, and look the tokens up there.
 struct FrameDesc {
     int32_t seg;       // sequence of the frame's first token
     int32_t end;       // response-packed index one past that sequence's last token
