@@ -257,8 +257,9 @@ using BwdCfg = HeadCfg<uint16_t, false>;
 // instructions for one operand).  Whole call, transposes -> now: 16414 tokens, H = 1024, V = 32000: 3.28 -> 2.91 ms; 3514
 // tokens, H = 5120, V = 152064: 14.38 -> 13.69 ms.
 template <int KMAJOR>
-static int launch_product(HeadParams& p, hipStream_t s) {
-    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, nullptr, s) != TPPO_OK)
+static int launch_product(HeadParams& p, void* arrivals, hipStream_t s) {
+    if (launch_sweep<HeadCfg<uint16_t, false, false, KMAJOR>, StoreEpilogue>(p, p.k_tiles > kAlignStages ? arrivals : nullptr, s) !=
+        TPPO_OK)
         return TPPO_ERR_LAUNCH;
     if (p.k_chunks == 1) return TPPO_OK;
     hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)(p.rest_tasks * (kTile / kSumRows))), dim3(kSumRows * kWave), 0, s, p);
@@ -380,7 +381,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.km_rows = (int)V; q.km_cols = (int)H;
             q.out = grad_hidden + m0 * H; q.ld_out = H; q.out_cols = H;
             plan_bwd_product(q, 0, mc, H, V, part, part_bytes);
-            if (launch_product<1>(q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<1>(q, arrivals, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
         // 3. grad_w[v, :] (+)= dZ^T[v, :] . Hid   (token role: columns of dZ; W role: rows of Hid^T; K = m_pad)
         if (grad_w) {
@@ -393,7 +394,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
             q.out = grad_w; q.ld_out = H; q.out_cols = H;
             q.accumulate = (m0 > 0 || accumulate_w) ? 1 : 0;
             plan_bwd_product(q, 1, mc, H, V, part, part_bytes);
-            if (launch_product<2>(q, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
+            if (launch_product<2>(q, arrivals, s) != TPPO_OK) return TPPO_ERR_LAUNCH;
         }
     }
     return TPPO_OK;

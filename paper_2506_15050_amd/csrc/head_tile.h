@@ -202,13 +202,19 @@ constexpr int kLgkm0 = 0xF | (3 << 14) | (0x7 << 4);      // ... and one that wa
 //   plain products:             a column is one tile of W-role rows; `rest` is the last output tiles, each cut
 //                               into k_chunks of the contraction, whose partial tiles a second kernel adds up.
 // Workgroups of an XCD re-align at every round boundary.  That wait is only a hint for
-// the caches: it is bounded and falls through, and nothing depends on it.  Plain products go without: their workgroups would
-// store 64 MB of output tiles all at the same time, and a contraction of some stages is short against that.  Second product, waiting
-// for each other -> not, us: V 46863 x H 3520, 185 tokens: 205 -> 170;  54900 x 1728, 61: 96 -> 78;  54342 x 1664, 1722: 355 -> 325;
-// 152064 x 5120, 3514: 4605 -> 4504;  first products: the same.
+// the caches: it is bounded and falls through, and nothing depends on it.  Plain products of up to kAlignStages stages go without:
+// their workgroups would store 64 MB of output tiles all at the same time, and a contraction of some stages is short against that.
+// Over thousands of stages those that drift apart read from HBM what their neighbours had in L2.  Waiting for each other -> not, us:
+//   stages      2: V 46863 x H 3520, 185 tokens: d/dW 205 -> 170        26: 54342 x 1664, 1722: d/dW 328 -> 319
+//              54: 152064 x 5120, 3514: d/dW 4536 -> 4459              125: 152064 x 5120, 8000: d/dW 9403 -> 9422
+//             256: 32000 x 1024, 16414: d/dW 870 -> 852                312: 152064 x 5120, 20000: d/dW 23372 -> 23306
+//             500: 32000 x 4096, 20000: d/dh 3854 -> 3830; 40000: 7804 -> 7887; 32000 x 1024, 16414: 828 -> 818
+//             625: 64000 x 2048, 40000: d/dW 7992 -> 8015             1000: 64000 x 5120, 30000: d/dh 14703 -> 14924
+//            1211: 152064 x 5120, 77528: d/dW 88920 -> 89951           937: 16000 x 4096, 60000: d/dW 5910 -> 5922
+//            2376: 152064 x 5120, 20000: d/dh 23414 -> 23749; 77528: 91866 -> 95332 (another card: 92100 -> 100500)
 // Small and narrow tiles have one list (`rest`), a workgroup per task up to 2^20 of them, and no re-alignment.
 constexpr int kSweepGroups = 256, kXcdGroups = kSweepGroups / 8, kRowBlock = 8;
-constexpr int kAlignSpins = 4096;
+constexpr int kAlignSpins = 4096, kAlignStages = 512;
 // Every workgroup says in a word of its own which round it has come to (0 when it starts) and waits for the words of its
 // XCD's workgroups that have a task in that round.  Nothing has to be cleared before the launch, as counters had to be: 20000 tokens
 // x V 4000, H 320: 84 -> 76 us; 13640 x 32000, H 1024: 4.6 us of a launch less.  Without any re-alignment H = 5120 loses 8 % on 63263
@@ -293,14 +299,14 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
-    if (kPersistent && !C::kOneTile && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
+    if (kPersistent && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
     const int t_first = xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
     const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
     const int round = t / kSweepGroups;
-    if (kPersistent && !C::kOneTile && round > 0 && p.arrivals)            // the first round starts aligned
+    if (kPersistent && round > 0 && p.arrivals)            // the first round starts aligned
         align_round(p.arrivals, xcd, slot, round, min(kXcdGroups, p.n_tasks - (t - slot)));
     const Task task = task_at<C::kOneTile>(p, t, p.k_tiles);
     const int64_t tok0 = (int64_t)task.row * kTileT;
@@ -873,7 +879,7 @@ static int launch_sweep(HeadParams& p, void* arrivals, hipStream_t s) {
     if (C::kLdsBytes > 64 * 1024 && !allow_lds(reinterpret_cast<const void*>(head_mfma_kernel<C, Epi>), C::kLdsBytes))
         return TPPO_ERR_LAUNCH;
     static_assert(C::kSmall || C::kNarrow || (kTile == C::kTileV && kTile == C::kTileT), "the schedule counts in these tiles");
-    p.arrivals = !C::kSmall && !C::kNarrow && !C::kOneTile && p.n_tasks > kSweepGroups ? static_cast<int32_t*>(arrivals) : nullptr;
+    p.arrivals = !C::kSmall && !C::kNarrow && p.n_tasks > kSweepGroups ? static_cast<int32_t*>(arrivals) : nullptr;
     constexpr int kMostGroups = 1 << 20;                            // (beyond that, several tasks per workgroup)
     const int tasks = (p.n_tasks + 7) / 8 * 8;
     const int groups = !C::kSmall && !C::kNarrow ? kSweepGroups : tasks < kMostGroups ? tasks : kMostGroups;

@@ -84,6 +84,33 @@ def test_logprob_grads_short_contractions(tp, M, V, H):
         check_logprob_grads(tp, *case, workspace=tp._workspace(least(256) - 256, "cuda"))
 
 
+@pytest.mark.parametrize("M,V,H", [(8300, 33000, 2048),    # grad_hidden: 33 x 8 output tiles, a round and eight more, 516 K steps
+                                   (32900, 4300, 4096)])   # grad_w: 17 x 16 tiles, 515 K steps of tokens
+def test_logprob_grads_aligned_rounds(tp, M, V, H):
+    """Products of several rounds whose workgroups wait for each other, at sampled rows of both results: plain torch in
+    64 bits from the same log-sum-exps."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    hidden = torch.randn(M, H, device="cuda", generator=gen).bfloat16()
+    w = (torch.randn(V, H, device="cuda", generator=gen) / H ** 0.5).bfloat16()
+    rows = torch.arange(M, device="cuda", dtype=torch.int32).flip(0)
+    targets, g = rows * 7 % V, torch.randn(M, device="cuda", generator=gen)
+    _, lse = tp.tppo_token_logprobs(hidden, w, rows, targets)
+    dh, dw = tp.tppo_token_logprobs_backward(hidden, w, rows, targets, lse, g)
+
+    def dz(t, v):                                           # of tokens t and vocabulary entries v
+        z = hidden[rows[t].long()].double() @ w[v].double().t()
+        hit = targets[t].long().unsqueeze(1) == v.unsqueeze(0)
+        return g[t].double().unsqueeze(1) * (hit.double() - torch.exp(z - lse[t].double().unsqueeze(1)))
+    every_t, every_v = torch.arange(M, device="cuda"), torch.arange(V, device="cuda")
+    t, v = every_t[::M // 60], every_v[::V // 60]
+    d = dz(t, every_v)
+    assert_within_term_bound(host(dh[t]), host(d @ w.double()), host(d.abs() @ w.double().abs()), "grad_hidden")
+    d = dz(every_t, v).t().contiguous()
+    h = hidden[rows.long()].double()
+    assert_within_term_bound(host(dw[v]), host(d @ h), host(d.abs() @ h.abs()), "grad_w")
+
+
 @pytest.mark.parametrize("f32", [False, True])
 @pytest.mark.parametrize("M,V", [(1, 1), (1, 129), (63, 127), (64, 128), (65, 1000), (130, 5003), (700, 2000)])
 @pytest.mark.parametrize("H", [64, 72, 192])
