@@ -163,7 +163,7 @@ __device__ __forceinline__ void keep_meta(MoreSeqs& more, const SeqMeta& x, bool
     __syncthreads();
 }
 
-// The sets of the tokens at or beyond `end` of sequence `seg` (the last one whose metadata the workgroup has fetched):
+// The sets of the tokens at or beyond `end` of sequence `seg` (the last one that is known without a look into memory):
 // token by token, moving on to the sequence that holds the token -- normally the next one, whose four
 // metadata words are asked for together; past empty sequences by bisection of the offsets, so the work is
 // bounded whatever the layout.  Offsets that are not a layout (decreasing, beyond the arrays) put a token in
@@ -236,6 +236,7 @@ __host__ __device__ __forceinline__ bool has_more(const LossParams& p, const Fra
     return d.end2 < min((item + 1) * (4 * kLossThreads), p.n_resp) && d.seg2 + 1 < p.B;
 }
 
+template <bool kFetch>
 __host__ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, bool more, const MoreSeqs& seqs,
                                                          int item, int tid, bool has_pol, bool has_val) {
     TokenSets ts;
@@ -254,7 +255,10 @@ __host__ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, co
             ts.val |= ((in1 && d.fin != 0) || (in2 && d.fin2 != 0)) ? 1 << e : 0;
         }
         // (a thread beyond the end of the arrays has no token to look for)
-        if (more && ts.n_tok > 0 && ts.first + ts.n_tok > d.end2) more_sets(p, seqs, d.seg2, d.end2, ts);
+        if ((more || !kFetch) && ts.n_tok > 0 && ts.first + ts.n_tok > d.end2) {
+            if (kFetch) more_sets(p, seqs, d.seg2, d.end2, ts);
+            else walk_sets(p, d.seg2, d.end2, ts);
+        }
     }
     ts.pol = (has_pol && ts.n_tok > 0) ? ts.pol & ((1 << ts.n_tok) - 1) : 0;
     ts.val = (has_val && ts.n_tok > 0) ? ts.val & ((1 << ts.n_tok) - 1) : 0;
@@ -400,7 +404,8 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
 
 // (Held to eight wavefronts a SIMD the lookup's 106 scalar registers become 78 and 54 spilled ones, and seven are faster, us,
 // seven -> eight: 157 tokens 5.6 -> 6.0, 942: 5.1 -> 5.5, 2.3 M 12.2 -> 12.7, 3.0 M in 6008 sequences 16.1 -> 17.0.)
-__global__ __launch_bounds__(kLossThreads, 6) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
+template <bool kFetch>
+__global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
     __shared__ double s_red[2 * kLossThreads / kWave];
     __shared__ int s_flag;
     __shared__ MoreSeqs s_more[2];
@@ -425,14 +430,14 @@ __global__ __launch_bounds__(kLossThreads, 6) void loss_kernel(LossParams p, tpp
     for (int f = blockIdx.x; f < count; f += gridDim.x) {
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
-        const bool more = has_more(p, d, f);
+        const bool more = kFetch && has_more(p, d, f);
         LossRegs cur = {};
         if (more) {
             const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
+        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val);
         loss_load_policy(cur, p, ts);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
@@ -510,8 +515,9 @@ struct GradParams {
     long long policy_denominator, value_denominator;     // <= 0: the call's own token counts
 };
 
+template <bool kFetch>
 __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams gp, tppo_loss_out* __restrict__ out,
-                                                                tppo_loss_stats* __restrict__ stats) {
+                                                                    tppo_loss_stats* __restrict__ stats) {
     __shared__ double s_red[kGradSums * kLossThreads / kWave];
     __shared__ int s_flag;
     __shared__ MoreSeqs s_more[2];
@@ -545,13 +551,13 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
     for (int f = blockIdx.x; f < count; f += gridDim.x) {
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
-        const bool more = has_more(p, d, f);
+        const bool more = kFetch && has_more(p, d, f);
         if (more) {
             const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
             which ^= 1;
             keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets(p, d, more, s_more[which], f, tid, has_pol, has_val);
+        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val);
         if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
         loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
@@ -710,6 +716,14 @@ static int loss_groups(int64_t n_resp, bool grad) {
     return frames < groups ? (int)frames : groups;
 }
 
+// Whether workgroups fetch the metadata of frames with more than two sequences (MoreSeqs).  Where a frame holds more of them
+// than they fetch in one go, on the average, the fetch is one more trip before the walk that most tokens need all the same: us,
+// fetching -> not, losses / derivatives: 1.0 M windows of one token 18.3 -> 15.6 / 22.9 -> 21.0;  50 000 of two 10.5 -> 9.0 / 13.3 -> 11.9;
+// 10 000 of 100 tokens and 300 empty ones after each 15.4 -> 14.3 / 21.0 -> 19.3.  Below: 20 000 of eight tokens, an empty one
+// after each, 8.0 (8.9) / 11.3 (12.1).
+static bool loss_fetches(int64_t B, int64_t n_resp) { return 4 * B < n_resp; }
+static_assert(4 * kLossThreads == kTileTokens, "a frame of as many sequences as are fetched: four tokens each");
+
 // checks shared by the forward and the backward entry point; on TPPO_OK `plan` points at a plan of this layout
 static int loss_prepare(int n_pol_ptr, int n_val_ptr, const int32_t* resp_off, const int32_t* keep_len,
                         const int32_t* done, int64_t B, int64_t n_resp, float eps_low, float eps_high, float xi_low,
@@ -786,7 +800,8 @@ extern "C" int tppo_ppo_losses(const float* logp_new, const float* logp_old, con
     LossParams p;
     fill_params(p, logp_new, logp_old, adv, v_new, v_old, ret, resp_off, keep_len, done, plan, status, B, n_resp, eps_low,
                 eps_high, xi_low, xi_high);
-    hipLaunchKernelGGL(loss_kernel, dim3(loss_groups(n_resp, false)), dim3(kLossThreads), 0, s, p, out);
+    hipLaunchKernelGGL(loss_fetches(B, n_resp) ? loss_kernel<true> : loss_kernel<false>, dim3(loss_groups(n_resp, false)),
+                       dim3(kLossThreads), 0, s, p, out);
     return launch_result();
 }
 
@@ -829,6 +844,7 @@ extern "C" int tppo_ppo_losses_backward(const float* logp_new, const float* logp
         hipLaunchKernelGGL(loss_tiny_kernel<true>, dim3(1), dim3(256), 0, s, gp, resp_off, out, stats);
         return launch_result();
     }
-    hipLaunchKernelGGL(loss_grad_kernel, dim3(loss_groups(n_resp, true)), dim3(kLossThreads), 0, s, gp, out, stats);
+    hipLaunchKernelGGL(loss_fetches(B, n_resp) ? loss_grad_kernel<true> : loss_grad_kernel<false>, dim3(loss_groups(n_resp, true)),
+                       dim3(kLossThreads), 0, s, gp, out, stats);
     return launch_result();
 }

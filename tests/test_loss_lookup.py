@@ -53,12 +53,14 @@ static void check(const Ints& win, const Ints& keep, const Ints& done) {
             fetched.seq[tid] = kept_words(x);
         }
         for (int tid = 0; tid < kLossThreads; ++tid) {
-            const TokenSets ts = token_sets(p, d, more, more ? fetched : *nobody, item, tid, true, true);
-            int want_pol = 0, want_val = 0;
-            for (int e = 0; e < ts.n_tok; ++e) want_pol |= pol[ts.first + e] << e, want_val |= val[ts.first + e] << e;
-            if (ts.pol != want_pol || ts.val != want_val) {
-                printf("B %d n %d item %d thread %d: %x %x, not %x %x\n", B, n, item, tid, ts.pol, ts.val, want_pol, want_val);
-                exit(1);
+            for (const TokenSets& ts : {token_sets<true>(p, d, more, more ? fetched : *nobody, item, tid, true, true),
+                                        token_sets<false>(p, d, false, *nobody, item, tid, true, true)}) {
+                int want_pol = 0, want_val = 0;
+                for (int e = 0; e < ts.n_tok; ++e) want_pol |= pol[ts.first + e] << e, want_val |= val[ts.first + e] << e;
+                if (ts.pol != want_pol || ts.val != want_val) {
+                    printf("B %d n %d item %d thread %d: %x %x, not %x %x\n", B, n, item, tid, ts.pol, ts.val, want_pol, want_val);
+                    exit(1);
+                }
             }
         }
     }
