@@ -114,7 +114,7 @@ struct MaxUnits {
 // the final merge across lane halves / waves.
 template <class C>
 struct LaneSoftmax {
-    static constexpr bool kPrefetch = false;
+    static constexpr bool kPrefetch = false, kDealt = false;
     typedef MaxUnits<C::kLogitMax> Units;
     float run_max[C::kTB], run_sum[C::kTB], tgt_logit[C::kTB];
     int tgt[C::kTB];

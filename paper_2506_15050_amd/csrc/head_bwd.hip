@@ -35,7 +35,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // stores: 3 % faster at H = 512, as fast there, 4 % slower at 4096 tokens, V = 152064, 2 % at H = 3584.)
 template <class C>
 struct DzEpilogue {
-    static constexpr bool kPrefetch = false;
+    static constexpr bool kPrefetch = false, kDealt = true;
     float lse2[C::kTB], g[C::kTB];
     int tgt[C::kTB];
 
@@ -130,7 +130,7 @@ struct DzAheadEpilogue : DzEpilogue<C> {
 // whole into its place among the partial tiles.
 template <class C>
 struct StoreEpilogue {
-    static constexpr bool kPrefetch = false;
+    static constexpr bool kPrefetch = false, kDealt = false;
     __device__ __forceinline__ void init(const HeadParams&, int64_t, int64_t, int, int) {}
 
     __device__ __forceinline__ void fold(typename C::Acc (&acc)[C::kVB][C::kTB], const HeadParams& p, const Task& task,

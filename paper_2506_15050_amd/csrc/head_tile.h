@@ -281,7 +281,8 @@ __host__ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int
 // Epi (the per-lane epilogue) provides
 //   init(p, tok0, m_eff, wt, lane)                          once per task,
 //   fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane)       after each finished tile of W rows; clears acc,
-//   finish(p, lds_scratch, task, tok0, m_eff, wv, wt, lane, tid)  after the task's tiles (workgroup-wide).
+//   finish(p, lds_scratch, task, tok0, m_eff, wv, wt, lane, tid)  after the task's tiles (workgroup-wide),
+//   kPrefetch  W's lines brought ahead in large tiles,   kDealt  small tiles dealt out one by one (launch_sweep).
 // what the chunks beyond a ragged H hold, in both operands
 static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
@@ -300,7 +301,8 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
 
     constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
     if (kPersistent && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
-    const int t_first = xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
+    const bool dealt = C::kSmall && Epi<C>::kDealt && p.rest.rows > 1;
+    const int t_first = dealt ? (int)blockIdx.x : xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
     for (int t = t_first; t < p.n_tasks; t += t_step) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
@@ -870,7 +872,10 @@ static bool allow_lds(const void* fn, int lds_bytes) {
 
 // Launch one sweep: large tiles one workgroup per CU, which re-align if there is more than one round; small and narrow tiles one
 // workgroup per task, as many for every XCD, which takes consecutive tasks (small tiles dealt out one by one, us: fp32, 2064
-// tokens x V 32000, H 1024: 1214, so: 1147; bf16, 1500 x 8000, H 5112: 322, 306).  A device that does not report 256 compute
+// tokens x V 32000, H 1024: 1214, so: 1147; bf16, 1500 x 8000, H 5112: 322, 306).  Only the derivative's small tiles of several
+// token tiles are dealt out, whose stores go slower where every XCD has a range of V of its own, us: 358 tokens x V 11732,
+// H 192: 21.0, so: 17.2;  400 x 10000, H 192: 19.9, 16.8;  700 x 6000, H 256: 21.8, 19.3;  120 x 13687, H 384: 14.5, 13.7;  436 x 987,
+// H 64: 7.6, 7.8; of one token tile, 34 x 24566, H 128: 9.6, 9.9.  A device that does not report 256 compute
 // units (a partition of the chip, another chip) is refused: the sweep would still be correct there, but its workgroups would
 // take turns instead of running side by side.
 template <class C, template <class> class Epi>
