@@ -7,7 +7,8 @@
 // per thread: a frame's descriptor names the sequence of its first token, and
 // a thread whose four tokens lie inside that sequence (all threads of most
 // frames) knows its share of both sets from two comparisons.  Of a frame of more than
-// two sequences the workgroup fetches the others' metadata into LDS.
+// two sequences the workgroup fetches the others' metadata into LDS (but for batches of
+// windows of a few tokens, loss_fetches).
 // No mask array is read, and a thread with no member of a set issues no loads
 // for that set (but for the first frame's policy arrays in the pass that writes
 // derivatives, loss_load_ahead).
