@@ -722,8 +722,8 @@ static int loss_groups(int64_t n_resp, bool grad) {
 // fetching -> not, losses / derivatives: 1.0 M windows of one token 18.3 -> 15.6 / 22.9 -> 21.0;  50 000 of two 10.5 -> 9.0 / 13.3 -> 11.9;
 // 10 000 of 100 tokens and 300 empty ones after each 15.4 -> 14.3 / 21.0 -> 19.3.  Below: 20 000 of eight tokens, an empty one
 // after each, 8.0 (8.9) / 11.3 (12.1).
+// (A workgroup fetches a sequence and has four tokens for each of its threads.)
 static bool loss_fetches(int64_t B, int64_t n_resp) { return 4 * B < n_resp; }
-static_assert(4 * kLossThreads == kTileTokens, "a frame of as many sequences as are fetched: four tokens each");
 
 // checks shared by the forward and the backward entry point; on TPPO_OK `plan` points at a plan of this layout
 static int loss_prepare(int n_pol_ptr, int n_val_ptr, const int32_t* resp_off, const int32_t* keep_len,
