@@ -42,6 +42,35 @@ __device__ __forceinline__ long long load_uniform(const long long* p) {
 // Compute units of the current device (asked once per device; <= 0 when the runtime cannot say).
 int device_compute_units();
 
+// Sums and scans over a wavefront by data-parallel moves: row_shr 1, 2, 4, 8, then row_bcast 15 and 31, each a step of some cycles,
+// where a shuffle is a trip through the LDS crossbar of more than a hundred.
+// Data-parallel move: lane i receives x of the lane the control word names; lanes without a
+// source (start of a row, a row that row_mask leaves out) receive 0.
+constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
+constexpr int kWaveShr1 = 0x138, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_move(int x) {
+    // where every row is written a lane without a source reads 0 by itself (bound_ctrl), and the destination
+    // needs no initial value -- one instruction instead of two
+    if constexpr (kRowMask == 0xF) return __builtin_amdgcn_mov_dpp(x, kCtrl, 0xF, 0xF, true);
+    else return __builtin_amdgcn_update_dpp(0, x, kCtrl, kRowMask, 0xF, false);
+}
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ double dpp_move(double x) {
+    return __hiloint2double(dpp_move<kCtrl, kRowMask>(__double2hiint(x)), dpp_move<kCtrl, kRowMask>(__double2loint(x)));
+}
+// sums over the lanes up to and including one's own: lane 63 has the wavefront's
+template <class T>
+__device__ __forceinline__ T wave_prefix(T x) {
+    x += dpp_move<kRowShr1, 0xF>(x);
+    x += dpp_move<kRowShr2, 0xF>(x);
+    x += dpp_move<kRowShr4, 0xF>(x);
+    x += dpp_move<kRowShr8, 0xF>(x);
+    x += dpp_move<kRowBcast15, 0xA>(x);                              // lane 15 / 47 into rows 1 / 3
+    x += dpp_move<kRowBcast31, 0xC>(x);                              // lane 31 into rows 2 and 3
+    return x;
+}
+
 // largest s in [lo, hi] with off[s] <= p  (off non-decreasing, off[lo] <= p)
 __device__ __forceinline__ int find_segment(const int32_t* off, int lo, int hi, int p) {
     while (lo < hi) {

@@ -72,25 +72,6 @@ static ScanConsts make_consts(double m) {
     return s;
 }
 
-// data-parallel primitive move: lane i receives x of the lane the control word names; lanes without a
-// source (start of a row, a row that row_mask leaves out) receive 0
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ double dpp_move(double x) {
-    if constexpr (kRowMask == 0xF) {
-        // every row is written: a lane without a source reads 0 by itself (bound_ctrl), and the destination
-        // needs no initial value -- one instruction per half instead of two
-        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), kCtrl, 0xF, 0xF, true);
-        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), kCtrl, 0xF, 0xF, true);
-        return __hiloint2double(hi, lo);
-    } else {
-        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, kRowMask, 0xF, false);
-        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, kRowMask, 0xF, false);
-        return __hiloint2double(hi, lo);
-    }
-}
-constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
-constexpr int kWaveShr1 = 0x138, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-
 __device__ __forceinline__ float wave_shr1(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kWaveShr1, 0xF, 0xF, true));
 }

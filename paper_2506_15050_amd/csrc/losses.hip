@@ -36,12 +36,17 @@ constexpr int kLossThreads = TPPO_LOSS_THREADS;
 constexpr int kLossParts = kTileTokens / (4 * kLossThreads);      // a workgroup takes this fraction of a frame, four tokens per thread
 static_assert(kLossParts >= 1 && kLossParts * 4 * kLossThreads == kTileTokens, "whole parts of a frame");
 // Most workgroups of the persistent grids.  Enough of them to keep the memory busy, and no more: the one that collects
-// the sums reads 4 (forward) or 10 words of each.  Measured, us: forward with 2048 / 1024 / 512 workgroups 14.5 / 12.8 /
+// the sums reads 4 (forward) or 8 words of each.  Measured, us: forward with 2048 / 1024 / 512 workgroups 14.5 / 12.8 /
 // 12.3 on 2.4 M tokens, 30.5 / 28.8 / 28.9 on 10 M, 52.4 / 50.7 / 53.0 on 20 M; with derivatives 2048 / 1024 / 512 take
 // 28 / 21.3 / 21.0 on 2.4 M tokens and 1024 / 512 take 49.3 / 55.9 on 10 M (768: the same up to 20 M, 2 % more on 40 M).
 constexpr int kLossGroups = 1024, kGradGroups = 1024;
 constexpr int kFinishSpin = 1 << 20;
-static_assert(kLossGroups <= kFinishGroups, "the plan holds partial sums for kFinishGroups workgroups");
+// Grids of up to so many workgroups, a frame each, are bound by their round trips: what they may need is asked for at once
+// (loss_load_ahead).  us, at most 256 -> 512 -> 1024 of them: 324 K tokens losses 6.26 -> 5.80 -> 5.83, derivatives 8.04 -> 7.66 -> 7.63;
+// 571 K 6.80 -> 6.8 -> 7.06, 9.53 -> 9.5 -> 9.10;  872 K 7.6 -> 7.6 -> 7.2, 10.1 -> 10.1 -> 10.3;  878 K, a tenth of the sequences finished,
+// 7.1 -> 7.1 -> 7.1, 9.4 -> 9.4 -> 9.6: beyond 512 what is asked for in vain costs as much as the trips.
+constexpr int kFewGroups = 512;
+static_assert(kFewGroups <= kLossGroups && kFewGroups <= kGradGroups, "a frame to a workgroup");
 
 struct LossParams {
     const float *logp_new, *logp_old, *adv, *v_new, *v_old, *ret;
@@ -51,6 +56,7 @@ struct LossParams {
     int B, n_resp;
     uint32_t tag;
     float ratio_lo, ratio_hi, xi_low, xi_high;
+    int all_ahead;                     // loss_load_ahead
 };
 
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, 4-byte aligned
@@ -84,27 +90,26 @@ __device__ __forceinline__ float value_term(float v, float vo, float r, float xl
     return value_undefined(d0, d1, vo) ? __builtin_nanf("") : fmaxf(d0 * d0, d1 * d1);
 }
 
-// The workgroup's sums of kSums values per thread, in a fixed order and with one pass through LDS for all of them:
-// valid in every thread.  s_red: kSums * (wavefronts of the workgroup) doubles.
+// The workgroup's sums of kSums values per thread, in a fixed order: a wavefront's by data-parallel moves, its last lane leaves them in
+// LDS, and after the one barrier whoever needs a sum adds up the wavefronts' with block_sum.  (Through shuffles, two barriers and a
+// loop over the launch's wavefront count, read from memory, a small batch took 0.7 to 2 us for two sums and 1.4 to 2.7 for five.)
+// s_red: kSums * (wavefronts of the workgroup) doubles.
 template <int kSums>
-__device__ __forceinline__ void block_sums(double (&x)[kSums], double* s_red) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)(blockDim.x >> 6);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-        for (int q = 0; q < kSums; ++q) x[q] += __shfl_down(x[q], off);
-    __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < kSums; ++q) s_red[q * waves + wave] = x[q];
-    }
-    __syncthreads();
+__device__ __forceinline__ void block_sums(const double (&x)[kSums], double* s_red) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < kSums; ++q) {
-        double t = 0.0;
-        for (int w = 0; w < waves; ++w) t += s_red[q * waves + w];
-        x[q] = t;
+        const double t = wave_prefix(x[q]);
+        if (lane == kWave - 1) s_red[wave * kSums + q] = t;
     }
+    __syncthreads();
+}
+template <int kSums, int kWaves>
+__device__ __forceinline__ double block_sum(const double* s_red, int q) {
+    double t = s_red[q];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) t += s_red[w * kSums + q];
+    return t;
 }
 
 // Four consecutive results per access; `n` = how many of the four exist.
@@ -201,14 +206,14 @@ __host__ __device__ __forceinline__ void walk_sets(const LossParams& p, int seg,
     }
 }
 
-// The same, looked up in what the workgroup has fetched of the sequences behind `seg`: the first one that ends beyond a
-// thread's first token by bisection, the others from there on.  Only tokens beyond all of them walk on.
-__host__ __device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& more, int seg, int end, TokenSets& ts) {
+// The same, looked up in what the workgroup has fetched of the sequences behind `seg`, of which the first `past` end at or before `end`:
+// the first one that ends beyond a thread's first token by bisection, the others from there on.  Only tokens beyond all of them walk on.
+__host__ __device__ __forceinline__ void more_sets(const LossParams& p, const MoreSeqs& more, int seg, int past, int end, TokenSets& ts) {
     int count = 0;
 #pragma unroll
     for (int w = 0; w < kLossThreads / kWave; ++w) count += more.in_frame[w];
     const int from = max(ts.first, end);
-    int j = 0, above = count;
+    int j = min(past, count), above = count;
     while (j < above) {
         const int m = j + ((above - j) >> 1);
         if (more.seq[m].y <= from) j = m + 1; else above = m;
@@ -237,9 +242,10 @@ __host__ __device__ __forceinline__ bool has_more(const LossParams& p, const Fra
     return d.end2 < min((item + 1) * (4 * kLossThreads), p.n_resp) && d.seg2 + 1 < p.B;
 }
 
+// from: the first sequence that was fetched (< 0: the one after the two that the descriptor knows)
 template <bool kFetch>
 __host__ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, const FrameDesc& d, bool more, const MoreSeqs& seqs,
-                                                         int item, int tid, bool has_pol, bool has_val) {
+                                                         int item, int tid, bool has_pol, bool has_val, int from = -1) {
     TokenSets ts;
     ts.first = item * (4 * kLossThreads) + 4 * tid;                // item: part item % kLossParts of frame item / kLossParts
     ts.n_tok = min(max(p.n_resp - ts.first, 0), 4);
@@ -257,7 +263,7 @@ __host__ __device__ __forceinline__ TokenSets token_sets(const LossParams& p, co
         }
         // (a thread beyond the end of the arrays has no token to look for)
         if ((more || !kFetch) && ts.n_tok > 0 && ts.first + ts.n_tok > d.end2) {
-            if (kFetch) more_sets(p, seqs, d.seg2, d.end2, ts);
+            if (kFetch) more_sets(p, seqs, from < 0 ? d.seg2 : from - 1, from < 0 ? 0 : d.seg2 + 1 - from, d.end2, ts);
             else walk_sets(p, d.seg2, d.end2, ts);
         }
     }
@@ -298,21 +304,28 @@ __device__ __forceinline__ void loss_load_value(LossRegs& x, const LossParams& p
     }
 }
 
-// The policy arrays' part of it before the plan is known, for a workgroup's first frame in the pass that writes derivatives: all
-// but the dropped tails are policy tokens, so little of it is asked for in vain, and the plan's header, the frame's descriptor
-// and these tokens are one round trip instead of three.  The value arrays follow the descriptor: a finished sequence is
-// what they need.  Derivatives alone, us, after the descriptor -> so, at a tenth / three tenths / nine tenths of finished sequences:
-// 100 K tokens 9.2 / 9.1 / 9.4 -> 9.0 / 9.1 / 9.4;  490 K 11.5 / 11.8 / 12.5 -> 11.2 / 11.5 / 11.9;  1 M 16.6 / 17.3 / 18.0 -> 15.7 / 16.8 /
-// 17.4;  4 M 25.8 / 27.2 / 31.0 -> 25.7 / 26.7 / 30.8.  All six arrays early: 17.3 / 17.4 / 17.3 at 1 M, 26.8 / 28.0 / 30.7 at 4 M.  The
-// pass that only sums gains nothing by it (1 M, a tenth / half / nine tenths: 9.5 / 11.0 / 11.4 -> 9.4 / 10.8 / 11.2, 2.3 M: 15.1 / 16.0 /
-// 17.7 -> 14.9 / 16.8 / 18.7) and waits for the descriptor.
-__device__ __forceinline__ void loss_load_ahead(LossRegs& x, const LossParams& p, int tid) {
+// What a workgroup asks for before the plan is known, so that the plan's header, the frame's descriptor and these are one round trip
+// instead of three:
+//   the first frame's policy arrays, in the pass that writes derivatives: all but the dropped tails are policy tokens, so little
+//     of it is asked for in vain.  Derivatives alone, us, after the descriptor -> so, at a tenth / three tenths / nine tenths of finished
+//     sequences: 490 K tokens 11.5 / 11.8 / 12.5 -> 11.2 / 11.5 / 11.9;  1 M 16.6 / 17.3 / 18.0 -> 15.7 / 16.8 / 17.4;  4 M 25.8 / 27.2 / 31.0 ->
+//     25.7 / 26.7 / 30.8.
+//   kFew, a grid of so few workgroups (kFewGroups) that latency is all they take: all six arrays, and all sequences' metadata, one per
+//     thread, if there are no more (all_ahead), for frames with more sequences than the two that the descriptor knows.
+template <bool kFew>
+__device__ __forceinline__ void loss_load_ahead(LossRegs& x, SeqMeta& all, const LossParams& p, int tid) {
     const int at = min((int)blockIdx.x * (4 * kLossThreads) + 4 * tid, p.n_resp - 4);
     if (p.logp_new) {
         x.ln = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_new + at));
         x.lo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.logp_old + at));
         x.a = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.adv + at));
     }
+    if (kFew && p.v_new) {
+        x.v = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_new + at));
+        x.vo = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.v_old + at));
+        x.r = __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p.ret + at));
+    }
+    if (kFew && p.all_ahead) all = load_meta(p, tid);
 }
 
 __device__ __forceinline__ float4u rotate_left(float4u t, int sh) {
@@ -332,58 +345,85 @@ __device__ __forceinline__ void unshift(LossRegs& x, const TokenSets& ts, int it
     x.v = rotate_left(x.v, sh); x.vo = rotate_left(x.vo, sh); x.r = rotate_left(x.r, sh);
 }
 
-// The sums of all workgroups, collected by the one with the highest id.  Every thread adds up the workgroups
-// tid, tid + blockDim, ... in that order, then the threads are added up in a fixed tree: deterministic.
-// The words of kBatch workgroups are asked for together -- a thread's polls are round trips through the L2, and
-// one after the other they would be the longest part of a call on a small batch; only a workgroup that has
-// not published yet is polled again (bounded).  Returns false when a wait gave up.
-template <int kSums, int kBatch>
-__device__ __forceinline__ bool collect_sums(const unsigned long long* words, uint32_t tag, int groups,
-                                             double (&tot)[kSums], double* s_red, int* s_flag) {
-    constexpr int kWords = 2 * kSums;
-    double acc[kSums];
-#pragma unroll
-    for (int q = 0; q < kSums; ++q) acc[q] = 0.0;
-    bool ok = true;
-    const int step = (int)blockDim.x;
-    for (int g0 = threadIdx.x; g0 < groups; g0 += step * kBatch) {
-        unsigned long long w[kBatch][kWords];
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int g = min(g0 + b * step, groups - 1);          // (a clamped duplicate is read and not used)
-#pragma unroll
-            for (int q = 0; q < kWords; ++q)
-                w[b][q] = __hip_atomic_load(words + (int64_t)g * kFinishWords + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int g = g0 + b * step;
-            if (g >= groups) break;
-            bool ready = true;
-#pragma unroll
-            for (int q = 0; q < kWords; ++q) ready = ready && (uint32_t)(w[b][q] >> 32) == tag;
-            for (int spin = 0; spin < kFinishSpin && !ready; ++spin) {
-                __builtin_amdgcn_s_sleep(2);
-                ready = true;
-#pragma unroll
-                for (int q = 0; q < kWords; ++q) {
-                    w[b][q] = __hip_atomic_load(words + (int64_t)g * kFinishWords + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ready = ready && (uint32_t)(w[b][q] >> 32) == tag;
-                }
-            }
-            ok = ok && ready;
-#pragma unroll
-            for (int q = 0; q < kSums; ++q)
-                acc[q] += ready ? (double)__uint_as_float((unsigned)w[b][2 * q]) + (double)__uint_as_float((unsigned)w[b][2 * q + 1]) : 0.0;
-        }
+// A workgroup publishes kWords words: of each of kSums - kCounts sums two (a double as hi + lo), of each of the kCounts last ones, whole
+// numbers below 2^24, one.
+template <int kSums, int kCounts>
+struct SumWords {
+    static constexpr int kFloats = 2 * (kSums - kCounts), kWords = kFloats + kCounts;
+    static_assert(kWords <= kFinishWords && kLossThreads % kWords == 0, "a workgroup's words, and threads that read one kind of them only");
+    __device__ static __forceinline__ void publish_sum(unsigned long long* mine, uint32_t tag, int q, double x) {
+        if (q < kSums - kCounts) publish(mine + 2 * q, tag, x);
+        else __hip_atomic_store(mine + kFloats + q - (kSums - kCounts), pack_word(tag, (float)x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (threadIdx.x == 0) *s_flag = 1;
-    __syncthreads();
-    if (!ok) *s_flag = 0;
+};
+
+// The sums of all workgroups, collected by the one with the highest id: valid in the last lane of its first wavefront.  The words lie one
+// after the other; consecutive threads read consecutive ones, every thread words of one kind only, kBatch of them asked for
+// together (bypassing the caches: each a trip to memory; with a thread to a workgroup's words, 80 bytes apart, the
+// requests were ten times as many), and again, bounded, until all of them are there.  Every thread adds up its words in order,
+// then the threads of a kind are added up in a fixed tree: deterministic.  False in *s_flag when a wait gave up.
+template <int kSums, int kCounts>
+__device__ __forceinline__ void collect_sums(const unsigned long long* words, uint32_t tag, int groups, double (&tot)[kSums],
+                                             double* s_fin, int* s_flag) {
+    typedef SumWords<kSums, kCounts> Words;
+    constexpr int kWords = Words::kWords, kPart = kLossThreads / kWords, kBatch = 16;
+    static_assert(kFinishGroups * kFinishWords % (kLossThreads * kBatch) == 0, "whole batches stay within the plan's words");
+    const unsigned tid = threadIdx.x, lane = tid & 63;
+    const int n = groups * kWords;
+    double acc = 0.0;
+    bool ok = true;
+    for (int first = 0; first < n; first += kLossThreads * kBatch) {
+        const int left = n - first - (int)tid;                     // of mine from here on: b * kLossThreads < left
+        unsigned long long w[kBatch];
+        uint32_t missing = 1;
+        for (int spin = 0; spin < kFinishSpin && missing != 0; ++spin) {
+            if (spin > 0) __builtin_amdgcn_s_sleep(1);
+            unsigned at = tid;
+            asm volatile("" : "+v"(at));                           // (no address kept over the rounds: the registers are full)
+            missing = 0;
 #pragma unroll
-    for (int q = 0; q < kSums; ++q) tot[q] = acc[q];
-    block_sums(tot, s_red);
-    return *s_flag != 0;
+            for (int b = 0; b < kBatch; ++b)
+                if (b * kLossThreads < n - first)
+                    w[b] = __hip_atomic_load(words + first + b * kLossThreads + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) missing |= b * kLossThreads < left ? (uint32_t)(w[b] >> 32) ^ tag : 0;
+        }
+        ok = ok && missing == 0;
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) acc += b * kLossThreads < left ? (double)__uint_as_float((unsigned)w[b]) : 0.0;
+    }
+    s_fin[tid] = acc;
+    if (!ok) *s_flag = 0;
+    __syncthreads();
+    if (tid >= kWave) return;
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) {
+        double t = 0.0;
+        for (unsigned k = lane; k < kPart; k += kWave) {
+            const double* of = s_fin + k * kWords;
+            t += q < kSums - kCounts ? of[2 * q] + of[2 * q + 1] : of[q + kSums - kCounts];
+        }
+        tot[q] = wave_prefix(t);
+    }
+}
+
+// A workgroup's sums (block_sums) become the batch's, in the last lane of a wavefront for which this returns true: at once in a grid of
+// one, else in the workgroup with the highest id, all others having published theirs.  s_flag was set before block_sums.
+template <int kSums, int kCounts>
+__device__ __forceinline__ bool finish_sums(unsigned long long* words, uint32_t tag, double (&tot)[kSums],
+                                            const double* s_red, double* s_fin, int* s_flag) {
+    constexpr int kWaves = kLossThreads / kWave;
+    const int tid = threadIdx.x;
+    if (gridDim.x == 1) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) tot[q] = block_sum<kSums, kWaves>(s_red, q);
+        return tid == kWave - 1;
+    }
+    typedef SumWords<kSums, kCounts> Words;
+    if (tid < kSums) Words::publish_sum(words + blockIdx.x * Words::kWords, tag, tid, block_sum<kSums, kWaves>(s_red, tid));
+    if (blockIdx.x != gridDim.x - 1) return false;
+    collect_sums<kSums, kCounts>(words, tag, (int)gridDim.x, tot, s_fin, s_flag);
+    return tid == kWave - 1;
 }
 
 __device__ __forceinline__ void write_losses(tppo_loss_out* out, double pol_terms, double val_terms, long long np,
@@ -405,13 +445,16 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
 
 // (Held to eight wavefronts a SIMD the lookup's 106 scalar registers become 78 and 54 spilled ones, and seven are faster, us,
 // seven -> eight: 157 tokens 5.6 -> 6.0, 942: 5.1 -> 5.5, 2.3 M 12.2 -> 12.7, 3.0 M in 6008 sequences 16.1 -> 17.0.)
-template <bool kFetch>
+template <bool kFetch, bool kFew>
 __global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
-    __shared__ double s_red[2 * kLossThreads / kWave];
+    __shared__ double s_red[2 * kLossThreads / kWave], s_fin[kLossThreads];
     __shared__ int s_flag;
     __shared__ MoreSeqs s_more[2];
-    const Plan pl = plan_open(p.plan);
     const int tid = threadIdx.x;
+    LossRegs first = {};
+    SeqMeta all = {};
+    if (kFew) loss_load_ahead<kFew>(first, all, p, tid);
+    const Plan pl = plan_open(p.plan);
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const bool plan_ok = pl.hdr->B == p.B && pl.hdr->n_resp == p.n_resp && pl.hdr->has_sets != 0 &&
                          pl.cap >= p.n_resp / kTileTokens + p.B + 1;
@@ -432,15 +475,18 @@ __global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(Loss
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const bool more = kFetch && has_more(p, d, f);
-        LossRegs cur = {};
+        const int from = kFew && p.all_ahead ? 0 : d.seg2 + 1;
         if (more) {
-            const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
+            const SeqMeta meta = kFew && p.all_ahead ? all : load_meta(p, from + tid);
             which ^= 1;
-            keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
+            keep_meta(s_more[which], meta, from + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val);
-        loss_load_policy(cur, p, ts);
-        loss_load_value(cur, p, ts);
+        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val, from);
+        LossRegs cur = first;
+        if (!kFew) {
+            loss_load_policy(cur, p, ts);
+            loss_load_value(cur, p, ts);
+        }
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
         if (ts.pol != 0) {
@@ -459,18 +505,13 @@ __global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(Loss
         }
         pol_acc += (double)pol_t;
         val_acc += (double)val_t;
+        if (kFew) break;                                           // (a frame to a workgroup)
     }
     double tot[2] = {pol_acc, val_acc};
+    if (tid == 0) s_flag = 1;
     block_sums(tot, s_red);
-    bool ok = true;
-    if (gridDim.x > 1) {                                           // (a grid of one has them all)
-        unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
-        if (tid < 2) publish(mine + 2 * tid, p.tag, tid == 0 ? tot[0] : tot[1]);
-        if (blockIdx.x != gridDim.x - 1) return;
-        ok = collect_sums<2, 4>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
-    }
-    if (tid == 0) {
-        if (!ok) {
+    if (finish_sums<2, 0>(pl.finish_words, p.tag, tot, s_red, s_fin, &s_flag)) {
+        if (s_flag == 0) {
             set_status(p.status, TPPO_STATUS_TIMEOUT);
             tot[0] = tot[1] = __builtin_nan("");
         }
@@ -506,7 +547,6 @@ __global__ void loss_empty_kernel(tppo_loss_out* __restrict__ out, tppo_loss_sta
 // (the plan holds them), so each derivative is final when it is written; tokens
 // outside a set get 0.
 constexpr int kGradSums = 5;       // policy terms, value terms, ratios, clipped policy tokens, clipped value tokens
-static_assert(2 * kGradSums <= kFinishWords, "a workgroup's sums must fit its tagged words");
 
 struct GradParams {
     LossParams fwd;
@@ -516,16 +556,17 @@ struct GradParams {
     long long policy_denominator, value_denominator;     // <= 0: the call's own token counts
 };
 
-template <bool kFetch>
+template <bool kFetch, bool kFew>
 __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams gp, tppo_loss_out* __restrict__ out,
                                                                     tppo_loss_stats* __restrict__ stats) {
-    __shared__ double s_red[kGradSums * kLossThreads / kWave];
+    __shared__ double s_red[kGradSums * kLossThreads / kWave], s_fin[kLossThreads];
     __shared__ int s_flag;
     __shared__ MoreSeqs s_more[2];
     const LossParams& p = gp.fwd;
     const int tid = threadIdx.x;
     LossRegs cur = {};
-    loss_load_ahead(cur, p, tid);
+    SeqMeta all = {};
+    loss_load_ahead<kFew>(cur, all, p, tid);
     const Plan pl = plan_open(p.plan);
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const bool plan_ok = pl.hdr->B == p.B && pl.hdr->n_resp == p.n_resp && pl.hdr->has_sets != 0 &&
@@ -553,14 +594,15 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         const FrameDesc d = checked_frame(ahead, p, tid);
         if (f + (int)gridDim.x < count) ahead = load_frame(pl.frames + (f + gridDim.x) / kLossParts);     // the next item's, meanwhile
         const bool more = kFetch && has_more(p, d, f);
+        const int from = kFew && p.all_ahead ? 0 : d.seg2 + 1;
         if (more) {
-            const SeqMeta meta = load_meta(p, d.seg2 + 1 + tid);
+            const SeqMeta meta = kFew && p.all_ahead ? all : load_meta(p, from + tid);
             which ^= 1;
-            keep_meta(s_more[which], meta, d.seg2 + 1 + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
+            keep_meta(s_more[which], meta, from + tid < p.B, (f + 1) * (4 * kLossThreads), tid);
         }
-        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val);
+        const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val, from);
         if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
-        loss_load_value(cur, p, ts);
+        if (!kFew) loss_load_value(cur, p, ts);
         unshift(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
         if (has_pol && ts.n_tok > 0) {
@@ -601,20 +643,14 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         pol_acc += (double)pol_t;
         val_acc += (double)val_t;
         ratio_acc += (double)ratio_t;
+        if (kFew) break;                                           // (a frame to a workgroup)
     }
-    if (gridDim.x == 1 && !out && !stats) return;
+    if (!out && !stats) return;                                    // (nobody asks for the sums)
     double tot[kGradSums] = {pol_acc, val_acc, ratio_acc, (double)pol_clipped, (double)val_clipped};
+    if (tid == 0) s_flag = 1;
     block_sums(tot, s_red);
-    bool ok = true;
-    if (gridDim.x > 1) {
-        unsigned long long* mine = pl.finish_words + (int64_t)blockIdx.x * kFinishWords;
-#pragma unroll
-        for (int q = 0; q < kGradSums; ++q)
-            if (tid == q) publish(mine + 2 * q, p.tag, tot[q]);
-        if (blockIdx.x != gridDim.x - 1 || (!out && !stats)) return;
-        ok = collect_sums<kGradSums, 2>(pl.finish_words, p.tag, (int)gridDim.x, tot, s_red, &s_flag);
-    }
-    if (tid == 0) {
+    if (finish_sums<kGradSums, 2>(pl.finish_words, p.tag, tot, s_red, s_fin, &s_flag)) {
+        const bool ok = s_flag != 0;
         if (!ok) {
             set_status(p.status, TPPO_STATUS_TIMEOUT);
 #pragma unroll
@@ -638,7 +674,8 @@ template <bool kGrad>
 __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int32_t* __restrict__ resp_off,
                                                         tppo_loss_out* __restrict__ out,
                                                         tppo_loss_stats* __restrict__ stats) {
-    __shared__ double s_red[kGradSums * 256 / kWave];
+    constexpr int kWaves = 256 / kWave;
+    __shared__ double s_cnt[2 * kWaves], s_red[kGradSums * kWaves];
     const LossParams& p = gp.fwd;
     const bool has_pol = p.logp_new != nullptr, has_val = p.v_new != nullptr;
     const int tid = threadIdx.x;
@@ -648,9 +685,9 @@ __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int
         if (has_pol) cnt_p += (double)min(max(p.keep_len[i], 0), win);
         if (has_val && p.done[i] != 0) cnt_v += (double)win;
     }
-    double cnt[2] = {cnt_p, cnt_v};
-    block_sums(cnt, s_red);
-    const long long np = (long long)cnt[0], nv = (long long)cnt[1];
+    const double cnt[2] = {cnt_p, cnt_v};
+    block_sums(cnt, s_cnt);
+    const long long np = (long long)block_sum<2, kWaves>(s_cnt, 0), nv = (long long)block_sum<2, kWaves>(s_cnt, 1);
     const long long den_p = gp.policy_denominator > 0 ? gp.policy_denominator : np;
     const long long den_v = gp.value_denominator > 0 ? gp.value_denominator : nv;
     const float pol_coef = den_p > 0 ? -gp.policy_scale / (float)den_p : 0.f;
@@ -688,9 +725,11 @@ __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int
             }
         }
     }
-    double (&tot)[kGradSums] = sums;
-    block_sums(tot, s_red);
+    block_sums(sums, s_red);
     if (tid == 0) {
+        double tot[kGradSums];
+#pragma unroll
+        for (int q = 0; q < kGradSums; ++q) tot[q] = block_sum<kGradSums, kWaves>(s_red, q);
         if (out) write_losses(out, tot[0], tot[1], np, nv);
         if (stats) {
             stats->ratio_mean = np > 0 ? (float)(tot[2] / (double)np) : 0.f;
@@ -724,6 +763,9 @@ static int loss_groups(int64_t n_resp, bool grad) {
 // after each, 8.0 (8.9) / 11.3 (12.1).
 // (A workgroup fetches a sequence and has four tokens for each of its threads.)
 static bool loss_fetches(int64_t B, int64_t n_resp) { return 4 * B < n_resp; }
+
+// a grid of few workgroups, a frame each
+static bool loss_few(int groups, int64_t n_resp) { return groups <= kFewGroups && n_resp <= (int64_t)groups * 4 * kLossThreads; }
 
 // checks shared by the forward and the backward entry point; on TPPO_OK `plan` points at a plan of this layout
 static int loss_prepare(int n_pol_ptr, int n_val_ptr, const int32_t* resp_off, const int32_t* keep_len,
@@ -762,6 +804,7 @@ static void fill_params(LossParams& p, const float* logp_new, const float* logp_
     p.tag = next_call_tag();
     p.ratio_lo = 1.f - eps_low; p.ratio_hi = 1.f + eps_high;
     p.xi_low = xi_low; p.xi_high = xi_high;
+    p.all_ahead = B <= kLossThreads;
 }
 
 }  // namespace tppo
@@ -801,8 +844,9 @@ extern "C" int tppo_ppo_losses(const float* logp_new, const float* logp_old, con
     LossParams p;
     fill_params(p, logp_new, logp_old, adv, v_new, v_old, ret, resp_off, keep_len, done, plan, status, B, n_resp, eps_low,
                 eps_high, xi_low, xi_high);
-    hipLaunchKernelGGL(loss_fetches(B, n_resp) ? loss_kernel<true> : loss_kernel<false>, dim3(loss_groups(n_resp, false)),
-                       dim3(kLossThreads), 0, s, p, out);
+    const int groups = loss_groups(n_resp, false);
+    hipLaunchKernelGGL((!loss_fetches(B, n_resp) ? loss_kernel<false, false> : loss_few(groups, n_resp) ? loss_kernel<true, true> : loss_kernel<true, false>),
+                       dim3(groups), dim3(kLossThreads), 0, s, p, out);
     return launch_result();
 }
 
@@ -845,7 +889,8 @@ extern "C" int tppo_ppo_losses_backward(const float* logp_new, const float* logp
         hipLaunchKernelGGL(loss_tiny_kernel<true>, dim3(1), dim3(256), 0, s, gp, resp_off, out, stats);
         return launch_result();
     }
-    hipLaunchKernelGGL(loss_fetches(B, n_resp) ? loss_grad_kernel<true> : loss_grad_kernel<false>, dim3(loss_groups(n_resp, true)),
-                       dim3(kLossThreads), 0, s, gp, out, stats);
+    const int groups = loss_groups(n_resp, true);
+    hipLaunchKernelGGL((!loss_fetches(B, n_resp) ? loss_grad_kernel<false, false> : loss_few(groups, n_resp) ? loss_grad_kernel<true, true> : loss_grad_kernel<true, false>),
+                       dim3(groups), dim3(kLossThreads), 0, s, gp, out, stats);
     return launch_result();
 }
