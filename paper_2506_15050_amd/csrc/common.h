@@ -71,6 +71,17 @@ __device__ __forceinline__ T wave_prefix(T x) {
     return x;
 }
 
+// the largest of non-negative numbers, the same in every lane
+__device__ __forceinline__ int wave_max(int x) {
+    x = max(x, dpp_move<kRowShr1, 0xF>(x));
+    x = max(x, dpp_move<kRowShr2, 0xF>(x));
+    x = max(x, dpp_move<kRowShr4, 0xF>(x));
+    x = max(x, dpp_move<kRowShr8, 0xF>(x));
+    x = max(x, dpp_move<kRowBcast15, 0xA>(x));
+    x = max(x, dpp_move<kRowBcast31, 0xC>(x));
+    return __builtin_amdgcn_readlane(x, kWave - 1);
+}
+
 // largest s in [lo, hi] with off[s] <= p  (off non-decreasing, off[lo] <= p)
 __device__ __forceinline__ int find_segment(const int32_t* off, int lo, int hi, int p) {
     while (lo < hi) {

@@ -28,12 +28,6 @@ __host__ __device__ __forceinline__ int window_tiles(int lo, int len) {
     return len > 0 ? ((lo + len - 1) / kTileTokens) - (lo / kTileTokens) + 1 : 0;
 }
 
-__device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) x = max(x, __shfl_xor(x, off));
-    return __builtin_amdgcn_readfirstlane(x);
-}
-
 // The sequence that follows [lo, end) inside the frame that holds its last token, if that frame is the sequence's to
 // describe (it begins there) and goes on: skipping at most kSkipEmpty empty ones; beyond that the consumers
 // look for themselves.  Looked up once per sequence, before its tiles are written: inside the loop over the tiles
@@ -104,9 +98,10 @@ struct BuildLds {
     int count[3][kBuildWaves][kLevels + 1];
     int sum[2][kLevels + 1];
     int first[kLevels + 1];                                // list position of the range's first tile of a level
-    int total, levels;                                     // (levels: build_list_by_level's, how many there are)
+    int total;
 };
 static_assert(kLevels < kWave, "one lane per level and one for the tiles beyond");
+static_assert(kBuildWaves == 16, "a row of 16 lanes holds a level's groups");
 
 template <class Ints>
 __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints resp_off, Ints keep_len, Ints done, bool sets,
@@ -125,9 +120,7 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
             counter += lane == l ? c : 0;
         }
         if (deepest > kLevels) {                                    // tiles beyond the sorted levels
-            int extra = max(tiles - kLevels, 0);
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) extra += __shfl_xor(extra, off);
+            const int extra = __builtin_amdgcn_readlane(wave_prefix(max(tiles - kLevels, 0)), kWave - 1);
             counter += lane == kLevels ? extra : 0;
         }
     };
@@ -176,12 +169,7 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
     __syncthreads();
     if (tid < kWave) {                                              // where each level starts for this range
         const int mine = tid <= kLevels ? s.sum[0][tid] : 0;
-        int inc = mine;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int y = __shfl_up(inc, off);
-            if (lane >= off) inc += y;
-        }
+        const int inc = wave_prefix(mine);
         if (tid <= kLevels) s.first[tid] = inc - mine + s.sum[1][tid];
         if (tid == kLevels) s.total = inc;
     }
@@ -215,12 +203,7 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
         }
         if (deepest > kLevels) {                                    // a sequence's deeper tiles stay together
             const int extra = max(tiles - kLevels, 0);
-            int inc = extra;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int y = __shfl_up(inc, off);
-                if (lane >= off) inc += y;
-            }
+            const int inc = wave_prefix(extra);
             int at = __builtin_amdgcn_readlane(at_level, kLevels) + inc - extra;
             for (int l = kLevels; l < tiles; ++l, ++at) {
                 if (at < cap) {
@@ -229,7 +212,7 @@ __device__ __forceinline__ void build_list(const Plan& pl, BuildLds& s, Ints res
                     note_frame(pl, d, lo, len, sets, keep, fin, next);
                 }
             }
-            const int total = __shfl(inc, kWave - 1);
+            const int total = __builtin_amdgcn_readlane(inc, kWave - 1);
             at_level += lane == kLevels ? total : 0;
         }
     }
@@ -271,41 +254,32 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
             counter = lane == l ? c : counter;
         }
         if (deepest > kLevels) {                                    // tiles beyond the sorted levels
-            int extra = max(tiles - kLevels, 0);
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) extra += __shfl_xor(extra, off);
+            const int extra = __builtin_amdgcn_readlane(wave_prefix(max(tiles - kLevels, 0)), kWave - 1);
             counter = lane == kLevels ? extra : counter;
         }
     }
     if (lane <= kLevels) s.count[0][wave][lane] = counter;
     __syncthreads();
-    if (wave == 0) {                                                // where each group's tiles of a level begin
-        int mine = 0;
-        if (lane < kLevels)
-            for (int g = 0; g < groups; ++g) mine += s.count[0][g][lane];
+    // Where each group's tiles of a level begin: 16 lanes a level for the groups, then every wavefront for itself the levels'
+    // beginnings, lane l's in `level_at`.  (One wavefront going through the groups for all took half a microsecond more.)
+    for (int l = tid / kBuildWaves; l <= kLevels; l += kBuildThreads / kBuildWaves) {
+        const int g = tid % kBuildWaves, mine = s.count[0][g][l];
         int inc = mine;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int y = __shfl_up(inc, off);
-            if (lane >= off) inc += y;
-        }
-        if (lane <= kLevels) {
-            int at = inc - mine;
-            for (int g = 0; g < groups; ++g) {
-                s.count[1][g][lane] = at;
-                at += s.count[0][g][lane];
-            }
-            if (lane == kLevels) s.total = at;
-        }
-        const int levels = __popcll(__ballot(mine > 0));
-        if (lane == 0) s.levels = levels;
+        inc += dpp_move<kRowShr1, 0xF>(inc);
+        inc += dpp_move<kRowShr2, 0xF>(inc);
+        inc += dpp_move<kRowShr4, 0xF>(inc);
+        inc += dpp_move<kRowShr8, 0xF>(inc);
+        s.count[1][g][l] = inc - mine;
+        if (g == kBuildWaves - 1) s.sum[0][l] = inc;
     }
     __syncthreads();
-    for (int task = part * kBuildWaves + wave, n = s.levels * groups; task < n; task += parts * kBuildWaves) {
+    const int of_level = lane <= kLevels ? s.sum[0][lane] : 0, up_to = wave_prefix(of_level), level_at = up_to - of_level;
+    const int levels = __popcll(__ballot(lane < kLevels && of_level > 0)), total = __builtin_amdgcn_readlane(up_to, kWave - 1);
+    for (int task = part * kBuildWaves + wave, n = levels * groups; task < n; task += parts * kBuildWaves) {
         const int l = task / groups, g = task - l * groups;
         if (s.count[0][g][l] == 0) continue;                        // (uniform)
         const int i = g * kWave + lane, tiles = tiles_at(i, nullptr);
-        const int at = s.count[1][g][l] + __popcll(__ballot(tiles > l) & below);
+        const int at = __builtin_amdgcn_readlane(level_at, l) + s.count[1][g][l] + __popcll(__ballot(tiles > l) & below);
         if (tiles > l && at < cap) {                                // (invalid offsets cannot overflow the list)
             const Tile d = make_tile(i, lo, len, tiles, l);
             pl.tiles[at] = d;
@@ -316,13 +290,7 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
     }
     if (deepest > kLevels && part == parts - 1) {                       // a sequence's deeper tiles stay together
         const int i = wave * kWave + lane, tiles = tiles_at(i, nullptr), extra = max(tiles - kLevels, 0);
-        int inc = extra;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int y = __shfl_up(inc, off);
-            if (lane >= off) inc += y;
-        }
-        const int begin = s.count[1][wave][kLevels] + inc - extra;
+        const int begin = __builtin_amdgcn_readlane(level_at, kLevels) + s.count[1][wave][kLevels] + wave_prefix(extra) - extra;
         for (unsigned long long todo = __ballot(extra > 0); todo != 0; todo &= todo - 1) {
             const int j = __ffsll(todo) - 1, seq = wave * kWave + j, n = __shfl(tiles, j), from = __shfl(begin, j);
             const int seq_lo = __shfl(lo, j), seq_len = __shfl(len, j);
@@ -337,8 +305,8 @@ __device__ __forceinline__ void build_list_by_level(const Plan& pl, BuildLds& s,
         }
     }
     if (part == parts - 1 && tid == 0) {
-        if (s.total > cap) set_status(status, TPPO_STATUS_BAD_LAYOUT);
-        pl.hdr->n_tiles = min(s.total, cap);
+        if (total > cap) set_status(status, TPPO_STATUS_BAD_LAYOUT);
+        pl.hdr->n_tiles = min(total, cap);
         pl.hdr->B = B;
         pl.hdr->n_resp = n_resp;
         pl.hdr->cap = cap;

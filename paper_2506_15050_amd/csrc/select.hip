@@ -12,7 +12,10 @@
 //            one sequence each); then the plan's builders and the workgroups that
 //            walk the tile list, side by side.
 // Launches and the chains of dependent loads inside them are what this costs; only beyond some ten million tokens do
-// the bytes written count.  Scan, plan and fill as three launches against now, in a pass over
+// the bytes written count.  Prefix sums go by data-parallel moves, a wavefront's totals by a lane each, and the one launch holds to 80
+// scalar registers, which is what two workgroups to a CU have room for: through shuffles, a loop over the wavefronts and 96 registers (the
+// second half of 512 workgroups began when the first had ended) the filter took, us: 126 tokens in 3 sequences 4.9 (now 3.6), 49 K in 100 5.2
+// (4.1), 571 K in 1000 6.4 (5.1), 2.3 M in 512 11.5 (7.5), 872 K in 1500 13.3 (9.9).  Scan, plan and fill as three launches against now, in a pass over
 // 2.4 M tokens in 512 sequences: 29 -> 11 us; 40 M tokens in 8704 sequences: 111 -> 62 us (278 MB of indices).
 #include "plan_build.h"
 
@@ -26,9 +29,15 @@ constexpr int kOneLaunchSeqs = kScanThreads;
 // 8.2 / 7.0 / 12.4, so 7.8 / 6.5 / 12.0; one by one 9.5 / 6.7 / 12.1.
 constexpr int kScanAhead = 8;
 constexpr int kListParts = 8;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
-constexpr int kQuarter = kBuildThreads / 4;                      // threads that share a tile of the compact list
+constexpr int kQuarter = kTileTokens / 4;                        // threads that share a tile of the compact list, four tokens each
 constexpr int kFillMaxGroups = 512;                             // two per CU
+// Those of the second launch that walk the compact tile list, four tiles a turn.  512 of them, one turn 8 MB on from the last, are slower
+// than fewer or more; the whole filter, us, 256 / 320 / 384 / 448 / 512 / 768 / 1024: 40 M tokens in 8704 sequences 61.1 / 57.2 / 54.9 / 55.2 /
+// 61.9 / 56.1 / 54.3, 14 M in 3000 31.2 / 30.0 / 29.6 / 30.0 / 31.3 / 29.6 / 30.0.  Four consecutive tokens a thread, 16-byte stores: 53.3 and 29.6 with
+// 384 (non-temporal ones: 82.9, 34.7).
+constexpr int kWalkGroups = 384;
 static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");
+static_assert(4 * kQuarter == kBuildThreads, "a workgroup of the second launch walks four tiles at a time");
 
 struct Sums { int win, keep, val, tiles; };     // window / kept / value tokens, tiles of the compact output
 
@@ -36,13 +45,15 @@ __device__ __forceinline__ Sums add4(Sums a, Sums b) {
     return {a.win + b.win, a.keep + b.keep, a.val + b.val, a.tiles + b.tiles};
 }
 
-__device__ __forceinline__ Sums shfl_up4(Sums a, int off) {
-    return {__shfl_up(a.win, off), __shfl_up(a.keep, off), __shfl_up(a.val, off), __shfl_up(a.tiles, off)};
+__device__ __forceinline__ Sums prefix4(Sums a) {
+    return {wave_prefix(a.win), wave_prefix(a.keep), wave_prefix(a.val), wave_prefix(a.tiles)};
 }
 
-__device__ __forceinline__ Sums shfl_xor4(Sums a, int off) {
-    return {__shfl_xor(a.win, off), __shfl_xor(a.keep, off), __shfl_xor(a.val, off), __shfl_xor(a.tiles, off)};
+__device__ __forceinline__ Sums lane_of(Sums a, int lane) {
+    return {__builtin_amdgcn_readlane(a.win, lane), __builtin_amdgcn_readlane(a.keep, lane), __builtin_amdgcn_readlane(a.val, lane),
+            __builtin_amdgcn_readlane(a.tiles, lane)};
 }
+__device__ __forceinline__ Sums lane63(Sums a) { return lane_of(a, kWave - 1); }
 
 static inline int64_t select_max_tiles(int64_t capacity, int64_t B) { return capacity / kTileTokens + B + 1; }
 
@@ -97,24 +108,20 @@ __global__ __launch_bounds__(kScanThreads) void select_scan_kernel(
     }
     for (int i = i_begin; i < i_end; ++i)
         mine = add4(mine, lengths_of(i == i_begin ? first : words_of(cu_seqlens, ctx_len, done, i), n_tok, tail_drop, status));
-    Sums inc = mine;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const Sums y = shfl_up4(inc, off);
-        if (lane >= off) inc = add4(inc, y);
-        ahead = add4(ahead, shfl_xor4(ahead, off));
+    const Sums inc = prefix4(mine), before = prefix4(ahead);
+    if (lane == kWave - 1) {
+        wave_tot[0][wave] = inc;
+        wave_tot[1][wave] = before;
     }
-    if (lane == kWave - 1) wave_tot[0][wave] = inc;
-    if (lane == 0) wave_tot[1][wave] = ahead;
     __syncthreads();
+    // the wavefronts' totals, a lane each: what comes before my wavefront, and all there is
+    constexpr int kWaves = kScanThreads / kWave;
+    const Sums none = {0, 0, 0, 0};
+    const Sums wave_inc = prefix4(lane < kWaves ? wave_tot[0][lane] : none), all_before = lane63(prefix4(lane < kWaves ? wave_tot[1][lane] : none));
+    const Sums total = add4(lane63(wave_inc), all_before);
     Sums run = {inc.win - mine.win, inc.keep - mine.keep, inc.val - mine.val, inc.tiles - mine.tiles};
-    Sums total = {0, 0, 0, 0};
-#pragma unroll 4
-    for (int w = 0; w < kScanThreads / kWave; ++w) {
-        if (w < wave) run = add4(run, wave_tot[0][w]);
-        run = add4(run, wave_tot[1][w]);
-        total = add4(total, add4(wave_tot[0][w], wave_tot[1][w]));
-    }
+    run = add4(run, all_before);
+    if (wave > 0) run = add4(run, lane_of(wave_inc, wave - 1));
     if (part == 0 && tid == 0) {
         resp_off[0] = 0;
         sel_off[0] = 0;
@@ -142,6 +149,30 @@ struct FillArgs {
     int n_tok;
     int32_t* status;
 };
+
+// (any `m`: 4-byte alignment will do)
+typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_some(int32_t* dst, int64_t m, const int (&x)[4], int n) {
+    if (n == 4) {
+        *reinterpret_cast<int4u*>(dst + m) = int4u{x[0], x[1], x[2], x[3]};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < n) dst[m + e] = x[e];
+    }
+}
+
+// the ids at four packed positions, the first `some` of them wanted; run: one after the other
+__device__ __forceinline__ void load_ids(const FillArgs& a, const int (&pos)[4], bool run, int some, int (&id)[4]) {
+    if (run && pos[0] >= 0 && pos[0] <= a.n_tok - 4) {
+        const int4u x = *reinterpret_cast<const int4u*>(a.input_ids + pos[0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) id[e] = x[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) id[e] = (e < some && pos[e] >= 0 && pos[e] < a.n_tok) ? a.input_ids[pos[e]] : -1;
+    }
+}
 
 // Second launch of the large case.  Workgroups 0 .. parts-1 build the plan's list and workgroup `parts` counts its
 // sets (none of these without a plan); the others zero the plan's words and walk the compact tile list, four
@@ -176,41 +207,26 @@ __global__ __launch_bounds__(kBuildThreads) void select_fill_kernel(FillArgs a, 
     const int quarter = threadIdx.x / kQuarter, tid = threadIdx.x % kQuarter;
     for (int w = worker * 4 + quarter; w < count; w += workers * 4) {
         const Tile t = tiles[w];
-        const int i = t.seg, len = t.len(), t0 = t.number() * kTileTokens;
-        const int first_pos = a.cu_seqlens[i] + a.ctx_len[i] + t0;  // packed position of the tile's first token
-        const int first_resp = resp_off[i] + t0;
-#pragma unroll
-        for (int q = 0; q < kTileTokens / kQuarter; ++q) {
-            const int k = q * kQuarter + tid;                        // lane-consecutive: coalesced stores
-            const int64_t m = (int64_t)t.start + k;
-            if (k < len) {
-                if (m >= a.capacity) {
-                    if (m == a.capacity) set_status(a.status, TPPO_STATUS_CAPACITY);
-                } else {
-                    const int pos = first_pos + k;
-                    if (a.sel_rows) a.sel_rows[m] = pos - 1;
-                    if (a.sel_targets) a.sel_targets[m] = (pos >= 0 && pos < a.n_tok) ? a.input_ids[pos] : -1;
-                    if (a.sel_resp_idx) a.sel_resp_idx[m] = first_resp + k;
-                }
-            }
+        const int i = t.seg, t0 = t.number() * kTileTokens, k = 4 * tid;
+        const int64_t m = (int64_t)t.start + k;
+        const int n = min(t.len() - k, 4), some = (int)max(min((int64_t)n, a.capacity - m), (int64_t)0);
+        if (n <= 0) continue;
+        if (some < n && m + some == a.capacity) set_status(a.status, TPPO_STATUS_CAPACITY);
+        const int pos = a.cu_seqlens[i] + a.ctx_len[i] + t0 + k;     // packed position of the first of the four
+        const int resp = resp_off[i] + t0 + k;
+        if (a.sel_rows) store_some(a.sel_rows, m, {pos - 1, pos, pos + 1, pos + 2}, some);
+        if (a.sel_targets) {
+            int id[4];
+            load_ids(a, {pos, pos + 1, pos + 2, pos + 3}, true, some, id);
+            store_some(a.sel_targets, m, id, some);
         }
+        if (a.sel_resp_idx) store_some(a.sel_resp_idx, m, {resp, resp + 1, resp + 2, resp + 3}, some);
     }
 }
 
 // The whole filter in one launch, B <= kOneLaunchSeqs.  Workgroups 0 .. parts - 1 write the plan's list, the first of them also
 // the small outputs; the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
 // sequence a thread finds by bisection of the offsets in LDS.
-typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void store_some(int32_t* dst, int64_t m, const int (&x)[4], int n) {
-    if (n == 4) {
-        *reinterpret_cast<int4u*>(dst + m) = int4u{x[0], x[1], x[2], x[3]};
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < n) dst[m + e] = x[e];
-    }
-}
-
 __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillArgs a, const int32_t* __restrict__ done, int B,
                                                                           int tail_drop, int32_t* __restrict__ resp_off,
                                                                           int32_t* __restrict__ sel_off,
@@ -218,7 +234,7 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
                                                                           int64_t* __restrict__ counts, int parts, int plan_cap,
                                                                           void* plan_raw) {
     __shared__ int32_t s_resp[kOneLaunchSeqs + 1], s_sel[kOneLaunchSeqs + 1], s_aux[2][kOneLaunchSeqs];
-    __shared__ int s_wave[2][kBuildWaves], s_val[kBuildWaves];
+    __shared__ int s_wave[3][kBuildWaves];
     __shared__ BuildLds s_build;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool lead = (int)blockIdx.x < parts, first = blockIdx.x == 0;
@@ -233,31 +249,28 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
     }
     const Plan pl = plan_view(plan_raw, plan_cap);
     if (plan_raw && !lead) clear_words(pl, worker, workers);         // (while the lengths are on their way)
-    int win = mine.win, keep = mine.keep, val = mine.val;            // inclusive prefix sums (val: only the total matters)
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int w = __shfl_up(win, off), k = __shfl_up(keep, off);
-        if (lane >= off) {
-            win += w;
-            keep += k;
-        }
-        val += __shfl_xor(val, off);
-    }
+    int win = wave_prefix(mine.win), keep = wave_prefix(mine.keep);  // inclusive prefix sums
+    const int val = wave_prefix(mine.val);
     if (lane == kWave - 1) {
         s_wave[0][wave] = win;
         s_wave[1][wave] = keep;
-        s_val[wave] = val;
+        s_wave[2][wave] = val;
     }
     __syncthreads();
-    for (int w = 0; w < wave; ++w) {
-        win += s_wave[0][w];
-        keep += s_wave[1][w];
+    // the wavefronts' totals, a lane each, and what comes before mine
+    const int at = min(lane, kBuildWaves - 1);
+    const int wins = wave_prefix(s_wave[0][at]), keeps = wave_prefix(s_wave[1][at]);
+    if (wave > 0) {
+        win += __builtin_amdgcn_readlane(wins, wave - 1);
+        keep += __builtin_amdgcn_readlane(keeps, wave - 1);
     }
     if (tid == 0) s_resp[0] = s_sel[0] = 0;
-    s_resp[tid + 1] = win;
-    s_sel[tid + 1] = keep;
-    s_aux[0][tid] = lead ? mine.keep : first_pos;
-    s_aux[1][tid] = fin;
+    if (tid < B) {
+        s_resp[tid + 1] = win;
+        s_sel[tid + 1] = keep;
+        s_aux[0][tid] = lead ? mine.keep : first_pos;
+        s_aux[1][tid] = fin;
+    }
     __syncthreads();
     const int n_kept = s_sel[B];
     if (lead) {
@@ -270,7 +283,8 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
             resp_off[0] = 0;
             sel_off[0] = 0;
             long long n_val = 0;
-            for (int w = 0; w < kBuildWaves; ++w) n_val += s_val[w];
+#pragma unroll
+            for (int w = 0; w < kBuildWaves; ++w) n_val += s_wave[2][w];
             counts[0] = n_kept;
             counts[1] = s_resp[B];
             counts[2] = n_val;
@@ -316,14 +330,7 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
             }
         }
         if (a.sel_targets) {
-            if (run && pos[0] >= 0 && pos[0] <= a.n_tok - 4) {
-                const int4u x = *reinterpret_cast<const int4u*>(a.input_ids + pos[0]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) id[e] = x[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) id[e] = (e < some && pos[e] >= 0 && pos[e] < a.n_tok) ? a.input_ids[pos[e]] : -1;
-            }
+            load_ids(a, pos, run, some, id);
             store_some(a.sel_targets, m, id, some);
         }
 #pragma unroll
@@ -390,7 +397,7 @@ extern "C" int tppo_select(const int32_t* cu_seqlens, const int32_t* ctx_len, co
     int32_t* n_tiles = want_fill ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) +
                                                               round_up((size_t)cap64 * sizeof(Tile), 256))
                                  : nullptr;
-    const int parts = build_parts(B), workers = (int)(most < kFillMaxGroups ? most : kFillMaxGroups);
+    const int parts = build_parts(B), workers = (int)(most < kWalkGroups ? most : kWalkGroups);
     hipLaunchKernelGGL(select_scan_kernel, dim3(parts), dim3(kScanThreads), 0, s, cu_seqlens, ctx_len,
                        done, (int)B, (int)n_tok, (int)tail_drop, parts, resp_off, sel_off, keep_len, counts,
                        tiles, (int)cap64, n_tiles, status);
