@@ -12,11 +12,11 @@
 //            one sequence each); then the plan's builders and the workgroups that
 //            walk the tile list, side by side.
 // Launches and the chains of dependent loads inside them are what this costs; only beyond some ten million tokens do
-// the bytes written count.  Prefix sums go by data-parallel moves, a wavefront's totals by a lane each, and the one launch holds to 80
-// scalar registers, which is what two workgroups to a CU have room for: through shuffles, a loop over the wavefronts and 96 registers (the
-// second half of 512 workgroups began when the first had ended) the filter took, us: 126 tokens in 3 sequences 4.9 (now 3.6), 49 K in 100 5.2
-// (4.1), 571 K in 1000 6.4 (5.1), 2.3 M in 512 11.5 (7.5), 872 K in 1500 13.3 (9.9).  Scan, plan and fill as three launches against now, in a pass over
-// 2.4 M tokens in 512 sequences: 29 -> 11 us; 40 M tokens in 8704 sequences: 111 -> 62 us (278 MB of indices).
+// the bytes written count.  Prefix sums go by data-parallel moves, a wavefront's totals by a lane each, and two workgroups of the one
+// launch fit a CU: through shuffles and a loop over the wavefronts, one workgroup to a CU (the second half of 512 began when the first
+// had ended) the filter took, us: 126 tokens in 3 sequences 4.9 (now 3.6), 49 K in 100 5.2 (4.1), 571 K in 1000 6.4 (5.1), 2.3 M in 512
+// 11.5 (7.5), 872 K in 1500 13.3 (9.9).  Scan, plan and fill as three launches, 2.4 M tokens in 512 sequences: 29 us (7.5); 40 M
+// tokens in 8704 sequences: 111 (53, 278 MB of indices).
 #include "plan_build.h"
 
 namespace tppo {
@@ -36,6 +36,10 @@ constexpr int kFillMaxGroups = 512;                             // two per CU
 // 61.9 / 56.1 / 54.3, 14 M in 3000 31.2 / 30.0 / 29.6 / 30.0 / 31.3 / 29.6 / 30.0.  Four consecutive tokens a thread, 16-byte stores: 53.3 and 29.6 with
 // 384 (non-temporal ones: 82.9, 34.7).
 constexpr int kWalkGroups = 384;
+// The one launch's workers: beyond kManyTurns turns of all of them a workgroup to each CU stores faster than two, the whole filter, us,
+// two -> one: 18 M tokens in 400 sequences 30.7 -> 26.2, in 1024 30.8 -> 29.2;  37 M in 800 60.2 -> 52.5;  8.2 M 16.7 (16.8);  7.5 M 15.7 (16.5);  2.3 M
+// 7.5 (9.4).  (In turns of their own, 4 MB apart, 256 workgroups take 31.5, 34.5 and 62.9; each its own range 26.6, 29.6 and 62.2.)
+constexpr int kManyTurns = 5, kManyGroups = 256;
 static_assert(kScanThreads == kBuildThreads, "the same workgroups scan and build");
 static_assert(4 * kQuarter == kBuildThreads, "a workgroup of the second launch walks four tiles at a time");
 
@@ -227,7 +231,8 @@ __global__ __launch_bounds__(kBuildThreads) void select_fill_kernel(FillArgs a, 
 // The whole filter in one launch, B <= kOneLaunchSeqs.  Workgroups 0 .. parts - 1 write the plan's list, the first of them also
 // the small outputs; the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
 // sequence a thread finds by bisection of the offsets in LDS.
-__global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillArgs a, const int32_t* __restrict__ done, int B,
+// (With 88 scalar registers, and the 16 that each wavefront has besides, a CU takes one workgroup: 2.3 M tokens 9.3 instead of 7.5.)
+__global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_num_sgpr(80))) void select_one_launch_kernel(FillArgs a, const int32_t* __restrict__ done, int B,
                                                                           int tail_drop, int32_t* __restrict__ resp_off,
                                                                           int32_t* __restrict__ sel_off,
                                                                           int32_t* __restrict__ keep_len,
@@ -303,7 +308,12 @@ __global__ __launch_bounds__(kBuildThreads) void select_one_launch_kernel(FillAr
     }
     if (!a.sel_rows && !a.sel_targets && !a.sel_resp_idx) return;
     const int64_t n = min((int64_t)n_kept, a.capacity);
-    for (int64_t m = ((int64_t)worker * kBuildThreads + tid) * 4; m < n; m += (int64_t)workers * kBuildThreads * 4) {
+    // Many turns are taken by a workgroup to a CU, the places of the others after its own (kManyTurns).
+    const int64_t turn = (int64_t)workers * kBuildThreads * 4;
+    const int active = n > kManyTurns * turn ? min(workers, kManyGroups) : workers;
+    if (worker >= active) return;
+    for (int place = worker; place < workers; place += active)
+    for (int64_t m = ((int64_t)place * kBuildThreads + tid) * 4; m < n; m += turn) {
         int lo = 0, hi = B - 1;                                      // the last sequence that begins at or before m
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
