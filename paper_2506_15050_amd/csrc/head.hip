@@ -280,7 +280,15 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
     const int64_t m_eff = m_actual ? min(M, *m_actual) : M;
     typedef MaxUnits<kLogitMax> Units;
     float mx = Units::kLeast, sum = 0.f, tz = 0.f;
+    // (what the end of the merge needs travels with the partials)
+    int64_t o = m, row = 0;
+    int tgt = 0;
     if (m < m_eff) {
+        if (sub == 0) {
+            if (out_index) o = out_index[m];
+            row = sel_rows[m];
+            tgt = sel_targets[m];
+        }
         const bool rest = m >= q.first_tokens;
         const float* part = rest ? q.rest + (m - q.first_tokens) : q.first + m;
         const int64_t stride = rest ? q.rest_stride : q.first_stride;
@@ -301,9 +309,6 @@ __global__ __launch_bounds__(kMergeTokens* kMergeLanes) void head_combine_kernel
     s_part[2][sub][tok] = tz;
     __syncthreads();
     if (sub != 0 || m >= m_eff) return;
-    const int64_t o = out_index ? (int64_t)out_index[m] : m;
-    const int64_t row = sel_rows[m];
-    const int tgt = sel_targets[m];
     const bool bad_row = row < 0 || row >= n_rows, bad_tgt = tgt < 0 || tgt >= V;
     if (bad_row || bad_tgt) {
         set_status(status, bad_row ? TPPO_STATUS_BAD_ROW : TPPO_STATUS_BAD_TARGET);
@@ -422,7 +427,10 @@ static int head_tiled(HeadParams& p, int64_t M, int64_t V, const int32_t* out_in
             rc = whole ? launch_sweep<HeadCfg<T, false, true>, LaneSoftmax>(p, ws, s)
                        : launch_sweep<HeadCfg<T, true, true>, LaneSoftmax>(p, ws, s);
     } else if constexpr (sizeof(T) == 2) {
-        rc = whole ? launch_sweep<Whole, LaneSoftmax>(p, ws, s) : launch_sweep<Ragged, LaneSoftmax>(p, ws, s);
+        typedef HeadCfg<T, false, false, 0, 4, false, true> Long;
+        rc = !whole                     ? launch_sweep<Ragged, LaneSoftmax>(p, ws, s)
+             : p.k_tiles >= kLongStages ? launch_sweep<Long, LaneSoftmax>(p, ws, s)
+                                        : launch_sweep<Whole, LaneSoftmax>(p, ws, s);
     }
     if (rc != TPPO_OK) return rc;
     const Partials q = {p.part_first, p.part_rest, first_tokens, first_tokens, rest_tokens, p.first.cols, p.rest.cols};

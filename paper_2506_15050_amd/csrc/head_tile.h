@@ -90,13 +90,21 @@ struct HeadParams {
 // last ones are waited for in vain where no third workgroup computes meanwhile.  fp32, us, late -> early, one workgroup to a CU:
 // 1600 tokens x V 32000, H 1024: 1184 -> 955;  4000 x 5000, H 2048: 939 -> 761;  two: 2064 x 45000, H 1024: 1647 -> 1604;  three: 2064 x
 // 32000: 1101 (1109);  3300 x 32000: 1788 (1807).
+// LONG (large tiles, sweeps of kLongStages and more): a task's set-up and its steps from tile to tile as they fit the K loop best.
+// Elsewhere they are lean: the parameters asked for anew by every task instead of kept over all, spilled lane by lane (params_again), the
+// rows of the token list all at once instead of one by one, a step to the next tile of W rows instead of every row's address.  us, LONG ->
+// lean:  5000 tokens x V 30000, H 64: 51.1 -> 48.2;  20000 x 10000, H 128: 85.0 -> 80.5;  13640 x 32000, H 1024: 665 -> 657;  8000 x 40000, H 2048:
+// 924 -> 918; narrow, 500 x 12000, H 1024: 27.4 -> 25.4;  900 x 5000, H 2048: 41.2 -> 39.2; ragged, 2516 x 50021, H 1000: 225.7 -> 222.9; but 6000 x
+// 50000, H 2560: 1163 -> 1167;  4000 x 50000, H 3584: 1067 -> 1072;  H 5120: 1523 -> 1535;  942 x 152064: 1227 -> 1235, where a set-up hardly counts
+// and the loop that the compiler makes of the rest, 8 bytes on from the other's place in a fetched line, does.
 // KMAJOR (bf16, large tiles): one operand lies in memory with K as the ROW index -- 1 the W-role one, 2 the token-role
 // one; element (row r, k) is at base[k * ld + r].  A stage of it is kBK rows of 512 bytes, K row k's 16-byte chunk c in
 // slot c ^ swz_k(k), and ds_read_b64_tr_b16 takes fragments out transposed: 16 lanes read 4 K rows x 16 columns, lane i
 // gets column i's four.  Two of them make the fragment one ds_read_b128 gives of the other layout.
-template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0, int TOKEN_BLOCKS = 4, bool FEW = false>
+constexpr int kLongStages = 36;
+template <typename T, bool RAGGED, bool SMALL = false, int KMAJOR = 0, int TOKEN_BLOCKS = 4, bool FEW = false, bool LONG = false>
 struct HeadCfg {
-    static constexpr bool kRagged = RAGGED, kSmall = SMALL;
+    static constexpr bool kRagged = RAGGED, kSmall = SMALL, kLong = LONG;
     static constexpr int kKMajor = KMAJOR;
     static constexpr bool kOneTile = KMAJOR != 0;      // products: a task is one output tile
     static constexpr int kEsz = sizeof(T), kPerChunk = 16 / kEsz;         // elements of a 16-byte chunk
@@ -255,9 +263,10 @@ __host__ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int
     if (x.rest) {
         g = p.rest;
         x.part = t - p.first_tasks;
-        chunk = x.part / p.rest_tasks;
-        id = p.rest_base + (x.part - chunk * p.rest_tasks);
+        id = p.rest_base + x.part;
         if (p.k_chunks > 1) {
+            chunk = x.part / p.rest_tasks;
+            id -= chunk * p.rest_tasks;
             x.k_begin = (int)((int64_t)all_k_tiles * chunk / p.k_chunks);
             x.k_tiles = (int)((int64_t)all_k_tiles * (chunk + 1) / p.k_chunks) - x.k_begin;
         }
@@ -266,16 +275,32 @@ __host__ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int
     const int height = min(kRowBlock, g.rows - block * kRowBlock);
     x.col = in_block / height;
     x.row = g.row0 + block * kRowBlock + in_block - x.col * height;
-    // Products, whose column is a tile, divide no 64-bit numbers, twice per task.  Backward calls, us: 64 tokens x V 2000, H 64: 25.6 ->
-    // 25.2;  225 x 11194, H 2304: 106.8 -> 105.9;  61 x 54900, H 1728: 190.8 -> 189.8;  185 x 46863, H 3520: 407 -> 405.
+    // Products, whose column is a tile, divide nothing more.  Backward calls, us, with the columns' division, twice per task -> without:
+    // 64 tokens x V 2000, H 64: 25.6 -> 25.2;  225 x 11194, H 2304: 106.8 -> 105.9;  61 x 54900, H 1728: 190.8 -> 189.8;  185 x 46863, H 3520: 407 -> 405.
     if (ONE_TILE) {
         x.v_begin = x.col * p.v_unit;
         x.v_end = min(p.V, x.v_begin + p.v_unit);
         return x;
     }
-    x.v_begin = (int)((int64_t)p.vocab_tiles * x.col / g.cols) * p.v_unit;
-    x.v_end = min(p.V, (int)((int64_t)p.vocab_tiles * (x.col + 1) / g.cols) * p.v_unit);
+    // vocab_tiles * col / cols and the same of col + 1, without 64-bit divisions: quotient and remainder of vocab_tiles by cols
+    const unsigned cols = g.cols, each = (unsigned)p.vocab_tiles / cols, over = (unsigned)p.vocab_tiles - each * cols;
+    const unsigned begin = over * x.col / cols, end = begin + (over * x.col - begin * cols + over >= cols);
+    x.v_begin = (int)(each * x.col + begin) * p.v_unit;
+    x.v_end = (int)min((int64_t)p.V, (int64_t)(each * (x.col + 1) + end) * p.v_unit);
     return x;
+}
+
+// The kernel's parameters where the launch left them, asked for anew: `HeadParams` has more words than there are scalar registers to keep
+// them in over the tasks, and what is kept is spilled lane by lane and read back at every use.
+__device__ __forceinline__ const HeadParams& params_again(const HeadParams& p) {
+#ifdef __HIP_DEVICE_COMPILE__
+    typedef const HeadParams __attribute__((address_space(4))) * Args;
+    Args at = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const HeadParams*)at;
+#else
+    return p;
+#endif
 }
 
 // Epi (the per-lane epilogue) provides
@@ -287,23 +312,24 @@ __host__ __device__ __forceinline__ Task task_at(const HeadParams& p, int t, int
 static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
 template <class C, template <class> class Epi>
-__global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void head_mfma_kernel(HeadParams p) {
+__global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void head_mfma_kernel(HeadParams args) {
     constexpr int kTileV = C::kTileV, kTileT = C::kTileT, kWaveV = C::kWaveV, kWaveT = C::kWaveT;
     constexpr int kVB = C::kVB, kTB = C::kTB;
     constexpr int kDmaPerWave = C::kDmaPerWave, kKSteps = C::kKSteps;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int64_t m_eff = p.m_actual ? min(p.M, *p.m_actual) : p.M;
+    const int64_t m_eff = args.m_actual ? min(args.M, *args.m_actual) : args.M;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wv = wave / C::kWavesT, wt = wave % C::kWavesT;
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     constexpr bool kPersistent = !C::kSmall && !C::kNarrow;
-    if (kPersistent && p.arrivals) arrive(p.arrivals, xcd, slot, 0);
-    const bool dealt = C::kSmall && Epi<C>::kDealt && p.rest.rows > 1;
+    if (kPersistent && args.arrivals) arrive(args.arrivals, xcd, slot, 0);
+    const bool dealt = C::kSmall && Epi<C>::kDealt && args.rest.rows > 1;
     const int t_first = dealt ? (int)blockIdx.x : xcd * ((int)gridDim.x >> 3) + slot, t_step = (int)gridDim.x;
-    for (int t = t_first; t < p.n_tasks; t += t_step) {
+    for (int t = t_first, n_tasks = args.n_tasks; t < n_tasks; t += t_step) {
+    const HeadParams& p = C::kLong ? args : params_again(args);
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));                           // a task's own: nothing derived from it is kept over the others
     const int lane = tid & 63, frag_row = lane % C::kMI, frag_grp = lane / C::kMI;
@@ -341,7 +367,22 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     unsigned issue_dst = dst_first;
     int64_t issue_kpos = k_first;
     int issue_left = p.km_rows - task.k_begin * C::kBK;                 // K rows from the stage to be issued on
+    auto token_of = [&](int q) {
+        const int64_t t = min(tok0 + (ld_row0 + q * C::kRowsPerDma - kTileV), m_eff - 1);
+        return t < 0 ? (int64_t)0 : t;                                 // (a W row's)
+    };
+    constexpr int kRowsPerWave = kDmaPerWave * C::kRowsPerDma;
+    auto is_w_row = [&](int q) {                                       // (the same for all lanes)
+        return !C::kLong && kTileV % kRowsPerWave == 0 ? wave < kTileV / kRowsPerWave : (wave * kDmaPerWave + q) * C::kRowsPerDma < kTileV;
+    };
     auto point_at_tile = [&](int v0, bool w_only) {
+        // The token rows that this wavefront stages, all of them asked for at once: one by one each is waited for before the next
+        // transfer's, eight trips to memory.
+        int listed[kDmaPerWave];
+        if (!C::kLong && C::kKMajor == 0 && p.sel_rows && !is_w_row(kDmaPerWave - 1)) {
+#pragma unroll
+            for (int q = 0; q < kDmaPerWave; ++q) listed[q] = p.sel_rows[token_of(q)];
+        }
 #pragma unroll
         for (int q = 0; q < kDmaPerWave; ++q) {
             if (C::kKMajor && k_major) {                                // (columns that do not exist: any others, never stored)
@@ -355,19 +396,34 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             }
             const int r = ld_row0 + q * C::kRowsPerDma;                 // staged row; < kTileV means a W row
             const int chunk = (ld_slot ^ C::swz(r)) * 16;
-            if ((wave * kDmaPerWave + q) * C::kRowsPerDma < kTileV) {      // (the same for all lanes)
+            if (is_w_row(q)) {
                 const int64_t v = min(v0 + r, v_end - 1);
                 src[q] = static_cast<const char*>(p.w) + v * ld_w + chunk;
             } else if (!w_only) {
-                const int64_t t = min(tok0 + (r - kTileV), m_eff - 1);
+                const int64_t t = C::kLong ? min(tok0 + (r - kTileV), m_eff - 1) : token_of(q);
                 if (C::kKMajor == 1) {
                     src[q] = static_cast<const char*>(p.hidden) + C::block_at(t, 0, p.ld_h) + chunk;
                     continue;
                 }
-                int64_t row = p.sel_rows ? (int64_t)p.sel_rows[t] : t;      // no list: rows in order
+                int64_t row = p.sel_rows ? (int64_t)(C::kLong ? p.sel_rows[t] : listed[q]) : t;      // no list: rows in order
                 row = min(max(row, (int64_t)0), p.n_rows - 1);
                 src[q] = static_cast<const char*>(p.hidden) + row * ld_h + chunk;
             }
+        }
+    };
+    // On to the next tile of W rows, the one from v0 on: the same step for all rows, but in a last tile with fewer of them, where what lies
+    // beyond is the last row again.  (Each row's address from its number takes three multiplications of 16 cycles.)
+    const int64_t w_step = (int64_t)kTileV * ld_w;
+    auto next_w_tile = [&](int v0) {
+        if (!is_w_row(0)) return;
+        if (v0 + kTileV <= v_end) {
+#pragma unroll
+            for (int q = 0; q < kDmaPerWave; ++q)
+                if (is_w_row(q)) src[q] += w_step;
+        } else {
+#pragma unroll
+            for (int q = 0; q < kDmaPerWave; ++q)
+                if (is_w_row(q)) src[q] += min(kTileV, v_end - 1 - v0 - (ld_row0 + q * C::kRowsPerDma) + kTileV) * ld_w;
         }
     };
     auto point_at_zeros = [&]() {       // a K-major operand's rows beyond the last K row, in a tile's last stage
@@ -411,7 +467,8 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
             issue_kt = 0;
             issue_kpos = k_first;
             issue_v += kTileV;
-            point_at_tile(issue_v, true);
+            if (C::kLong) point_at_tile(issue_v, true);
+            else next_w_tile(issue_v);
         }
         point_at_zeros();
         find_zeros();
@@ -602,7 +659,7 @@ __global__ __launch_bounds__(C::kThreads, C::kGroupsPerCu * C::kWaves / 4) void 
     if (C::kOneTile) epi.fold(acc, p, task, tok0, m_eff, v0, wv, wt, lane);
     if (kPrefetch) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));            // (this workgroup's LDS is somebody else's after its end)
     __syncthreads();                    // every fragment read is done before the stages are reused
-    epi.finish(p, reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
+    epi.finish(C::kLong ? args : params_again(args), reinterpret_cast<float*>(smem), task, tok0, m_eff, wv, wt, lane, tid);
     __syncthreads();                    // merge buffer is read before the next task's transfers land
     }
 }
