@@ -139,8 +139,10 @@ struct HeadCfg {
     static constexpr int kDmaPerWave = kDmaPerStage / kWaves;
     static constexpr int kKSteps = (kChunks / 4) * kVB;
     // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
-    // a full memory queue
-    static constexpr int kSpread = FEW ? 8 : SMALL ? kKSteps * kMfmaPerStep : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
+    // a full memory queue.  Small tiles, over 16 (all there are) / 14 / 12 / 10 / 8 of fp32's groups of four: 2064 tokens x V 32000, H 1024 1100 /
+    // 1095 / 1089 / 1109 / 1109 us;  6000 x 32000 3168 / 3144 / 3127 / 3183 / -;  2064 x 32000, H 256 290 / 290 / 289 / 294 / -: three workgroups cover
+    // for each other, but not for transfers that go out at a stage's end and are waited for there.  (Without transfers, 1024 us.)
+    static constexpr int kSpread = FEW ? 8 : SMALL ? 12 : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");
     static_assert(kKSteps % 2 == 0, "fragment double buffering assumes an even number of K steps");
