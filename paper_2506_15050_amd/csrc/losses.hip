@@ -328,21 +328,35 @@ __device__ __forceinline__ void loss_load_ahead(LossRegs& x, SeqMeta& all, const
     if (kFew && p.all_ahead) all = load_meta(p, tid);
 }
 
+// kFew: by one and by two places, a few selects, where the end of the array is somebody's last frame and everybody waits for it (us, one select
+// of four for each -> so: 126 tokens losses 5.0 -> 4.2, derivatives 6.2 -> 5.4;  49 K 6.2 -> 5.5, 7.8 -> 7.1).  The loops over many frames
+// are scheduled worse around it (40 M tokens, derivatives 165 -> 169) and keep the other.
+template <bool kFew>
 __device__ __forceinline__ float4u rotate_left(float4u t, int sh) {
     float4u o;
+    if constexpr (kFew) {
+        float4u by1;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        o[e] = sh == 0 ? t[e] : sh == 1 ? t[(e + 1) & 3] : sh == 2 ? t[(e + 2) & 3] : t[(e + 3) & 3];
+        for (int e = 0; e < 4; ++e) by1[e] = sh & 1 ? t[(e + 1) & 3] : t[e];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = sh & 2 ? by1[(e + 2) & 3] : by1[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            o[e] = sh == 0 ? t[e] : sh == 1 ? t[(e + 1) & 3] : sh == 2 ? t[(e + 2) & 3] : t[(e + 3) & 3];
+    }
     return o;
 }
 
 // the array's last few tokens were loaded as part of its last 16 bytes: move them into place (only in the last
 // frame, and there for at most one thread)
+template <bool kFew>
 __device__ __forceinline__ void unshift(LossRegs& x, const TokenSets& ts, int item, int n_resp) {
     if (__builtin_expect((item + 1) * (4 * kLossThreads) <= n_resp, 1)) return;   // wave-uniform: not the array's end
+    if (kFew && (n_resp & 3) == 0) return;                                        // ... or four by four up to it
     const int sh = ts.n_tok > 0 ? max(ts.first - (n_resp - 4), 0) : 0;
-    x.ln = rotate_left(x.ln, sh); x.lo = rotate_left(x.lo, sh); x.a = rotate_left(x.a, sh);
-    x.v = rotate_left(x.v, sh); x.vo = rotate_left(x.vo, sh); x.r = rotate_left(x.r, sh);
+    x.ln = rotate_left<kFew>(x.ln, sh); x.lo = rotate_left<kFew>(x.lo, sh); x.a = rotate_left<kFew>(x.a, sh);
+    x.v = rotate_left<kFew>(x.v, sh); x.vo = rotate_left<kFew>(x.vo, sh); x.r = rotate_left<kFew>(x.r, sh);
 }
 
 // A workgroup publishes kWords words: of each of kSums - kCounts sums two (a double as hi + lo), of each of the kCounts last ones, whole
@@ -487,7 +501,7 @@ __global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(Loss
             loss_load_policy(cur, p, ts);
             loss_load_value(cur, p, ts);
         }
-        unshift(cur, ts, f, p.n_resp);
+        unshift<kFew>(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f;                            // this thread's <= 8 terms of the frame
         if (ts.pol != 0) {
 #pragma unroll
@@ -603,7 +617,7 @@ __global__ __launch_bounds__(kLossThreads, 4) void loss_grad_kernel(GradParams g
         const TokenSets ts = token_sets<kFetch>(p, d, more, s_more[which], f, tid, has_pol, has_val, from);
         if (f != (int)blockIdx.x) loss_load_policy(cur, p, ts);
         if (!kFew) loss_load_value(cur, p, ts);
-        unshift(cur, ts, f, p.n_resp);
+        unshift<kFew>(cur, ts, f, p.n_resp);
         float pol_t = 0.f, val_t = 0.f, ratio_t = 0.f;
         if (has_pol && ts.n_tok > 0) {
             float gl[4] = {0.f, 0.f, 0.f, 0.f};
