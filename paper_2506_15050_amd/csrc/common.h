@@ -56,6 +56,10 @@ __device__ __forceinline__ int dpp_move(int x) {
     else return __builtin_amdgcn_update_dpp(0, x, kCtrl, kRowMask, 0xF, false);
 }
 template <int kCtrl, int kRowMask>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __int_as_float(dpp_move<kCtrl, kRowMask>(__float_as_int(x)));
+}
+template <int kCtrl, int kRowMask>
 __device__ __forceinline__ double dpp_move(double x) {
     return __hiloint2double(dpp_move<kCtrl, kRowMask>(__double2hiint(x)), dpp_move<kCtrl, kRowMask>(__double2loint(x)));
 }

@@ -20,7 +20,9 @@ typedef uint32_t vh_weights __attribute__((ext_vector_type(4), aligned(2)));   /
 // wavefront and no loop over groups: nothing waits for a workgroup's slowest row.
 // Measured, hidden states that no cache holds: 94639 rows of H = 5120, 140 us = 6.9 TB/s; of H = 1024, 30 us = 6.4; 20000 of H = 3584,
 // 24 us.  One row per wavefront, two plain loads in flight, the weights as fp32 in LDS and a persistent grid took
-// 221, 52 and 40 us; plain instead of non-temporal loads cost 14 %, one row per wavefront 13 % at H = 1024.
+// 221, 52 and 40 us; plain instead of non-temporal loads cost 14 %, one row per wavefront 13 % at H = 1024.  A row's sum over the lanes by
+// data-parallel moves instead of shuffles, rows in a cache: 4000 of H = 512 2.8 -> 2.6 us, 6000 of H = 2048 5.4 -> 5.1.  (One row a wavefront and
+// four steps in flight: 2000 of H = 5120 6.1 -> 5.6, 4000 of them 7.7 -> 8.6, of H = 512 2.6 -> 3.2.)
 template <int kRows>
 __global__ __launch_bounds__(kVhThreads) void value_head_kernel(
     const uint16_t* __restrict__ hidden, int64_t n_rows, int H, int64_t ld_h, const uint16_t* __restrict__ w,
@@ -66,10 +68,9 @@ __global__ __launch_bounds__(kVhThreads) void value_head_kernel(
     float total = 0.f;                                          // lane r: row r's sum
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
-        float s = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        total = lane == r ? s : total;
+        const float s = wave_prefix((acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]));
+        const float sum = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), kWave - 1));   // (by all lanes, whoever keeps it)
+        total = lane == r ? sum : total;
     }
     if (lane < kRows && t0 + lane < m_eff) {
         const int64_t o = out_index ? (int64_t)out_index[t0 + lane] : t0 + lane;
