@@ -402,11 +402,8 @@ __device__ __forceinline__ void tile_back(const TileIn& x, const TileMid& m, con
             carry_a = powi(p.sa.qtile, lane) * ba;
             carry_r = powi(p.sr.qtile, lane) * br;
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            carry_a += __shfl_xor(carry_a, off);
-            carry_r += __shfl_xor(carry_r, off);
-        }
+        carry_a = read_lane63(wave_prefix(carry_a));
+        carry_r = read_lane63(wave_prefix(carry_r));
         if (t.number() >= kWave) {                                  // I am some tile's 64th: a full tile, since after != 0
             double ta = 0.0, tr = 0.0;
 #pragma unroll
