@@ -1,10 +1,11 @@
 // Python side of the C ABI (tppo.h), native: turns a call's tensors into pointers, allocates its results, and calls.  The
 // smallest passes are bound by what happens here, once a call: through ctypes and torch's Python functions a token filter
-// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 12.6, 9.1, 4.2 and 4.0.
+// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 7.7, 8.5, 3.7 and 4.0.
 // What is taken and what is refused is what ctypes and the binding's own assertions take and refuse; sizes, ranges and NULLs are
 // the C entry points' own business.
 #include <Python.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <torch/csrc/Device.h>
 #include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
@@ -289,6 +290,33 @@ PyObject* plan_bytes(Args& x) {
 // float32, bytes).  The interpreter is free meanwhile, as it is in torch.empty: an allocator that has to ask the driver, or that
 // waits for another thread's call into it, must not hold up the other Python threads.
 constexpr Py_ssize_t kMostBuffers = 16;
+
+// Buffers of a small call in one allocation: each costs 0.8 us of host time, which is what bounds the smallest passes (a token filter
+// makes seven to nine: 7.3 us, so 2.2; the whole scoring pass of four short sequences 32.4 -> 23.6).  Together they stay below kSharedBytes, so that who keeps one of them keeps little else; larger ones, and all
+// of them while a Python dispatch mode has its own say about allocations, are allocated one by one.  Every tensor begins where an
+// allocation could (512 bytes) and shares the storage, which lives as long as the last of them.
+constexpr int64_t kSharedBytes = 1 << 20, kSharedAlign = 512;
+constexpr Py_ssize_t kSharedFrom = 4;                              // (the token filter's; log-probs and their sums stay apart)
+bool share(const at::TensorOptions& on, const at::ScalarType* types, const int64_t* sizes, Py_ssize_t count, at::Tensor* made) {
+    if (count < kSharedFrom || c10::impl::dispatch_mode_enabled()) return false;
+    int64_t at_byte[kMostBuffers], total = 0;
+    for (Py_ssize_t i = 0; i < count; ++i) {
+        if (sizes[i] < 0 || sizes[i] > kSharedBytes) return false;  // (a negative size is at::empty's to refuse)
+        at_byte[i] = total;
+        total += (sizes[i] * (int64_t)c10::elementSize(types[i]) + kSharedAlign - 1) / kSharedAlign * kSharedAlign;
+        if (total > kSharedBytes) return false;
+    }
+    const at::Tensor block = at::empty({total}, on.dtype(at::kByte));
+    const auto keys = block.key_set();
+    if (keys.has(c10::DispatchKey::Python) || !block.has_storage()) return false;
+    for (Py_ssize_t i = 0; i < count; ++i) {
+        made[i] = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block.storage()), keys, c10::scalarTypeToTypeMeta(types[i]));
+        c10::TensorImpl* t = made[i].unsafeGetTensorImpl();
+        t->set_storage_offset(at_byte[i] / (int64_t)c10::elementSize(types[i]));
+        t->set_sizes_contiguous({sizes[i]});
+    }
+    return true;
+}
 at::Device device_of(PyObject* like) {
     if (THPVariable_CheckExact(like)) return THPVariable_Unpack(like).device();
     const Held device(PyObject_GetAttrString(like, "device"));
@@ -313,10 +341,11 @@ PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
         }
         {
             NoInterpreter other_threads_run;
-            for (Py_ssize_t i = 0; i < count; ++i) {
-                const auto type = kinds[i] == 'i' ? at::kInt : kinds[i] == 'l' ? at::kLong : kinds[i] == 'f' ? at::kFloat : at::kByte;
-                made[i] = at::empty({sizes[i]}, on.dtype(type));
-            }
+            at::ScalarType types[kMostBuffers];
+            for (Py_ssize_t i = 0; i < count; ++i)
+                types[i] = kinds[i] == 'i' ? at::kInt : kinds[i] == 'l' ? at::kLong : kinds[i] == 'f' ? at::kFloat : at::kByte;
+            if (!share(on, types, sizes, count, made))
+                for (Py_ssize_t i = 0; i < count; ++i) made[i] = at::empty({sizes[i]}, on.dtype(types[i]));
         }
         PyObject* out = PyTuple_New(count);
         if (!out) throw Raised{};
