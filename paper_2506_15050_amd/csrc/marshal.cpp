@@ -4,6 +4,7 @@
 // What is taken and what is refused is what ctypes and the binding's own assertions take and refuse; sizes, ranges and NULLs are
 // the C entry points' own business.
 #include <Python.h>
+#include <ATen/Context.h>
 #include <ATen/ops/empty.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <torch/csrc/Device.h>
@@ -292,13 +293,22 @@ PyObject* plan_bytes(Args& x) {
 constexpr Py_ssize_t kMostBuffers = 16;
 
 // Buffers of a small call in one allocation: each costs 0.8 us of host time, which is what bounds the smallest passes (a token filter
-// makes seven to nine: 7.3 us, so 2.2; the whole scoring pass of four short sequences 32.4 -> 23.6).  Together they stay below kSharedBytes, so that who keeps one of them keeps little else; larger ones, and all
-// of them while a Python dispatch mode has its own say about allocations, are allocated one by one.  Every tensor begins where an
-// allocation could (512 bytes) and shares the storage, which lives as long as the last of them.
+// makes seven to nine: 7.3 us, so 2.2; the whole scoring pass of four short sequences 32.4 -> 23.6).  Together they stay below
+// kSharedBytes, so that who keeps one of them keeps little else; larger ones are allocated one by one, and so are all of them while a
+// dispatch mode, a transform, a trace or the fill of deterministic runs has its own say about allocations: the pieces are made here,
+// past the dispatcher, and have to be what it would have made, plain tensors.  Every tensor begins where an allocation could (512
+// bytes) and shares the storage, which lives as long as the last of them.
 constexpr int64_t kSharedBytes = 1 << 20, kSharedAlign = 512;
 constexpr Py_ssize_t kSharedFrom = 4;                              // (the token filter's; log-probs and their sums stay apart)
+const c10::DispatchKeySet kPlainKeys({c10::DispatchKey::CPU, c10::DispatchKey::CUDA, c10::DispatchKey::ADInplaceOrView,
+                                      c10::DispatchKey::AutogradCPU, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::AutocastCPU,
+                                      c10::DispatchKey::AutocastCUDA});
+bool undisturbed() {                                               // nothing beyond the usual takes part in this thread's calls
+    return !c10::impl::dispatch_mode_enabled() && c10::default_included_set.has_all(c10::impl::tls_local_dispatch_key_set().included_) &&
+           !at::globalContext().deterministicAlgorithms();         // (which fills what is allocated, by type)
+}
 bool share(const at::TensorOptions& on, const at::ScalarType* types, const int64_t* sizes, Py_ssize_t count, at::Tensor* made) {
-    if (count < kSharedFrom || c10::impl::dispatch_mode_enabled()) return false;
+    if (count < kSharedFrom || !undisturbed()) return false;
     int64_t at_byte[kMostBuffers], total = 0;
     for (Py_ssize_t i = 0; i < count; ++i) {
         if (sizes[i] < 0 || sizes[i] > kSharedBytes) return false;  // (a negative size is at::empty's to refuse)
@@ -308,7 +318,7 @@ bool share(const at::TensorOptions& on, const at::ScalarType* types, const int64
     }
     const at::Tensor block = at::empty({total}, on.dtype(at::kByte));
     const auto keys = block.key_set();
-    if (keys.has(c10::DispatchKey::Python) || !block.has_storage()) return false;
+    if (!kPlainKeys.has_all(keys) || !block.has_storage()) return false;
     for (Py_ssize_t i = 0; i < count; ++i) {
         made[i] = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block.storage()), keys, c10::scalarTypeToTypeMeta(types[i]));
         c10::TensorImpl* t = made[i].unsafeGetTensorImpl();

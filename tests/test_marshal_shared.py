@@ -53,3 +53,37 @@ def test_others_do_not(native):  # noqa: F811
     with Mode():
         made = native.empties(like, "iiil", 2, 2, 1, 3)
     assert len(seen) == 4 and storages(made) == 4
+
+
+def test_transforms_and_traces_allocate_for_themselves(native):  # noqa: F811
+    like, kinds, sizes = torch.zeros(1), "iiflb", (4, 5, 6, 7, 8)
+    seen = {}
+
+    def within(name, wrapped):
+        made = native.empties(like, kinds, *sizes)
+        seen[name] = [wrapped(t) for t in made], [t.dtype for t in made], [tuple(t.shape) for t in made]
+        return made
+
+    def graded(x):
+        made = within("grad", torch._C._functorch.is_gradtrackingtensor)
+        made[2].fill_(2.0)
+        return (x * made[2]).sum()
+
+    assert torch.equal(torch.func.grad(graded)(torch.ones(6)), torch.full((6,), 2.0))
+    torch.vmap(lambda x: x + within("vmap", lambda t: not torch._C._functorch.is_batchedtensor(t))[2].zero_())(torch.ones(3, 6))
+    torch.func.functionalize(lambda x: x + within("functionalize", torch._is_functional_tensor)[2].zero_())(torch.ones(6))
+    traced = torch.jit.trace(lambda x: x + within("trace", lambda t: True)[2].zero_(), torch.ones(6), check_trace=False)
+    assert str(traced.graph).count("aten::empty") >= 1 and torch.equal(traced(torch.ones(6)), torch.ones(6))
+    assert set(seen) == {"grad", "vmap", "functionalize", "trace"}
+    for ok, types, shapes in seen.values():
+        assert all(ok) and types == [KINDS[k] for k in kinds] and shapes == [(n,) for n in sizes]
+    before = torch.are_deterministic_algorithms_enabled()
+    try:
+        torch.use_deterministic_algorithms(True)
+        made = native.empties(like, kinds, *sizes)
+    finally:
+        torch.use_deterministic_algorithms(before)
+    assert storages(made) == 5 and int(made[0][0]) == torch.iinfo(torch.int32).max
+    with torch.inference_mode():
+        assert storages(made_of(native, kinds, sizes)) == 1
+    assert storages(made_of(native, kinds, sizes)) == 1
