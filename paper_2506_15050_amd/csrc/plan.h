@@ -35,8 +35,9 @@
 //                    of the tile alone, then the same four with everything to
 //                    its right included.  Indexed by Tile::slot(), which numbers
 //                    a sequence's tiles consecutively.
-//   finish_words[kFinishGroups][kFinishWords]   partial sums of a reduction
-//                    kernel's workgroups, in the same tagged form
+//   finish_words[kFinishGroups * kFinishWords]   partial sums of a reduction
+//                    kernel's workgroups, in the same tagged form, one workgroup's
+//                    words (as many as the kernel has) behind the other's
 // Whoever builds the list (tppo_select, tppo_plan_build, or an entry point that
 // was given no plan and builds its own in its workspace) zeroes all tagged
 // words.  Every later launch tags what it writes with its own call number
@@ -53,7 +54,7 @@ constexpr int kLevels = 32;                    // levels the list is sorted by
 constexpr int kScanWords = 8;                  // tagged words per tile
 constexpr int kBuildThreads = 1024;
 constexpr int kFinishGroups = 2048;            // most workgroups a reduction kernel may launch
-constexpr int kFinishWords = 10;               // tagged words per workgroup: five sums as hi + lo
+constexpr int kFinishWords = 10;               // room for tagged words per workgroup: five sums as hi + lo
 
 static_assert(kTileTokens <= (1 << kTileShift), "Tile::pos_len packs the length below the tile number");
 
@@ -99,7 +100,7 @@ struct Plan {
     Tile* tiles;
     FrameDesc* frames;                   // [cap], by frame number; the set fields are meaningful when hdr->has_sets
     unsigned long long* scan_words;      // [cap][kScanWords], by Tile::slot()
-    unsigned long long* finish_words;    // [kFinishGroups][kFinishWords]
+    unsigned long long* finish_words;    // [kFinishGroups * kFinishWords]
     int cap;
 };
 
