@@ -1,11 +1,12 @@
 // Python side of the C ABI (tppo.h), native: turns a call's tensors into pointers, allocates its results, and calls.  The
 // smallest passes are bound by what happens here, once a call: through ctypes and torch's Python functions a token filter
-// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 7.7, 8.5, 3.7 and 4.0.
+// with its plan took 18.8 us of host time, log-probs 10.6, EGAE 5.7 and losses 6.0; here 9.1, 8.7, 3.6 and 3.9.
 // What is taken and what is refused is what ctypes and the binding's own assertions take and refuse; sizes, ranges and NULLs are
 // the C entry points' own business.
 #include <Python.h>
 #include <ATen/Context.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <torch/csrc/Device.h>
 #include <torch/csrc/DynamicTypes.h>
@@ -13,6 +14,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
+#include <utility>
 
 #include "tppo.h"
 
@@ -292,14 +294,12 @@ PyObject* plan_bytes(Args& x) {
 // waits for another thread's call into it, must not hold up the other Python threads.
 constexpr Py_ssize_t kMostBuffers = 16;
 
-// Buffers of a small call in one allocation: each costs 0.8 us of host time, which is what bounds the smallest passes (a token filter
-// makes seven to nine: 7.3 us, so 2.2; the whole scoring pass of four short sequences 32.4 -> 23.6).  Together they stay below
-// kSharedBytes, so that who keeps one of them keeps little else; larger ones are allocated one by one, and so are all of them while a
-// dispatch mode, a transform, a trace or the fill of deterministic runs has its own say about allocations: the pieces are made here,
-// past the dispatcher, and have to be what it would have made, plain tensors.  Every tensor begins where an allocation could (512
-// bytes) and shares the storage, which lives as long as the last of them.
-constexpr int64_t kSharedBytes = 1 << 20, kSharedAlign = 512;
-constexpr Py_ssize_t kSharedFrom = 4;                              // (the token filter's; log-probs and their sums stay apart)
+// Each buffer is an allocation of its own, as torch.empty's: a caller may resize it, give it as `out`, save it, keep it, and record a
+// stream's use of it without the others.  (Pieces of one allocation are cheaper still and allow none of these: what grows runs into the
+// next piece, and storages of their own over one block are none that the device's allocator knows to record a stream for.)  The first
+// is at::empty's; the others are made here from its storage's allocator, past the dispatcher, whose way costs more than the allocation
+// (a token filter's nine: 7.3 us of host time, so 4.4; pieces of one block 2.15), unless a dispatch mode, a transform, a trace or the
+// fill of deterministic runs has its own say about allocations.
 const c10::DispatchKeySet kPlainKeys({c10::DispatchKey::CPU, c10::DispatchKey::CUDA, c10::DispatchKey::ADInplaceOrView,
                                       c10::DispatchKey::AutogradCPU, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::AutocastCPU,
                                       c10::DispatchKey::AutocastCUDA});
@@ -307,25 +307,21 @@ bool undisturbed() {                                               // nothing be
     return !c10::impl::dispatch_mode_enabled() && c10::default_included_set.has_all(c10::impl::tls_local_dispatch_key_set().included_) &&
            !at::globalContext().deterministicAlgorithms();         // (which fills what is allocated, by type)
 }
-bool share(const at::TensorOptions& on, const at::ScalarType* types, const int64_t* sizes, Py_ssize_t count, at::Tensor* made) {
-    if (count < kSharedFrom || !undisturbed()) return false;
-    int64_t at_byte[kMostBuffers], total = 0;
-    for (Py_ssize_t i = 0; i < count; ++i) {
-        if (sizes[i] < 0 || sizes[i] > kSharedBytes) return false;  // (a negative size is at::empty's to refuse)
-        at_byte[i] = total;
-        total += (sizes[i] * (int64_t)c10::elementSize(types[i]) + kSharedAlign - 1) / kSharedAlign * kSharedAlign;
-        if (total > kSharedBytes) return false;
+void allocate(const at::TensorOptions& on, const at::ScalarType* types, const int64_t* sizes, Py_ssize_t count, at::Tensor* made) {
+    if (count == 0) return;
+    made[0] = at::empty({sizes[0]}, on.dtype(types[0]));
+    Py_ssize_t i = 1;
+    const auto keys = made[0].key_set();
+    if (count > 1 && undisturbed() && kPlainKeys.has_all(keys) && made[0].has_storage() && made[0].storage().allocator()) {
+        const c10::DeviceGuard there(made[0].device());
+        // (sizes that are none, or too many bytes for a number, are at::empty's to refuse)
+        for (; i < count && sizes[i] >= 0 && sizes[i] <= INT64_MAX / 8; ++i) {
+            c10::Storage own(c10::Storage::use_byte_size_t(), (size_t)sizes[i] * c10::elementSize(types[i]), made[0].storage().allocator(), true);
+            made[i] = at::detail::make_tensor<c10::TensorImpl>(std::move(own), keys, c10::scalarTypeToTypeMeta(types[i]));
+            made[i].unsafeGetTensorImpl()->set_sizes_contiguous({sizes[i]});
+        }
     }
-    const at::Tensor block = at::empty({total}, on.dtype(at::kByte));
-    const auto keys = block.key_set();
-    if (!kPlainKeys.has_all(keys) || !block.has_storage()) return false;
-    for (Py_ssize_t i = 0; i < count; ++i) {
-        made[i] = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block.storage()), keys, c10::scalarTypeToTypeMeta(types[i]));
-        c10::TensorImpl* t = made[i].unsafeGetTensorImpl();
-        t->set_storage_offset(at_byte[i] / (int64_t)c10::elementSize(types[i]));
-        t->set_sizes_contiguous({sizes[i]});
-    }
-    return true;
+    for (; i < count; ++i) made[i] = at::empty({sizes[i]}, on.dtype(types[i]));
 }
 at::Device device_of(PyObject* like) {
     if (THPVariable_CheckExact(like)) return THPVariable_Unpack(like).device();
@@ -354,8 +350,7 @@ PyObject* empties(PyObject*, PyObject* const* args, Py_ssize_t n) {
             at::ScalarType types[kMostBuffers];
             for (Py_ssize_t i = 0; i < count; ++i)
                 types[i] = kinds[i] == 'i' ? at::kInt : kinds[i] == 'l' ? at::kLong : kinds[i] == 'f' ? at::kFloat : at::kByte;
-            if (!share(on, types, sizes, count, made))
-                for (Py_ssize_t i = 0; i < count; ++i) made[i] = at::empty({sizes[i]}, on.dtype(types[i]));
+            allocate(on, types, sizes, count, made);
         }
         PyObject* out = PyTuple_New(count);
         if (!out) throw Raised{};
