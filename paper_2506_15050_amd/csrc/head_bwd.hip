@@ -250,7 +250,6 @@ static int launch_transpose(const uint16_t* src, int64_t rows, int64_t cols, int
 }
 
 using BwdCfg = HeadCfg<uint16_t, false>;
-using LongCfg = HeadCfg<uint16_t, false, false, 0, 4, false, true>;
 
 // out[M, N] (+)= tokens[M, K] . w_role[N, K]^T, one of the two K-major, divided by plan_bwd_product.
 // Transposing W and dZ first (both operands read along K, b128 fragments) moves 2 x 2 bytes per entry of both through
@@ -372,7 +371,7 @@ extern "C" int tppo_token_logprobs_backward(const void* hidden, int64_t n_rows, 
         if ((narrow            ? launch_narrow<false, DzEpilogue>(narrow, p, s)
              : small           ? launch_sweep<SmallShape, DzEpilogue>(p, arrivals, s)
              : H <= kPrefetchH ? launch_sweep<BwdCfg, DzAheadEpilogue>(p, arrivals, s)
-                               : launch_sweep<LongCfg, DzEpilogue>(p, arrivals, s)) != TPPO_OK)
+                               : launch_sweep<BwdCfg, DzEpilogue>(p, arrivals, s)) != TPPO_OK)
             return TPPO_ERR_LAUNCH;
         // 2. grad_hidden[m0 + t, :] = dZ[t, :] . W   (token role: dZ rows; W role: columns of W; K = v_pad)
         if (grad_hidden) {

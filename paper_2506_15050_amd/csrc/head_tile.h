@@ -90,13 +90,16 @@ struct HeadParams {
 // last ones are waited for in vain where no third workgroup computes meanwhile.  fp32, us, late -> early, one workgroup to a CU:
 // 1600 tokens x V 32000, H 1024: 1184 -> 955;  4000 x 5000, H 2048: 939 -> 761;  two: 2064 x 45000, H 1024: 1647 -> 1604;  three: 2064 x
 // 32000: 1101 (1109);  3300 x 32000: 1788 (1807).
-// LONG (large tiles, sweeps of kLongStages and more): a task's set-up and its steps from tile to tile as they fit the K loop best.
+// LONG (large tiles, the log-softmax over kLongStages and more): a task's set-up and its steps from tile to tile as they fit the K loop best.
 // Elsewhere they are lean: the parameters asked for anew by every task instead of kept over all, spilled lane by lane (params_again), the
 // rows of the token list all at once instead of one by one, a step to the next tile of W rows instead of every row's address.  us, LONG ->
 // lean:  5000 tokens x V 30000, H 64: 51.1 -> 48.2;  20000 x 10000, H 128: 85.0 -> 80.5;  13640 x 32000, H 1024: 665 -> 657;  8000 x 40000, H 2048:
-// 924 -> 918; narrow, 500 x 12000, H 1024: 27.4 -> 25.4;  900 x 5000, H 2048: 41.2 -> 39.2; ragged, 2516 x 50021, H 1000: 225.7 -> 222.9; but 6000 x
-// 50000, H 2560: 1163 -> 1167;  4000 x 50000, H 3584: 1067 -> 1072;  H 5120: 1523 -> 1535;  942 x 152064: 1227 -> 1235, where a set-up hardly counts
-// and the loop that the compiler makes of the rest, 8 bytes on from the other's place in a fetched line, does.
+// 924 -> 918; narrow, 500 x 12000, H 1024: 27.4 -> 25.4;  900 x 5000, H 2048: 41.2 -> 39.2; ragged, 2516 x 50021, H 1000: 225.7 -> 222.9.  Where a
+// set-up hardly counts, the loop that the compiler makes of the rest does, 8 bytes on from the other's place in a fetched line: 6000 x 50000,
+// H 2560: 1184 -> 1187;  12000 x 32000, H 4096: 2302 -> 2311;  4000 x 50000, H 3584: 1085 -> 1091;  H 5120: 1551 -> 1564;  20000: 7277 -> 7330;  942 x
+// 152064: 1252 -> 1261; though 6000 x 50000, H 2304: 1042 -> 1035;  8000 x 40000, H 3072: 1438 -> 1432.  The derivative's sweep is lean at any
+// length: 1500 x 9001, H 1600: 47.4 -> 46.2;  8206 x 32000, H 1792: 794 -> 788;  H 2304: 993 -> 983;  H 3584: 1496 -> 1483;  8000 x 100000, H 4096:
+// 4897 -> 4870;  3514 x 152064, H 5120: 4284 -> 4287;  9000: 10506 -> 10492;  40000 x 32000, H 2048: 4317 -> 4319.
 // KMAJOR (bf16, large tiles): one operand lies in memory with K as the ROW index -- 1 the W-role one, 2 the token-role
 // one; element (row r, k) is at base[k * ld + r].  A stage of it is kBK rows of 512 bytes, K row k's 16-byte chunk c in
 // slot c ^ swz_k(k), and ds_read_b64_tr_b16 takes fragments out transposed: 16 lanes read 4 K rows x 16 columns, lane i

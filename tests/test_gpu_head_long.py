@@ -1,5 +1,5 @@
-"""Both forms of the large tiles' sweep on whole stages, either side of the line between them (kLongStages), and the long form under
-the derivative: a ragged last tile of W rows, token tiles cut short by the device's own count."""
+"""Both forms of the large tiles' log-softmax on whole stages, either side of the line between them (kLongStages), and the derivative's
+sweep, which has one form, either side of the same line: a ragged last tile of W rows, token tiles cut short by the device's own count."""
 
 import numpy as np
 import pytest
