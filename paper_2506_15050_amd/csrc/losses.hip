@@ -360,7 +360,7 @@ __device__ __forceinline__ void unshift(LossRegs& x, const TokenSets& ts, int it
 }
 
 // A workgroup publishes kWords words: of each of kSums - kCounts sums two (a double as hi + lo), of each of the kCounts last ones, whole
-// numbers below 2^24, one.
+// numbers up to 2^24 (countable), one.
 template <int kSums, int kCounts>
 struct SumWords {
     static constexpr int kFloats = 2 * (kSums - kCounts), kWords = kFloats + kCounts;
@@ -756,6 +756,10 @@ __global__ __launch_bounds__(256) void loss_tiny_kernel(GradParams gp, const int
     }
 }
 
+// Whether no workgroup of so many has more tokens than fp32 counts one by one (SumWords: the clipped ones).
+constexpr bool countable(int64_t frames, int groups) { return (frames + groups - 1) / groups * (4 * kLossThreads) <= 1 << 24; }
+static_assert(countable(INT32_MAX / (4 * kLossThreads) + 1, kGradGroups), "the largest batch, by the grid that counts");
+
 // Workgroups of the persistent grids.  Nothing depends on all of them being resident at once: only the
 // workgroup dispatched last waits, and only for workgroups dispatched before it.
 static int loss_groups(int64_t n_resp, bool grad) {
@@ -764,7 +768,7 @@ static int loss_groups(int64_t n_resp, bool grad) {
 #ifdef TPPO_TUNING
     if (const char* e = getenv("TPPO_LOSS_GROUPS")) {
         const int forced = atoi(e);
-        if (forced >= 1 && forced <= kFinishGroups) groups = forced;
+        if (forced >= 1 && forced <= kFinishGroups && countable(frames, forced)) groups = forced;
     }
 #endif
     return frames < groups ? (int)frames : groups;

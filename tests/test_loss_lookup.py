@@ -95,11 +95,48 @@ int main() {
 }
 """
 
+# workgroups of the largest and other batches, of the product's grids and (argument: built for tuning) of grids whose size the
+# environment gives
+GROUPS = r"""
+#include "losses.hip"
+#include <cstdio>
+#include <cstdlib>
+namespace tppo {
+uint32_t next_call_tag() { return 1; }
+int launch_plan_build(const int32_t*, const int32_t*, const int32_t*, int64_t, int64_t, int64_t, void*, int32_t*, hipStream_t) { return 0; }
+}
+int main() {
+    for (const char* groups : {"", "1", "2", "100", "127", "128", "1024", "2048", "2049", "-5"}) {
+        setenv("TPPO_LOSS_GROUPS", groups, 1);
+        for (int64_t n : {(int64_t)1, (int64_t)1 << 20, ((int64_t)1 << 24) - 1, (int64_t)1 << 24, ((int64_t)1 << 24) + 1, (int64_t)INT32_MAX})
+            for (bool grad : {false, true}) printf("%s,%ld,%d\n", groups, (long)n, tppo::loss_groups(n, grad));
+    }
+}
+"""
+
+
+def compiled(at, program, *flags):
+    at.with_suffix(".hip").write_text(program)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", *flags, "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(at.with_suffix(".hip")), "-o", str(at)],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    return str(at)
+
+
+def test_a_workgroups_tokens_can_be_counted_in_fp32(tmp_path):
+    for flags in ((), ("-DTPPO_TUNING",)):
+        out = subprocess.run([compiled(tmp_path / "groups", GROUPS, *flags)], check=True, stdout=subprocess.PIPE, text=True, timeout=60).stdout
+        rows = [line.split(",") for line in out.splitlines()]
+        assert len(rows) == 120
+        for forced, n, groups in ((f, int(n), int(g)) for f, n, g in rows):
+            frames = -(-n // 1024)
+            assert 1 <= groups <= min(frames, 2048) and -(-frames // groups) * 1024 <= 1 << 24, (forced, n, groups)
+            if flags and forced.isdigit() and 128 <= int(forced) <= 2048:
+                assert groups == min(frames, int(forced))
+            if not flags:
+                assert groups == min(frames, 1024)
+
 
 def test_lookup_reads_what_was_fetched(tmp_path):
-    (tmp_path / "lookup.hip").write_text(PROGRAM)
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
-                    os.path.join(ROOT, "paper_2506_15050_amd", "csrc"), str(tmp_path / "lookup.hip"), "-o", str(tmp_path / "lookup")],
-                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-    ran = subprocess.run([str(tmp_path / "lookup")], stdout=subprocess.PIPE, text=True, timeout=120)
+    ran = subprocess.run([compiled(tmp_path / "lookup", PROGRAM)], stdout=subprocess.PIPE, text=True, timeout=120)
     assert ran.returncode == 0 and ran.stdout == "314 layouts, frames with more: 1\n", (ran.returncode, ran.stdout)
