@@ -1,5 +1,5 @@
 """The loss passes' grids of few workgroups: either side of the most they take, of the most sequences whose metadata is asked for at
-once, and of the grids whose sums one, two or more batches of the collecting workgroup's reads bring in."""
+once, and of the grids whose sums a part of one batch, one or two of the collecting workgroup's reads bring in."""
 import numpy as np
 import pytest
 

@@ -1,6 +1,7 @@
 """Which sets a token of the loss passes belongs to (csrc/losses.hip, token_sets, run on the host): every thread of every
 workgroup against the definition, and no thread reads the sequences' words in a frame that the workgroup has not fetched
-them for, batches that end in empty windows among them."""
+them for, batches that end in empty windows among them.  Of batches that one fetch holds, also with all sequences fetched from the
+first one on, as by grids of few workgroups."""
 import os
 import subprocess
 
@@ -20,7 +21,7 @@ int launch_plan_build(const int32_t*, const int32_t*, const int32_t*, int64_t, i
 using namespace tppo;
 typedef std::vector<int> Ints;
 static const MoreSeqs* nobody;                                      // reading it ends the program
-static int frames_with_more;
+static int frames_with_more, frames_of_all;
 static void check(const Ints& win, const Ints& keep, const Ints& done) {
     const int B = (int)win.size();
     Ints off(B + 1, 0);
@@ -41,19 +42,28 @@ static void check(const Ints& win, const Ints& keep, const Ints& done) {
         for (int t = off[i]; t < off[i + 1]; ++t) pol[t] = t - off[i] < keep[i], val[t] = done[i] != 0;
     LossParams p = {};
     p.resp_off = off.data(); p.keep_len = keep.data(); p.done = done.data(); p.B = B; p.n_resp = n;
-    MoreSeqs fetched;
+    MoreSeqs fetched, all;
     for (int item = 0; item * 4 * kLossThreads < n; ++item) {
         const FrameDesc d = frames[item / kLossParts];
         const bool more = has_more(p, d, item);
         frames_with_more += more;
-        for (int w = 0; w < kLossThreads / kWave; ++w) fetched.in_frame[w] = 0;
-        for (int tid = 0; tid < kLossThreads; ++tid) {              // (keep_meta)
-            const SeqMeta x = load_meta(p, d.seg2 + 1 + tid);
-            fetched.in_frame[tid / kWave] += d.seg2 + 1 + tid < B && x.lo < (item + 1) * (4 * kLossThreads);
-            fetched.seq[tid] = kept_words(x);
-        }
+        const bool one_fetch = B <= kLossThreads;                   // (all_ahead)
+        frames_of_all += more && one_fetch;
+        auto fetch = [&](MoreSeqs& into, int from) {                // (keep_meta)
+            for (int w = 0; w < kLossThreads / kWave; ++w) into.in_frame[w] = 0;
+            for (int tid = 0; tid < kLossThreads; ++tid) {
+                const SeqMeta x = load_meta(p, from + tid);
+                into.in_frame[tid / kWave] += from + tid < B && x.lo < (item + 1) * (4 * kLossThreads);
+                into.seq[tid] = kept_words(x);
+            }
+        };
+        fetch(fetched, d.seg2 + 1);
+        fetch(all, 0);
         for (int tid = 0; tid < kLossThreads; ++tid) {
             for (const TokenSets& ts : {token_sets<true>(p, d, more, more ? fetched : *nobody, item, tid, true, true),
+                                        token_sets<true>(p, d, more, more ? fetched : *nobody, item, tid, true, true, d.seg2 + 1),
+                                        one_fetch ? token_sets<true>(p, d, more, more ? all : *nobody, item, tid, true, true, 0)
+                                                  : token_sets<false>(p, d, false, *nobody, item, tid, true, true),
                                         token_sets<false>(p, d, false, *nobody, item, tid, true, true)}) {
                 int want_pol = 0, want_val = 0;
                 for (int e = 0; e < ts.n_tok; ++e) want_pol |= pol[ts.first + e] << e, want_val |= val[ts.first + e] << e;
@@ -73,7 +83,11 @@ int main() {
     nobody = static_cast<const MoreSeqs*>(mmap(nullptr, 1 << 20, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0));
     std::vector<Ints> layouts = {{700, 0}, {700, 1, 0}, {700, 0, 0}, {1500, 3, 0, 0}, {1024, 5, 0}, {1024, 0}, {4, 0}, {700},
                                  repeat({5, 3}, 300, 0), repeat({700}, 300, 0), repeat({700, 1}, 70, 0), repeat({1, 1}, 600, 2),
-                                 repeat({1023, 1}, 300, 1), repeat({}, 1500, 1)};
+                                 repeat({1023, 1}, 300, 1), repeat({}, 1500, 1),
+                                 repeat({}, 255, 1), repeat({}, 256, 1), repeat({}, 257, 1), repeat({}, 255, 9), repeat({}, 256, 9),
+                                 repeat({3000}, 255, 9), repeat({3000}, 254, 2), repeat({0, 0, 700}, 253, 4), repeat(repeat({}, 200, 0), 56, 9),
+                                 repeat(repeat(repeat({}, 100, 0), 90, 3), 66, 0), repeat(repeat(repeat({5}, 200, 0), 54, 7), 1, 0),
+                                 repeat(repeat(repeat({}, 250, 0), 5, 400), 1, 1), repeat(repeat({2000}, 127, 0), 128, 5)};
     srand(3);
     for (int k = 0; k < 300; ++k) {                                 // runs of empty, short and long windows, often at the end
         Ints win = {1 + rand() % 900};
@@ -91,7 +105,7 @@ int main() {
         }
         check(win, keep, done);
     }
-    printf("%d layouts, frames with more: %d\n", (int)layouts.size(), frames_with_more > 100);
+    printf("%d layouts, frames with more: %d %d\n", (int)layouts.size(), frames_with_more > 100, frames_of_all > 100);
 }
 """
 
@@ -139,4 +153,4 @@ def test_a_workgroups_tokens_can_be_counted_in_fp32(tmp_path):
 
 def test_lookup_reads_what_was_fetched(tmp_path):
     ran = subprocess.run([compiled(tmp_path / "lookup", PROGRAM)], stdout=subprocess.PIPE, text=True, timeout=120)
-    assert ran.returncode == 0 and ran.stdout == "314 layouts, frames with more: 1\n", (ran.returncode, ran.stdout)
+    assert ran.returncode == 0 and ran.stdout == "327 layouts, frames with more: 1 1\n", (ran.returncode, ran.stdout)
