@@ -30,7 +30,9 @@ constexpr int kOneLaunchSeqs = kScanThreads;
 constexpr int kScanAhead = 8;
 constexpr int kListParts = 8;                                   // workgroups for the list of more than 128 sequences (plan_build.h)
 constexpr int kQuarter = kTileTokens / 4;                        // threads that share a tile of the compact list, four tokens each
-constexpr int kFillMaxGroups = 512;                             // two per CU
+// Workgroups on the chip at once, two on each of its 256 CUs.  (This and the lines below are fixed for the whole chip: a partition of it
+// gets the same results from grids that are not tuned for it.)
+constexpr int kFillMaxGroups = 512;
 // Those of the second launch that walk the compact tile list, four tiles a turn.  512 of them, one turn 8 MB on from the last, are slower
 // than fewer or more; the whole filter, us, 256 / 320 / 384 / 448 / 512 / 768 / 1024: 40 M tokens in 8704 sequences 61.1 / 57.2 / 54.9 / 55.2 /
 // 61.9 / 56.1 / 54.3, 14 M in 3000 31.2 / 30.0 / 29.6 / 30.0 / 31.3 / 29.6 / 30.0.  Four consecutive tokens a thread, 16-byte stores: 53.3 and 29.6 with
@@ -232,12 +234,9 @@ __global__ __launch_bounds__(kBuildThreads) void select_fill_kernel(FillArgs a, 
 // the small outputs; the others zero the plan's words and write the kept tokens, four consecutive ones per thread and turn, whose
 // sequence a thread finds by bisection of the offsets in LDS.
 // (With 88 scalar registers, and the 16 that each wavefront has besides, a CU takes one workgroup: 2.3 M tokens 9.3 instead of 7.5.)
-__global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_num_sgpr(80))) void select_one_launch_kernel(FillArgs a, const int32_t* __restrict__ done, int B,
-                                                                          int tail_drop, int32_t* __restrict__ resp_off,
-                                                                          int32_t* __restrict__ sel_off,
-                                                                          int32_t* __restrict__ keep_len,
-                                                                          int64_t* __restrict__ counts, int parts, int plan_cap,
-                                                                          void* plan_raw) {
+__global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_num_sgpr(80))) void select_one_launch_kernel(
+    FillArgs a, const int32_t* __restrict__ done, int B, int tail_drop, int32_t* __restrict__ resp_off, int32_t* __restrict__ sel_off,
+    int32_t* __restrict__ keep_len, int64_t* __restrict__ counts, int parts, int plan_cap, void* plan_raw) {
     __shared__ int32_t s_resp[kOneLaunchSeqs + 1], s_sel[kOneLaunchSeqs + 1], s_aux[2][kOneLaunchSeqs];
     __shared__ int s_wave[3][kBuildWaves];
     __shared__ BuildLds s_build;
@@ -312,41 +311,42 @@ __global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_num_sgpr(80)))
     const int64_t turn = (int64_t)workers * kBuildThreads * 4;
     const int active = n > kManyTurns * turn ? min(workers, kManyGroups) : workers;
     if (worker >= active) return;
-    for (int place = worker; place < workers; place += active)
-    for (int64_t m = ((int64_t)place * kBuildThreads + tid) * 4; m < n; m += turn) {
-        int lo = 0, hi = B - 1;                                      // the last sequence that begins at or before m
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_sel[mid] <= m) lo = mid; else hi = mid - 1;
-        }
-        const int some = (int)min(n - m, (int64_t)4);
-        int pos[4], resp[4], id[4];
-        const bool run = m + 4 <= s_sel[lo + 1];                     // all four in one sequence
-        if (run) {
-            const int t = (int)m - s_sel[lo];
-            const int p0 = s_aux[0][lo] + t, r0 = s_resp[lo] + t;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pos[e] = p0 + e;
-                resp[e] = r0 + e;
+    for (int place = worker; place < workers; place += active) {
+        for (int64_t m = ((int64_t)place * kBuildThreads + tid) * 4; m < n; m += turn) {
+            int lo = 0, hi = B - 1;                                      // the last sequence that begins at or before m
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_sel[mid] <= m) lo = mid; else hi = mid - 1;
             }
-        } else {
+            const int some = (int)min(n - m, (int64_t)4);
+            int pos[4], resp[4], id[4];
+            const bool run = m + 4 <= s_sel[lo + 1];                     // all four in one sequence
+            if (run) {
+                const int t = (int)m - s_sel[lo];
+                const int p0 = s_aux[0][lo] + t, r0 = s_resp[lo] + t;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                while (lo < B - 1 && s_sel[lo + 1] <= (int)m + e) ++lo;
-                const int t = (int)m + e - s_sel[lo];
-                pos[e] = s_aux[0][lo] + t;
-                resp[e] = s_resp[lo] + t;
+                for (int e = 0; e < 4; ++e) {
+                    pos[e] = p0 + e;
+                    resp[e] = r0 + e;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    while (lo < B - 1 && s_sel[lo + 1] <= (int)m + e) ++lo;
+                    const int t = (int)m + e - s_sel[lo];
+                    pos[e] = s_aux[0][lo] + t;
+                    resp[e] = s_resp[lo] + t;
+                }
             }
-        }
-        if (a.sel_targets) {
-            load_ids(a, pos, run, some, id);
-            store_some(a.sel_targets, m, id, some);
-        }
+            if (a.sel_targets) {
+                load_ids(a, pos, run, some, id);
+                store_some(a.sel_targets, m, id, some);
+            }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pos[e] -= 1;
-        if (a.sel_rows) store_some(a.sel_rows, m, pos, some);
-        if (a.sel_resp_idx) store_some(a.sel_resp_idx, m, resp, some);
+            for (int e = 0; e < 4; ++e) pos[e] -= 1;
+            if (a.sel_rows) store_some(a.sel_rows, m, pos, some);
+            if (a.sel_resp_idx) store_some(a.sel_resp_idx, m, resp, some);
+        }
     }
 }
 
