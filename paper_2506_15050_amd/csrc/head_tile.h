@@ -144,7 +144,9 @@ struct HeadCfg {
     // a wave issues the transfers of a stage one by one between its next kSpread MFMAs, so that it never sits in
     // a full memory queue.  Small tiles, over 16 (all there are) / 14 / 12 / 10 / 8 of fp32's groups of four: 2064 tokens x V 32000, H 1024 1100 /
     // 1095 / 1089 / 1109 / 1109 us;  6000 x 32000 3168 / 3144 / 3127 / 3183 / -;  2064 x 32000, H 256 290 / 290 / 289 / 294 / -: three workgroups cover
-    // for each other, but not for transfers that go out at a stage's end and are waited for there.  (Without transfers, 1024 us.)
+    // for each other, but not for transfers that go out at a stage's end and are waited for there.  (Without transfers, 1024 us.)  bf16, over all
+    // 16 MFMAs -> 12: log-probs, 146 x V 5000, H 1024 15.1 -> 14.5;  700 x 6000, H 256 14.4 -> 14.0;  300 x 1000, H 256 9.10 -> 8.98;  1030 x 3000,
+    // H 64 9.26 -> 9.25; backward calls 0 to 1 % (146 x 5000 56.5 -> 55.8, 358 x 11732, H 192 58.9 -> 58.7); none of twelve sizes slower.
     static constexpr int kSpread = FEW ? 8 : SMALL ? 12 : TOKEN_BLOCKS == 1 ? 16 : 8 * TOKEN_BLOCKS;
     static_assert(kDmaPerWave * kWaves == kDmaPerStage, "transfers must divide evenly over the waves");
     static_assert(kTileV % kRowsPerDma == 0, "a transfer may not straddle W and token rows");

@@ -10,8 +10,9 @@
 // two sequences the workgroup fetches the others' metadata into LDS (but for batches of
 // windows of a few tokens, loss_fetches).
 // No mask array is read, and a thread with no member of a set issues no loads
-// for that set (but for the first frame's policy arrays in the pass that writes
-// derivatives, loss_load_ahead).
+// for that set (but for what is asked for before the plan is known: all arrays in
+// grids of few workgroups, the first frame's policy arrays in others of the
+// pass that writes derivatives, loss_load_ahead).
 //
 // One launch per call.  A persistent grid walks the frames; a thread issues all loads of its share of a
 // frame at once (non-temporal 16-byte accesses, consecutive lanes on consecutive 16 bytes, no branch and no wait
@@ -36,9 +37,10 @@ constexpr int kLossThreads = TPPO_LOSS_THREADS;
 constexpr int kLossParts = kTileTokens / (4 * kLossThreads);      // a workgroup takes this fraction of a frame, four tokens per thread
 static_assert(kLossParts >= 1 && kLossParts * 4 * kLossThreads == kTileTokens, "whole parts of a frame");
 // Most workgroups of the persistent grids.  Enough of them to keep the memory busy, and no more: the one that collects
-// the sums reads 4 (forward) or 8 words of each.  Measured, us: forward with 2048 / 1024 / 512 workgroups 14.5 / 12.8 /
-// 12.3 on 2.4 M tokens, 30.5 / 28.8 / 28.9 on 10 M, 52.4 / 50.7 / 53.0 on 20 M; with derivatives 2048 / 1024 / 512 take
-// 28 / 21.3 / 21.0 on 2.4 M tokens and 1024 / 512 take 49.3 / 55.9 on 10 M (768: the same up to 20 M, 2 % more on 40 M).
+// the sums reads 4 (forward) or 8 words of each.  Measured, us, 2048 / 1024 / 768 / 512 workgroups: forward 10.3 / 10.1 / 9.9 /
+// 10.8 on 2.3 M tokens in 512 sequences, 14.3 / 15.6 / 17.4 / 21.2 on 3.0 M in 6008, 31.8 / 31.5 / 31.0 / 31.4 on 10 M in 2200, 59.7 / 59.0 /
+// 57.0 / 57.7 on 20 M in 4400; with derivatives 16.0 / 15.7 / 15.0 / 16.8, 20.7 / 20.1 / 22.8 / 27.4, 49.5 / 49.1 / 48.3 / 53.3 and 98.0 / 93.1 / 91.5 /
+// 102.5: short windows want many.
 constexpr int kLossGroups = 1024, kGradGroups = 1024;
 constexpr int kFinishSpin = 1 << 20;
 // Grids of up to so many workgroups, a frame each, are bound by their round trips: what they may need is asked for at once
@@ -140,13 +142,13 @@ struct TokenSets {
 // The metadata of the sequences that follow the two a frame's descriptor knows, one per thread of the workgroup: one round
 // trip.  Every thread behind the second boundary looking for itself, token by token and from the fourth sequence on by
 // bisection in memory, took, us: 3.0 M tokens in 6008 sequences losses 23.0 (now 16.1), derivatives 31.9 (23.7);  3.4 M in
-// 2703: 18.9 (16.3), 28.0 (23.6);  8.2 M in 3260: 32.2 (27.8), 47.1 (44.4);  4600 in 100: 8.4 (8.0), 10.8 (10.6).  A sequence's
-// four words are one read of LDS: as four arrays, read token by token, 19.0 and 26.5 at 3.0 M.
-// The policy arrays wait for the lookup: short unfinished sequences keep few tokens or none.  Asked for by every thread beside the
-// metadata instead, with 0.2 / 0.5 / 0.8 / 1 of 3.0 M tokens in windows of 64 .. 512 kept: losses 15.9 / 16.8 / 17.1 / 17.0 (now
+// 2703: 18.9 (16.3), 28.0 (23.6);  8.2 M in 3260: 32.2 (27.8), 47.1 (44.4).  A sequence's
+// four words are one read of LDS: as four arrays, read token by token, 19.0 and 26.5 at 3.0 M.  (All of these, and those below, with sums
+// through shuffles, on both sides; a pass of the first takes 15.4 now.)
+// The policy arrays wait for the lookup, but for those that loss_load_ahead asks for: short unfinished sequences keep few tokens or
+// none.  Asked for by every thread beside the metadata instead, with 0.2 / 0.5 / 0.8 / 1 of 3.0 M tokens in windows of 64 .. 512 kept: losses 15.9 / 16.8 / 17.1 / 17.0 (now
 // 14.9 / 16.0 / 16.7 / 17.4), derivatives 23.9 / 25.2 / 25.6 / 26.0 (22.7 / 23.7 / 24.1 / 24.9); the three layouts above 16.0, 16.2,
-// 28.1 and 24.2, 24.1, 44.7; a batch of 942 tokens, no such frame among them, 4.4 (4.3), after the other kernels of a scoring
-// pass 5.6 (5.1).
+// 28.1 and 24.2, 24.1, 44.7.  (Grids of few workgroups, which wait for nothing else, are faster so: kFewGroups.)
 struct MoreSeqs {
     int4 seq[kLossThreads];                      // a sequence's first token, its end, the end of its policy tokens, finished
     int in_frame[kLossThreads / kWave];          // how many of a wavefront's begin before the frame's end
@@ -308,8 +310,8 @@ __device__ __forceinline__ void loss_load_value(LossRegs& x, const LossParams& p
 // instead of three:
 //   the first frame's policy arrays, in the pass that writes derivatives: all but the dropped tails are policy tokens, so little
 //     of it is asked for in vain.  Derivatives alone, us, after the descriptor -> so, at a tenth / three tenths / nine tenths of finished
-//     sequences: 490 K tokens 11.5 / 11.8 / 12.5 -> 11.2 / 11.5 / 11.9;  1 M 16.6 / 17.3 / 18.0 -> 15.7 / 16.8 / 17.4;  4 M 25.8 / 27.2 / 31.0 ->
-//     25.7 / 26.7 / 30.8.
+//     sequences: 1 M tokens 16.6 / 17.3 / 18.0 -> 15.7 / 16.8 / 17.4;  4 M 25.8 / 27.2 / 31.0 -> 25.7 / 26.7 / 30.8 (with sums through
+//     shuffles, on both sides).
 //   kFew, a grid of so few workgroups (kFewGroups) that latency is all they take: all six arrays, and all sequences' metadata, one per
 //     thread, if there are no more (all_ahead), for frames with more sequences than the two that the descriptor knows.
 template <bool kFew>
@@ -457,8 +459,8 @@ __device__ __forceinline__ void write_invalid(tppo_loss_out* out) {
     out->n_policy = out->n_value = 0;
 }
 
-// (Held to eight wavefronts a SIMD the lookup's 106 scalar registers become 78 and 54 spilled ones, and seven are faster, us,
-// seven -> eight: 157 tokens 5.6 -> 6.0, 942: 5.1 -> 5.5, 2.3 M 12.2 -> 12.7, 3.0 M in 6008 sequences 16.1 -> 17.0.)
+// (The lookup's scalar registers leave seven wavefronts a SIMD.  Held to eight, which spills them, us, seven -> eight: 129 tokens 4.2 ->
+// 4.5, 4521 in 100 sequences 5.7 -> 6.2, 43 K in 100 5.3 -> 5.6, 2.3 M in 512 9.6 -> 9.9, 3.0 M in 6008 15.4 -> 16.3, 20 M 58.7 -> 59.2.)
 template <bool kFetch, bool kFew>
 __global__ __launch_bounds__(kLossThreads, kFetch ? 6 : 8) void loss_kernel(LossParams p, tppo_loss_out* __restrict__ out) {
     __shared__ double s_red[2 * kLossThreads / kWave], s_fin[kLossThreads];
@@ -778,7 +780,7 @@ static int loss_groups(int64_t n_resp, bool grad) {
 // than they fetch in one go, on the average, the fetch is one more trip before the walk that most tokens need all the same: us,
 // fetching -> not, losses / derivatives: 1.0 M windows of one token 18.3 -> 15.6 / 22.9 -> 21.0;  50 000 of two 10.5 -> 9.0 / 13.3 -> 11.9;
 // 10 000 of 100 tokens and 300 empty ones after each 15.4 -> 14.3 / 21.0 -> 19.3.  Below: 20 000 of eight tokens, an empty one
-// after each, 8.0 (8.9) / 11.3 (12.1).
+// after each, 8.0 (8.9) / 11.3 (12.1).  (All with sums through shuffles, on both sides.)
 // (A workgroup fetches a sequence and has four tokens for each of its threads.)
 static bool loss_fetches(int64_t B, int64_t n_resp) { return 4 * B < n_resp; }
 
