@@ -1,5 +1,5 @@
 """Thin binding of libtppo.so (see include/tppo.h for the contract): ctypes, and for the calls of a training step a native
-half (csrc/marshal.cpp), which checks, allocates and calls in two thirds to nine tenths of the time (figures there).
+half (csrc/marshal.cpp), which checks, allocates and calls in half to four fifths of the time (figures there).
 
 Argument marshalling only: every step of the path runs in the HIP kernels.
 PyTorch provides device memory and the current HIP stream.  There is no CPU
